@@ -28,9 +28,9 @@ struct Layout {
     size_t total = 0;
     size_t remap, map, perm_src, perm_full, rp0, ci0, lead1, anc, g_u1, srp, sci, srow, tptr, tidx;
     size_t red_ptr[kMaxLv], red_src[kMaxLv], dom_ptr[kMaxLv], dom_blk[kMaxLv], dom_ab[kMaxLv];
-    size_t ganc, gpos, gmask, cp_ptr[kMaxLv], lmask, gorder, gu1_slot, gu1_mask, gw_pos, gw_li, gw_mask;
+    size_t ganc, gpos, gmask, cp_ptr[kMaxLv], lmask, gorder, gu1_slot, gu1_mask, gw_pos, gw_li, gw_mask, hptr, hy, hidx;
     size_t H64, H32, A[kMaxLv], inv64[kMaxLv], inv32[kMaxLv];
-    size_t b, x, r, z, p0, p1, q, r1, q1, y[kMaxLv], rc[kMaxLv], cpart, qpart, P_sigma, P_rr, P_bb, P_rho0, P_rho1, st, flag;
+    size_t b, x, r, z, p0, p1, q, r1, q1, yall, y[kMaxLv], rc[kMaxLv], cpart, qpart, P_sigma, P_rr, P_bb, P_rho0, P_rho1, st, flag;
     size_t inverse_bytes = 0;
 
     size_t take(size_t bytes) {
@@ -71,6 +71,9 @@ struct Shape {
     size_t n_tidx = 0;            // transposed entries of the symmetric storage
     size_t nnzA[kMaxLv] = {};     // blocks of A_l (level 0: nnzb)
     size_t n_domblk[kMaxLv] = {}; // inversion gather entries of each level
+    bool halo = false;            // the two-launch iteration's unit lists (Plan::hptr)
+    size_t n_hy = 0;
+    int maxH = 0;                 // most units of one group
 };
 
 Shape shape_of(const Plan& P) {
@@ -81,6 +84,9 @@ Shape shape_of(const Plan& P) {
         S.nnzA[l] = l == 0 ? static_cast<size_t>(P.nnzb) : P.ciA[l].size();
         S.n_domblk[l] = P.dom_blk[l].size();
     }
+    S.halo = P.halo;
+    S.n_hy = P.hy.size();
+    S.maxH = P.maxH;
     return S;
 }
 
@@ -108,7 +114,7 @@ struct mas_handle {
     size_t ws_size = 0;
     char* uploaded_to = nullptr;
     bool built = false;
-    bool fuse_ok = false;  // the SpMV kernels can stage the restriction of q (three launches per iteration)
+    bool fuse_ok = false;  // two launches per iteration (set_fusion)
     DevState* st_host = nullptr;  // pinned: [0] last blocking read, [1..2] per-batch copies
     int* flag_host = nullptr;     // pinned
     hipEvent_t ev[kEvCount]{};
@@ -207,6 +213,11 @@ void make_layout(mas_handle* h) {
     Y.ganc = Y.take(I * gtab);
     Y.gpos = Y.take(I * gtab);
     Y.gmask = Y.take(sizeof(uint64_t) * gtab);
+    if (Z.halo) {
+        Y.hptr = Y.take(I * (static_cast<size_t>(P.G) + 1));
+        Y.hy = Y.take(I * Z.n_hy);
+        Y.hidx = Y.take(sizeof(uint16_t) * (P.sym && !mixed ? nsb : static_cast<size_t>(P.nnzb)));
+    }
     if (P.sym) {
         Y.srp = Y.take(I * (static_cast<size_t>(P.NS) + 1));
         Y.sci = Y.take(I * nsb);
@@ -245,15 +256,23 @@ void make_layout(mas_handle* h) {
     Y.q = Y.take(vec);
     Y.r1 = Y.take(Dd * 3 * (P.L > 1 ? P.units[1] : 1));
     Y.q1 = Y.take(Dd * 3 * (P.L > 1 ? P.units[1] : 1));
-    for (int l = 1; l < P.L; ++l) Y.y[l] = Y.take(Dd * 3 * static_cast<size_t>(P.ndom[l]) * P.N);
+    // the coarse corrections of all levels end to end (one index reaches any)
+    size_t ny = 0;
+    for (int l = 1; l < P.L; ++l) {
+        Y.y[l] = Dd * 3 * ny;
+        ny += static_cast<size_t>(P.ndom[l]) * P.N;
+    }
+    Y.yall = Y.take(Dd * 3 * ny);
+    for (int l = 1; l < P.L; ++l) Y.y[l] += Y.yall;
     for (int l = 2; l < P.L; ++l) Y.rc[l] = Y.take(Dd * 3 * static_cast<size_t>(P.ndom[l]) * P.N);
     Y.cpart = Y.take(Dd * 3 * std::max(P.n_cpart, 1));
     Y.qpart = Y.take(Dd * 3 * std::max(P.n_cpart, 1));
     Y.P_sigma = Y.take(Dd * P.G);
     Y.P_rr = Y.take(Dd * P.G);
     Y.P_bb = Y.take(Dd * P.G);
-    Y.P_rho0 = Y.take(Dd * P.G);
-    Y.P_rho1 = Y.take(Dd * P.G);
+    const size_t nrho = static_cast<size_t>(P.G) + rec_coarse_blocks(P.L, P.N, P.ndom.data());
+    Y.P_rho0 = Y.take(Dd * nrho);
+    Y.P_rho1 = Y.take(Dd * nrho);
     Y.st = Y.take(sizeof(DevState));
     Y.flag = Y.take(I);
 }
@@ -304,6 +323,14 @@ SolverView view(const mas_handle* h) {
     v.ganc = at<int>(h, Y.ganc);
     v.gpos = at<int>(h, Y.gpos);
     v.gmask = at<uint64_t>(h, Y.gmask);
+    if (h->shape.halo) {
+        v.hptr = at<int>(h, Y.hptr);
+        v.hy = at<int>(h, Y.hy);
+        v.hidx = at<uint16_t>(h, Y.hidx);
+        v.maxH = h->shape.maxH;
+    }
+    v.yall = at<double>(h, Y.yall);
+    v.ncb = rec_coarse_blocks(P.L, P.N, P.ndom.data());
     v.cpart = at<double>(h, Y.cpart);
     v.qpart = at<double>(h, Y.qpart);
     v.P_sigma = at<double>(h, Y.P_sigma);
@@ -381,6 +408,13 @@ int upload_plan(mas_handle* h, hipStream_t s) {
         HIP_TRY(hipMemcpyAsync(h->ws + Y.srow, P.srow.data(), P.srow.size(), hipMemcpyHostToDevice, s));
         HIP_TRY(put(Y.tptr, P.tptr));
         HIP_TRY(put(Y.tidx, P.tidx));
+    }
+    if (h->shape.halo) {
+        const std::vector<uint16_t>& hidx =
+            P.sym && h->opts.precision != MAS_PRECISION_MIXED ? P.hidx_sym : P.hidx;
+        HIP_TRY(put(Y.hptr, P.hptr));
+        HIP_TRY(put(Y.hy, P.hy));
+        HIP_TRY(hipMemcpyAsync(h->ws + Y.hidx, hidx.data(), sizeof(uint16_t) * hidx.size(), hipMemcpyHostToDevice, s));
     }
     HIP_TRY(put(Y.rp0, P.rp0));
     HIP_TRY(put(Y.ci0, P.ci0));
@@ -468,6 +502,12 @@ int place_device_plan(mas_handle* h, hipStream_t s) {
         D.tptr = at<int>(h, Y.tptr);
         D.tidx = at<int>(h, Y.tidx);
     }
+    if (h->shape.halo) {
+        D.hptr = at<int>(h, Y.hptr);
+        D.hy = at<int>(h, Y.hy);
+        D.hidx = at<uint16_t>(h, Y.hidx);
+        D.hidx_sym = P.sym && h->opts.precision != MAS_PRECISION_MIXED ? 1 : 0;
+    }
     for (int l = 0; l < P.L; ++l) {
         if (l >= 1) {
             D.red_ptr[l] = at<int>(h, Y.red_ptr[l]);
@@ -515,13 +555,15 @@ int read_state(mas_handle* h, const SolverView& v, hipStream_t s) {
 }
 
 // The PCG driver shared by pcg_solve and pcg_adjoint.  Iteration k takes
-// three launches:
-//   p = z + beta p, q = H p (sigma partials) and the restriction of q ->
-//   convergence test on r_{k-1}, alpha, C_l r_k = C_l r_{k-1} - alpha C_l q_k
-//   and the coarse apply -> x += alpha p, r -= alpha q (||r||^2 partials),
-//   level-0 apply and prolongation (rho partials);
+// two launches:
+//   p = z + beta p, q = H p (sigma partials), the restriction of q and the
+//   convergence test on r_{k-1} ->
+//   alpha, x += alpha p, r -= alpha q (||r||^2 partials), the level-0 apply
+//   and, beside it, C_l r_k = C_l r_{k-1} - alpha C_l q_k and the coarse apply
+//   (rho partials of both); the prolongation follows in the next SpMV;
 // every replace_every-th iteration (and every iteration when the SpMV cannot
-// lend shared memory to the restriction) restricts r_k itself instead:
+// lend shared memory to the restriction or to the groups' coarse
+// corrections) restricts r_k itself instead:
 //   SpMV -> x/r update with the restriction of r_k -> [mixed: FP64 residual
 //   replacement] -> convergence test on r_k and coarse apply -> level-0
 //   apply, which also bounds the rounding the recurrence accumulates.
@@ -562,21 +604,19 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
     // state is copied into a pinned slot; the host looks at a batch's copy
     // only once the next batch is queued, so the device never waits for the
     // host.  Kernels queued after a stop return at once.
+    bool split = false;  // z still lacks the coarse corrections (the last apply was launch_apply_rec)
     auto direct = [&](int kk) { return !h->fuse_ok || kk % opt.replace_every == 0; };
     auto batch = [&](int nb) -> int {
         for (int i = 0; i < nb; ++i) {
             ++k;
             if (!direct(k)) {
-                HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, true, s); }, 2 * k));
-                HIP_TRY(timed(
-                    h, kKCoarse, s,
-                    [&] { return launch_apply_coarse(v, mixed, kApplyRec, k, 0.0, false, mixed, false, s); },
-                    2 * k));
-                HIP_TRY(timed(h, kKLevel0Upd, s, [&] { return launch_apply_level0(v, mixed, kApplyRec, k, s); },
-                              2 * k));
+                HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, true, split, s); }, 2 * k));
+                HIP_TRY(timed(h, kKLevel0Upd, s, [&] { return launch_apply_rec(v, mixed, k, s); }, 2 * k));
+                split = true;
                 continue;
             }
-            HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, false, s); }, 2 * k));
+            HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, false, split, s); }, 2 * k));
+            split = false;
             HIP_TRY(timed(h, kKUpdate, s, [&] { return launch_update(v, k, s); }, 2 * k));
             bool replaced = false;
             if (mixed && k % opt.replace_every == 0) {
@@ -586,7 +626,7 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
             HIP_TRY(apply_iter(h, v, mixed, k, replaced, s));
         }
         // a last iteration by recurrence leaves its decision to the next
-        // coarse launch: at max_iter, take it here
+        // SpMV: at max_iter, take it here
         if (k == opt.max_iter && k > 0 && !direct(k))
             HIP_TRY(launch_apply_coarse(v, mixed, kApplyIter, k, 0.0, false, mixed, false, s, true));
         return MAS_OK;
@@ -618,6 +658,7 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
         HIP_TRY(launch_clear_stop(v, s));
         HIP_TRY(timed(h, kKResidual, s, [&] { return launch_residual(v, kResidConfirm, v.r, s); }, 2 * k));
         HIP_TRY(apply_iter(h, v, mixed, k, true, s));
+        split = false;
         if ((rc = read_state(h, v, s)) != MAS_OK) return rc;
         if (st.done || st.status < 0) break;
     }
@@ -678,15 +719,18 @@ namespace {
 
 void set_fusion(mas_handle* h) {
     const Plan& R = h->plan;
-    // three launches per iteration where the SpMV's restriction of q takes
+    // two launches per iteration where the SpMV's restriction of q takes
     // one pass of its threads (restrict_fast_ok): on systems whose groups
     // have many more coarse units (a group of the membrane + bodies system
     // has up to 448 writers), the longer restriction in the SpMV costs more
     // than the x/r update launch it saves, and every iteration restricts r
-    // directly
+    // directly; and where the groups' coarse corrections fit in the 64 KB of
+    // LDS a workgroup may have beside the rest (groups that read more than
+    // kMaxHalo units have no lists at all)
     h->fuse_ok = sizeof(double) * (3 * static_cast<size_t>(R.RG) + restrict_smem_doubles(R.RG, R.W1, R.L)) <=
                      spmv_restrict_capacity() &&
-                 restrict_fast_ok(R.W1, R.GW, spmv_threads());
+                 restrict_fast_ok(R.W1, R.GW, spmv_threads()) && h->shape.halo &&
+                 spmv_shared_bytes(R.RG, R.maxT, R.sym) + sizeof(double) * 3 * h->shape.maxH <= (size_t{64} << 10);
 }
 
 int analyze_impl(mas_handle* h, int32_t n_rows, int32_t nnzb, const int32_t* row_ptr, const int32_t* col_idx,
@@ -1139,6 +1183,8 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
     HIP_TRY(hipMemcpyAsync(&c, R.counts, sizeof(c), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(g_u1.data(), R.g_u1, sizeof(int) * g_u1.size(), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(gsz.data(), R.gstore, sizeof(int) * gsz.size(), hipMemcpyDeviceToHost, s));
+    int n_halo = 0;
+    HIP_TRY(hipMemcpyAsync(&n_halo, R.hptr + G, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
 
     // the new plan: the partition and its maps stay, every size is new
@@ -1176,6 +1222,9 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
     Shape Z;
     Z.nsb = Q.sym ? static_cast<size_t>(n_sym) : static_cast<size_t>(nnzb);
     Z.n_tidx = static_cast<size_t>(n_tidx);
+    Z.halo = c.h_max <= kMaxHalo;
+    Z.maxH = Z.halo ? c.h_max : 0;
+    Z.n_hy = Z.halo ? static_cast<size_t>(n_halo) * (S.L - 1) : 0;
     PlacedShape ps{};
     ps.S = S;
     ps.sym = Q.sym ? 1 : 0;

@@ -165,22 +165,24 @@ __device__ __forceinline__ void keep_loads_issued() { asm volatile("" ::: "memor
 
 // sum_partials split in two, so that the loads can be issued early and their
 // latency overlap other loads: partials_load() fetches thread t's bucket
-// entries p[t], p[t + 256], ... into registers (n <= 1024), partials_sum()
-// adds them in sum_partials' order (same bits) and folds the buckets.  For
-// n > 1024 partials_sum() falls back to sum_partials.  Every thread issues
-// its four loads unconditionally, at indices clamped to [0, n) (n >= 1), so
-// that no branch separates them from the loads issued after them and a wait
-// for them need not wait for those too; partials_sum() reads only the
-// entries below n.
+// entries p[t], p[t + 256], ... into registers (n <= 256 kPer),
+// partials_sum() adds them in sum_partials' order (same bits) and folds the
+// buckets.  For larger n partials_sum() falls back to sum_partials.  Every
+// thread issues its kPer loads unconditionally, at indices clamped to [0, n)
+// (n >= 1), so that no branch separates them from the loads issued after
+// them and a wait for them need not wait for those too; partials_sum() reads
+// only the entries below n.
+template <int kPer = 4>
 struct PartialLoads {
-    double v[4];
+    double v[kPer];
 };
 
-__device__ inline PartialLoads partials_load(const double* __restrict__ p, int n) {
-    PartialLoads L;
+template <int kPer = 4>
+__device__ inline PartialLoads<kPer> partials_load(const double* __restrict__ p, int n) {
+    PartialLoads<kPer> L;
     const int t = threadIdx.x;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < kPer; ++j) {
         L.v[j] = p[min(t + 256 * j, n - 1)];
     }
     return L;
@@ -188,18 +190,23 @@ __device__ inline PartialLoads partials_load(const double* __restrict__ p, int n
 
 // kReuse = false leaves out the closing barrier, for a caller whose next
 // write to buf follows another barrier.
-template <bool kReuse = true>
-__device__ inline double partials_sum(const PartialLoads& L, const double* __restrict__ p, int n, double* buf) {
-    if (n > 1024) return sum_partials(p, n, buf);
+template <bool kReuse = true, int kPer = 4>
+__device__ inline double partials_sum(const PartialLoads<kPer>& L, const double* __restrict__ p, int n, double* buf) {
+    static_assert(kPer % 4 == 0, "whole rounds of sum_partials");
+    if (n > 256 * kPer) return sum_partials(p, n, buf);
     const int t = threadIdx.x;
     if (t < 256) {  // as in partials_load: bucket t holds p[t], p[t + 256], ... below n
         double s = 0.0;
-        if (t + 768 < n) {
-            s += (L.v[0] + L.v[1]) + (L.v[2] + L.v[3]);
-        } else {
-            if (t < n) s += L.v[0];
-            if (t + 256 < n) s += L.v[1];
-            if (t + 512 < n) s += L.v[2];
+#pragma unroll
+        for (int r = 0; r < kPer; r += 4) {
+            const int i = t + 256 * r;
+            if (i + 768 < n) {
+                s += (L.v[r] + L.v[r + 1]) + (L.v[r + 2] + L.v[r + 3]);
+            } else {
+                if (i < n) s += L.v[r];
+                if (i + 256 < n) s += L.v[r + 1];
+                if (i + 512 < n) s += L.v[r + 2];
+            }
         }
         buf[t] = s;
     }

@@ -75,6 +75,16 @@ struct SolverView {
     const int* gw_li;
     const uint64_t* gw_mask;
     const int* cp_ptr[kMaxLv];    // l >= 2: [S_l + 1]
+    // two-launch iteration: the level-1 units whose coarse correction group g
+    // reads, [hptr[g], hptr[g + 1]) (its own first); their corrections'
+    // positions in yall at every level, [(L-1) hptr[g] + (l-1) n + i]; the
+    // local unit of every block of the SpMV's storage with a column outside
+    // the group
+    const int* hptr;
+    const int* hy;
+    const uint16_t* hidx;
+    int maxH;  // most units of one group
+    int ncb;   // coarse workgroups of the apply (rec_coarse_blocks)
     // stored slot-ordered matrix (9 planes: H64 of nsb, H32 of nnzb values)
     double* H64;
     float* H32;
@@ -86,7 +96,8 @@ struct SolverView {
     double* p[2];  // search direction p_k lives in p[k & 1]
     // coarse vectors: r1 [3*units[1]], y_l [3*ndom[l]*N] for l >= 1, coarse partials [3*n_cpart]
     double* r1;
-    double* y[kMaxLv];
+    double* y[kMaxLv];  // laid end to end from yall
+    double* yall;
     double* cpart;
     // the same restrictions of q = H p (q1, qpart), and the restricted
     // residual C_l r of levels l >= 2 ([3*ndom[l]*N]) that the coarse apply
@@ -94,7 +105,8 @@ struct SolverView {
     double* q1;
     double* qpart;
     double* rc[kMaxLv];
-    // per-group partial sums [G] each
+    // per-group partial sums [G] each (P_rho: [G + ncb], the coarse
+    // workgroups' r_l^T y_l after the groups')
     double *P_sigma, *P_rr, *P_bb, *P_rho[2];
     DevState* st;
     int* flag;  // inversion status
@@ -108,6 +120,15 @@ struct SolverView {
 constexpr int kPackedN = 48;
 constexpr int kPacked = kPackedN * (kPackedN + 1) / 2;
 __host__ __device__ constexpr int packed_col(int j) { return j * kPackedN - (j * (j - 1)) / 2; }
+
+// Workgroups of the coarse levels in the apply of a two-launch iteration:
+// for N = 16 four level-1 domains per workgroup, else one domain each.
+constexpr int kRecLevel1 = 4;
+inline int rec_coarse_blocks(int L, int N, const int* ndom) {
+    int n = 0;
+    for (int l = 1; l < L; ++l) n += (l == 1 && N == 16) ? (ndom[l] + kRecLevel1 - 1) / kRecLevel1 : ndom[l];
+    return n;
+}
 
 // Build-phase views.
 struct BuildView {
@@ -135,25 +156,31 @@ enum ResidMode {
     kResidConfirm = 2,  // as kResidReplace, run after the host cleared a stop
     kResidFinal = 3     // scratch = b - H x with ||.||^2 only
 };
-// MAS apply modes.
+// MAS apply modes of the separate coarse and level-0 launches.
 //  kApplyPlain: z = M^-1 r outside PCG (no decision, no partials).
 //  kApplyInit:  the first apply of a solve; decision on r_0 with ||b||.
 //  kApplyIter:  iteration k after the x/r update kernel restricted r_k:
 //               coarse residuals straight from that restriction (kept for
 //               the recurrence), decision on r_k.
-//  kApplyRec:   iteration k without the x/r update kernel: the coarse launch
-//               forms alpha_k and C_l r_k = C_l r_{k-1} - alpha_k C_l q_k from
-//               the restriction of q_k the SpMV left, and takes the decision
-//               on r_{k-1}; the level-0 launch performs x += alpha p,
-//               r -= alpha q itself and leaves the ||r_k||^2 partials.
-enum ApplyMode { kApplyPlain = 0, kApplyInit = 1, kApplyIter = 2, kApplyRec = 3 };
+// An iteration by recurrence applies in one launch (launch_apply_rec): alpha_k,
+// C_l r_k = C_l r_{k-1} - alpha_k C_l q_k from the restriction of q_k the SpMV
+// left and the coarse corrections y_l beside x += alpha p, r -= alpha q and
+// z = Inv_0 r; the next SpMV adds the corrections to z where it reads it and
+// takes the decision on r_k.
+enum ApplyMode { kApplyPlain = 0, kApplyInit = 1, kApplyIter = 2 };
 
 // spmv.hip
 hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void* val, bool f32, const double* x,
                             double* y, hipStream_t s);
 // iteration k: p_k = z_{k-1} + beta p_{k-1} (p_1 = z_0) into p[k & 1], q = H p_k, sigma partials;
-// restrict_q: also the restriction of q to the coarse levels (q1, qpart)
-hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool restrict_q, hipStream_t s);
+// restrict_q: also the restriction of q to the coarse levels (q1, qpart);
+// split: z_{k-1} is v.z plus the coarse corrections in yall (the previous
+// iteration ran launch_apply_rec), and one workgroup more takes the decision
+// on r_{k-1}
+hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool restrict_q, bool split, hipStream_t s);
+// Shared memory of the SpMV kernels besides a group's staged corrections
+// (maxH units of 24 bytes).
+size_t spmv_shared_bytes(int RG, int maxT, bool sym);
 // Bytes of shared memory the SpMV kernels can lend to the restriction of q
 // after their stream (their product planes).
 size_t spmv_restrict_capacity();
@@ -184,6 +211,9 @@ hipError_t launch_invert(const BuildView& b, const double* Hu, bool want32, hipS
 hipError_t launch_apply_coarse(const SolverView& v, bool f32, int mode, int k, double tol, bool x0_given, bool mixed,
                                bool rr_true, hipStream_t s, bool decision_only = false);
 hipError_t launch_apply_level0(const SolverView& v, bool f32, int mode, int k, hipStream_t s);
+// Iteration k by recurrence: x/r update, level 0 and the coarse levels in
+// one launch (see ApplyMode).
+hipError_t launch_apply_rec(const SolverView& v, bool f32, int k, hipStream_t s);
 
 // assemble.hip: block-list assembly (scratch in the caller's workspace).
 struct AsmLayout {

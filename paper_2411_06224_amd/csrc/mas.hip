@@ -3,6 +3,7 @@
 // preconditioner" in Sec. 4.3).
 #include <algorithm>
 
+#include "decision.hpp"
 #include "launch.hpp"
 
 namespace maspcg {
@@ -283,65 +284,73 @@ __global__ void __launch_bounds__(kInvThreads) k_invert(BuildView B, const doubl
 }
 
 // ------------------------------------------------------------------ apply
-constexpr int kFlagX0 = 1, kFlagMixed = 2, kFlagRrTrue = 4;
 constexpr int kRound = 8;  // coarse partials loaded per round by one lane
 
-// Workgroup 0 of the coarse launch takes the convergence decision of the
-// iteration: it sums the ||r||^2 partials (and ||b||^2 for the first
-// apply) and records rr, the iteration count and, when ||r|| <= tol ||b||,
-// the stop for the host and every later kernel.  In mixed precision a stop
-// on the recurrence is marked for confirmation on the FP64 residual.
-__device__ void convergence_decision(const SolverView& v, int mode, int k, double tol, int flags, double* buf) {
-    DevState* st = v.st;
-    if (st->done) return;
-    const double rr = sum_partials(v.P_rr, v.G, buf);
-    if (mode == kApplyInit) {
-        const double bb = sum_partials(v.P_bb, v.G, buf);
-        const double tol2 = tol * tol * bb;
-        const bool bad = !finite(bb) || !finite(rr);
-        const bool stop = bad || bb == 0.0 || ((flags & kFlagX0) && rr <= tol2);
-        if (threadIdx.x == 0) {
-            st->bb = bb;
-            st->tol2 = tol2;
-            st->rr = rr;
-            st->iter = 0;
-            if (stop) {
-                st->status = bad ? -6 : 0;
-                st->done = 1;
-            }
+// Sum of a unit's partials part[m0 .. m1) (three components each) over 16
+// lanes, lane sub taking m0 + sub, + 16, + 32, ... in this order, then folded
+// within the lanes' DPP row.  kR are loaded per round (at clamped indices, the
+// ones past the range not added) so that their latencies overlap: a unit of
+// the top levels has partials from about a hundred groups.
+template <int kR>
+__device__ __forceinline__ void gather_unit16(const double* __restrict__ part, int m0, int m1, int sub, double& s0,
+                                              double& s1, double& s2) {
+    s0 = s1 = s2 = 0.0;
+    for (int m = m0 + sub; m < m1; m += 16 * kR) {
+        double a0[kR], a1[kR], a2[kR];
+#pragma unroll
+        for (int j = 0; j < kR; ++j) {
+            const int mj = min(m + 16 * j, m1 - 1);
+            a0[j] = part[3 * mj];
+            a1[j] = part[3 * mj + 1];
+            a2[j] = part[3 * mj + 2];
         }
-    } else {
-        const bool bad = !finite(rr);
-        const bool conv = rr <= st->tol2;
-        if (threadIdx.x == 0) {
-            st->rr = rr;
-            st->iter = k;
-            if (bad || conv) {
-                st->status = bad ? -6 : (((flags & kFlagMixed) && !(flags & kFlagRrTrue)) ? kStatusConvergedRecurrence : 0);
-                st->done = 1;
+#pragma unroll
+        for (int j = 0; j < kR; ++j)
+            if (m + 16 * j < m1) {
+                s0 += a0[j];
+                s1 += a1[j];
+                s2 += a2[j];
             }
+    }
+    s0 = row16_sum(s0);
+    s1 = row16_sum(s1);
+    s2 = row16_sum(s2);
+}
+
+// The same over a whole wave (other domain sizes): two loads in flight per
+// lane.
+__device__ __forceinline__ void gather_unit64(const double* __restrict__ part, int m0, int m1, int lane, double& s0,
+                                              double& s1, double& s2) {
+    s0 = s1 = s2 = 0.0;
+    for (int m = m0 + lane; m < m1; m += 128) {
+        const int mb = m + 64;
+        s0 += part[3 * m];
+        s1 += part[3 * m + 1];
+        s2 += part[3 * m + 2];
+        if (mb < m1) {
+            s0 += part[3 * mb];
+            s1 += part[3 * mb + 1];
+            s2 += part[3 * mb + 2];
         }
     }
+    s0 = wave_sum(s0);
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
 }
 
 // Coarse levels l >= 1 (workgroups 1.. of the launch, one per domain, all
-// levels at once): r_l for the domain's N units, then y_l = Inv_{l,d} r_l.
-// Straight from the residual's restriction (kApplyInit, kApplyIter,
-// kApplyPlain): level 1 from r_1, higher levels as sums of the per-group
+// levels at once): r_l for the domain's N units straight from the residual's
+// restriction -- level 1 from r_1, higher levels as sums of the per-group
 // partials the restriction left for each unit (a contiguous range per unit;
 // for N = 16 sixteen lanes per unit, all units at once, else one wave per
-// unit); levels >= 2 keep that r_l in rc_l.  By recurrence (kApplyRec,
-// iteration k): alpha_k = rho_{k-1} / sigma_k from the partials, and
-// r_l <- r_l - alpha_k (C_l q_k) with C_l q_k gathered in the same way from
-// the restriction of q_k the SpMV left (q_1, qpart); the unit's r_l (r_1 or
-// rc_l) is updated in place, each unit by the one workgroup of its domain.
+// unit), kept in rc_l inside PCG -- then y_l = Inv_{l,d} r_l.
 template <typename TI, int kN>
 __global__ void __launch_bounds__(256) k_apply_coarse(SolverView v, DomTable tab, int mode, int k, double tol,
                                                       int flags) {
     __shared__ double rl[128];
     __shared__ double buf[256];
     if (blockIdx.x == 0) {
-        if (mode != kApplyPlain) convergence_decision(v, mode, mode == kApplyRec ? k - 1 : k, tol, flags, buf);
+        if (mode != kApplyPlain) convergence_decision(v, mode == kApplyInit, k, tol, flags, buf);
         return;
     }
     const int gb = blockIdx.x - 1;
@@ -352,7 +361,6 @@ __global__ void __launch_bounds__(256) k_apply_coarse(SolverView v, DomTable tab
     const int u0 = d * N;
     const int nu = min(N, v.units[l] - u0);
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-    const bool rec = mode == kApplyRec;
     const TI* inv;
     if constexpr (sizeof(TI) == 8)
         inv = v.inv64[l];
@@ -374,93 +382,22 @@ __global__ void __launch_bounds__(256) k_apply_coarse(SolverView v, DomTable tab
             }
         }
     }
-    // recurrence: the sigma partials and the unit's previous r_l, issued
-    // with the inverse loads (N = 16: lane 0 of each unit's 16-lane segment
-    // holds the unit's three components; level 1: thread t < 3 nu holds
-    // entry t of the domain's r_1 and q_1)
-    PartialLoads sig{};
-    double rho = 0.0, prev0 = 0.0, prev1 = 0.0, prev2 = 0.0, q1v = 0.0;
-    if (rec) {
-        sig = partials_load(v.P_sigma, v.G);
-        rho = v.st->rho[(k - 1) & 1];
-        if (l == 1) {
-            const int e = 3 * u0 + min(t, 3 * nu - 1);
-            prev0 = v.r1[e];
-            q1v = v.q1[e];
-        } else if (kN == 16) {
-            const int e = 3 * (u0 + min(t >> 4, nu - 1));
-            prev0 = v.rc[l][e];
-            prev1 = v.rc[l][e + 1];
-            prev2 = v.rc[l][e + 2];
-        }
-    }
     // the stop flag is read once these loads are in flight; after a stop
     // nothing is written
     const int stop = v.st->done;
     keep_loads_issued();
-    if ((mode == kApplyIter || rec) && stop) return;
-    double alpha = 0.0;
-    if (rec) {
-        const double sigma = partials_sum(sig, v.P_sigma, v.G, buf);
-        if (!(sigma > 0.0) || !finite(sigma) || !finite(rho)) return;  // the level-0 launch reports it
-        alpha = rho / sigma;
-    }
+    if (mode == kApplyIter && stop) return;
     const bool keep = mode != kApplyPlain;  // r_l of levels >= 2 kept for the recurrence
     if (l == 1) {
-        if (t < n) {
-            double val = 0.0;
-            if (t < 3 * nu) {
-                if (rec) {
-                    val = prev0 - alpha * q1v;
-                    v.r1[3 * u0 + t] = val;
-                } else {
-                    val = v.r1[3 * u0 + t];
-                }
-            }
-            rl[t] = val;
-        }
+        if (t < n) rl[t] = t < 3 * nu ? v.r1[3 * u0 + t] : 0.0;
     } else if constexpr (kN == 16) {
-        // all 16 units at once: 16 lanes per unit stride over its partials,
-        // then fold within the 16-lane segment
         const int* cp = v.cp_ptr[l];
-        const double* part = rec ? v.qpart : v.cpart;
         const int a = t >> 4, sub = t & 15;
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        if (a < nu) {
-            // the lane's partials m0 + sub, + 16, + 32, ... in this order;
-            // kRound are loaded per round (at clamped indices, the ones past
-            // the range not added) so that their latencies overlap: a unit of
-            // the top levels has partials from about a hundred groups, which
-            // one round then covers
-            const int m0 = cp[u0 + a], m1 = cp[u0 + a + 1];
-            for (int m = m0 + sub; m < m1; m += 16 * kRound) {
-                double a0[kRound], a1[kRound], a2[kRound];
-#pragma unroll
-                for (int j = 0; j < kRound; ++j) {
-                    const int mj = min(m + 16 * j, m1 - 1);
-                    a0[j] = part[3 * mj];
-                    a1[j] = part[3 * mj + 1];
-                    a2[j] = part[3 * mj + 2];
-                }
-#pragma unroll
-                for (int j = 0; j < kRound; ++j)
-                    if (m + 16 * j < m1) {
-                        s0 += a0[j];
-                        s1 += a1[j];
-                        s2 += a2[j];
-                    }
-            }
-        }
-        s0 = row16_sum(s0);  // a unit's 16 lanes are one DPP row of the wave
-        s1 = row16_sum(s1);
-        s2 = row16_sum(s2);
+        const bool own = a < nu;
+        double s0, s1, s2;
+        gather_unit16<kRound>(v.cpart, own ? cp[u0 + a] : 0, own ? cp[u0 + a + 1] : 0, sub, s0, s1, s2);
         if (sub == 0) {
-            if (rec && a < nu) {
-                s0 = prev0 - alpha * s0;
-                s1 = prev1 - alpha * s1;
-                s2 = prev2 - alpha * s2;
-            }
-            if (keep && a < nu) {
+            if (keep && own) {
                 double* rc = v.rc[l] + 3 * (u0 + a);
                 rc[0] = s0;
                 rc[1] = s1;
@@ -472,39 +409,16 @@ __global__ void __launch_bounds__(256) k_apply_coarse(SolverView v, DomTable tab
         }
     } else {
         const int* cp = v.cp_ptr[l];
-        const double* part = rec ? v.qpart : v.cpart;
         for (int a = w; a < N; a += 4) {
-            double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-            if (a < nu) {
-                const int m0 = cp[u0 + a], m1 = cp[u0 + a + 1];
-                for (int m = m0 + lane; m < m1; m += 128) {
-                    const int mb = m + 64;  // two independent loads in flight per lane
-                    s0 += part[3 * m];
-                    s1 += part[3 * m + 1];
-                    s2 += part[3 * m + 2];
-                    if (mb < m1) {
-                        s0 += part[3 * mb];
-                        s1 += part[3 * mb + 1];
-                        s2 += part[3 * mb + 2];
-                    }
-                }
-            }
-            s0 = wave_sum(s0);
-            s1 = wave_sum(s1);
-            s2 = wave_sum(s2);
+            const bool own = a < nu;
+            double s0, s1, s2;
+            gather_unit64(v.cpart, own ? cp[u0 + a] : 0, own ? cp[u0 + a + 1] : 0, lane, s0, s1, s2);
             if (lane == 0) {
-                if (a < nu) {
+                if (keep && own) {
                     double* rc = v.rc[l] + 3 * (u0 + a);
-                    if (rec) {
-                        s0 = rc[0] - alpha * s0;
-                        s1 = rc[1] - alpha * s1;
-                        s2 = rc[2] - alpha * s2;
-                    }
-                    if (keep) {
-                        rc[0] = s0;
-                        rc[1] = s1;
-                        rc[2] = s2;
-                    }
+                    rc[0] = s0;
+                    rc[1] = s1;
+                    rc[2] = s2;
                 }
                 rl[3 * a] = s0;
                 rl[3 * a + 1] = s1;
@@ -535,63 +449,40 @@ __global__ void __launch_bounds__(256) k_apply_coarse(SolverView v, DomTable tab
 }
 
 constexpr int kPreLevels = 8;  // coarse levels whose corrections are prefetched
+constexpr int kGroupThreads = 384;
 
-// The x/r update of iteration k fused into the level-0 apply (kApplyRec):
-// alpha_k = rho_{k-1} / sigma_k from the partials, x += alpha p_k and
-// r -= alpha q_k on the thread's DOF (one per thread, slots of the group;
-// the vectors are padded to whole groups).  The loads are issued by
-// fused_load with the kernel's other early loads; fused_update returns
-// false, after flagging NOT_SPD (or NOT_FINITE) from group 0, when
-// sigma <= 0 or a value is not finite: every workgroup sees the same sigma
-// and returns without writing.  buf: 256 doubles of shared memory.
-struct FusedLoads {
-    PartialLoads sig;
-    double rho, x, p, r, q;
-};
-
-__device__ __forceinline__ FusedLoads fused_load(const SolverView& v, int k, long long i) {
-    FusedLoads F;
-    F.sig = partials_load(v.P_sigma, v.G);
-    F.rho = v.st->rho[(k - 1) & 1];
-    F.x = v.x[i];
-    F.p = v.p[k & 1][i];
-    F.r = v.r[i];
-    F.q = v.q[i];
-    return F;
+// Row i of the inverse of level-0 domain d times its residual rd (LDS),
+// full column-major layout.
+template <typename TI, int kN>
+__device__ __forceinline__ double full_row(const TI* __restrict__ inv0, int n, int d, int row, const double* rd) {
+    const TI* inv = inv0 + (long long)d * n * n + row;
+    double acc = 0.0;
+    if constexpr (kN > 0) {
+#pragma unroll
+        for (int kk = 0; kk < 3 * kN; ++kk) acc += inv_load(inv + kk * 3 * kN) * rd[kk];
+    } else {
+#pragma unroll 8
+        for (int kk = 0; kk < n; ++kk) acc += inv_load(inv + kk * n) * rd[kk];
+    }
+    return acc;
 }
 
-__device__ __forceinline__ bool fused_update(const SolverView& v, int k, int g, long long i, bool live,
-                                             const FusedLoads& F, double* buf, double& rv) {
-    const double sigma = partials_sum(F.sig, v.P_sigma, v.G, buf);
-    if (!(sigma > 0.0) || !finite(sigma) || !finite(F.rho)) {
-        if (g == 0 && threadIdx.x == 0) {
-            v.st->status = (finite(sigma) && finite(F.rho)) ? -2 : -6;
-            v.st->done = 1;
-            v.st->iter = k - 1;
-        }
-        return false;
-    }
-    const double alpha = F.rho / sigma;
-    rv = 0.0;
-    if (live) {
-        v.x[i] = F.x + alpha * F.p;
-        rv = F.r - alpha * F.q;
-        v.r[i] = rv;
-    }
-    return true;
+template <typename TI>
+__device__ __forceinline__ const TI* level0_inverses(const SolverView& v) {
+    if constexpr (sizeof(TI) == 8)
+        return v.inv64[0];
+    else
+        return v.inv32[0];
 }
 
 // Level 0 over a group of D0 domains, one thread per DOF:
 //   z = Inv_{0,d} r_d + sum_{l >= 1} y_l[unit of the slot at level l]
 // (prolongation of every coarse level, Supp. Eq. 6) and the partial of
-// rho = r^T z; kApplyRec first performs the x/r update of iteration k and
-// also leaves the partial of ||r_k||^2.  Returns at once after a stop.
+// rho = r^T z.  Returns at once after a stop.
 template <typename TI, int kN, int kMode>
-__global__ void __launch_bounds__(384) k_apply_level0(SolverView v, int k) {
-    constexpr bool kFused = kMode == kApplyRec;
-    __shared__ double rs[384];
+__global__ void __launch_bounds__(kGroupThreads) k_apply_level0(SolverView v, int k) {
+    __shared__ double rs[kGroupThreads];
     __shared__ double red[16];
-    __shared__ double pbuf[kFused ? 256 : 1];
     const int N = kN > 0 ? kN : v.N;
     const int n = 3 * N;
     const int g = xcd_group(blockIdx.x, v.G), t = threadIdx.x;
@@ -605,44 +496,21 @@ __global__ void __launch_bounds__(384) k_apply_level0(SolverView v, int k) {
 #pragma unroll
     for (int j = 0; j < kPreLevels; ++j)
         u[j] = (live && j + 1 < v.L) ? v.anc[static_cast<long long>(j) * v.NS + slot] : -1;
-    FusedLoads F{};
-    double rv = 0.0;
-    if constexpr (kFused)
-        F = fused_load(v, k, base + t);
-    else
-        rv = live ? v.r[base + t] : 0.0;
+    const double rv = live ? v.r[base + t] : 0.0;
     // the stop flag is read once these loads are in flight; after a stop
     // nothing is written
     const int stop = v.st->done;
     keep_loads_issued();
     if (kMode != kApplyPlain && stop) return;
-    if constexpr (kFused) {
-        if (!fused_update(v, k, g, base + t, live, F, pbuf, rv)) return;
-    }
     double ycor[kPreLevels];
 #pragma unroll
     for (int j = 0; j < kPreLevels; ++j) ycor[j] = u[j] >= 0 ? v.y[j + 1][3 * u[j] + c] : 0.0;
-    if (t < 384) rs[t] = rv;
+    rs[t] = rv;
     __syncthreads();
     double zv = 0.0;
     if (live) {
         const int dl = t / n, row = t - dl * n;
-        const int d = g * v.D0 + dl;
-        const TI* inv;
-        if constexpr (sizeof(TI) == 8)
-            inv = v.inv64[0];
-        else
-            inv = v.inv32[0];
-        inv += (long long)d * n * n + row;
-        const double* rd = rs + dl * n;
-        double acc = 0.0;
-        if constexpr (kN > 0) {
-#pragma unroll
-            for (int kk = 0; kk < 3 * kN; ++kk) acc += inv_load(inv + kk * 3 * kN) * rd[kk];
-        } else {
-#pragma unroll 8
-            for (int kk = 0; kk < n; ++kk) acc += inv_load(inv + kk * n) * rd[kk];
-        }
+        double acc = full_row<TI, kN>(level0_inverses<TI>(v), n, g * v.D0 + dl, row, rs + dl * n);
 #pragma unroll
         for (int j = 0; j < kPreLevels; ++j)
             if (u[j] >= 0) acc += ycor[j];
@@ -665,101 +533,63 @@ __global__ void __launch_bounds__(384) k_apply_level0(SolverView v, int k) {
         v.z[base + t] = zv;
     }
     if (kMode == kApplyPlain) return;
-    if constexpr (kFused) {
-        double prho, prr;
-        block_sum2_last(rv * zv, rv * rv, red, prho, prr);
-        if (t == 0) {
-            v.P_rho[k & 1][g] = prho;
-            v.P_rr[g] = prr;
-        }
-    } else {
-        const double part = block_sum_last(rv * zv, red);
-        if (t == 0) v.P_rho[k & 1][g] = part;
-    }
+    const double part = block_sum_last(rv * zv, red);
+    if (t == 0) v.P_rho[k & 1][g] = part;
 }
 
-// Level 0 with the symmetric-packed FP64 inverses (domain size 16), over a
-// group of D0 domains: the packed inverses of two domains at a time
+// The symmetric-packed FP64 inverses (domain size 16) of a group's domains
+// times their residuals: the packed inverses of two domains at a time
 // (18.8 KB, contiguous) are staged in LDS with coalesced loads, the next
 // pair's loads in flight (in registers) while the current pair is
 // multiplied.  (With FP32 inverses the full layout streams faster: the
-// staging rounds, not the bytes, then bound the kernel.)  Four
-// threads per row each take twelve columns: entry (i, kk) of the inverse is
-// (kk, i) of the stored lower triangle when kk > i.  The rows' sums go to
-// LDS; then, one thread per DOF as in k_apply_level0,
-//   z = Inv_{0,d} r_d + sum_{l >= 1} y_l[unit of the slot at level l]
-// and the partial of rho = r^T z.  Returns at once after a stop.
+// staging rounds, not the bytes, then bound the kernel.)  Four threads per
+// row each take twelve columns: entry (i, kk) of the inverse is (kk, i) of
+// the stored lower triangle when kk > i.
 constexpr int kPairs = 2;                                // domains staged per round
-constexpr int kStageLoads = (kPairs * kPacked + 383) / 384;  // entries per thread and round
+constexpr int kStageLoads = (kPairs * kPacked + kGroupThreads - 1) / kGroupThreads;  // entries per thread and round
 
-template <typename TI, int kMode>
-__global__ void __launch_bounds__(384) k_apply_level0_packed(SolverView v, int k) {
-    constexpr bool kFused = kMode == kApplyRec;
-    __shared__ double rs[384];
-    __shared__ double zs[384];
-    __shared__ TI stage[kPairs * kPacked];
-    __shared__ double red[16];
-    const int g = xcd_group(blockIdx.x, v.G), t = threadIdx.x;
-    const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
-    const bool live = t < nd * 48;
-    const long long base = 3LL * g * v.RG;
-    const int slot = g * v.RG + t / 3, c = t % 3;
-    const TI* inv;
-    if constexpr (sizeof(TI) == 8)
-        inv = v.inv64[0];
-    else
-        inv = v.inv32[0];
-    inv += static_cast<long long>(g) * v.D0 * kPacked;
-    const int rounds = (nd + kPairs - 1) / kPairs;
-    // the first pair, then the corrections of the slot (prolongation) and r
-    TI nxt[kStageLoads];
-    auto fetch = [&](int p) {
-        const int cnt = min(kPairs, nd - kPairs * p) * kPacked;
-        const TI* src = inv + static_cast<long long>(kPairs * p) * kPacked;
+struct PackedPair {
+    double nxt[kStageLoads];
+};
+
+__device__ __forceinline__ void fetch_pair(PackedPair& P, const double* __restrict__ inv, int p, int nd) {
+    const int cnt = min(kPairs, nd - kPairs * p) * kPacked;
+    const double* src = inv + static_cast<long long>(kPairs * p) * kPacked;
 #pragma unroll
-        for (int j = 0; j < kStageLoads; ++j) {
-            const int e = t + 384 * j;
-            nxt[j] = e < cnt ? inv_load<TI, false>(src + e) : TI(0);
-        }
-    };
-    fetch(0);
-    FusedLoads F{};
-    double rv = 0.0;
-    if constexpr (kFused)
-        F = fused_load(v, k, base + t);
-    else
-        rv = live ? v.r[base + t] : 0.0;
-    // the stop flag is read once these loads are in flight; after a stop
-    // nothing is written
-    const int stop = v.st->done;
-    keep_loads_issued();
-    if (kMode != kApplyPlain && stop) return;
-    if constexpr (kFused) {
-        // zs is first written after the first round's barrier
-        if (!fused_update(v, k, g, base + t, live, F, zs, rv)) return;
+    for (int j = 0; j < kStageLoads; ++j) {
+        const int e = threadIdx.x + kGroupThreads * j;
+        P.nxt[j] = e < cnt ? inv_load<double, false>(src + e) : 0.0;
     }
-    if (t < 384) rs[t] = rv;
+}
+
+// zs[48 d + i] = (Inv_{0,d} r_d)_i for the nd domains of the group, whose
+// first pair is already fetched into P; rs: their residuals (visible after
+// the first barrier here).  Ends with a barrier.
+__device__ __forceinline__ void packed_rounds(PackedPair& P, const double* __restrict__ inv, int nd, const double* rs,
+                                              double* zs, double* stage) {
+    const int t = threadIdx.x;
+    const int rounds = (nd + kPairs - 1) / kPairs;
     const int row = t >> 2, q = t & 3;  // 96 rows of a pair, four quarters each
     const int dl = row / 48, i = row - 48 * dl;
     for (int p = 0; p < rounds; ++p) {
         const int cnt = min(kPairs, nd - kPairs * p) * kPacked;
 #pragma unroll
         for (int j = 0; j < kStageLoads; ++j) {
-            const int e = t + 384 * j;
-            if (e < cnt) stage[e] = nxt[j];
+            const int e = t + kGroupThreads * j;
+            if (e < cnt) stage[e] = P.nxt[j];
         }
         __syncthreads();  // the pair (and, the first time, r) are visible
-        if (p + 1 < rounds) fetch(p + 1);
+        if (p + 1 < rounds) fetch_pair(P, inv, p + 1, nd);
         const int d = kPairs * p + dl;
         double s = 0.0;
         if (d < nd) {
-            const TI* Ad = stage + dl * kPacked;
+            const double* Ad = stage + dl * kPacked;
             const double* rd = rs + 48 * d;
 #pragma unroll
             for (int m = 0; m < 12; ++m) {
                 const int kk = 12 * q + m;
                 const int idx = kk <= i ? packed_col(kk) + i - kk : packed_col(i) + kk - i;
-                s += static_cast<double>(Ad[idx]) * rd[kk];
+                s += Ad[idx] * rd[kk];
             }
         }
         // the row's four quarters, added as (q0 + q1) + (q2 + q3)
@@ -768,6 +598,31 @@ __global__ void __launch_bounds__(384) k_apply_level0_packed(SolverView v, int k
         if (q == 0 && d < nd) zs[48 * d + i] = s;
         __syncthreads();  // stage free for the next pair
     }
+}
+
+// k_apply_level0 with the symmetric-packed inverses (packed_rounds).
+template <int kMode>
+__global__ void __launch_bounds__(kGroupThreads) k_apply_level0_packed(SolverView v, int k) {
+    __shared__ double rs[kGroupThreads];
+    __shared__ double zs[kGroupThreads];
+    __shared__ double stage[kPairs * kPacked];
+    __shared__ double red[16];
+    const int g = xcd_group(blockIdx.x, v.G), t = threadIdx.x;
+    const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
+    const bool live = t < nd * 48;
+    const long long base = 3LL * g * v.RG;
+    const int slot = g * v.RG + t / 3, c = t % 3;
+    const double* inv = v.inv64[0] + static_cast<long long>(g) * v.D0 * kPacked;
+    PackedPair P;
+    fetch_pair(P, inv, 0, nd);
+    const double rv = live ? v.r[base + t] : 0.0;
+    // the stop flag is read once these loads are in flight; after a stop
+    // nothing is written
+    const int stop = v.st->done;
+    keep_loads_issued();
+    if (kMode != kApplyPlain && stop) return;
+    rs[t] = rv;
+    packed_rounds(P, inv, nd, rs, zs, stage);
     // the corrections of the slot (prolongation) at every coarse level,
     // loaded after the rounds (registers held through them would cost a
     // workgroup per CU): all unit ids at once, then all corrections at once
@@ -788,16 +643,251 @@ __global__ void __launch_bounds__(384) k_apply_level0_packed(SolverView v, int k
         v.z[base + t] = zv;
     }
     if (kMode == kApplyPlain) return;
-    if constexpr (kFused) {
-        double prho, prr;
-        block_sum2_last(rv * zv, rv * rv, red, prho, prr);
-        if (t == 0) {
-            v.P_rho[k & 1][g] = prho;
-            v.P_rr[g] = prr;
+    const double part = block_sum_last(rv * zv, red);
+    if (t == 0) v.P_rho[k & 1][g] = part;
+}
+
+// ---------------------------------------------- apply of a two-launch iteration
+// Iteration k by recurrence, in one launch after the SpMV.  Every workgroup
+// forms alpha_k = rho_{k-1} / sigma_k from the sigma partials; then
+//  - a group workgroup performs x += alpha p_k and r -= alpha q_k on its DOF
+//    and z = Inv_{0,d} r_d, with the partials of r^T z and ||r_k||^2;
+//  - a coarse workgroup updates the restricted residual of its units,
+//    C_l r_k = C_l r_{k-1} - alpha_k C_l q_k (level 1 in r_1, levels >= 2 in
+//    rc_l, C_l q_k gathered from the restriction of q_k the SpMV left; each
+//    unit has one writer), and computes y_l = Inv_{l,d} C_l r_k and the
+//    partial of (C_l r_k)^T y_l.
+// rho_k = r^T z + sum_l (C_l r)^T y_l is the sum of both kinds of partials.
+// The two do not depend on each other: the prolongation, which would make
+// level 0 wait for the coarse levels, is left to the next SpMV.  So the
+// coarse levels, a chain of round trips to memory that leaves most of the
+// machine idle (7-9 us as a launch of its own at 48^3), run beside the
+// streaming of the level-0 inverses.  Four level-1 domains share a workgroup
+// (two threads per row); a domain of a higher level, whose units gather up to
+// a hundred partials each, has one to itself (eight threads per row).
+struct RecTable {
+    int off[kMaxLv + 1];  // first coarse workgroup of each level >= 1
+    int pad;              // coarse workgroups rounded up to whole rounds of XCDs
+};
+
+// alpha_k, or false (after flagging NOT_SPD or NOT_FINITE from group 0) when
+// sigma <= 0 or a value is not finite: every workgroup sees the same sigma
+// and returns without writing.
+__device__ __forceinline__ bool rec_alpha(const SolverView& v, int k, bool report, const PartialLoads<>& sig,
+                                          double rho, double* buf, double& alpha) {
+    const double sigma = partials_sum(sig, v.P_sigma, v.G, buf);
+    if (!(sigma > 0.0) || !finite(sigma) || !finite(rho)) {
+        if (report && threadIdx.x == 0) {
+            v.st->status = (finite(sigma) && finite(rho)) ? -2 : -6;
+            v.st->done = 1;
+            v.st->iter = k - 1;
+        }
+        return false;
+    }
+    alpha = rho / sigma;
+    return true;
+}
+
+constexpr int kRecRound = 4;  // partials per lane and round in the coarse workgroups of this launch
+
+// rl[384], buf[256], sum[384], red[16]: shared memory.
+template <typename TI, int kN>
+__device__ __forceinline__ void rec_coarse(const SolverView& v, const RecTable& tab, int k, int b, double* rl,
+                                           double* buf, double* sum, double* red) {
+    const int t = threadIdx.x;
+    int l = 1;
+    while (l + 1 < v.L && b >= tab.off[l + 1]) ++l;
+    const int N = kN > 0 ? kN : v.N, n = 3 * N;
+    const TI* invl;
+    if constexpr (sizeof(TI) == 8)
+        invl = v.inv64[l];
+    else
+        invl = v.inv32[l];
+    PartialLoads<> sig = partials_load(v.P_sigma, v.G);
+    const double rho = v.st->rho[(k - 1) & 1];
+    double part = 0.0;
+    if (kN == 16 && l == 1) {
+        constexpr int kCols = 24;
+        const int dl = t / 96, half = t % 96 / 48, row = t % 48;
+        const int d = kRecLevel1 * (b - tab.off[1]) + dl;
+        const bool dom = d < v.ndom[1];
+        const int e = 48 * d + row;
+        const bool own = dom && half == 0 && e < 3 * v.units[1];
+        const int ec = own ? e : 0;
+        const double prev = v.r1[ec], qv = v.q1[ec];
+        double pre[kCols];
+        const TI* inv = invl + (dom ? static_cast<long long>(d) * 2304 : 0) + 48 * kCols * half + row;
+#pragma unroll
+        for (int j = 0; j < kCols; ++j) pre[j] = inv_load<TI, false>(inv + 48 * j);
+        const int stop = v.st->done;
+        keep_loads_issued();
+        if (stop) return;
+        double alpha;
+        if (!rec_alpha(v, k, false, sig, rho, buf, alpha)) return;
+        double r = 0.0;
+        if (own) {
+            r = prev - alpha * qv;
+            v.r1[e] = r;
+        }
+        if (half == 0) rl[48 * dl + row] = r;
+        __syncthreads();
+        double a = 0.0;
+#pragma unroll
+        for (int j = 0; j < kCols; ++j) a += pre[j] * rl[48 * dl + kCols * half + j];
+        if (half == 1) sum[48 * dl + row] = a;
+        __syncthreads();
+        if (half == 0 && dom) {
+            a += sum[48 * dl + row];
+            v.y[1][e] = a;
+            part = r * a;
         }
     } else {
-        const double part = block_sum_last(rv * zv, red);
-        if (t == 0) v.P_rho[k & 1][g] = part;
+        const int d = b - tab.off[l];
+        const int u0 = d * N, nu = min(N, v.units[l] - u0);
+        constexpr int kParts = 8, kCols = 6;  // N = 16
+        const int row = t % 48, seg = t / 48;
+        const TI* inv = invl + static_cast<long long>(d) * n * n;
+        double pre[kCols];
+        double p0 = 0.0, p1 = 0.0, p2 = 0.0, q1v = 0.0;
+        int m0 = 0, m1 = 0;
+        if constexpr (kN == 16) {
+#pragma unroll
+            for (int j = 0; j < kCols; ++j) pre[j] = inv_load<TI, false>(inv + 48 * (kCols * seg + j) + row);
+            const int u = u0 + min(t >> 4, nu - 1);
+            p0 = v.rc[l][3 * u];
+            p1 = v.rc[l][3 * u + 1];
+            p2 = v.rc[l][3 * u + 2];
+            m0 = v.cp_ptr[l][u];
+            m1 = v.cp_ptr[l][u + 1];
+        } else if (l == 1) {
+            const int e = 3 * u0 + min(t, 3 * nu - 1);
+            p0 = v.r1[e];
+            q1v = v.q1[e];
+        }
+        const int stop = v.st->done;
+        keep_loads_issued();
+        if (stop) return;
+        double alpha;
+        if (!rec_alpha(v, k, false, sig, rho, buf, alpha)) return;
+        double r = 0.0;
+        if (kN != 16 && l == 1) {
+            if (t < 3 * nu) {
+                r = p0 - alpha * q1v;
+                v.r1[3 * u0 + t] = r;
+            }
+            if (t < n) rl[t] = r;
+        } else {
+            auto put = [&](int a, bool own, double c0, double c1, double c2, double s0, double s1, double s2) {
+                if (own) {
+                    s0 = c0 - alpha * s0;
+                    s1 = c1 - alpha * s1;
+                    s2 = c2 - alpha * s2;
+                    double* rc = v.rc[l] + 3 * (u0 + a);
+                    rc[0] = s0;
+                    rc[1] = s1;
+                    rc[2] = s2;
+                }
+                rl[3 * a] = own ? s0 : 0.0;
+                rl[3 * a + 1] = own ? s1 : 0.0;
+                rl[3 * a + 2] = own ? s2 : 0.0;
+            };
+            double s0, s1, s2;
+            if constexpr (kN == 16) {
+                const int a = t >> 4, sub = t & 15;
+                if (t < 256) {  // whole waves
+                    gather_unit16<kRecRound>(v.qpart, m0, m1, sub, s0, s1, s2);
+                    if (sub == 0) put(a, a < nu, p0, p1, p2, s0, s1, s2);
+                }
+            } else {
+                const int lane = t & 63;
+                for (int a = t >> 6; a < N; a += kGroupThreads / 64) {
+                    const bool own = a < nu;
+                    gather_unit64(v.qpart, own ? v.cp_ptr[l][u0 + a] : 0, own ? v.cp_ptr[l][u0 + a + 1] : 0, lane, s0,
+                                  s1, s2);
+                    if (lane == 0) {
+                        const double* rc = v.rc[l] + 3 * (u0 + min(a, nu - 1));
+                        put(a, own, rc[0], rc[1], rc[2], s0, s1, s2);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if constexpr (kN == 16) {
+            double a = 0.0;
+#pragma unroll
+            for (int j = 0; j < kCols; ++j) a += pre[j] * rl[kCols * seg + j];
+            sum[t] = a;  // [part][row]
+            __syncthreads();
+            if (t < 48) {
+#pragma unroll
+                for (int j = 1; j < kParts; ++j) a += sum[48 * j + t];
+                v.y[l][3 * u0 + t] = a;
+                part = rl[t] * a;
+            }
+        } else if (t < n) {
+            double a = 0.0;
+#pragma unroll 8
+            for (int kk = 0; kk < n; ++kk) a += inv_load<TI, false>(inv + static_cast<long long>(kk) * n + t) * rl[kk];
+            v.y[l][3 * u0 + t] = a;
+            part = rl[t] * a;
+        }
+    }
+    part = block_sum_last(part, red);
+    if (t == 0) v.P_rho[k & 1][v.G + b] = part;
+}
+
+template <typename TI, int kN>
+__global__ void __launch_bounds__(kGroupThreads) k_apply_rec(SolverView v, RecTable tab, int k) {
+    constexpr bool kPackedInv = kN == 16 && sizeof(TI) == 8;
+    __shared__ double rs[kGroupThreads];
+    __shared__ double zs[kGroupThreads];
+    __shared__ double stage[kPackedInv ? kPairs * kPacked : kGroupThreads];
+    __shared__ double red[16];
+    const int t = threadIdx.x;
+    if (static_cast<int>(blockIdx.x) < tab.pad) {
+        if (static_cast<int>(blockIdx.x) < v.ncb) rec_coarse<TI, kN>(v, tab, k, blockIdx.x, rs, zs, stage, red);
+        return;
+    }
+    const int N = kN > 0 ? kN : v.N;
+    const int n = 3 * N;
+    const int g = xcd_group(blockIdx.x - tab.pad, v.G);
+    const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
+    const bool live = t < nd * n;
+    const long long i = 3LL * g * v.RG + (live ? t : 0);
+    PackedPair P;
+    const double* inv = v.inv64[0] + static_cast<long long>(g) * v.D0 * kPacked;
+    if constexpr (kPackedInv) fetch_pair(P, inv, 0, nd);
+    const PartialLoads<> sig = partials_load(v.P_sigma, v.G);
+    const double rho = v.st->rho[(k - 1) & 1];
+    const double xv = v.x[i], pv = v.p[k & 1][i], ro = v.r[i], qv = v.q[i];
+    // the stop flag is read once these loads are in flight; after a stop
+    // nothing is written
+    const int stop = v.st->done;
+    keep_loads_issued();
+    if (stop) return;
+    double alpha;
+    if (!rec_alpha(v, k, g == 0, sig, rho, zs, alpha)) return;  // zs is first written after a later barrier
+    double rv = 0.0;
+    if (live) {
+        v.x[i] = xv + alpha * pv;
+        rv = ro - alpha * qv;
+        v.r[i] = rv;
+    }
+    rs[t] = rv;
+    double zv = 0.0;
+    if constexpr (kPackedInv) {
+        packed_rounds(P, inv, nd, rs, zs, stage);
+        if (live) zv = zs[t];
+    } else {
+        __syncthreads();
+        if (live) zv = full_row<TI, kN>(level0_inverses<TI>(v), n, g * v.D0 + t / n, t % n, rs + t / n * n);
+    }
+    if (live) v.z[i] = zv;
+    double prho, prr;
+    block_sum2_last(rv * zv, rv * rv, red, prho, prr);
+    if (t == 0) {
+        v.P_rho[k & 1][g] = prho;
+        v.P_rr[g] = prr;
     }
 }
 
@@ -872,25 +962,22 @@ hipError_t launch_apply_coarse(const SolverView& v, bool f32, int mode, int k, d
 template <typename TI, int kN>
 void launch_level0_t(const SolverView& v, int mode, int k, hipStream_t s) {
     dim3 g(v.G), b(round_waves(3 * v.RG));
-    if (kN == 16 && v.packed0 && sizeof(TI) == 8) {
+    if constexpr (kN == 16 && sizeof(TI) == 8) {
+        b = dim3(kGroupThreads);
         if (mode == kApplyPlain)
-            launch_kernel((k_apply_level0_packed<TI, kApplyPlain>), g, b, 0, s, v, k);
+            launch_kernel(k_apply_level0_packed<kApplyPlain>, g, b, 0, s, v, k);
         else if (mode == kApplyInit)
-            launch_kernel((k_apply_level0_packed<TI, kApplyInit>), g, b, 0, s, v, k);
-        else if (mode == kApplyIter)
-            launch_kernel((k_apply_level0_packed<TI, kApplyIter>), g, b, 0, s, v, k);
+            launch_kernel(k_apply_level0_packed<kApplyInit>, g, b, 0, s, v, k);
         else
-            launch_kernel((k_apply_level0_packed<TI, kApplyRec>), g, b, 0, s, v, k);
-        return;
+            launch_kernel(k_apply_level0_packed<kApplyIter>, g, b, 0, s, v, k);
+    } else {
+        if (mode == kApplyPlain)
+            launch_kernel((k_apply_level0<TI, kN, kApplyPlain>), g, b, 0, s, v, k);
+        else if (mode == kApplyInit)
+            launch_kernel((k_apply_level0<TI, kN, kApplyInit>), g, b, 0, s, v, k);
+        else
+            launch_kernel((k_apply_level0<TI, kN, kApplyIter>), g, b, 0, s, v, k);
     }
-    if (mode == kApplyPlain)
-        launch_kernel((k_apply_level0<TI, kN, kApplyPlain>), g, b, 0, s, v, k);
-    else if (mode == kApplyInit)
-        launch_kernel((k_apply_level0<TI, kN, kApplyInit>), g, b, 0, s, v, k);
-    else if (mode == kApplyIter)
-        launch_kernel((k_apply_level0<TI, kN, kApplyIter>), g, b, 0, s, v, k);
-    else
-        launch_kernel((k_apply_level0<TI, kN, kApplyRec>), g, b, 0, s, v, k);
 }
 
 hipError_t launch_apply_level0(const SolverView& v, bool f32, int mode, int k, hipStream_t s) {
@@ -900,6 +987,27 @@ hipError_t launch_apply_level0(const SolverView& v, bool f32, int mode, int k, h
     } else {
         if (f32) launch_level0_t<float, 0>(v, mode, k, s);
         else launch_level0_t<double, 0>(v, mode, k, s);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_apply_rec(const SolverView& v, bool f32, int k, hipStream_t s) {
+    RecTable tab{};
+    int acc = 0;
+    for (int l = 1; l < v.L; ++l) {
+        tab.off[l] = acc;
+        acc += l == 1 && v.N == 16 ? ceil_div(v.ndom[1], kRecLevel1) : v.ndom[l];
+    }
+    for (int l = v.L; l <= kMaxLv; ++l) tab.off[l] = acc;
+    if (acc != v.ncb) return hipErrorInvalidValue;  // the P_rho arrays hold G + ncb partials
+    tab.pad = ceil_div(acc, kXcds) * kXcds;
+    dim3 g(tab.pad + v.G), b(kGroupThreads);
+    if (v.N == 16) {
+        if (f32) launch_kernel((k_apply_rec<float, 16>), g, b, 0, s, v, tab, k);
+        else launch_kernel((k_apply_rec<double, 16>), g, b, 0, s, v, tab, k);
+    } else {
+        if (f32) launch_kernel((k_apply_rec<float, 0>), g, b, 0, s, v, tab, k);
+        else launch_kernel((k_apply_rec<double, 0>), g, b, 0, s, v, tab, k);
     }
     return hipGetLastError();
 }

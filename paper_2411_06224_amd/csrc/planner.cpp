@@ -361,6 +361,69 @@ void symmetric_storage(Plan& P) {
     P.sym = P.RG <= 256 && P.maxT <= kMaxTransposed;
 }
 
+// The level-1 units each group's SpMV reads (see Plan::hptr).
+void halo_units(Plan& P) {
+    const int NS = P.NS, RG = P.RG, G = P.G;
+    P.halo = false;
+    P.maxH = 0;
+    P.hptr.assign(static_cast<size_t>(G) + 1, 0);
+    std::vector<int> units;
+    std::vector<int> ext;
+    std::vector<int> seen(P.L > 1 ? P.units[1] : 0, -1);
+    for (int g = 0; g < G && P.L > 1; ++g) {
+        const int r0 = g * RG, r1 = std::min(r0 + RG, NS);
+        ext.clear();
+        for (int k = P.rp0[r0]; k < P.rp0[r1]; ++k) {
+            const int j = P.ci0[k];
+            if (j >= r0 && j < r1) continue;
+            const int u = P.anc[j];
+            if (seen[u] != g) {
+                seen[u] = g;
+                ext.push_back(u);
+            }
+        }
+        const int n = P.g_u1[g + 1] - P.g_u1[g] + static_cast<int>(ext.size());
+        P.maxH = std::max(P.maxH, n);
+        if (n > kMaxHalo) {
+            P.maxH = 0;
+            P.hptr.clear();
+            return;
+        }
+        std::sort(ext.begin(), ext.end());
+        for (int u = P.g_u1[g]; u < P.g_u1[g + 1]; ++u) units.push_back(u);
+        units.insert(units.end(), ext.begin(), ext.end());
+        P.hptr[g + 1] = static_cast<int>(units.size());
+    }
+    P.halo = true;
+    std::vector<long long> base(P.L + 1, 0);  // first position of each level's correction
+    for (int l = 1; l < P.L; ++l) base[l + 1] = base[l] + static_cast<long long>(P.ndom[l]) * P.N;
+    P.hy.resize(units.size() * static_cast<size_t>(std::max(P.L - 1, 0)));
+    P.hidx.assign(P.ci0.size(), 0);
+    P.hidx_sym.assign(P.sym ? P.sci.size() : 0, 0);
+    std::vector<int> local(P.L > 1 ? P.units[1] : 0, 0);
+    for (int g = 0; g < G && P.L > 1; ++g) {
+        const int r0 = g * RG, r1 = std::min(r0 + RG, NS), h0 = P.hptr[g], n = P.hptr[g + 1] - h0;
+        int* y = P.hy.data() + static_cast<size_t>(P.L - 1) * h0;
+        for (int i = 0; i < n; ++i) {
+            int a = units[h0 + i];
+            local[a] = i;
+            for (int l = 1; l < P.L; ++l) {
+                if (l > 1) a = P.up[l - 1][a];
+                y[static_cast<size_t>(l - 1) * n + i] = static_cast<int>(base[l] + a);
+            }
+        }
+        size_t o = P.sym ? P.srp[r0] : 0;
+        for (int s = r0; s < r1; ++s)
+            for (int k = P.rp0[s]; k < P.rp0[s + 1]; ++k) {
+                const int j = P.ci0[k];
+                const bool inside = j >= r0 && j < r1;
+                const uint16_t h = inside ? 0 : static_cast<uint16_t>(local[P.anc[j]]);
+                P.hidx[k] = h;
+                if (P.sym && (!inside || j >= s)) P.hidx_sym[o++] = h;
+            }
+    }
+}
+
 // Workgroup order of the SpMV.  The group kernels give each XCD a
 // contiguous range of groups, dispatched in order.  Groups with far more
 // stored blocks than the mean (rows coupled to many distant columns, such as
@@ -713,6 +776,7 @@ std::string analyze(int V, int nnzb, const int32_t* row_ptr, const int32_t* col_
         }
 
     symmetric_storage(P);
+    halo_units(P);
     spmv_order(P);
 
     // ---- per-node units for reports

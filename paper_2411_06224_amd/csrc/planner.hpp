@@ -13,6 +13,11 @@ constexpr int kMaxLevels = 16;
 // The symmetric storage keeps a group's transposed-entry list in LDS; groups
 // with more entries than this use the full storage.
 constexpr int kMaxTransposed = 4096;
+// The SpMV of a two-launch iteration stages the coarse correction of every
+// level-1 unit a group of rows reads (its own and those of the columns
+// outside the group) in LDS: 24 bytes each, so 512 take 12 KB beside the
+// product planes.  A system with a larger group keeps the direct iteration.
+constexpr int kMaxHalo = 512;
 // The group kernels deal workgroup b to XCD b % kXcdCount, each XCD taking a
 // contiguous range of groups (xcd_group on the device).
 constexpr int kXcdCount = 8;
@@ -104,6 +109,20 @@ struct Plan {
     std::vector<int> srp, sci, sperm, tptr, tidx;
     std::vector<uint8_t> srow;
     int maxT = 0;
+
+    // Level-1 units whose coarse correction group g reads, at [hptr[g],
+    // hptr[g+1]): its own (ascending), then those of its rows' columns outside
+    // the group (ascending).  hy holds, for unit i of the group's n and level
+    // l >= 1, the position of its ancestor's correction in the coarse
+    // vectors laid end to end (level 1 first, ndom[l] * N units each), at
+    // [(L-1) hptr[g] + (l-1) n + i].  hidx / hidx_sym: the group's local unit
+    // of every slot-ordered / symmetrically stored block whose column lies
+    // outside the group (0 for the others).  All empty (halo = false) when
+    // some group reads more than kMaxHalo units.
+    bool halo = false;
+    int maxH = 0;  // most units of one group
+    std::vector<int> hptr, hy;
+    std::vector<uint16_t> hidx, hidx_sym;
 
     // SpMV group of each workgroup when the groups' stored blocks are
     // uneven (empty: the contiguous per-XCD mapping of the group kernels)

@@ -11,6 +11,7 @@
 // node classes of the tet cube) or long contact / affine rows cost the same
 // per block.  Products and sums are FP64; FP32-stored values are widened on
 // load.
+#include "decision.hpp"
 #include "launch.hpp"
 #include "restrict.hpp"
 
@@ -74,16 +75,24 @@ struct Blocks {
 };
 
 // The vector H multiplies: x itself, or the new search direction
-// z + beta p formed on the fly from the previous one.
+// z + beta p formed on the fly from the previous one.  h: the group's local
+// unit of the column (kUnits: its coarse correction, staged in LDS, is still
+// to be added to z).
 struct XVec {
+    static constexpr bool kUnits = false;
     const double* __restrict__ x;
-    __device__ __forceinline__ double at(int i) const { return x[i]; }
+    __device__ __forceinline__ double at(int i, int) const { return x[i]; }
 };
+template <bool kSplit>
 struct XDir {
+    static constexpr bool kUnits = kSplit;
     const double* __restrict__ z;
     const double* __restrict__ p;
     double beta;
-    __device__ __forceinline__ double at(int i) const { return __fma_rn(beta, p[i], z[i]); }
+    const double* ycor;  // LDS, 3 per local unit
+    __device__ __forceinline__ double at(int i, int h) const {
+        return __fma_rn(beta, p[i], kSplit ? z[i] + ycor[h] : z[i]);
+    }
 };
 
 // Column indices of this thread's blocks t, t + 256, ... of the chunk
@@ -94,15 +103,22 @@ constexpr int kRowPer = kChunk / kThreads;
 
 struct ChunkCols {
     int j[kRowPer];
+    int h[kRowPer];  // local unit of each column (kUnits)
 };
 
-__device__ __forceinline__ ChunkCols chunk_cols(const int* __restrict__ ci, int cs, int ke) {
+template <bool kUnits = false>
+__device__ __forceinline__ ChunkCols chunk_cols(const int* __restrict__ ci, int cs, int ke,
+                                                const uint16_t* __restrict__ hidx = nullptr) {
     ChunkCols c;
 #pragma unroll
-    for (int kk = 0; kk < kRowPer; ++kk) c.j[kk] = 0;
+    for (int kk = 0; kk < kRowPer; ++kk) c.j[kk] = c.h[kk] = 0;
     if (cs < ke) {
 #pragma unroll
-        for (int kk = 0; kk < kRowPer; ++kk) c.j[kk] = ci[min(cs + static_cast<int>(threadIdx.x) + kk * kThreads, ke - 1)];
+        for (int kk = 0; kk < kRowPer; ++kk) {
+            const int k = min(cs + static_cast<int>(threadIdx.x) + kk * kThreads, ke - 1);
+            c.j[kk] = ci[k];
+            if constexpr (kUnits) c.h[kk] = hidx[k];
+        }
     }
     return c;
 }
@@ -122,7 +138,8 @@ __device__ __forceinline__ int spmv_group(const SolverView& v) {
 template <typename T, bool kPlanar, typename X, bool kLds = false>
 __device__ __forceinline__ void stream_rows(const int* __restrict__ rp, const int* __restrict__ ci,
                                             Blocks<T, kPlanar> H, X x, int r0, int r1, double* prod,
-                                            double (&acc)[2], const ChunkCols& first, const double* xs = nullptr) {
+                                            double (&acc)[2], const ChunkCols& first, const double* xs = nullptr,
+                                            const uint16_t* __restrict__ hidx = nullptr) {
     const int t = threadIdx.x;
     const int nown = 3 * (r1 - r0);
     int rb[2], re[2];
@@ -154,16 +171,17 @@ __device__ __forceinline__ void stream_rows(const int* __restrict__ rp, const in
                 x1 = xs[3 * jl + 1];
                 x2 = xs[3 * jl + 2];
             } else {
-                x0 = x.at(3 * j);
-                x1 = x.at(3 * j + 1);
-                x2 = x.at(3 * j + 2);
+                const int h = 3 * cc.h[kk];
+                x0 = x.at(3 * j, h);
+                x1 = x.at(3 * j + 1, h + 1);
+                x2 = x.at(3 * j + 2, h + 2);
             }
             const int e = k - cs;
             prod[e] = H.at(k, 0) * x0 + H.at(k, 1) * x1 + H.at(k, 2) * x2;
             prod[kPlane + e] = H.at(k, 3) * x0 + H.at(k, 4) * x1 + H.at(k, 5) * x2;
             prod[2 * kPlane + e] = H.at(k, 6) * x0 + H.at(k, 7) * x1 + H.at(k, 8) * x2;
         }
-        nc = chunk_cols(ci, cs + kChunk, ke);  // the next chunk's columns, in flight through the sums
+        nc = chunk_cols<X::kUnits>(ci, cs + kChunk, ke, hidx);  // the next chunk's columns, in flight through the sums
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -198,18 +216,21 @@ constexpr int kSymPer = kSymChunk / kThreads;
 struct SymCols {
     int j[kSymPer];
     int r[kSymPer];
+    int h[kSymPer];  // local unit of each column (kUnits)
 };
 
+template <bool kUnits = false>
 __device__ __forceinline__ SymCols sym_cols(const SolverView& v, int cs, int ke) {
     SymCols c;
 #pragma unroll
-    for (int kk = 0; kk < kSymPer; ++kk) c.j[kk] = c.r[kk] = 0;
+    for (int kk = 0; kk < kSymPer; ++kk) c.j[kk] = c.r[kk] = c.h[kk] = 0;
     if (cs < ke) {
 #pragma unroll
         for (int kk = 0; kk < kSymPer; ++kk) {
             const int k = min(cs + static_cast<int>(threadIdx.x) + kk * kThreads, ke - 1);
             c.j[kk] = v.sci[k];
             c.r[kk] = v.srow[k];
+            if constexpr (kUnits) c.h[kk] = v.hidx[k];
         }
     }
     return c;
@@ -255,9 +276,10 @@ __device__ __forceinline__ void stream_sym(const SolverView& v, const T* __restr
                 x1 = xs[3 * jl + 1];
                 x2 = xs[3 * jl + 2];
             } else {
-                x0 = xg.at(3 * j);
-                x1 = xg.at(3 * j + 1);
-                x2 = xg.at(3 * j + 2);
+                const int h = 3 * cc.h[kk];
+                x0 = xg.at(3 * j, h);
+                x1 = xg.at(3 * j + 1, h + 1);
+                x2 = xg.at(3 * j + 2, h + 2);
             }
             const double h0 = static_cast<double>(H[k]), h1 = static_cast<double>(H[st + k]),
                          h2 = static_cast<double>(H[2 * st + k]), h3 = static_cast<double>(H[3 * st + k]),
@@ -275,7 +297,7 @@ __device__ __forceinline__ void stream_sym(const SolverView& v, const T* __restr
                 prod[5 * kSymPlane + e] = h2 * y0 + h5 * y1 + h8 * y2;
             }
         }
-        nc = sym_cols(v, cs + kSymChunk, ke);  // the next chunk's columns, in flight through the sums
+        nc = sym_cols<X::kUnits>(v, cs + kSymChunk, ke);  // the next chunk's columns, in flight through the sums
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -345,46 +367,138 @@ __device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, 
     }
 }
 
+// The coarse corrections of a group's level-1 units (kSplit), sum over the
+// levels of y_l at the unit's ancestors, level 1 first: the same sum in every
+// group that reads a unit.  unit_load issues the position loads of a thread's
+// first item (unit t / 3, component t % 3), unit_gather the corrections of
+// its first kUnitLevels levels; unit_stage adds up, takes the further levels
+// and items, and leaves them in LDS.  The first item's two round trips
+// overlap the rho sum.
+constexpr int kUnitLevels = 8;
+
+struct UnitLoads {
+    int n;                   // 3 x units of the group
+    const int* pos;          // position of the thread's item at level 1; levels n / 3 apart
+    int at[kUnitLevels];
+    double y[kUnitLevels];
+};
+
+__device__ __forceinline__ UnitLoads unit_load(const SolverView& v, int g) {
+    UnitLoads U;
+    const int h0 = v.hptr[g], n = v.hptr[g + 1] - h0;
+    U.n = 3 * n;
+    U.pos = v.hy + static_cast<long long>(v.L - 1) * h0;
+    const int i = min(static_cast<int>(threadIdx.x) / 3, n - 1);
+#pragma unroll
+    for (int l = 0; l < kUnitLevels; ++l) U.at[l] = n > 0 && l + 1 < v.L ? U.pos[l * n + i] : 0;
+    return U;
+}
+
+__device__ __forceinline__ void unit_gather(const SolverView& v, UnitLoads& U) {
+    const int c = threadIdx.x % 3;
+#pragma unroll
+    for (int l = 0; l < kUnitLevels; ++l) U.y[l] = l + 1 < v.L ? v.yall[3LL * U.at[l] + c] : 0.0;
+}
+
+__device__ __forceinline__ void unit_stage(const SolverView& v, const UnitLoads& U, double* ycor) {
+    const int n = U.n / 3;
+    for (int e = threadIdx.x; e < U.n; e += kThreads) {
+        const int i = e / 3, c = e - 3 * i;
+        double s = 0.0;
+        if (e < kThreads) {
+#pragma unroll
+            for (int l = 0; l < kUnitLevels; ++l)
+                if (l + 1 < v.L) s += U.y[l];
+        }
+        for (int l0 = e < kThreads ? kUnitLevels : 0; l0 + 1 < v.L; l0 += kUnitLevels) {
+            int at[kUnitLevels];
+            double y[kUnitLevels];
+#pragma unroll
+            for (int l = 0; l < kUnitLevels; ++l) at[l] = U.pos[min(l0 + l, v.L - 2) * n + i];
+#pragma unroll
+            for (int l = 0; l < kUnitLevels; ++l) y[l] = v.yall[3LL * at[l] + c];
+#pragma unroll
+            for (int l = 0; l < kUnitLevels; ++l)
+                if (l0 + l + 1 < v.L) s += y[l];
+        }
+        ycor[e] = s;
+    }
+}
+
+// The group's own units are the first of its list: local unit of slot s.
+__device__ __forceinline__ int own_unit(const SolverView& v, int g, int slot) {
+    return v.L > 1 ? v.anc[slot] - v.g_u1[g] : -1;  // negative: empty slot or no coarse level
+}
+
+// Workgroup G of a split SpMV takes the decision on r_{k-1}.
+__device__ __forceinline__ bool decide_only(const SolverView& v, int k, int flags, double* buf) {
+    if (static_cast<int>(blockIdx.x) < v.G) return false;
+    convergence_decision(v, false, k - 1, 0.0, flags, buf);
+    return true;
+}
+
+constexpr int kRhoPer = 8;  // rho partials a thread loads ahead: up to 2048 in all
+
 // PCG iteration k over the solver's group of slots: the new direction
 // p_k = z_{k-1} + beta_{k-1} p_{k-1} (beta = rho_{k-1} / rho_{k-2} summed from
-// the group partials; p_1 = z_0) is formed first on the group's own slots
-// (into LDS and p_k) and, for columns outside the group, wherever H gathers
-// it; q = H p_k and the partial of p_k^T q.  Every workgroup forms the same
-// beta and the same fused multiply-add, so a direction entry has the same
-// bits in every workgroup that reads it.
-template <typename T, int kRQ>
-__global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __restrict__ H, int k) {
+// the partials; p_1 = z_0) is formed first on the group's own slots (into LDS
+// and p_k) and, for columns outside the group, wherever H gathers it; q = H p_k
+// and the partial of p_k^T q.  Every workgroup forms the same beta, the same
+// coarse corrections and the same fused multiply-add, so a direction entry has
+// the same bits in every workgroup that reads it.
+//
+// kSplit: z_{k-1} = v.z + the coarse corrections, which the level-0 apply left
+// out so that it need not wait for the coarse levels.  A group reads few
+// distinct level-1 units (about 60 at 48^3, with nine levels), so it sums
+// each unit's levels once into LDS; an outside column then costs one 16-bit
+// index and three LDS reads more.
+template <typename T, int kRQ, bool kSplit>
+__global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __restrict__ H, int k, int flags) {
     __shared__ double prod[3 * kPlane];
     __shared__ double buf[256];
-    __shared__ double xs[384];
+    extern __shared__ double dyn[];  // xs[3 RG] (+ ycor[3 maxH])
+    if (kSplit && decide_only(v, k, flags, buf)) return;
     const int t = threadIdx.x;
     const int g = spmv_group(v);
     const int r0 = g * v.RG, r1 = min(r0 + v.RG, v.NS);
     const int nown = 3 * (r1 - r0);
+    double* xs = dyn;
+    double* ycor = dyn + 3 * v.RG;
     // every independent load before the first wait: the rho partials first
     // (needed first; loads complete in issue order), then the group's own
     // entries of z and p_{k-1}, unconditionally at clamped indices (see
     // partials_load)
     const double* Prho = v.P_rho[(k - 1) & 1];
-    const PartialLoads rl = partials_load(Prho, v.G);
+    const int nrho = kSplit ? v.G + v.ncb : v.G;
+    UnitLoads U{};
+    if constexpr (kSplit) U = unit_load(v, g);
+    const auto rl = partials_load<kSplit ? kRhoPer : 4>(Prho, nrho);
     const double* pold = k > 1 ? v.p[(k - 1) & 1] : v.z;  // k = 1: p_1 = z_0 (+ 0 * z_0)
     double zo[2], po[2];
+    int un[2] = {-1, -1};
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        const long long e = 3LL * r0 + min(t + q * kThreads, nown - 1);
+        const int o = min(t + q * kThreads, nown - 1);
+        const long long e = 3LL * r0 + o;
         zo[q] = v.z[e];
         po[q] = pold[e];
+        if constexpr (kSplit) un[q] = own_unit(v, g, r0 + o / 3);
     }
-    const ChunkCols c0 = chunk_cols(v.ci0, v.rp0[r0], v.rp0[r1]);
+    const ChunkCols c0 = chunk_cols<kSplit>(v.ci0, v.rp0[r0], v.rp0[r1], v.hidx);
     RestrictLoads<> pl{};
     if constexpr (kRQ) pl = restrict_load(v, g);
     const int stop = v.st->done;
     keep_loads_issued();
     if (stop) return;  // after a stop nothing is written
-    // rho_{k-1} from the group partials; rho_{k-2} as the previous SpMV recorded it
+    // rho_{k-1} from the partials; rho_{k-2} as the previous SpMV recorded it
     const double rk2 = v.st->rho[k & 1];
-    const double rk1 = partials_sum<false>(rl, Prho, v.G, buf);  // buf is next written after later barriers
+    if constexpr (kSplit) unit_gather(v, U);
+    const double rk1 = partials_sum<false>(rl, Prho, nrho, buf);  // buf is next written after later barriers
     if (g == 0 && t == 0) v.st->rho[(k - 1) & 1] = rk1;
+    if constexpr (kSplit) {
+        unit_stage(v, U, ycor);
+        __syncthreads();
+    }
     const double beta = k > 1 ? rk1 / rk2 : 0.0;
     double* pk = v.p[k & 1];
     double pv[2];
@@ -393,6 +507,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
         const int o = t + q * kThreads;
         pv[q] = 0.0;
         if (o < nown) {
+            if (kSplit && un[q] >= 0) zo[q] += ycor[3 * un[q] + o % 3];
             pv[q] = __fma_rn(beta, po[q], zo[q]);
             pk[3LL * r0 + o] = pv[q];
             xs[o] = pv[q];
@@ -400,59 +515,72 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     }
     __syncthreads();
     double acc[2];
-    stream_rows<T, true, XDir, true>(v.rp0, v.ci0, Blocks<T, true>{H, v.nnzb}, XDir{v.z, pold, beta}, r0, r1, prod,
-                                     acc, c0, xs);
+    stream_rows<T, true, XDir<kSplit>, true>(v.rp0, v.ci0, Blocks<T, true>{H, v.nnzb},
+                                             XDir<kSplit>{v.z, pold, beta, ycor}, r0, r1, prod, acc, c0, xs, v.hidx);
     finish_pq<kRQ>(v, g, nown, r0, acc, pv, prod, buf, pl);
 }
 
 // k_spmv_pq on the group-symmetric storage: the group forms the new
 // direction on its own slots first (into LDS and p_k) and gathers it only for
 // columns outside the group.
-template <typename T, int kRQ>
-__global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T* __restrict__ H, int k) {
+template <typename T, int kRQ, bool kSplit>
+__global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T* __restrict__ H, int k, int flags) {
     __shared__ double prod[6 * kSymPlane];
     __shared__ double buf[256];
-    extern __shared__ double dyn[];  // xs[3 RG] doubles + tl[maxT] ints
+    extern __shared__ double dyn[];  // xs[3 RG] doubles (+ ycor[3 maxH]) + tl[maxT] ints
+    if (kSplit && decide_only(v, k, flags, buf)) return;
     const int t = threadIdx.x;
     const int g = spmv_group(v);
     const int r0 = g * v.RG, r1 = min(r0 + v.RG, v.NS);
     const int nown = 3 * (r1 - r0);
     double* xs = dyn;
-    int* tl = reinterpret_cast<int*>(dyn + 3 * v.RG);
+    double* ycor = dyn + 3 * v.RG;
+    int* tl = reinterpret_cast<int*>(ycor + (kSplit ? 3 * v.maxH : 0));
     // every independent load before the first wait: the rho partials first
     // (needed first; loads complete in issue order), then the group's own
     // entries of z and p_{k-1} and its transposed-entry list, all
     // unconditionally at clamped indices (see partials_load); the list goes
     // to LDS only after the rho sum
     const double* Prho = v.P_rho[(k - 1) & 1];
-    const PartialLoads rl = partials_load(Prho, v.G);
+    const int nrho = kSplit ? v.G + v.ncb : v.G;
+    UnitLoads U{};
+    if constexpr (kSplit) U = unit_load(v, g);
+    const auto rl = partials_load<kSplit ? kRhoPer : 4>(Prho, nrho);
     const double* pold = k > 1 ? v.p[(k - 1) & 1] : v.z;  // k = 1: p_1 = z_0 (+ 0 * z_0)
     double zo[2], po[2];
+    int un[2] = {-1, -1};
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        const long long e = 3LL * r0 + min(t + q * kThreads, nown - 1);
+        const int o = min(t + q * kThreads, nown - 1);
+        const long long e = 3LL * r0 + o;
         zo[q] = v.z[e];
         po[q] = pold[e];
+        if constexpr (kSplit) un[q] = own_unit(v, g, r0 + o / 3);
     }
     const int tb0 = v.tptr[r0], tn = v.tptr[r1] - tb0;
     const int* tsrc = tn > 0 ? v.tidx + tb0 : v.srp;  // srp: a stand-in with entries when the list is empty
     int tlr[kTlRegs];
 #pragma unroll
     for (int j = 0; j < kTlRegs; ++j) tlr[j] = tsrc[min(t + j * kThreads, max(tn - 1, 0))];
-    const SymCols c0 = sym_cols(v, v.srp[r0], v.srp[r1]);
+    const SymCols c0 = sym_cols<kSplit>(v, v.srp[r0], v.srp[r1]);
     RestrictLoads<> pl{};
     if constexpr (kRQ) pl = restrict_load(v, g);
     const int stop = v.st->done;
     keep_loads_issued();
     if (stop) return;  // after a stop nothing is written
     const double rk2 = v.st->rho[k & 1];
-    // rho_{k-1} from the group partials; rho_{k-2} as the previous SpMV recorded it
-    const double rk1 = partials_sum<false>(rl, Prho, v.G, buf);  // buf is next written after later barriers
+    if constexpr (kSplit) unit_gather(v, U);
+    // rho_{k-1} from the partials; rho_{k-2} as the previous SpMV recorded it
+    const double rk1 = partials_sum<false>(rl, Prho, nrho, buf);  // buf is next written after later barriers
     if (g == 0 && t == 0) v.st->rho[(k - 1) & 1] = rk1;
 #pragma unroll
     for (int j = 0; j < kTlRegs; ++j)
         if (t + j * kThreads < tn) tl[t + j * kThreads] = tlr[j];
     for (int e = t + kTlRegs * kThreads; e < tn; e += kThreads) tl[e] = v.tidx[tb0 + e];
+    if constexpr (kSplit) {
+        unit_stage(v, U, ycor);
+        __syncthreads();
+    }
     const double beta = k > 1 ? rk1 / rk2 : 0.0;
     double* pk = v.p[k & 1];
     double pv[2];
@@ -461,6 +589,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
         const int o = t + q * kThreads;
         pv[q] = 0.0;
         if (o < nown) {
+            if (kSplit && un[q] >= 0) zo[q] += ycor[3 * un[q] + o % 3];
             pv[q] = __fma_rn(beta, po[q], zo[q]);
             pk[3LL * r0 + o] = pv[q];
         }
@@ -468,7 +597,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     }
     __syncthreads();
     double acc[2];
-    stream_sym<T>(v, H, XDir{v.z, pold, beta}, xs, tl, tb0, r0, r1, prod, acc, c0);
+    stream_sym<T>(v, H, XDir<kSplit>{v.z, pold, beta, ycor}, xs, tl, tb0, r0, r1, prod, acc, c0);
     finish_pq<kRQ>(v, g, nown, r0, acc, pv, prod, buf, pl);
 }
 
@@ -539,27 +668,38 @@ hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void
     return hipGetLastError();
 }
 
-template <int kRQ>
+template <int kRQ, bool kSplit>
 void launch_spmv_pq_t(const SolverView& v, bool f32, int k, hipStream_t s) {
-    dim3 g(v.G), b(kThreads);
+    dim3 g(v.G + (kSplit ? 1 : 0)), b(kThreads);
+    const int flags = f32 ? kFlagMixed : 0;
+    const size_t vec = sizeof(double) * 3 * (static_cast<size_t>(v.RG) + (kSplit ? v.maxH : 0));
     if (v.sym && !f32) {
-        const size_t shmem = sizeof(double) * 3 * v.RG + sizeof(int) * v.maxT;
-        launch_kernel(k_spmv_pq_sym<double, kRQ>, g, b, shmem, s, v, static_cast<const double*>(v.H64), k);
+        launch_kernel(k_spmv_pq_sym<double, kRQ, kSplit>, g, b, vec + sizeof(int) * v.maxT, s, v,
+                      static_cast<const double*>(v.H64), k, flags);
     } else if (f32) {
-        launch_kernel(k_spmv_pq<float, kRQ>, g, b, 0, s, v, static_cast<const float*>(v.H32), k);
+        launch_kernel(k_spmv_pq<float, kRQ, kSplit>, g, b, vec, s, v, static_cast<const float*>(v.H32), k, flags);
     } else {
-        launch_kernel(k_spmv_pq<double, kRQ>, g, b, 0, s, v, static_cast<const double*>(v.H64), k);
+        launch_kernel(k_spmv_pq<double, kRQ, kSplit>, g, b, vec, s, v, static_cast<const double*>(v.H64), k, flags);
     }
 }
 
-hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool restrict_q, hipStream_t s) {
-    if (!restrict_q)
-        launch_spmv_pq_t<0>(v, f32, k, s);
-    else if (v.rfast)
-        launch_spmv_pq_t<1>(v, f32, k, s);
-    else
+hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool restrict_q, bool split, hipStream_t s) {
+    if (restrict_q && !v.rfast)
         return hipErrorInvalidValue;  // the solver restricts q in the SpMV only where restrict_fast_ok holds
+    if (restrict_q && split)
+        launch_spmv_pq_t<1, true>(v, f32, k, s);
+    else if (restrict_q)
+        launch_spmv_pq_t<1, false>(v, f32, k, s);
+    else if (split)
+        launch_spmv_pq_t<0, true>(v, f32, k, s);
+    else
+        launch_spmv_pq_t<0, false>(v, f32, k, s);
     return hipGetLastError();
+}
+
+size_t spmv_shared_bytes(int RG, int maxT, bool sym) {
+    return sizeof(double) * (max(3 * kPlane, 6 * kSymPlane) + 256 + 3 * static_cast<size_t>(RG)) +
+           (sym ? sizeof(int) * static_cast<size_t>(maxT) : 0);
 }
 
 int spmv_threads() { return kThreads; }
