@@ -28,7 +28,7 @@ struct Layout {
     size_t total = 0;
     size_t remap, map, perm_src, perm_full, rp0, ci0, lead1, anc, g_u1, srp, sci, srow, tptr, tidx;
     size_t red_ptr[kMaxLv], red_src[kMaxLv], dom_ptr[kMaxLv], dom_blk[kMaxLv], dom_ab[kMaxLv];
-    size_t ganc, gpos, gmask, cp_ptr[kMaxLv], lmask, gorder, gu1_slot, gu1_mask, gw_pos, gw_li, gw_mask, hptr, hy, hidx;
+    size_t ganc, gpos, gmask, cp_ptr[kMaxLv], lmask, gorder, gu1_slot, gu1_mask, gw_pos, gw_li, gw_mask, hptr, hu, h2ptr, hy, hpar, hidx;
     size_t H64, H32, A[kMaxLv], inv64[kMaxLv], inv32[kMaxLv];
     size_t b, x, r, z, p0, p1, q, r1, q1, yall, y[kMaxLv], rc[kMaxLv], cpart, qpart, P_sigma, P_rr, P_bb, P_rho0, P_rho1, st, flag;
     size_t inverse_bytes = 0;
@@ -72,8 +72,8 @@ struct Shape {
     size_t nnzA[kMaxLv] = {};     // blocks of A_l (level 0: nnzb)
     size_t n_domblk[kMaxLv] = {}; // inversion gather entries of each level
     bool halo = false;            // the two-launch iteration's unit lists (Plan::hptr)
-    size_t n_hy = 0;
-    int maxH = 0;                 // most units of one group
+    size_t n_hu = 0, n_hy = 0;
+    int maxH = 0, maxH2 = 0;      // most units / level-2 entries of one group
 };
 
 Shape shape_of(const Plan& P) {
@@ -85,8 +85,10 @@ Shape shape_of(const Plan& P) {
         S.n_domblk[l] = P.dom_blk[l].size();
     }
     S.halo = P.halo;
+    S.n_hu = P.hu.size();
     S.n_hy = P.hy.size();
     S.maxH = P.maxH;
+    S.maxH2 = P.maxH2;
     return S;
 }
 
@@ -187,7 +189,6 @@ void make_layout(mas_handle* h) {
     Y = Layout();
     const bool mixed = h->opts.precision == MAS_PRECISION_MIXED;
     const size_t I = sizeof(int), Dd = sizeof(double), F = sizeof(float);
-    const int n = 3 * P.N;
     Y.remap = Y.take(I * P.NS);
     Y.map = Y.take(I * P.V);
     const Shape& Z = h->shape;
@@ -215,7 +216,10 @@ void make_layout(mas_handle* h) {
     Y.gmask = Y.take(sizeof(uint64_t) * gtab);
     if (Z.halo) {
         Y.hptr = Y.take(I * (static_cast<size_t>(P.G) + 1));
+        Y.hu = Y.take(I * Z.n_hu);
+        Y.h2ptr = Y.take(I * (static_cast<size_t>(P.G) + 1));
         Y.hy = Y.take(I * Z.n_hy);
+        Y.hpar = Y.take(sizeof(uint16_t) * Z.n_hu);
         Y.hidx = Y.take(sizeof(uint16_t) * (P.sym && !mixed ? nsb : static_cast<size_t>(P.nnzb)));
     }
     if (P.sym) {
@@ -239,10 +243,9 @@ void make_layout(mas_handle* h) {
     Y.H32 = mixed ? Y.take(F * 9 * static_cast<size_t>(P.nnzb)) : 0;
     for (int l = 1; l < P.L; ++l) Y.A[l] = Y.take(Dd * 9 * Z.nnzA[l]);
     for (int l = 0; l < P.L; ++l) {
-        const size_t cnt = static_cast<size_t>(P.ndom[l]) * n * n;
-        const size_t cnt64 = (l == 0 && P.N == 16) ? static_cast<size_t>(P.ndom[l]) * kPacked : cnt;
-        Y.inv64[l] = Y.take(Dd * cnt64);
-        Y.inverse_bytes += mixed ? F * cnt : Dd * cnt64;
+        const size_t cnt = inverse_entries(P.N, P.ndom[l]);
+        Y.inv64[l] = Y.take(Dd * cnt);
+        Y.inverse_bytes += mixed ? F * cnt : Dd * cnt;
         if (mixed) Y.inv32[l] = Y.take(F * cnt);
     }
     // slot vectors padded to whole groups so group kernels never branch on the tail
@@ -268,9 +271,9 @@ void make_layout(mas_handle* h) {
     Y.cpart = Y.take(Dd * 3 * std::max(P.n_cpart, 1));
     Y.qpart = Y.take(Dd * 3 * std::max(P.n_cpart, 1));
     Y.P_sigma = Y.take(Dd * P.G);
-    Y.P_rr = Y.take(Dd * P.G);
+    Y.P_rr = Y.take(Dd * std::max(P.G, apply_blocks(P.N, P.M, P.G)));
     Y.P_bb = Y.take(Dd * P.G);
-    const size_t nrho = static_cast<size_t>(P.G) + rec_coarse_blocks(P.L, P.N, P.ndom.data());
+    const size_t nrho = static_cast<size_t>(apply_blocks(P.N, P.M, P.G)) + all_coarse_blocks(P.L, P.N, P.ndom.data());
     Y.P_rho0 = Y.take(Dd * nrho);
     Y.P_rho1 = Y.take(Dd * nrho);
     Y.st = Y.take(sizeof(DevState));
@@ -283,7 +286,6 @@ SolverView view(const mas_handle* h) {
     SolverView v{};
     v.V = P.V;
     v.N = P.N;
-    v.packed0 = P.N == 16 ? 1 : 0;
     v.M = P.M;
     v.NS = P.NS;
     v.L = P.L;
@@ -325,12 +327,17 @@ SolverView view(const mas_handle* h) {
     v.gmask = at<uint64_t>(h, Y.gmask);
     if (h->shape.halo) {
         v.hptr = at<int>(h, Y.hptr);
+        v.hu = at<int>(h, Y.hu);
+        v.h2ptr = at<int>(h, Y.h2ptr);
         v.hy = at<int>(h, Y.hy);
+        v.hpar = at<uint16_t>(h, Y.hpar);
         v.hidx = at<uint16_t>(h, Y.hidx);
         v.maxH = h->shape.maxH;
+        v.maxH2 = h->shape.maxH2;
     }
     v.yall = at<double>(h, Y.yall);
-    v.ncb = rec_coarse_blocks(P.L, P.N, P.ndom.data());
+    v.ncb = all_coarse_blocks(P.L, P.N, P.ndom.data());
+    v.GA = apply_blocks(P.N, P.M, P.G);
     v.cpart = at<double>(h, Y.cpart);
     v.qpart = at<double>(h, Y.qpart);
     v.P_sigma = at<double>(h, Y.P_sigma);
@@ -369,7 +376,6 @@ BuildView build_view(const mas_handle* h) {
     BuildView b{};
     b.L = P.L;
     b.N = P.N;
-    b.packed0 = P.N == 16 ? 1 : 0;
     b.nnzb = P.nnzb;
     for (int l = 0; l < P.L; ++l) {
         b.units[l] = P.units[l];
@@ -413,8 +419,15 @@ int upload_plan(mas_handle* h, hipStream_t s) {
         const std::vector<uint16_t>& hidx =
             P.sym && h->opts.precision != MAS_PRECISION_MIXED ? P.hidx_sym : P.hidx;
         HIP_TRY(put(Y.hptr, P.hptr));
+        HIP_TRY(put(Y.hu, P.hu));
+        HIP_TRY(put(Y.h2ptr, P.h2ptr));
         HIP_TRY(put(Y.hy, P.hy));
-        HIP_TRY(hipMemcpyAsync(h->ws + Y.hidx, hidx.data(), sizeof(uint16_t) * hidx.size(), hipMemcpyHostToDevice, s));
+        auto put16 = [&](size_t off, const std::vector<uint16_t>& x) -> hipError_t {
+            if (x.empty()) return hipSuccess;
+            return hipMemcpyAsync(h->ws + off, x.data(), sizeof(uint16_t) * x.size(), hipMemcpyHostToDevice, s);
+        };
+        HIP_TRY(put16(Y.hpar, P.hpar));
+        HIP_TRY(put16(Y.hidx, hidx));
     }
     HIP_TRY(put(Y.rp0, P.rp0));
     HIP_TRY(put(Y.ci0, P.ci0));
@@ -504,7 +517,10 @@ int place_device_plan(mas_handle* h, hipStream_t s) {
     }
     if (h->shape.halo) {
         D.hptr = at<int>(h, Y.hptr);
+        D.hu = at<int>(h, Y.hu);
+        D.h2ptr = at<int>(h, Y.h2ptr);
         D.hy = at<int>(h, Y.hy);
+        D.hpar = at<uint16_t>(h, Y.hpar);
         D.hidx = at<uint16_t>(h, Y.hidx);
         D.hidx_sym = P.sym && h->opts.precision != MAS_PRECISION_MIXED ? 1 : 0;
     }
@@ -628,7 +644,7 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
         // a last iteration by recurrence leaves its decision to the next
         // SpMV: at max_iter, take it here
         if (k == opt.max_iter && k > 0 && !direct(k))
-            HIP_TRY(launch_apply_coarse(v, mixed, kApplyIter, k, 0.0, false, mixed, false, s, true));
+            HIP_TRY(launch_decision(v, k, mixed, s));
         return MAS_OK;
     };
     int inflight = 0, head = 0, next = 0;  // batch copies not yet looked at; ring slots 1 + (0|1)
@@ -730,7 +746,8 @@ void set_fusion(mas_handle* h) {
     h->fuse_ok = sizeof(double) * (3 * static_cast<size_t>(R.RG) + restrict_smem_doubles(R.RG, R.W1, R.L)) <=
                      spmv_restrict_capacity() &&
                  restrict_fast_ok(R.W1, R.GW, spmv_threads()) && h->shape.halo &&
-                 spmv_shared_bytes(R.RG, R.maxT, R.sym) + sizeof(double) * 3 * h->shape.maxH <= (size_t{64} << 10);
+                 spmv_shared_bytes(R.RG, R.maxT, R.sym) + sizeof(double) * 3 * (h->shape.maxH + h->shape.maxH2) <=
+                     (size_t{64} << 10);
 }
 
 int analyze_impl(mas_handle* h, int32_t n_rows, int32_t nnzb, const int32_t* row_ptr, const int32_t* col_idx,
@@ -1183,8 +1200,9 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
     HIP_TRY(hipMemcpyAsync(&c, R.counts, sizeof(c), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(g_u1.data(), R.g_u1, sizeof(int) * g_u1.size(), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(gsz.data(), R.gstore, sizeof(int) * gsz.size(), hipMemcpyDeviceToHost, s));
-    int n_halo = 0;
+    int n_halo = 0, n_halo2 = 0;
     HIP_TRY(hipMemcpyAsync(&n_halo, R.hptr + G, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(&n_halo2, R.h2ptr + G, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
 
     // the new plan: the partition and its maps stay, every size is new
@@ -1224,7 +1242,9 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
     Z.n_tidx = static_cast<size_t>(n_tidx);
     Z.halo = c.h_max <= kMaxHalo;
     Z.maxH = Z.halo ? c.h_max : 0;
-    Z.n_hy = Z.halo ? static_cast<size_t>(n_halo) * (S.L - 1) : 0;
+    Z.maxH2 = Z.halo ? c.h2_max : 0;
+    Z.n_hu = Z.halo ? static_cast<size_t>(n_halo) : 0;
+    Z.n_hy = Z.halo && S.L > 2 ? static_cast<size_t>(n_halo2) * (S.L - 2) : 0;
     PlacedShape ps{};
     ps.S = S;
     ps.sym = Q.sym ? 1 : 0;
@@ -1298,34 +1318,36 @@ int mas_get_inverses(const mas_handle* h, int32_t level, int32_t precision, doub
     if (want32 && h->opts.precision != MAS_PRECISION_MIXED) return MAS_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int n = 3 * P.N;
-    const size_t nd = static_cast<size_t>(P.ndom[level]), full = nd * n * n;
+    const size_t nd = static_cast<size_t>(P.ndom[level]), stored = inverse_entries(P.N, P.ndom[level]);
+    // the stored inverses, widened
+    std::vector<double> tmp(stored);
     if (want32) {
-        std::vector<float> tmp(full);
-        HIP_TRY(hipMemcpyAsync(tmp.data(), h->ws + h->lay.inv32[level], sizeof(float) * full, hipMemcpyDeviceToHost,
+        std::vector<float> t32(stored);
+        HIP_TRY(hipMemcpyAsync(t32.data(), h->ws + h->lay.inv32[level], sizeof(float) * stored, hipMemcpyDeviceToHost,
                                s));
         HIP_TRY(hipStreamSynchronize(s));
-        for (size_t e = 0; e < full; ++e) out[e] = static_cast<double>(tmp[e]);
-        return MAS_OK;
-    }
-    if (level == 0 && P.N == 16) {  // symmetric-packed: lower triangle column by column
-        std::vector<double> tmp(nd * kPacked);
-        HIP_TRY(hipMemcpyAsync(tmp.data(), h->ws + h->lay.inv64[0], sizeof(double) * tmp.size(),
-                               hipMemcpyDeviceToHost, s));
+        std::copy(t32.begin(), t32.end(), tmp.begin());
+    } else {
+        HIP_TRY(hipMemcpyAsync(tmp.data(), h->ws + h->lay.inv64[level], sizeof(double) * stored, hipMemcpyDeviceToHost,
+                               s));
         HIP_TRY(hipStreamSynchronize(s));
-        for (size_t d = 0; d < nd; ++d) {
-            const double* src = tmp.data() + d * kPacked;
-            double* dst = out + d * n * n;
-            for (int j = 0; j < n; ++j)
-                for (int i = j; i < n; ++i) {
-                    const double val = src[packed_col(j) + i - j];
-                    dst[static_cast<size_t>(j) * n + i] = val;
-                    dst[static_cast<size_t>(i) * n + j] = val;
-                }
-        }
+    }
+    if (P.N != 16) {
+        std::copy(tmp.begin(), tmp.end(), out);
         return MAS_OK;
     }
-    HIP_TRY(hipMemcpyAsync(out, h->ws + h->lay.inv64[level], sizeof(double) * full, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    for (size_t d = 0; d < nd; ++d) {  // packed pairs
+        const double* src = tmp.data() + d / 2 * kPairEntries;
+        const int half = static_cast<int>(d % 2);
+        double* dst = out + d * n * n;
+        for (int j = 0; j < n; ++j)
+            for (int i = j; i < n; ++i) {
+                double val = src[want32 ? pair_at<float>(half, i, j) : pair_at<double>(half, i, j)];
+                if (half == 0 && i == j) val *= 2.0;  // stored halved
+                dst[static_cast<size_t>(j) * n + i] = val;
+                dst[static_cast<size_t>(i) * n + j] = val;
+            }
+    }
     return MAS_OK;
 }
 

@@ -17,13 +17,18 @@ struct DevState {
     double tol2;     // tol^2 * ||b||^2
     double rr_true;  // ||b - H x||^2 from the final residual
     double rho[2];   // rho_j = r_j^T z_j in rho[j & 1], written by the SpMV of iteration j + 1
-    int32_t done;    // 1: stop; later kernels of the solve return at once
+    int32_t done;    // not 0: stop; later kernels of the solve return at once (see spmv_mark)
     int32_t iter;    // iterations completed
     int32_t status;  // 0 ok, -2 not SPD, -6 not finite, 2 = converged on the recurrence (FP64 check pending)
     int32_t pad;
 };
 
 constexpr int kStatusConvergedRecurrence = 2;
+
+// Stop flag left by the decision that runs beside the SpMV of iteration k:
+// the workgroups of that same launch take no notice of it (whether they would
+// see it is a race), so what they write does not depend on it.
+__host__ __device__ constexpr int spmv_mark(int k) { return k + 2; }
 
 // ------------------------------------------------------------ XCD placement
 
@@ -46,10 +51,15 @@ __host__ __device__ inline int xcd_group(int b, int G) {
 // each row of 16 lanes, so every source lane exists); FP64 moved as two
 // 32-bit halves.
 template <int kCtrl>
-__device__ __forceinline__ double dpp_add(double x) {
+__device__ __forceinline__ double dpp_get(double x) {
     const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), kCtrl, 0xf, 0xf, false);
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), kCtrl, 0xf, 0xf, false);
-    return x + __hiloint2double(hi, lo);
+    return __hiloint2double(hi, lo);
+}
+
+template <int kCtrl>
+__device__ __forceinline__ double dpp_add(double x) {
+    return x + dpp_get<kCtrl>(x);
 }
 
 __device__ __forceinline__ double lane_value(double x, int lane) {

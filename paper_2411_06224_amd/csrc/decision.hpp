@@ -7,16 +7,17 @@ namespace maspcg {
 
 constexpr int kFlagX0 = 1, kFlagMixed = 2, kFlagRrTrue = 4;
 
-// Sums the ||r_k||^2 partials (init: and those of ||b||^2) and records rr,
+// Sums the n_rr partials of ||r_k||^2 (init: and those of ||b||^2) and records rr,
 // the iteration count and, when ||r|| <= tol ||b||, the stop for the host
 // and every later kernel.  In mixed precision a stop on the recurrence is
-// marked for confirmation on the FP64 residual.  Needs blockDim.x >= 256 and
+// marked for confirmation on the FP64 residual.  mark: the non-zero value of
+// the stop flag.  Needs blockDim.x >= 256 and
 // buf[256] doubles of shared memory.
 __device__ inline void convergence_decision(const SolverView& v, bool init, int k, double tol, int flags,
-                                            double* buf) {
+                                            int n_rr, int mark, double* buf) {
     DevState* st = v.st;
     if (st->done) return;
-    const double rr = sum_partials(v.P_rr, v.G, buf);
+    const double rr = sum_partials(v.P_rr, n_rr, buf);
     if (init) {
         const double bb = sum_partials(v.P_bb, v.G, buf);
         const double tol2 = tol * tol * bb;
@@ -29,7 +30,7 @@ __device__ inline void convergence_decision(const SolverView& v, bool init, int 
             st->iter = 0;
             if (stop) {
                 st->status = bad ? -6 : 0;
-                st->done = 1;
+                st->done = mark;
             }
         }
     } else {
@@ -40,7 +41,7 @@ __device__ inline void convergence_decision(const SolverView& v, bool init, int 
             st->iter = k;
             if (bad || conv) {
                 st->status = bad ? -6 : (((flags & kFlagMixed) && !(flags & kFlagRrTrue)) ? kStatusConvergedRecurrence : 0);
-                st->done = 1;
+                st->done = mark;
             }
         }
     }

@@ -34,7 +34,6 @@ void launch_kernel(F kernel, dim3 grid, dim3 block, uint32_t shmem, hipStream_t 
 struct SolverView {
     int V, N, M, NS, L, nnzb;
     int D0, RG, G;  // work groups: D0 level-0 domains = RG slots; G groups
-    int packed0;    // 1: FP64 level-0 inverses symmetric-packed (N == 16)
     int sym;        // 1: H64 holds the group-symmetric storage (nsb blocks), 0: the full slot-ordered H;
                     // H32 (mixed) always holds the full storage (nnzb blocks)
     int nsb;        // blocks of the stored slot-ordered H (H64 / H32 planes)
@@ -75,20 +74,21 @@ struct SolverView {
     const int* gw_li;
     const uint64_t* gw_mask;
     const int* cp_ptr[kMaxLv];    // l >= 2: [S_l + 1]
-    // two-launch iteration: the level-1 units whose coarse correction group g
-    // reads, [hptr[g], hptr[g + 1]) (its own first); their corrections'
-    // positions in yall at every level, [(L-1) hptr[g] + (l-1) n + i]; the
-    // local unit of every block of the SpMV's storage with a column outside
-    // the group
-    const int* hptr;
-    const int* hy;
-    const uint16_t* hidx;
-    int maxH;  // most units of one group
-    int ncb;   // coarse workgroups of the apply (rec_coarse_blocks)
+    // two-launch iteration (Plan::hptr): the level-1 units whose coarse
+    // correction group g reads, [hptr[g], hptr[g + 1]) (its own first), and
+    // the group's local index of each one's level-2 unit; those level-2
+    // entries, [h2ptr[g], h2ptr[g + 1]), with their corrections' positions in
+    // yall at every level >= 2; the local unit of every block of the SpMV's
+    // storage with a column outside the group
+    const int *hptr, *hu, *h2ptr, *hy;
+    const uint16_t *hpar, *hidx;
+    int maxH, maxH2;  // most units / level-2 entries of one group
+    int ncb;   // coarse workgroups of the apply (all_coarse_blocks)
+    int GA;    // level-0 workgroups of the apply (apply_blocks): its rho (and, by recurrence, ||r||^2) partials
     // stored slot-ordered matrix (9 planes: H64 of nsb, H32 of nnzb values)
     double* H64;
     float* H32;
-    // inverses per level, column-major (3N)^2 per domain
+    // inverses per level: packed pairs (N = 16) or column-major (3N)^2 per domain
     double* inv64[kMaxLv];
     float* inv32[kMaxLv];
     // vectors in slot order (3*NS doubles)
@@ -105,35 +105,74 @@ struct SolverView {
     double* q1;
     double* qpart;
     double* rc[kMaxLv];
-    // per-group partial sums [G] each (P_rho: [G + ncb], the coarse
-    // workgroups' r_l^T y_l after the groups')
+    // partial sums: one per group [G] (P_rr: one per level-0 workgroup of the
+    // apply [GA] after an iteration by recurrence), P_rho [GA + ncb]: the
+    // level-0 workgroups' r^T z, then (by recurrence) the coarse workgroups'
+    // r_l^T y_l
     double *P_sigma, *P_rr, *P_bb, *P_rho[2];
     DevState* st;
     int* flag;  // inversion status
 };
 
-// The FP64 level-0 inverses of domain size 16 are stored symmetric-packed:
-// the lower triangle of the 48 x 48 inverse column by column (column j holds
-// rows j..47, so entry (i, j), i >= j, sits at packed_col(j) + i - j), 1176
-// entries per domain.  The FP32 copy, other levels and other domain sizes
-// keep the full column-major (3N)^2 block.
-constexpr int kPackedN = 48;
-constexpr int kPacked = kPackedN * (kPackedN + 1) / 2;
-__host__ __device__ constexpr int packed_col(int j) { return j * kPackedN - (j * (j - 1)) / 2; }
+// Inverses of domain size 16 (FP64 and FP32, every level) are stored
+// symmetric-packed for a wave that multiplies a pair of domains (2p, 2p + 1)
+// straight out of its registers (mas.hip, pair_product): 2352 entries per
+// pair, those of two lower triangles.  Of each domain's 48 x 48 inverse the
+// three 16 x 16 tiles (1,0), (2,0), (2,1) below the diagonal are kept whole;
+// the diagonal tiles of the two domains share tiles, the first domain's lower
+// triangle (diagonal halved, so that using an entry for its row and for its
+// column counts the diagonal once) and the second's strictly upper one, whose
+// diagonal follows the nine tiles.  Entry (r, c) of a tile sits in lane
+// r + 16 (c / 4) as its entry c % 4, 16 bytes of a lane side by side.  Other
+// domain sizes keep full column-major (3N)^2 blocks.
+constexpr int kPairEntries = 2352;
+constexpr int kTile = 256;
+constexpr int kPairDiag = 9 * kTile;  // the second domain's diagonal
 
-// Workgroups of the coarse levels in the apply of a two-launch iteration:
-// for N = 16 four level-1 domains per workgroup, else one domain each.
-constexpr int kRecLevel1 = 4;
-inline int rec_coarse_blocks(int L, int N, const int* ndom) {
+// Place of entry (r, c) in its tile.
+template <typename TI>
+__host__ __device__ constexpr int tile_at(int r, int c) {
+    const int lane = r + 16 * (c >> 2), v = c & 3;
+    return sizeof(TI) == 8 ? (v >> 1) * 128 + 2 * lane + (v & 1) : 4 * lane + v;
+}
+
+// Tile below the diagonal, block row I > J, of the pair's first (half = 0) or
+// second domain.
+__host__ __device__ constexpr int tile_below(int I, int J, int half) { return 3 * half + (I == 1 ? 0 : 1 + J); }
+
+// Place of entry (i, j), i >= j, of a domain's inverse in its pair.
+template <typename TI>
+__host__ __device__ constexpr int pair_at(int half, int i, int j) {
+    const int I = i / 16, J = j / 16, r = i % 16, c = j % 16;
+    return I > J                ? kTile * tile_below(I, J, half) + tile_at<TI>(r, c)
+           : half == 0          ? kTile * (6 + I) + tile_at<TI>(r, c)
+           : r == c             ? kPairDiag + i
+                                : kTile * (6 + I) + tile_at<TI>(c, r);
+}
+
+// Stored inverse entries of nd domains of size N.
+inline size_t inverse_entries(int N, int nd) {
+    return N == 16 ? static_cast<size_t>((nd + 1) / 2) * kPairEntries : static_cast<size_t>(nd) * 9 * N * N;
+}
+
+// Workgroups of the apply.  N = 16: kApplyDomains consecutive level-0 (or
+// level-1) domains per workgroup, two of its four waves each, and one pair of
+// domains of the levels above per workgroup; other sizes: one group of
+// level-0 domains (apply_blocks = G) and one coarse domain each.
+constexpr int kApplyDomains = 8;
+inline int apply_blocks(int N, int M, int G) { return N == 16 ? (M + kApplyDomains - 1) / kApplyDomains : G; }
+inline int coarse_blocks(int N, int l, int nd) {
+    return N == 16 ? (l == 1 ? (nd + kApplyDomains - 1) / kApplyDomains : (nd + 1) / 2) : nd;
+}
+inline int all_coarse_blocks(int L, int N, const int* ndom) {
     int n = 0;
-    for (int l = 1; l < L; ++l) n += (l == 1 && N == 16) ? (ndom[l] + kRecLevel1 - 1) / kRecLevel1 : ndom[l];
+    for (int l = 1; l < L; ++l) n += coarse_blocks(N, l, ndom[l]);
     return n;
 }
 
 // Build-phase views.
 struct BuildView {
     int L, N, nnzb;
-    int packed0;  // FP64 level-0 inverses symmetric-packed (N == 16)
     int units[kMaxLv];
     int ndom[kMaxLv];
     int nnzA[kMaxLv];
@@ -179,7 +218,7 @@ hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void
 // on r_{k-1}
 hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool restrict_q, bool split, hipStream_t s);
 // Shared memory of the SpMV kernels besides a group's staged corrections
-// (maxH units of 24 bytes).
+// (24 bytes for each of maxH units and maxH2 level-2 entries).
 size_t spmv_shared_bytes(int RG, int maxT, bool sym);
 // Bytes of shared memory the SpMV kernels can lend to the restriction of q
 // after their stream (their product planes).
@@ -207,9 +246,10 @@ hipError_t launch_invert(const BuildView& b, const double* Hu, bool want32, hipS
 // Coarse levels plus the convergence decision (mode as ApplyMode; k = 0:
 // the initial apply); rr_true: the residual partials hold b - H x rather
 // than the recurrence (residual replacement, FP64 confirmation).
-// decision_only: workgroup 0 alone (the decision on r_k, mode kApplyIter).
 hipError_t launch_apply_coarse(const SolverView& v, bool f32, int mode, int k, double tol, bool x0_given, bool mixed,
-                               bool rr_true, hipStream_t s, bool decision_only = false);
+                               bool rr_true, hipStream_t s);
+// The decision on r_k alone, after an iteration k by recurrence.
+hipError_t launch_decision(const SolverView& v, int k, bool mixed, hipStream_t s);
 hipError_t launch_apply_level0(const SolverView& v, bool f32, int mode, int k, hipStream_t s);
 // Iteration k by recurrence: x/r update, level 0 and the coarse levels in
 // one launch (see ApplyMode).

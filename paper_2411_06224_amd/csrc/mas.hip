@@ -2,6 +2,7 @@
 // inversion and the apply (Supp. Eq. 4-6; algorithm "Compute MAS
 // preconditioner" in Sec. 4.3).
 #include <algorithm>
+#include <type_traits>
 
 #include "decision.hpp"
 #include "launch.hpp"
@@ -11,11 +12,9 @@ namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-// Inverse entries in the apply.  Full-layout level-0 FP64 inverses (136 MB
-// at the 48^3 cube) do not fit the 256 MB MALL next to H, so they are
-// streamed with non-temporal loads that leave the caches to H, the vectors
-// and the coarse inverses (kStream); the symmetric-packed FP64 set (69 MB),
-// the FP32 set of the mixed solve and the coarse levels (16 MB) fit and are
+// Inverse entries in the apply of domain sizes other than 16 (full layout):
+// FP64 level-0 inverses are streamed with non-temporal loads that leave the
+// caches to H, the vectors and the coarse inverses (kStream); the others are
 // read through the caches.
 template <typename TI, bool kStream = true>
 __device__ __forceinline__ double inv_load(const TI* p) {
@@ -107,6 +106,34 @@ __device__ __forceinline__ int level_of(const DomTable& tab, int L, int g) {
 
 constexpr int kInvWaves = 4;
 constexpr int kInvThreads = 64 * kInvWaves;
+
+// A domain's share of its packed pair (launch.hpp) from the inverse in LDS,
+// zero on empty lanes: thread t writes entry t of each tile below the
+// diagonal and, of each diagonal tile, the triangle that is this domain's.
+template <typename TO>
+__device__ __forceinline__ void store_packed(TO* __restrict__ out, const double* A, int LD, int half,
+                                             unsigned long long occ) {
+    const int t = threadIdx.x;
+    const int lane = sizeof(TO) == 8 ? (t >> 1) & 63 : t >> 2;
+    const int v = sizeof(TO) == 8 ? 2 * (t >> 7) + (t & 1) : t & 3;
+    const int r = lane & 15, c = 4 * (lane >> 4) + v;  // tile_at<TO>(r, c) == t
+    auto value = [&](int i, int j) {
+        const bool live = ((occ >> (i / 3)) & 1ull) && ((occ >> (j / 3)) & 1ull);
+        return live ? 0.5 * (A[i * LD + j] + A[j * LD + i]) : 0.0;
+    };
+#pragma unroll
+    for (int I = 1; I < 3; ++I)
+#pragma unroll
+        for (int J = 0; J < I; ++J)
+            out[kTile * tile_below(I, J, half) + t] = static_cast<TO>(value(16 * I + r, 16 * J + c));
+#pragma unroll
+    for (int I = 0; I < 3; ++I) {
+        if (half == 0 && r >= c)
+            out[kTile * (6 + I) + t] = static_cast<TO>((r == c ? 0.5 : 1.0) * value(16 * I + r, 16 * I + c));
+        if (half == 1 && r < c) out[kTile * (6 + I) + t] = static_cast<TO>(value(16 * I + c, 16 * I + r));
+    }
+    if (half == 1 && t < 48) out[kPairDiag + t] = static_cast<TO>(value(t, t));
+}
 
 template <int T>
 __global__ void __launch_bounds__(kInvThreads) k_invert(BuildView B, const double* __restrict__ Hu, int want32,
@@ -258,67 +285,187 @@ __global__ void __launch_bounds__(kInvThreads) k_invert(BuildView B, const doubl
     }
     if (w == 0 && !ok && lane == 0) atomicOr(B.flag, 1);
 
-    const bool packed = l == 0 && B.packed0;
-    if (packed) {
-        // FP64: symmetric-packed lower triangle (the mean of the two
-        // triangles of the computed inverse), zero on empty lanes
-        double* o64 = B.inv64[0] + (long long)d * kPacked;
-        for (int j = w; j < kPackedN; j += kInvWaves)  // column j (rows j..47) by wave j % 4
-            for (int i = j + lane; i < kPackedN; i += 64) {
-                const bool live = ((occ >> (i / 3)) & 1ull) && ((occ >> (j / 3)) & 1ull);
-                o64[packed_col(j) + i - j] = live ? 0.5 * (A[i * LD + j] + A[j * LD + i]) : 0.0;
-            }
+    if constexpr (T == 3) {
+        if (N == 16) {  // packed pairs, each entry the mean of the computed inverse's two triangles
+            const long long pair = static_cast<long long>(d >> 1) * kPairEntries;
+            store_packed(B.inv64[l] + pair, A, LD, d & 1, occ);
+            if (want32) store_packed(B.inv32[l] + pair, A, LD, d & 1, occ);
+            return;
+        }
     }
     // column-major n x n, zero rows/columns on empty lanes
     const long long off = (long long)d * n * n;
-    double* o64 = packed ? nullptr : B.inv64[l] + off;
+    double* o64 = B.inv64[l] + off;
     float* o32 = want32 ? B.inv32[l] + off : nullptr;
-    if (o64 || o32)
-        for (int e = tid; e < n * n; e += kInvThreads) {
-            const int col = e / n, row = e - col * n;
-            const bool live = ((occ >> (row / 3)) & 1ull) && ((occ >> (col / 3)) & 1ull);
-            const double val = live ? A[row * LD + col] : 0.0;
-            if (o64) o64[e] = val;
-            if (o32) o32[e] = static_cast<float>(val);
-        }
+    for (int e = tid; e < n * n; e += kInvThreads) {
+        const int col = e / n, row = e - col * n;
+        const bool live = ((occ >> (row / 3)) & 1ull) && ((occ >> (col / 3)) & 1ull);
+        const double val = live ? A[row * LD + col] : 0.0;
+        o64[e] = val;
+        if (o32) o32[e] = static_cast<float>(val);
+    }
 }
 
 // ------------------------------------------------------------------ apply
-constexpr int kRound = 8;  // coarse partials loaded per round by one lane
+// First coarse workgroup of each level >= 1 (coarse_blocks per level).
+struct CoarseTable {
+    int off[kMaxLv + 1];
+};
 
-// Sum of a unit's partials part[m0 .. m1) (three components each) over 16
-// lanes, lane sub taking m0 + sub, + 16, + 32, ... in this order, then folded
-// within the lanes' DPP row.  kR are loaded per round (at clamped indices, the
-// ones past the range not added) so that their latencies overlap: a unit of
-// the top levels has partials from about a hundred groups.
-template <int kR>
-__device__ __forceinline__ void gather_unit16(const double* __restrict__ part, int m0, int m1, int sub, double& s0,
-                                              double& s1, double& s2) {
-    s0 = s1 = s2 = 0.0;
-    for (int m = m0 + sub; m < m1; m += 16 * kR) {
-        double a0[kR], a1[kR], a2[kR];
-#pragma unroll
-        for (int j = 0; j < kR; ++j) {
-            const int mj = min(m + 16 * j, m1 - 1);
-            a0[j] = part[3 * mj];
-            a1[j] = part[3 * mj + 1];
-            a2[j] = part[3 * mj + 2];
-        }
-#pragma unroll
-        for (int j = 0; j < kR; ++j)
-            if (m + 16 * j < m1) {
-                s0 += a0[j];
-                s1 += a1[j];
-                s2 += a2[j];
-            }
-    }
-    s0 = row16_sum(s0);
-    s1 = row16_sum(s1);
-    s2 = row16_sum(s2);
+__device__ __forceinline__ int coarse_level(const CoarseTable& tab, int L, int b) {
+    int l = 1;
+    while (l + 1 < L && b >= tab.off[l + 1]) ++l;
+    return l;
 }
 
-// The same over a whole wave (other domain sizes): two loads in flight per
-// lane.
+template <typename TI>
+__device__ __forceinline__ const TI* inverses(const SolverView& v, int l) {
+    if constexpr (sizeof(TI) == 8)
+        return v.inv64[l];
+    else
+        return v.inv32[l];
+}
+
+// ---- domain size 16: a wave multiplies a pair of domains out of registers
+// The pair's packed inverses (launch.hpp; 18.8 KB in FP64) are 36 entries
+// per lane and one diagonal entry of the second domain per row, loaded as
+// 16-byte loads, 1 KB contiguous per wave and load, all in flight at once:
+// the launch then streams while its scalars (alpha) are still being formed,
+// nothing is staged in LDS and no barrier separates the loads.  Lane
+// (c16, g4) = (lane % 16, lane / 16) holds row c16, columns 4 g4 .. 4 g4 + 3
+// of every tile.
+template <typename TI>
+struct PairRegs {
+    TI a[9][4];
+    TI diag[2];  // the second domain's diagonal at the lane's rows (see pair_rows)
+};
+
+// Rows of the pair a lane owns in the vectors: e = lane and, for lanes below
+// 32, lane + 64 (0..47: the first domain, 48..95: the second).
+__device__ __forceinline__ int pair_row(int lane, int q) { return lane + 64 * q; }
+__device__ __forceinline__ bool pair_owns(int lane, int q) { return q == 0 || lane < 32; }
+
+template <typename TI>
+__device__ __forceinline__ void pair_load(PairRegs<TI>& P, const TI* __restrict__ pair, int lane) {
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+        if constexpr (sizeof(TI) == 8) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const double2 x = *reinterpret_cast<const double2*>(pair + kTile * j + 128 * h + 2 * lane);
+                P.a[j][2 * h] = x.x;
+                P.a[j][2 * h + 1] = x.y;
+            }
+        } else {
+            const float4 x = *reinterpret_cast<const float4*>(pair + kTile * j + 4 * lane);
+            P.a[j][0] = x.x;
+            P.a[j][1] = x.y;
+            P.a[j][2] = x.z;
+            P.a[j][3] = x.w;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int i = pair_row(lane, q) - 48;
+        P.diag[q] = pair[kPairDiag + min(max(i, 0), 47)];
+    }
+}
+
+// Sums of col[0..3] over the 16 lanes of a row: lane l of the row ends with
+// the sum of col[l % 4].
+__device__ __forceinline__ double row16_sum4(const double (&col)[4], int lane) {
+    const bool b0 = lane & 1, b1 = lane & 2;
+    const double k0 = (b0 ? col[1] : col[0]) + dpp_get<0xb1>(b0 ? col[0] : col[1]);  // quad_perm [1, 0, 3, 2]
+    const double k1 = (b0 ? col[3] : col[2]) + dpp_get<0xb1>(b0 ? col[2] : col[3]);
+    double k = (b1 ? k1 : k0) + dpp_get<0x4e>(b1 ? k0 : k1);  // quad_perm [2, 3, 0, 1]
+    k = dpp_add<0x128>(k);                                    // row_ror 8
+    return dpp_add<0x124>(k);                                 // row_ror 4
+}
+
+// Orders the wave's LDS writes before its later reads (other lanes' data): a
+// wave's LDS accesses execute in order, so this only holds the compiler.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int kPairLds = 96 + 5 * 96;  // doubles of LDS per wave: the vector, four row parts and the column part
+
+// out[q] = the pair's product at the lane's rows, x[q] the vector there
+// (zero on rows that hold nothing).  sm: kPairLds doubles of the wave's own;
+// no barrier: the wave's LDS accesses stay in order.  An entry below the
+// diagonal is used for its row and for its column; a tile's row sums are
+// folded over the four lane groups through LDS, its column sums over the 16
+// lanes of a row by DPP, the four columns at once.
+template <typename TI>
+__device__ __forceinline__ void pair_product(const PairRegs<TI>& P, const double (&x)[2], double* sm, int lane,
+                                             double (&out)[2]) {
+    double* xs = sm;
+    double* part = sm + 96;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (pair_owns(lane, q)) xs[pair_row(lane, q)] = x[q];
+    wave_lds_sync();
+    const int c16 = lane & 15, g4 = lane >> 4;
+    double row[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
+#pragma unroll
+    for (int J = 0; J < 3; ++J)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            // one block column of one domain at a time: with more operands
+            // read ahead the entries would no longer fit in 128 registers
+            __builtin_amdgcn_sched_barrier(0);
+            double xc[4], col[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                xc[v] = xs[48 * h + 16 * J + 4 * g4 + v];
+                col[v] = 0.0;
+            }
+#pragma unroll
+            for (int I = J; I < 3; ++I) {
+                const double xr = xs[48 * h + 16 * I + c16];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    double a = static_cast<double>(P.a[I > J ? tile_below(I, J, h) : 6 + J][v]);
+                    if (I == J) a = (c16 >= 4 * g4 + v) == (h == 0) ? a : 0.0;  // the domain's triangle
+                    row[h][I] += a * xc[v];
+                    col[v] += a * xr;
+                }
+            }
+            // the row sums are formed here, not once their entries have all
+            // been kept for the end
+#pragma unroll
+            for (int I = J; I < 3; ++I) asm volatile("" : "+v"(row[h][I]));
+            const double k = row16_sum4(col, lane);
+            if (c16 < 4) part[4 * 96 + 48 * h + 16 * J + 4 * g4 + c16] = k;
+        }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int I = 0; I < 3; ++I) part[96 * g4 + 48 * h + 16 * I + c16] = row[h][I];
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int e = pair_row(lane, q);
+        out[q] = 0.0;
+        if (pair_owns(lane, q)) {
+            double s = ((part[e] + part[96 + e]) + (part[192 + e] + part[288 + e])) + part[384 + e];
+            if (e >= 48) s += static_cast<double>(P.diag[q]) * x[q];
+            out[q] = s;
+        }
+    }
+}
+
+constexpr int kPairThreads = 256;  // four waves
+constexpr int kPairWaves = 4;      // waves per SIMD: 128 registers, 72 of them the FP64 pair's entries
+
+// ---- other domain sizes
+constexpr int kGroupThreads = 384;
+
+// Sum of a unit's partials part[m0 .. m1) (three components each) over a
+// wave: two loads in flight per lane.
 __device__ __forceinline__ void gather_unit64(const double* __restrict__ part, int m0, int m1, int lane, double& s0,
                                               double& s1, double& s2) {
     s0 = s1 = s2 = 0.0;
@@ -338,535 +485,496 @@ __device__ __forceinline__ void gather_unit64(const double* __restrict__ part, i
     s2 = wave_sum(s2);
 }
 
-// Coarse levels l >= 1 (workgroups 1.. of the launch, one per domain, all
-// levels at once): r_l for the domain's N units straight from the residual's
-// restriction -- level 1 from r_1, higher levels as sums of the per-group
-// partials the restriction left for each unit (a contiguous range per unit;
-// for N = 16 sixteen lanes per unit, all units at once, else one wave per
-// unit), kept in rc_l inside PCG -- then y_l = Inv_{l,d} r_l.
-template <typename TI, int kN>
-__global__ void __launch_bounds__(256) k_apply_coarse(SolverView v, DomTable tab, int mode, int k, double tol,
-                                                      int flags) {
-    __shared__ double rl[128];
-    __shared__ double buf[256];
-    if (blockIdx.x == 0) {
-        if (mode != kApplyPlain) convergence_decision(v, mode == kApplyInit, k, tol, flags, buf);
-        return;
-    }
-    const int gb = blockIdx.x - 1;
-    int l = 1;
-    while (l + 1 < v.L && gb >= tab.off[l + 1]) ++l;
-    const int d = gb - tab.off[l];
-    const int N = kN > 0 ? kN : v.N, n = 3 * N;
-    const int u0 = d * N;
-    const int nu = min(N, v.units[l] - u0);
-    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-    const TI* inv;
-    if constexpr (sizeof(TI) == 8)
-        inv = v.inv64[l];
-    else
-        inv = v.inv32[l];
-    inv += static_cast<long long>(d) * n * n;
-    // N = 16: four threads per row, each holding a quarter of the row's
-    // inverse entries, loaded before the gather so that both are in flight
-    constexpr int kParts = 4;
-    constexpr int kCols = kN > 0 ? (3 * kN + kParts - 1) / kParts : 1;
-    double pre[kCols];
-    const int prow = t % n, ppart = t / n;
-    if constexpr (kN > 0) {
-        if (t < kParts * n) {
-#pragma unroll
-            for (int j = 0; j < kCols; ++j) {
-                const int kk = ppart * kCols + j;
-                pre[j] = kk < n ? inv_load<TI, false>(inv + static_cast<long long>(kk) * n + prow) : 0.0;
-            }
-        }
-    }
-    // the stop flag is read once these loads are in flight; after a stop
-    // nothing is written
-    const int stop = v.st->done;
-    keep_loads_issued();
-    if (mode == kApplyIter && stop) return;
-    const bool keep = mode != kApplyPlain;  // r_l of levels >= 2 kept for the recurrence
-    if (l == 1) {
-        if (t < n) rl[t] = t < 3 * nu ? v.r1[3 * u0 + t] : 0.0;
-    } else if constexpr (kN == 16) {
-        const int* cp = v.cp_ptr[l];
-        const int a = t >> 4, sub = t & 15;
-        const bool own = a < nu;
-        double s0, s1, s2;
-        gather_unit16<kRound>(v.cpart, own ? cp[u0 + a] : 0, own ? cp[u0 + a + 1] : 0, sub, s0, s1, s2);
-        if (sub == 0) {
-            if (keep && own) {
-                double* rc = v.rc[l] + 3 * (u0 + a);
-                rc[0] = s0;
-                rc[1] = s1;
-                rc[2] = s2;
-            }
-            rl[3 * a] = s0;
-            rl[3 * a + 1] = s1;
-            rl[3 * a + 2] = s2;
-        }
-    } else {
-        const int* cp = v.cp_ptr[l];
-        for (int a = w; a < N; a += 4) {
-            const bool own = a < nu;
-            double s0, s1, s2;
-            gather_unit64(v.cpart, own ? cp[u0 + a] : 0, own ? cp[u0 + a + 1] : 0, lane, s0, s1, s2);
-            if (lane == 0) {
-                if (keep && own) {
-                    double* rc = v.rc[l] + 3 * (u0 + a);
-                    rc[0] = s0;
-                    rc[1] = s1;
-                    rc[2] = s2;
-                }
-                rl[3 * a] = s0;
-                rl[3 * a + 1] = s1;
-                rl[3 * a + 2] = s2;
-            }
-        }
-    }
-    __syncthreads();
-    if constexpr (kN > 0) {
-        __shared__ double quarter[kParts][3 * kN];
-        if (t < kParts * n) {
-            double a = 0.0;
-#pragma unroll
-            for (int j = 0; j < kCols; ++j) {
-                const int kk = ppart * kCols + j;
-                if (kk < n) a += pre[j] * rl[kk];
-            }
-            quarter[ppart][prow] = a;
-        }
-        __syncthreads();
-        if (t < n) v.y[l][3 * u0 + t] = ((quarter[0][t] + quarter[1][t]) + quarter[2][t]) + quarter[3][t];
-    } else if (t < n) {
-        double acc = 0.0;
-#pragma unroll 8
-        for (int kk = 0; kk < n; ++kk) acc += inv_load<TI, false>(inv + static_cast<long long>(kk) * n + t) * rl[kk];
-        v.y[l][3 * u0 + t] = acc;
-    }
-}
-
-constexpr int kPreLevels = 8;  // coarse levels whose corrections are prefetched
-constexpr int kGroupThreads = 384;
-
-// Row i of the inverse of level-0 domain d times its residual rd (LDS),
-// full column-major layout.
-template <typename TI, int kN>
-__device__ __forceinline__ double full_row(const TI* __restrict__ inv0, int n, int d, int row, const double* rd) {
-    const TI* inv = inv0 + (long long)d * n * n + row;
+// Row `row` of a domain's inverse (full column-major layout) times rd (LDS).
+template <typename TI, bool kStream>
+__device__ __forceinline__ double full_row(const TI* __restrict__ inv, int n, int row, const double* rd) {
     double acc = 0.0;
-    if constexpr (kN > 0) {
-#pragma unroll
-        for (int kk = 0; kk < 3 * kN; ++kk) acc += inv_load(inv + kk * 3 * kN) * rd[kk];
-    } else {
 #pragma unroll 8
-        for (int kk = 0; kk < n; ++kk) acc += inv_load(inv + kk * n) * rd[kk];
-    }
+    for (int kk = 0; kk < n; ++kk) acc += inv_load<TI, kStream>(inv + static_cast<long long>(kk) * n + row) * rd[kk];
     return acc;
 }
 
-template <typename TI>
-__device__ __forceinline__ const TI* level0_inverses(const SolverView& v) {
-    if constexpr (sizeof(TI) == 8)
-        return v.inv64[0];
-    else
-        return v.inv32[0];
-}
-
-// Level 0 over a group of D0 domains, one thread per DOF:
-//   z = Inv_{0,d} r_d + sum_{l >= 1} y_l[unit of the slot at level l]
-// (prolongation of every coarse level, Supp. Eq. 6) and the partial of
-// rho = r^T z.  Returns at once after a stop.
-template <typename TI, int kN, int kMode>
-__global__ void __launch_bounds__(kGroupThreads) k_apply_level0(SolverView v, int k) {
-    __shared__ double rs[kGroupThreads];
-    __shared__ double red[16];
-    const int N = kN > 0 ? kN : v.N;
-    const int n = 3 * N;
-    const int g = xcd_group(blockIdx.x, v.G), t = threadIdx.x;
-    const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
-    const bool live = t < nd * n;
-    const long long base = 3LL * g * v.RG;
-    const int slot = g * v.RG + t / 3, c = t % 3;
-    // coarse corrections of the slot (prolongation), loaded with r so that
-    // their latency ends before the inverse stream starts
-    int u[kPreLevels];
-#pragma unroll
-    for (int j = 0; j < kPreLevels; ++j)
-        u[j] = (live && j + 1 < v.L) ? v.anc[static_cast<long long>(j) * v.NS + slot] : -1;
-    const double rv = live ? v.r[base + t] : 0.0;
-    // the stop flag is read once these loads are in flight; after a stop
-    // nothing is written
-    const int stop = v.st->done;
-    keep_loads_issued();
-    if (kMode != kApplyPlain && stop) return;
-    double ycor[kPreLevels];
-#pragma unroll
-    for (int j = 0; j < kPreLevels; ++j) ycor[j] = u[j] >= 0 ? v.y[j + 1][3 * u[j] + c] : 0.0;
-    rs[t] = rv;
-    __syncthreads();
-    double zv = 0.0;
-    if (live) {
-        const int dl = t / n, row = t - dl * n;
-        double acc = full_row<TI, kN>(level0_inverses<TI>(v), n, g * v.D0 + dl, row, rs + dl * n);
-#pragma unroll
-        for (int j = 0; j < kPreLevels; ++j)
-            if (u[j] >= 0) acc += ycor[j];
-        if (v.L > kPreLevels + 1) {
-            // deeper hierarchies: the remaining levels' unit ids at once, then
-            // their corrections at once
-            constexpr int kRest = kMaxLv - 1 - kPreLevels;
-            int ur[kRest];
-#pragma unroll
-            for (int j = 0; j < kRest; ++j)
-                ur[j] = kPreLevels + 1 + j < v.L ? v.anc[static_cast<long long>(kPreLevels + j) * v.NS + slot] : -1;
-            double yr[kRest];
-#pragma unroll
-            for (int j = 0; j < kRest; ++j) yr[j] = ur[j] >= 0 ? v.y[kPreLevels + 1 + j][3 * ur[j] + c] : 0.0;
-#pragma unroll
-            for (int j = 0; j < kRest; ++j)
-                if (ur[j] >= 0) acc += yr[j];
-        }
-        zv = acc;
-        v.z[base + t] = zv;
-    }
-    if (kMode == kApplyPlain) return;
-    const double part = block_sum_last(rv * zv, red);
-    if (t == 0) v.P_rho[k & 1][g] = part;
-}
-
-// The symmetric-packed FP64 inverses (domain size 16) of a group's domains
-// times their residuals: the packed inverses of two domains at a time
-// (18.8 KB, contiguous) are staged in LDS with coalesced loads, the next
-// pair's loads in flight (in registers) while the current pair is
-// multiplied.  (With FP32 inverses the full layout streams faster: the
-// staging rounds, not the bytes, then bound the kernel.)  Four threads per
-// row each take twelve columns: entry (i, kk) of the inverse is (kk, i) of
-// the stored lower triangle when kk > i.
-constexpr int kPairs = 2;                                // domains staged per round
-constexpr int kStageLoads = (kPairs * kPacked + kGroupThreads - 1) / kGroupThreads;  // entries per thread and round
-
-struct PackedPair {
-    double nxt[kStageLoads];
+// ---- the scalars of an iteration by recurrence
+struct RecLoads {
+    PartialLoads<> sig;
+    double rho;
 };
 
-__device__ __forceinline__ void fetch_pair(PackedPair& P, const double* __restrict__ inv, int p, int nd) {
-    const int cnt = min(kPairs, nd - kPairs * p) * kPacked;
-    const double* src = inv + static_cast<long long>(kPairs * p) * kPacked;
-#pragma unroll
-    for (int j = 0; j < kStageLoads; ++j) {
-        const int e = threadIdx.x + kGroupThreads * j;
-        P.nxt[j] = e < cnt ? inv_load<double, false>(src + e) : 0.0;
-    }
+__device__ __forceinline__ RecLoads rec_load(const SolverView& v, int k) {
+    RecLoads R;
+    R.sig = partials_load(v.P_sigma, v.G);
+    R.rho = v.st->rho[(k - 1) & 1];
+    return R;
 }
 
-// zs[48 d + i] = (Inv_{0,d} r_d)_i for the nd domains of the group, whose
-// first pair is already fetched into P; rs: their residuals (visible after
-// the first barrier here).  Ends with a barrier.
-__device__ __forceinline__ void packed_rounds(PackedPair& P, const double* __restrict__ inv, int nd, const double* rs,
-                                              double* zs, double* stage) {
-    const int t = threadIdx.x;
-    const int rounds = (nd + kPairs - 1) / kPairs;
-    const int row = t >> 2, q = t & 3;  // 96 rows of a pair, four quarters each
-    const int dl = row / 48, i = row - 48 * dl;
-    for (int p = 0; p < rounds; ++p) {
-        const int cnt = min(kPairs, nd - kPairs * p) * kPacked;
-#pragma unroll
-        for (int j = 0; j < kStageLoads; ++j) {
-            const int e = t + kGroupThreads * j;
-            if (e < cnt) stage[e] = P.nxt[j];
-        }
-        __syncthreads();  // the pair (and, the first time, r) are visible
-        if (p + 1 < rounds) fetch_pair(P, inv, p + 1, nd);
-        const int d = kPairs * p + dl;
-        double s = 0.0;
-        if (d < nd) {
-            const double* Ad = stage + dl * kPacked;
-            const double* rd = rs + 48 * d;
-#pragma unroll
-            for (int m = 0; m < 12; ++m) {
-                const int kk = 12 * q + m;
-                const int idx = kk <= i ? packed_col(kk) + i - kk : packed_col(i) + kk - i;
-                s += Ad[idx] * rd[kk];
-            }
-        }
-        // the row's four quarters, added as (q0 + q1) + (q2 + q3)
-        s = dpp_add<0xb1>(s);  // quad_perm [1, 0, 3, 2]
-        s = dpp_add<0x4e>(s);  // quad_perm [2, 3, 0, 1]
-        if (q == 0 && d < nd) zs[48 * d + i] = s;
-        __syncthreads();  // stage free for the next pair
-    }
-}
-
-// k_apply_level0 with the symmetric-packed inverses (packed_rounds).
-template <int kMode>
-__global__ void __launch_bounds__(kGroupThreads) k_apply_level0_packed(SolverView v, int k) {
-    __shared__ double rs[kGroupThreads];
-    __shared__ double zs[kGroupThreads];
-    __shared__ double stage[kPairs * kPacked];
-    __shared__ double red[16];
-    const int g = xcd_group(blockIdx.x, v.G), t = threadIdx.x;
-    const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
-    const bool live = t < nd * 48;
-    const long long base = 3LL * g * v.RG;
-    const int slot = g * v.RG + t / 3, c = t % 3;
-    const double* inv = v.inv64[0] + static_cast<long long>(g) * v.D0 * kPacked;
-    PackedPair P;
-    fetch_pair(P, inv, 0, nd);
-    const double rv = live ? v.r[base + t] : 0.0;
-    // the stop flag is read once these loads are in flight; after a stop
-    // nothing is written
-    const int stop = v.st->done;
-    keep_loads_issued();
-    if (kMode != kApplyPlain && stop) return;
-    rs[t] = rv;
-    packed_rounds(P, inv, nd, rs, zs, stage);
-    // the corrections of the slot (prolongation) at every coarse level,
-    // loaded after the rounds (registers held through them would cost a
-    // workgroup per CU): all unit ids at once, then all corrections at once
-    int u[kMaxLv - 1];
-#pragma unroll
-    for (int j = 0; j < kMaxLv - 1; ++j)
-        u[j] = (live && j + 1 < v.L) ? v.anc[static_cast<long long>(j) * v.NS + slot] : -1;
-    double ycor[kMaxLv - 1];
-#pragma unroll
-    for (int j = 0; j < kMaxLv - 1; ++j) ycor[j] = u[j] >= 0 ? v.y[j + 1][3 * u[j] + c] : 0.0;
-    double zv = 0.0;
-    if (live) {
-        double acc = zs[t];
-#pragma unroll
-        for (int j = 0; j < kMaxLv - 1; ++j)
-            if (u[j] >= 0) acc += ycor[j];
-        zv = acc;
-        v.z[base + t] = zv;
-    }
-    if (kMode == kApplyPlain) return;
-    const double part = block_sum_last(rv * zv, red);
-    if (t == 0) v.P_rho[k & 1][g] = part;
-}
-
-// ---------------------------------------------- apply of a two-launch iteration
-// Iteration k by recurrence, in one launch after the SpMV.  Every workgroup
-// forms alpha_k = rho_{k-1} / sigma_k from the sigma partials; then
-//  - a group workgroup performs x += alpha p_k and r -= alpha q_k on its DOF
-//    and z = Inv_{0,d} r_d, with the partials of r^T z and ||r_k||^2;
-//  - a coarse workgroup updates the restricted residual of its units,
-//    C_l r_k = C_l r_{k-1} - alpha_k C_l q_k (level 1 in r_1, levels >= 2 in
-//    rc_l, C_l q_k gathered from the restriction of q_k the SpMV left; each
-//    unit has one writer), and computes y_l = Inv_{l,d} C_l r_k and the
-//    partial of (C_l r_k)^T y_l.
-// rho_k = r^T z + sum_l (C_l r)^T y_l is the sum of both kinds of partials.
-// The two do not depend on each other: the prolongation, which would make
-// level 0 wait for the coarse levels, is left to the next SpMV.  So the
-// coarse levels, a chain of round trips to memory that leaves most of the
-// machine idle (7-9 us as a launch of its own at 48^3), run beside the
-// streaming of the level-0 inverses.  Four level-1 domains share a workgroup
-// (two threads per row); a domain of a higher level, whose units gather up to
-// a hundred partials each, has one to itself (eight threads per row).
-struct RecTable {
-    int off[kMaxLv + 1];  // first coarse workgroup of each level >= 1
-    int pad;              // coarse workgroups rounded up to whole rounds of XCDs
-};
-
-// alpha_k, or false (after flagging NOT_SPD or NOT_FINITE from group 0) when
-// sigma <= 0 or a value is not finite: every workgroup sees the same sigma
-// and returns without writing.
-__device__ __forceinline__ bool rec_alpha(const SolverView& v, int k, bool report, const PartialLoads<>& sig,
-                                          double rho, double* buf, double& alpha) {
-    const double sigma = partials_sum(sig, v.P_sigma, v.G, buf);
-    if (!(sigma > 0.0) || !finite(sigma) || !finite(rho)) {
+// alpha_k = rho_{k-1} / sigma_k, or false (after flagging NOT_SPD or
+// NOT_FINITE where report is set) when sigma <= 0 or a value is not finite:
+// every workgroup sees the same sigma and returns without writing.  buf: 256
+// doubles of shared memory, not written again before another barrier.
+__device__ __forceinline__ bool rec_alpha(const SolverView& v, int k, bool report, const RecLoads& R, double* buf,
+                                          double& alpha) {
+    const double sigma = partials_sum<false>(R.sig, v.P_sigma, v.G, buf);
+    if (!(sigma > 0.0) || !finite(sigma) || !finite(R.rho)) {
         if (report && threadIdx.x == 0) {
-            v.st->status = (finite(sigma) && finite(rho)) ? -2 : -6;
+            v.st->status = (finite(sigma) && finite(R.rho)) ? -2 : -6;
             v.st->done = 1;
             v.st->iter = k - 1;
         }
         return false;
     }
-    alpha = rho / sigma;
+    alpha = R.rho / sigma;
     return true;
 }
 
-constexpr int kRecRound = 4;  // partials per lane and round in the coarse workgroups of this launch
+// ---- coarse levels
+// Workgroup b of the coarse levels: r_l of its domains' units, then y_l =
+// Inv_{l,d} r_l.  kRec (iteration k by recurrence): r_l <- r_l - alpha_k
+// (C_l q_k) from the restriction of q_k the SpMV left (q_1, qpart), in place
+// (r_1, rc_l; each unit has one writer), and the partial of r_l^T y_l.
+// Otherwise straight from the residual's restriction (r_1, cpart), kept in
+// rc_l for the recurrence unless mode is kApplyPlain.  Level 1 has its values
+// in r_1; a unit of a higher level sums the contiguous range of per-group
+// partials the restriction left for it (up to about a hundred at the top).
 
-// rl[384], buf[256], sum[384], red[16]: shared memory.
-template <typename TI, int kN>
-__device__ __forceinline__ void rec_coarse(const SolverView& v, const RecTable& tab, int k, int b, double* rl,
-                                           double* buf, double* sum, double* red) {
-    const int t = threadIdx.x;
-    int l = 1;
-    while (l + 1 < v.L && b >= tab.off[l + 1]) ++l;
-    const int N = kN > 0 ? kN : v.N, n = 3 * N;
-    const TI* invl;
-    if constexpr (sizeof(TI) == 8)
-        invl = v.inv64[l];
-    else
-        invl = v.inv32[l];
-    PartialLoads<> sig = partials_load(v.P_sigma, v.G);
-    const double rho = v.st->rho[(k - 1) & 1];
-    double part = 0.0;
-    if (kN == 16 && l == 1) {
-        constexpr int kCols = 24;
-        const int dl = t / 96, half = t % 96 / 48, row = t % 48;
-        const int d = kRecLevel1 * (b - tab.off[1]) + dl;
-        const bool dom = d < v.ndom[1];
-        const int e = 48 * d + row;
-        const bool own = dom && half == 0 && e < 3 * v.units[1];
-        const int ec = own ? e : 0;
-        const double prev = v.r1[ec], qv = v.q1[ec];
-        double pre[kCols];
-        const TI* inv = invl + (dom ? static_cast<long long>(d) * 2304 : 0) + 48 * kCols * half + row;
+// Domain size 16: eight level-1 domains, a pair per wave, or one pair of a
+// higher level (three waves gather, one multiplies).  sm: 4 kPairLds doubles, buf: 256, red: 16.
+constexpr int kItem = 8;     // partials of an item
+constexpr int kItems = 192;  // items at a time: one per thread of the gathering waves
+
+template <typename TI, bool kRec>
+__device__ __forceinline__ void coarse_pairs(const SolverView& v, const CoarseTable& tab, int mode, int k, int b,
+                                             double* sm, double* buf, double* red) {
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int l = coarse_level(tab, v.L, b);
+    const int pairs = (v.ndom[l] + 1) / 2, nrow = 3 * v.units[l];
+    RecLoads R{};
+    if constexpr (kRec) R = rec_load(v, k);
+    PairRegs<TI> P;
+    double x[2] = {0.0, 0.0}, out[2] = {0.0, 0.0}, part = 0.0;
+    if (l == 1) {
+        const int p = 4 * (b - tab.off[1]) + w;
+        int e[2];
+        bool own[2];
+        double prev[2], qv[2] = {0.0, 0.0};
 #pragma unroll
-        for (int j = 0; j < kCols; ++j) pre[j] = inv_load<TI, false>(inv + 48 * j);
+        for (int q = 0; q < 2; ++q) {
+            e[q] = 96 * p + pair_row(lane, q);
+            own[q] = pair_owns(lane, q) && e[q] < nrow;
+            prev[q] = v.r1[own[q] ? e[q] : 0];
+            if constexpr (kRec) qv[q] = v.q1[own[q] ? e[q] : 0];
+        }
+        pair_load(P, inverses<TI>(v, 1) + static_cast<long long>(min(p, pairs - 1)) * kPairEntries, lane);
         const int stop = v.st->done;
         keep_loads_issued();
-        if (stop) return;
-        double alpha;
-        if (!rec_alpha(v, k, false, sig, rho, buf, alpha)) return;
-        double r = 0.0;
-        if (own) {
-            r = prev - alpha * qv;
-            v.r1[e] = r;
-        }
-        if (half == 0) rl[48 * dl + row] = r;
-        __syncthreads();
-        double a = 0.0;
+        if (mode != kApplyPlain && stop) return;
+        double alpha = 0.0;
+        if (kRec && !rec_alpha(v, k, false, R, buf, alpha)) return;
 #pragma unroll
-        for (int j = 0; j < kCols; ++j) a += pre[j] * rl[48 * dl + kCols * half + j];
-        if (half == 1) sum[48 * dl + row] = a;
-        __syncthreads();
-        if (half == 0 && dom) {
-            a += sum[48 * dl + row];
-            v.y[1][e] = a;
-            part = r * a;
+        for (int q = 0; q < 2; ++q) {
+            if (!own[q]) continue;
+            x[q] = kRec ? prev[q] - alpha * qv[q] : prev[q];
+            if (kRec) v.r1[e[q]] = x[q];
+        }
+        if (p < pairs) {
+            pair_product(P, x, sm + w * kPairLds, lane, out);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (own[q]) {
+                    v.y[1][e[q]] = out[q];
+                    part += x[q] * out[q];
+                }
         }
     } else {
-        const int d = b - tab.off[l];
-        const int u0 = d * N, nu = min(N, v.units[l] - u0);
-        constexpr int kParts = 8, kCols = 6;  // N = 16
-        const int row = t % 48, seg = t / 48;
-        const TI* inv = invl + static_cast<long long>(d) * n * n;
-        double pre[kCols];
-        double p0 = 0.0, p1 = 0.0, p2 = 0.0, q1v = 0.0;
+        // waves 0 to 2 gather, wave 3 holds the inverses.  A unit of the top
+        // levels can have hundreds of partials beside units that have a few,
+        // so the pair's partials are dealt as items of up to kItem of one
+        // unit, one per thread: two round trips (the ranges, the partials)
+        // whatever their spread.  Items are summed in order per (unit,
+        // component).
+        const int p = b - tab.off[l];
+        const int u0 = 32 * p, nu = min(32, v.units[l] - u0);
+        int* first = reinterpret_cast<int*>(sm + 3 * kPairLds);  // [33] first item of each unit
+        int* from = first + 34;                                  // [32] its first partial
+        int* to = from + 32;                                     // [32] end of its partials
+        double* isum = sm + kPairLds;                            // [3 kItems] sums of the items at hand
+        const int* cp = v.cp_ptr[l] + u0;
+        const double* src = kRec ? v.qpart : v.cpart;
+        const bool entry = t < 96 && t < 3 * nu;
+        double prev = 0.0;
+        if (kRec && entry) prev = v.rc[l][3 * u0 + t];
         int m0 = 0, m1 = 0;
-        if constexpr (kN == 16) {
-#pragma unroll
-            for (int j = 0; j < kCols; ++j) pre[j] = inv_load<TI, false>(inv + 48 * (kCols * seg + j) + row);
-            const int u = u0 + min(t >> 4, nu - 1);
-            p0 = v.rc[l][3 * u];
-            p1 = v.rc[l][3 * u + 1];
-            p2 = v.rc[l][3 * u + 2];
-            m0 = v.cp_ptr[l][u];
-            m1 = v.cp_ptr[l][u + 1];
-        } else if (l == 1) {
-            const int e = 3 * u0 + min(t, 3 * nu - 1);
-            p0 = v.r1[e];
-            q1v = v.q1[e];
+        if (t < nu) {
+            m0 = cp[t];
+            m1 = cp[t + 1];
         }
         const int stop = v.st->done;
         keep_loads_issued();
-        if (stop) return;
-        double alpha;
-        if (!rec_alpha(v, k, false, sig, rho, buf, alpha)) return;
-        double r = 0.0;
-        if (kN != 16 && l == 1) {
-            if (t < 3 * nu) {
-                r = p0 - alpha * q1v;
-                v.r1[3 * u0 + t] = r;
+        if (mode != kApplyPlain && stop) return;
+        if (w == 0) {
+            int n = (m1 - m0 + kItem - 1) / kItem;
+#pragma unroll
+            for (int o = 1; o < 32; o <<= 1) {
+                const int below = __shfl_up(n, o);
+                if (lane >= o) n += below;
             }
-            if (t < n) rl[t] = r;
-        } else {
-            auto put = [&](int a, bool own, double c0, double c1, double c2, double s0, double s1, double s2) {
-                if (own) {
-                    s0 = c0 - alpha * s0;
-                    s1 = c1 - alpha * s1;
-                    s2 = c2 - alpha * s2;
-                    double* rc = v.rc[l] + 3 * (u0 + a);
-                    rc[0] = s0;
-                    rc[1] = s1;
-                    rc[2] = s2;
-                }
-                rl[3 * a] = own ? s0 : 0.0;
-                rl[3 * a + 1] = own ? s1 : 0.0;
-                rl[3 * a + 2] = own ? s2 : 0.0;
-            };
-            double s0, s1, s2;
-            if constexpr (kN == 16) {
-                const int a = t >> 4, sub = t & 15;
-                if (t < 256) {  // whole waves
-                    gather_unit16<kRecRound>(v.qpart, m0, m1, sub, s0, s1, s2);
-                    if (sub == 0) put(a, a < nu, p0, p1, p2, s0, s1, s2);
-                }
-            } else {
-                const int lane = t & 63;
-                for (int a = t >> 6; a < N; a += kGroupThreads / 64) {
-                    const bool own = a < nu;
-                    gather_unit64(v.qpart, own ? v.cp_ptr[l][u0 + a] : 0, own ? v.cp_ptr[l][u0 + a + 1] : 0, lane, s0,
-                                  s1, s2);
-                    if (lane == 0) {
-                        const double* rc = v.rc[l] + 3 * (u0 + min(a, nu - 1));
-                        put(a, own, rc[0], rc[1], rc[2], s0, s1, s2);
-                    }
-                }
+            if (lane < 32) {
+                if (lane == 0) first[0] = 0;
+                first[lane + 1] = n;
+                from[lane] = m0;
+                to[lane] = m1;
             }
         }
         __syncthreads();
-        if constexpr (kN == 16) {
-            double a = 0.0;
+        const int items = first[32];
+        // item it into isum[it % kItems]; many: with all its loads in flight
+        auto gather = [&](int it, auto many) {
+            int a = 0;
 #pragma unroll
-            for (int j = 0; j < kCols; ++j) a += pre[j] * rl[kCols * seg + j];
-            sum[t] = a;  // [part][row]
-            __syncthreads();
-            if (t < 48) {
+            for (int step = 16; step > 0; step >>= 1)
+                if (first[a + step] <= it) a += step;
+            const int f = from[a] + kItem * (it - first[a]), e = min(f + kItem, to[a]);
+            double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+            if constexpr (many.value) {
+                double c0[kItem], c1[kItem], c2[kItem];
 #pragma unroll
-                for (int j = 1; j < kParts; ++j) a += sum[48 * j + t];
-                v.y[l][3 * u0 + t] = a;
-                part = rl[t] * a;
+                for (int j = 0; j < kItem; ++j) {
+                    const int mj = min(f + j, e - 1);
+                    c0[j] = src[3 * mj];
+                    c1[j] = src[3 * mj + 1];
+                    c2[j] = src[3 * mj + 2];
+                }
+#pragma unroll
+                for (int j = 0; j < kItem; ++j)
+                    if (f + j < e) {
+                        s0 += c0[j];
+                        s1 += c1[j];
+                        s2 += c2[j];
+                    }
+            } else {
+#pragma unroll 1
+                for (int m = f; m < e; ++m) {
+                    s0 += src[3 * m];
+                    s1 += src[3 * m + 1];
+                    s2 += src[3 * m + 2];
+                }
             }
-        } else if (t < n) {
-            double a = 0.0;
-#pragma unroll 8
-            for (int kk = 0; kk < n; ++kk) a += inv_load<TI, false>(inv + static_cast<long long>(kk) * n + t) * rl[kk];
-            v.y[l][3 * u0 + t] = a;
-            part = rl[t] * a;
+            isum[3 * t] = s0;
+            isum[3 * t + 1] = s1;
+            isum[3 * t + 2] = s2;
+        };
+        if (t < kItems && t < items) gather(t, std::true_type{});
+        // (after the gather in the text, so that its registers are not counted
+        // on top of these)
+        if (w == 3) pair_load(P, inverses<TI>(v, l) + static_cast<long long>(p) * kPairEntries, lane);
+        double s = 0.0;
+        for (int i0 = 0;;) {
+            __syncthreads();
+            if (entry) {
+                const int a = t / 3, c = t - 3 * a;
+                const int hi = min(first[a + 1] - i0, kItems);
+#pragma unroll 4
+                for (int i = max(first[a] - i0, 0); i < hi; ++i) s += isum[3 * i + c];
+            }
+            i0 += kItems;
+            if (i0 >= items) break;
+            __syncthreads();
+            if (t < kItems && i0 + t < items) gather(i0 + t, std::false_type{});  // (rare; few registers)
+        }
+        double alpha = 0.0;
+        if (kRec && !rec_alpha(v, k, false, R, buf, alpha)) return;
+        if (t < 96) {
+            const double r = entry ? (kRec ? prev - alpha * s : s) : 0.0;
+            if (entry && mode != kApplyPlain) v.rc[l][3 * u0 + t] = r;
+            sm[t] = r;
+        }
+        __syncthreads();
+        if (w == 3) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) x[q] = pair_owns(lane, q) ? sm[pair_row(lane, q)] : 0.0;
+            pair_product(P, x, sm + kPairLds, lane, out);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int e = pair_row(lane, q);
+                if (pair_owns(lane, q) && e < 3 * nu) {
+                    v.y[l][3 * u0 + e] = out[q];
+                    part += x[q] * out[q];
+                }
+            }
         }
     }
-    part = block_sum_last(part, red);
-    if (t == 0) v.P_rho[k & 1][v.G + b] = part;
+    if constexpr (kRec) {
+        part = block_sum_last(part, red);
+        if (t == 0) v.P_rho[k & 1][v.GA + b] = part;
+    }
 }
 
+// Other domain sizes: one domain per workgroup, a wave per unit for the
+// gather, a thread per row.  rl: 128 doubles, buf: 256, red: 16.
+template <typename TI, bool kRec>
+__device__ __forceinline__ void coarse_domain(const SolverView& v, const CoarseTable& tab, int mode, int k, int b,
+                                              double* rl, double* buf, double* red) {
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    const int l = coarse_level(tab, v.L, b);
+    const int d = b - tab.off[l], N = v.N, n = 3 * N;
+    const int u0 = d * N, nu = min(N, v.units[l] - u0);
+    RecLoads R{};
+    if constexpr (kRec) R = rec_load(v, k);
+    const int stop = v.st->done;
+    keep_loads_issued();
+    if (mode != kApplyPlain && stop) return;
+    double alpha = 0.0;
+    if (kRec && !rec_alpha(v, k, false, R, buf, alpha)) return;
+    if (l == 1) {
+        double r = 0.0;
+        if (t < 3 * nu) {
+            r = v.r1[3 * u0 + t];
+            if constexpr (kRec) {
+                r -= alpha * v.q1[3 * u0 + t];
+                v.r1[3 * u0 + t] = r;
+            }
+        }
+        if (t < n) rl[t] = r;
+    } else {
+        const int* cp = v.cp_ptr[l];
+        for (int a = w; a < N; a += static_cast<int>(blockDim.x >> 6)) {
+            const bool own = a < nu;
+            double s[3];
+            gather_unit64(kRec ? v.qpart : v.cpart, own ? cp[u0 + a] : 0, own ? cp[u0 + a + 1] : 0, lane, s[0], s[1],
+                          s[2]);
+            if (lane == 0) {
+                double* rc = v.rc[l] + 3 * (u0 + a);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const double r = own ? (kRec ? rc[c] - alpha * s[c] : s[c]) : 0.0;
+                    if (own && mode != kApplyPlain) rc[c] = r;
+                    rl[3 * a + c] = r;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    double part = 0.0;
+    if (t < n) {
+        const double y = full_row<TI, false>(inverses<TI>(v, l) + static_cast<long long>(d) * n * n, n, t, rl);
+        v.y[l][3 * u0 + t] = y;
+        part = rl[t] * y;
+    }
+    if constexpr (kRec) {
+        part = block_sum_last(part, red);
+        if (t == 0) v.P_rho[k & 1][v.GA + b] = part;
+    }
+}
+
+// The coarse levels as a launch of their own (outside the recurrence), with
+// the convergence decision on the n_rr partials of ||r||^2 in workgroup 0.
 template <typename TI, int kN>
-__global__ void __launch_bounds__(kGroupThreads) k_apply_rec(SolverView v, RecTable tab, int k) {
-    constexpr bool kPackedInv = kN == 16 && sizeof(TI) == 8;
-    __shared__ double rs[kGroupThreads];
-    __shared__ double zs[kGroupThreads];
-    __shared__ double stage[kPackedInv ? kPairs * kPacked : kGroupThreads];
-    __shared__ double red[16];
-    const int t = threadIdx.x;
-    if (static_cast<int>(blockIdx.x) < tab.pad) {
-        if (static_cast<int>(blockIdx.x) < v.ncb) rec_coarse<TI, kN>(v, tab, k, blockIdx.x, rs, zs, stage, red);
+__global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_coarse(SolverView v, CoarseTable tab, int mode, int k,
+                                                               double tol, int flags, int n_rr) {
+    __shared__ double sm[kN == 16 ? 4 * kPairLds : 128];
+    __shared__ double buf[256];
+    if (blockIdx.x == 0) {
+        if (mode != kApplyPlain) convergence_decision(v, mode == kApplyInit, k, tol, flags, n_rr, 1, buf);
         return;
     }
-    const int N = kN > 0 ? kN : v.N;
-    const int n = 3 * N;
-    const int g = xcd_group(blockIdx.x - tab.pad, v.G);
+    if constexpr (kN == 16)
+        coarse_pairs<TI, false>(v, tab, mode, k, blockIdx.x - 1, sm, buf, nullptr);
+    else
+        coarse_domain<TI, false>(v, tab, mode, k, blockIdx.x - 1, sm, buf, nullptr);
+}
+
+// ---- level 0
+// Sum over l >= 1 of y_l at the slot's unit (prolongation of every coarse
+// level, Supp. Eq. 6): eight levels' unit ids at once, then their
+// corrections at once.
+constexpr int kProlong = 8;
+
+__device__ __forceinline__ double prolong(const SolverView& v, int slot, int c) {
+    double s = 0.0;
+    for (int l0 = 0; l0 + 1 < v.L; l0 += kProlong) {
+        int u[kProlong];
+        double y[kProlong];
+#pragma unroll
+        for (int j = 0; j < kProlong; ++j)
+            u[j] = l0 + j + 1 < v.L ? v.anc[static_cast<long long>(l0 + j) * v.NS + slot] : -1;
+#pragma unroll
+        for (int j = 0; j < kProlong; ++j) y[j] = u[j] >= 0 ? v.y[l0 + j + 1][3 * u[j] + c] : 0.0;
+#pragma unroll
+        for (int j = 0; j < kProlong; ++j) s += y[j];
+    }
+    return s;
+}
+
+// z = Inv_{0,d} r_d + the prolongation of the coarse corrections and, inside
+// PCG, the partial of rho = r^T z.  Domain size 16: eight domains per
+// workgroup, a pair per wave.
+template <typename TI, int kMode>
+__global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_level0_pairs(SolverView v, int k) {
+    __shared__ double sm[4 * kPairLds];
+    __shared__ double red[4];
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int b = xcd_group(blockIdx.x, v.GA);
+    const int p = 4 * b + w;
+    const bool live = 2 * p < v.M;
+    int e[2];
+    bool own[2];
+    double x[2], out[2] = {0.0, 0.0}, cor[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        e[q] = 96 * p + pair_row(lane, q);
+        own[q] = pair_owns(lane, q) && e[q] < 3 * v.NS;
+        x[q] = own[q] ? v.r[e[q]] : 0.0;
+    }
+    PairRegs<TI> P;
+    pair_load(P, inverses<TI>(v, 0) + static_cast<long long>(live ? p : 0) * kPairEntries, lane);
+    const int stop = v.st->done;
+    keep_loads_issued();
+    if (kMode != kApplyPlain && stop) return;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) cor[q] = own[q] ? prolong(v, e[q] / 3, e[q] % 3) : 0.0;
+    if (live) pair_product(P, x, sm + w * kPairLds, lane, out);
+    double part = 0.0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (own[q]) {
+            const double z = out[q] + cor[q];
+            v.z[e[q]] = z;
+            part += x[q] * z;
+        }
+    if (kMode == kApplyPlain) return;
+    part = block_sum_last(part, red);
+    if (t == 0) v.P_rho[k & 1][b] = part;
+}
+
+// The same for other domain sizes: a group of D0 domains per workgroup, one
+// thread per DOF.
+template <typename TI, int kMode>
+__global__ void __launch_bounds__(kGroupThreads) k_apply_level0(SolverView v, int k) {
+    __shared__ double rs[kGroupThreads];
+    __shared__ double red[16];
+    const int n = 3 * v.N;
+    const int g = xcd_group(blockIdx.x, v.G), t = threadIdx.x;
     const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
     const bool live = t < nd * n;
-    const long long i = 3LL * g * v.RG + (live ? t : 0);
-    PackedPair P;
-    const double* inv = v.inv64[0] + static_cast<long long>(g) * v.D0 * kPacked;
-    if constexpr (kPackedInv) fetch_pair(P, inv, 0, nd);
-    const PartialLoads<> sig = partials_load(v.P_sigma, v.G);
-    const double rho = v.st->rho[(k - 1) & 1];
-    const double xv = v.x[i], pv = v.p[k & 1][i], ro = v.r[i], qv = v.q[i];
+    const long long base = 3LL * g * v.RG;
+    const double rv = live ? v.r[base + t] : 0.0;
+    const int stop = v.st->done;
+    keep_loads_issued();
+    if (kMode != kApplyPlain && stop) return;
+    const double cor = live ? prolong(v, g * v.RG + t / 3, t % 3) : 0.0;
+    rs[t] = rv;
+    __syncthreads();
+    double zv = 0.0;
+    if (live) {
+        const int dl = t / n;
+        zv = full_row<TI, true>(inverses<TI>(v, 0) + static_cast<long long>(g * v.D0 + dl) * n * n, n, t - dl * n,
+                                rs + dl * n) +
+             cor;
+        v.z[base + t] = zv;
+    }
+    if (kMode == kApplyPlain) return;
+    const double part = block_sum_last(rv * zv, red);
+    if (t == 0) v.P_rho[k & 1][g] = part;
+}
+
+// ---- apply of a two-launch iteration
+// Iteration k by recurrence, in one launch after the SpMV.  Every workgroup
+// forms alpha_k from the sigma partials; the first workgroups take the coarse
+// levels (coarse_pairs / coarse_domain), the others perform x += alpha p_k and
+// r -= alpha q_k on their level-0 domains and z = Inv_{0,d} r_d, with the
+// partials of r^T z and ||r_k||^2.  rho_k = r^T z + sum_l (C_l r)^T y_l is the
+// sum of both kinds of partials.  The two do not depend on each other: the
+// prolongation, which would make level 0 wait for the coarse levels, is left
+// to the next SpMV.  So the coarse levels, a chain of round trips to memory
+// that leaves most of the machine idle (7-9 us as a launch of its own at
+// 48^3), run beside the streaming of the level-0 inverses.
+// pad: coarse workgroups rounded up to whole rounds of XCDs.
+template <typename TI>
+__global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_rec_pairs(SolverView v, CoarseTable tab, int pad, int k) {
+    __shared__ double sm[4 * kPairLds];
+    __shared__ double buf[256];
+    __shared__ double red[16];
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (static_cast<int>(blockIdx.x) < pad) {
+        if (static_cast<int>(blockIdx.x) < v.ncb) coarse_pairs<TI, true>(v, tab, kApplyIter, k, blockIdx.x, sm, buf, red);
+        return;
+    }
+    const int b = xcd_group(blockIdx.x - pad, v.GA);
+    const int p = 4 * b + w;
+    const bool live = 2 * p < v.M;
+    const RecLoads R = rec_load(v, k);
+    int e[2];
+    bool own[2];
+    double xv[2], pv[2], ro[2], qv[2];
+    const double* pk = v.p[k & 1];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        e[q] = 96 * p + pair_row(lane, q);
+        own[q] = pair_owns(lane, q) && e[q] < 3 * v.NS;
+        const int i = own[q] ? e[q] : 0;
+        xv[q] = v.x[i];
+        pv[q] = pk[i];
+        ro[q] = v.r[i];
+        qv[q] = v.q[i];
+    }
+    PairRegs<TI> P;
+    pair_load(P, inverses<TI>(v, 0) + static_cast<long long>(live ? p : 0) * kPairEntries, lane);
     // the stop flag is read once these loads are in flight; after a stop
     // nothing is written
     const int stop = v.st->done;
     keep_loads_issued();
     if (stop) return;
     double alpha;
-    if (!rec_alpha(v, k, g == 0, sig, rho, zs, alpha)) return;  // zs is first written after a later barrier
+    if (!rec_alpha(v, k, b == 0, R, buf, alpha)) return;
+    double x[2], out[2] = {0.0, 0.0}, prho = 0.0, prr = 0.0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        x[q] = 0.0;
+        if (!own[q]) continue;
+        v.x[e[q]] = xv[q] + alpha * pv[q];
+        x[q] = ro[q] - alpha * qv[q];
+        v.r[e[q]] = x[q];
+    }
+    if (live) pair_product(P, x, sm + w * kPairLds, lane, out);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (!own[q]) continue;
+        v.z[e[q]] = out[q];
+        prho += x[q] * out[q];
+        prr += x[q] * x[q];
+    }
+    double srho, srr;
+    block_sum2_last(prho, prr, red, srho, srr);
+    if (t == 0) {
+        v.P_rho[k & 1][b] = srho;
+        v.P_rr[b] = srr;
+    }
+}
+
+template <typename TI>
+__global__ void __launch_bounds__(kGroupThreads) k_apply_rec(SolverView v, CoarseTable tab, int pad, int k) {
+    __shared__ double rs[kGroupThreads];
+    __shared__ double buf[256];
+    __shared__ double red[16];
+    const int t = threadIdx.x;
+    if (static_cast<int>(blockIdx.x) < pad) {
+        if (static_cast<int>(blockIdx.x) < v.ncb) coarse_domain<TI, true>(v, tab, kApplyIter, k, blockIdx.x, rs, buf, red);
+        return;
+    }
+    const int n = 3 * v.N;
+    const int g = xcd_group(blockIdx.x - pad, v.G);
+    const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
+    const bool live = t < nd * n;
+    const long long i = 3LL * g * v.RG + (live ? t : 0);
+    const RecLoads R = rec_load(v, k);
+    const double xv = v.x[i], pv = v.p[k & 1][i], ro = v.r[i], qv = v.q[i];
+    const int stop = v.st->done;
+    keep_loads_issued();
+    if (stop) return;
+    double alpha;
+    if (!rec_alpha(v, k, g == 0, R, buf, alpha)) return;
     double rv = 0.0;
     if (live) {
         v.x[i] = xv + alpha * pv;
@@ -874,15 +982,14 @@ __global__ void __launch_bounds__(kGroupThreads) k_apply_rec(SolverView v, RecTa
         v.r[i] = rv;
     }
     rs[t] = rv;
+    __syncthreads();
     double zv = 0.0;
-    if constexpr (kPackedInv) {
-        packed_rounds(P, inv, nd, rs, zs, stage);
-        if (live) zv = zs[t];
-    } else {
-        __syncthreads();
-        if (live) zv = full_row<TI, kN>(level0_inverses<TI>(v), n, g * v.D0 + t / n, t % n, rs + t / n * n);
+    if (live) {
+        const int dl = t / n;
+        zv = full_row<TI, true>(inverses<TI>(v, 0) + static_cast<long long>(g * v.D0 + dl) * n * n, n, t - dl * n,
+                                rs + dl * n);
+        v.z[i] = zv;
     }
-    if (live) v.z[i] = zv;
     double prho, prr;
     block_sum2_last(rv * zv, rv * rv, red, prho, prr);
     if (t == 0) {
@@ -944,71 +1051,87 @@ hipError_t launch_invert(const BuildView& b, const double* Hu, bool want32, hipS
     return hipGetLastError();
 }
 
+namespace {
+
+CoarseTable coarse_table(const SolverView& v) {
+    CoarseTable t{};
+    int acc = 0;
+    for (int l = 1; l < v.L; ++l) {
+        t.off[l] = acc;
+        acc += coarse_blocks(v.N, l, v.ndom[l]);
+    }
+    for (int l = v.L; l <= kMaxLv; ++l) t.off[l] = acc;
+    return t;
+}
+
+template <typename TI>
+void launch_level0_t(const SolverView& v, int mode, int k, hipStream_t s) {
+    if (v.N == 16) {
+        dim3 g(v.GA), b(kPairThreads);
+        if (mode == kApplyPlain)
+            launch_kernel((k_apply_level0_pairs<TI, kApplyPlain>), g, b, 0, s, v, k);
+        else if (mode == kApplyInit)
+            launch_kernel((k_apply_level0_pairs<TI, kApplyInit>), g, b, 0, s, v, k);
+        else
+            launch_kernel((k_apply_level0_pairs<TI, kApplyIter>), g, b, 0, s, v, k);
+        return;
+    }
+    dim3 g(v.G), b(round_waves(3 * v.RG));
+    if (mode == kApplyPlain)
+        launch_kernel((k_apply_level0<TI, kApplyPlain>), g, b, 0, s, v, k);
+    else if (mode == kApplyInit)
+        launch_kernel((k_apply_level0<TI, kApplyInit>), g, b, 0, s, v, k);
+    else
+        launch_kernel((k_apply_level0<TI, kApplyIter>), g, b, 0, s, v, k);
+}
+
+template <typename TI>
+void launch_rec_t(const SolverView& v, int k, hipStream_t s) {
+    const CoarseTable tab = coarse_table(v);
+    const int pad = ceil_div(v.ncb, kXcds) * kXcds;
+    dim3 g(pad + v.GA);
+    if (v.N == 16)
+        launch_kernel(k_apply_rec_pairs<TI>, g, dim3(kPairThreads), 0, s, v, tab, pad, k);
+    else
+        launch_kernel(k_apply_rec<TI>, g, dim3(kGroupThreads), 0, s, v, tab, pad, k);
+}
+
+}  // namespace
+
 hipError_t launch_apply_coarse(const SolverView& v, bool f32, int mode, int k, double tol, bool x0_given, bool mixed,
-                               bool rr_true, hipStream_t s, bool decision_only) {
-    const DomTable tab = make_table(v.ndom, 1, v.L);
-    const int total = decision_only ? 1 : 1 + tab.off[kMaxLv];  // workgroup 0 decides convergence
+                               bool rr_true, hipStream_t s) {
+    const CoarseTable tab = coarse_table(v);
+    const dim3 g(1 + v.ncb), b(kPairThreads);  // workgroup 0 decides convergence
     const int flags = (x0_given ? kFlagX0 : 0) | (mixed ? kFlagMixed : 0) | (rr_true ? kFlagRrTrue : 0);
     if (v.N == 16) {
-        if (f32) launch_kernel((k_apply_coarse<float, 16>), dim3(total), dim3(256), 0, s, v, tab, mode, k, tol, flags);
-        else launch_kernel((k_apply_coarse<double, 16>), dim3(total), dim3(256), 0, s, v, tab, mode, k, tol, flags);
+        if (f32) launch_kernel((k_apply_coarse<float, 16>), g, b, 0, s, v, tab, mode, k, tol, flags, v.G);
+        else launch_kernel((k_apply_coarse<double, 16>), g, b, 0, s, v, tab, mode, k, tol, flags, v.G);
     } else {
-        if (f32) launch_kernel((k_apply_coarse<float, 0>), dim3(total), dim3(256), 0, s, v, tab, mode, k, tol, flags);
-        else launch_kernel((k_apply_coarse<double, 0>), dim3(total), dim3(256), 0, s, v, tab, mode, k, tol, flags);
+        if (f32) launch_kernel((k_apply_coarse<float, 0>), g, b, 0, s, v, tab, mode, k, tol, flags, v.G);
+        else launch_kernel((k_apply_coarse<double, 0>), g, b, 0, s, v, tab, mode, k, tol, flags, v.G);
     }
     return hipGetLastError();
 }
 
-template <typename TI, int kN>
-void launch_level0_t(const SolverView& v, int mode, int k, hipStream_t s) {
-    dim3 g(v.G), b(round_waves(3 * v.RG));
-    if constexpr (kN == 16 && sizeof(TI) == 8) {
-        b = dim3(kGroupThreads);
-        if (mode == kApplyPlain)
-            launch_kernel(k_apply_level0_packed<kApplyPlain>, g, b, 0, s, v, k);
-        else if (mode == kApplyInit)
-            launch_kernel(k_apply_level0_packed<kApplyInit>, g, b, 0, s, v, k);
-        else
-            launch_kernel(k_apply_level0_packed<kApplyIter>, g, b, 0, s, v, k);
-    } else {
-        if (mode == kApplyPlain)
-            launch_kernel((k_apply_level0<TI, kN, kApplyPlain>), g, b, 0, s, v, k);
-        else if (mode == kApplyInit)
-            launch_kernel((k_apply_level0<TI, kN, kApplyInit>), g, b, 0, s, v, k);
-        else
-            launch_kernel((k_apply_level0<TI, kN, kApplyIter>), g, b, 0, s, v, k);
-    }
+hipError_t launch_decision(const SolverView& v, int k, bool mixed, hipStream_t s) {
+    launch_kernel((k_apply_coarse<double, 0>), dim3(1), dim3(kPairThreads), 0, s, v, CoarseTable{},
+                  static_cast<int>(kApplyIter), k, 0.0, mixed ? kFlagMixed : 0, v.GA);
+    return hipGetLastError();
 }
 
 hipError_t launch_apply_level0(const SolverView& v, bool f32, int mode, int k, hipStream_t s) {
-    if (v.N == 16) {
-        if (f32) launch_level0_t<float, 16>(v, mode, k, s);
-        else launch_level0_t<double, 16>(v, mode, k, s);
-    } else {
-        if (f32) launch_level0_t<float, 0>(v, mode, k, s);
-        else launch_level0_t<double, 0>(v, mode, k, s);
-    }
+    if (f32)
+        launch_level0_t<float>(v, mode, k, s);
+    else
+        launch_level0_t<double>(v, mode, k, s);
     return hipGetLastError();
 }
 
 hipError_t launch_apply_rec(const SolverView& v, bool f32, int k, hipStream_t s) {
-    RecTable tab{};
-    int acc = 0;
-    for (int l = 1; l < v.L; ++l) {
-        tab.off[l] = acc;
-        acc += l == 1 && v.N == 16 ? ceil_div(v.ndom[1], kRecLevel1) : v.ndom[l];
-    }
-    for (int l = v.L; l <= kMaxLv; ++l) tab.off[l] = acc;
-    if (acc != v.ncb) return hipErrorInvalidValue;  // the P_rho arrays hold G + ncb partials
-    tab.pad = ceil_div(acc, kXcds) * kXcds;
-    dim3 g(tab.pad + v.G), b(kGroupThreads);
-    if (v.N == 16) {
-        if (f32) launch_kernel((k_apply_rec<float, 16>), g, b, 0, s, v, tab, k);
-        else launch_kernel((k_apply_rec<double, 16>), g, b, 0, s, v, tab, k);
-    } else {
-        if (f32) launch_kernel((k_apply_rec<float, 0>), g, b, 0, s, v, tab, k);
-        else launch_kernel((k_apply_rec<double, 0>), g, b, 0, s, v, tab, k);
-    }
+    if (f32)
+        launch_rec_t<float>(v, k, s);
+    else
+        launch_rec_t<double>(v, k, s);
     return hipGetLastError();
 }
 

@@ -361,67 +361,126 @@ void symmetric_storage(Plan& P) {
     P.sym = P.RG <= 256 && P.maxT <= kMaxTransposed;
 }
 
-// The level-1 units each group's SpMV reads (see Plan::hptr).
+// The level-1 units each group's SpMV reads (see Plan::hptr).  Groups are
+// independent: ranges of them on up to eight threads.
 void halo_units(Plan& P) {
-    const int NS = P.NS, RG = P.RG, G = P.G;
-    P.halo = false;
-    P.maxH = 0;
-    P.hptr.assign(static_cast<size_t>(G) + 1, 0);
-    std::vector<int> units;
-    std::vector<int> ext;
-    std::vector<int> seen(P.L > 1 ? P.units[1] : 0, -1);
-    for (int g = 0; g < G && P.L > 1; ++g) {
-        const int r0 = g * RG, r1 = std::min(r0 + RG, NS);
-        ext.clear();
-        for (int k = P.rp0[r0]; k < P.rp0[r1]; ++k) {
-            const int j = P.ci0[k];
-            if (j >= r0 && j < r1) continue;
-            const int u = P.anc[j];
-            if (seen[u] != g) {
-                seen[u] = g;
-                ext.push_back(u);
-            }
-        }
-        const int n = P.g_u1[g + 1] - P.g_u1[g] + static_cast<int>(ext.size());
-        P.maxH = std::max(P.maxH, n);
-        if (n > kMaxHalo) {
-            P.maxH = 0;
-            P.hptr.clear();
-            return;
-        }
-        std::sort(ext.begin(), ext.end());
-        for (int u = P.g_u1[g]; u < P.g_u1[g + 1]; ++u) units.push_back(u);
-        units.insert(units.end(), ext.begin(), ext.end());
-        P.hptr[g + 1] = static_cast<int>(units.size());
-    }
+    const int NS = P.NS, RG = P.RG, G = P.G, L = P.L;
     P.halo = true;
-    std::vector<long long> base(P.L + 1, 0);  // first position of each level's correction
-    for (int l = 1; l < P.L; ++l) base[l + 1] = base[l] + static_cast<long long>(P.ndom[l]) * P.N;
-    P.hy.resize(units.size() * static_cast<size_t>(std::max(P.L - 1, 0)));
+    P.maxH = P.maxH2 = 0;
+    P.hptr.assign(static_cast<size_t>(G) + 1, 0);
+    P.h2ptr.assign(static_cast<size_t>(G) + 1, 0);
     P.hidx.assign(P.ci0.size(), 0);
     P.hidx_sym.assign(P.sym ? P.sci.size() : 0, 0);
-    std::vector<int> local(P.L > 1 ? P.units[1] : 0, 0);
-    for (int g = 0; g < G && P.L > 1; ++g) {
-        const int r0 = g * RG, r1 = std::min(r0 + RG, NS), h0 = P.hptr[g], n = P.hptr[g + 1] - h0;
-        int* y = P.hy.data() + static_cast<size_t>(P.L - 1) * h0;
-        for (int i = 0; i < n; ++i) {
-            int a = units[h0 + i];
-            local[a] = i;
-            for (int l = 1; l < P.L; ++l) {
-                if (l > 1) a = P.up[l - 1][a];
-                y[static_cast<size_t>(l - 1) * n + i] = static_cast<int>(base[l] + a);
+    if (L < 2) return;
+    const int hw = static_cast<int>(std::thread::hardware_concurrency());
+    const int T = P.ci0.size() >= (1u << 16) ? std::max(1, std::min({hw, 8, G})) : 1;
+    struct Part {
+        std::vector<int> hu, list2;
+        std::vector<uint16_t> hpar;
+        int maxH = 0, maxH2 = 0;
+        bool fits = true;
+    };
+    std::vector<Part> parts(T);
+    auto each = [&](auto&& f) {
+        std::vector<std::thread> th;
+        for (int w = 1; w < T; ++w) th.emplace_back(f, w);
+        f(0);
+        for (auto& x : th) x.join();
+    };
+    auto begin = [&](int w) { return static_cast<int>(static_cast<long long>(G) * w / T); };
+    // units and level-2 entries of each group, and the blocks' local units
+    each([&](int w) {
+        Part& R = parts[w];
+        std::vector<int> ext, two;
+        std::vector<int> local(P.units[1], 0), seen(P.units[1], -1), seen2(L > 2 ? P.units[2] : 0, -1);
+        for (int g = begin(w); g < begin(w + 1); ++g) {
+            const int r0 = g * RG, r1 = std::min(r0 + RG, NS);
+            ext.clear();
+            for (int k = P.rp0[r0]; k < P.rp0[r1]; ++k) {
+                const int j = P.ci0[k];
+                if (j >= r0 && j < r1) continue;
+                const int u = P.anc[j];
+                if (seen[u] != g) {
+                    seen[u] = g;
+                    ext.push_back(u);
+                }
+            }
+            const int own = P.g_u1[g + 1] - P.g_u1[g], n = own + static_cast<int>(ext.size());
+            R.maxH = std::max(R.maxH, n);
+            if (n > kMaxHalo) {
+                R.fits = false;
+                return;
+            }
+            std::sort(ext.begin(), ext.end());
+            const size_t h0 = R.hu.size();
+            for (int u = P.g_u1[g]; u < P.g_u1[g + 1]; ++u) R.hu.push_back(u);
+            R.hu.insert(R.hu.end(), ext.begin(), ext.end());
+            for (int i = 0; i < n; ++i) local[R.hu[h0 + i]] = i;
+            two.clear();
+            if (L > 2)
+                for (int i = 0; i < n; ++i) {
+                    const int a = P.up[1][R.hu[h0 + i]];
+                    if (seen2[a] != g) {
+                        seen2[a] = g;
+                        two.push_back(a);
+                    }
+                }
+            std::sort(two.begin(), two.end());
+            for (int i = 0; i < n; ++i)
+                R.hpar.push_back(
+                    L > 2 ? static_cast<uint16_t>(std::lower_bound(two.begin(), two.end(), P.up[1][R.hu[h0 + i]]) -
+                                                  two.begin())
+                          : 0);
+            R.list2.insert(R.list2.end(), two.begin(), two.end());
+            R.maxH2 = std::max(R.maxH2, static_cast<int>(two.size()));
+            P.hptr[g + 1] = n;
+            P.h2ptr[g + 1] = static_cast<int>(two.size());
+            size_t o = P.sym ? P.srp[r0] : 0;
+            for (int s = r0; s < r1; ++s)
+                for (int k = P.rp0[s]; k < P.rp0[s + 1]; ++k) {
+                    const int j = P.ci0[k];
+                    const bool inside = j >= r0 && j < r1;
+                    const uint16_t h = inside ? 0 : static_cast<uint16_t>(local[P.anc[j]]);
+                    P.hidx[k] = h;
+                    if (P.sym && (!inside || j >= s)) P.hidx_sym[o++] = h;
+                }
+        }
+    });
+    std::vector<int> list2;
+    for (Part& R : parts) {
+        if (!R.fits) {
+            P.halo = false;
+            P.maxH = P.maxH2 = 0;
+            for (auto* x : {&P.hptr, &P.hu, &P.h2ptr}) x->clear();
+            for (auto* x : {&P.hpar, &P.hidx, &P.hidx_sym}) x->clear();
+            return;
+        }
+        P.maxH = std::max(P.maxH, R.maxH);
+        P.maxH2 = std::max(P.maxH2, R.maxH2);
+        P.hu.insert(P.hu.end(), R.hu.begin(), R.hu.end());
+        P.hpar.insert(P.hpar.end(), R.hpar.begin(), R.hpar.end());
+        list2.insert(list2.end(), R.list2.begin(), R.list2.end());
+    }
+    for (int g = 0; g < G; ++g) {
+        P.hptr[g + 1] += P.hptr[g];
+        P.h2ptr[g + 1] += P.h2ptr[g];
+    }
+    std::vector<long long> base(L + 1, 0);  // first position of each level's corrections
+    for (int l = 1; l < L; ++l) base[l + 1] = base[l] + static_cast<long long>(P.ndom[l]) * P.N;
+    P.hy.resize(list2.size() * static_cast<size_t>(std::max(L - 2, 0)));
+    each([&](int w) {
+        for (int g = begin(w); g < begin(w + 1) && L > 2; ++g) {
+            const int h0 = P.h2ptr[g], n = P.h2ptr[g + 1] - h0;
+            int* y = P.hy.data() + static_cast<size_t>(L - 2) * h0;
+            for (int i = 0; i < n; ++i) {
+                int a = list2[h0 + i];
+                for (int l = 2; l < L; ++l) {
+                    if (l > 2) a = P.up[l - 1][a];
+                    y[static_cast<size_t>(l - 2) * n + i] = static_cast<int>(base[l] + a);
+                }
             }
         }
-        size_t o = P.sym ? P.srp[r0] : 0;
-        for (int s = r0; s < r1; ++s)
-            for (int k = P.rp0[s]; k < P.rp0[s + 1]; ++k) {
-                const int j = P.ci0[k];
-                const bool inside = j >= r0 && j < r1;
-                const uint16_t h = inside ? 0 : static_cast<uint16_t>(local[P.anc[j]]);
-                P.hidx[k] = h;
-                if (P.sym && (!inside || j >= s)) P.hidx_sym[o++] = h;
-            }
-    }
+    });
 }
 
 // Workgroup order of the SpMV.  The group kernels give each XCD a

@@ -112,17 +112,19 @@ struct Plan {
 
     // Level-1 units whose coarse correction group g reads, at [hptr[g],
     // hptr[g+1]): its own (ascending), then those of its rows' columns outside
-    // the group (ascending).  hy holds, for unit i of the group's n and level
-    // l >= 1, the position of its ancestor's correction in the coarse
-    // vectors laid end to end (level 1 first, ndom[l] * N units each), at
-    // [(L-1) hptr[g] + (l-1) n + i].  hidx / hidx_sym: the group's local unit
+    // the group (ascending); hu: the unit; hpar: the local index of its level-2
+    // unit among the distinct ones (ascending), which [h2ptr[g], h2ptr[g+1])
+    // lists: hy holds, for entry i of the group's n2 and level l >= 2, the
+    // position of its ancestor's correction in the coarse vectors laid end to
+    // end (level 1 first, ndom[l] * N units each), at
+    // [(L-2) h2ptr[g] + (l-2) n2 + i].  hidx / hidx_sym: the group's local unit
     // of every slot-ordered / symmetrically stored block whose column lies
     // outside the group (0 for the others).  All empty (halo = false) when
     // some group reads more than kMaxHalo units.
     bool halo = false;
-    int maxH = 0;  // most units of one group
-    std::vector<int> hptr, hy;
-    std::vector<uint16_t> hidx, hidx_sym;
+    int maxH = 0, maxH2 = 0;  // most units, most level-2 entries of one group
+    std::vector<int> hptr, hu, h2ptr, hy;
+    std::vector<uint16_t> hpar, hidx, hidx_sym;
 
     // SpMV group of each workgroup when the groups' stored blocks are
     // uneven (empty: the contiguous per-XCD mapping of the group kernels)

@@ -51,7 +51,7 @@ __global__ void k_rp_counts_init(ReplanCounts* __restrict__ c) {
     }
     for (int l = 0; l <= kMaxLv; ++l) c->cbase[l] = 0;
     c->gw_max = 0;
-    c->h_max = 0;
+    c->h_max = c->h2_max = 0;
 }
 
 __global__ void k_rp_store(int* __restrict__ dst, const int* __restrict__ src) {
@@ -419,93 +419,42 @@ __global__ void k_rp_group_writers(int G, int NS, int L, const int* __restrict__
     atomicMax(&c->gw_max, n);
 }
 
-// The level-1 units of a group's columns outside the group, gathered by its
-// workgroup into a hash set in LDS (linear probing; -1: empty).  Insertion
-// stops once more than kMaxHalo are found, so the set, four times that size,
-// never fills and every probe ends.
+// A set of units in LDS, filled by a workgroup (linear probing; -1: empty).
+// Insertion stops once more than kMaxHalo are found, so the set, four times
+// that size, never fills and every probe ends.
 constexpr int kHaloTable = 4 * kMaxHalo;
 
-__device__ __forceinline__ void halo_collect(int NS, int RG, int g, const int* __restrict__ rp,
-                                             const int* __restrict__ ci, const int* __restrict__ sn1, int* table,
-                                             int* found) {
+__device__ __forceinline__ void set_clear(int* table, int* found) {
     for (int i = threadIdx.x; i < kHaloTable; i += blockDim.x) table[i] = -1;
     if (threadIdx.x == 0) *found = 0;
     __syncthreads();
-    const int r0 = g * RG, r1 = min(r0 + RG, NS);
-    for (int p = rp[r0] + threadIdx.x; p < rp[r1]; p += blockDim.x) {
-        const int j = ci[p];
-        if (j >= r0 && j < r1) continue;
-        if (*static_cast<volatile int*>(found) > kMaxHalo) break;
-        const int u = sn1[j];
-        unsigned h = static_cast<unsigned>(u) * 2654435761u >> 16;
-        for (int probe = 0; probe < kHaloTable; ++probe, ++h) {
-            const int was = atomicCAS(table + h % kHaloTable, -1, u);
-            if (was == u) break;
-            if (was == -1) {
-                atomicAdd(found, 1);
-                break;
-            }
+}
+
+__device__ __forceinline__ void set_insert(int* table, int* found, int u) {
+    if (*static_cast<volatile int*>(found) > kMaxHalo) return;
+    unsigned h = static_cast<unsigned>(u) * 2654435761u >> 16;
+    for (int probe = 0; probe < kHaloTable; ++probe, ++h) {
+        const int was = atomicCAS(table + h % kHaloTable, -1, u);
+        if (was == u) return;
+        if (was == -1) {
+            atomicAdd(found, 1);
+            return;
         }
     }
+}
+
+// The set's members, ascending, into list[kMaxHalo] (padded with INT_MAX);
+// at most kMaxHalo members.
+__device__ __forceinline__ void set_sorted(const int* table, int* found, int* list) {
+    const int t = threadIdx.x;
     __syncthreads();
-}
-
-// Units group g's SpMV reads: its own level-1 units and the distinct ones of
-// its outside columns (kMaxHalo + 1 stands for more than kMaxHalo).
-__global__ void __launch_bounds__(kRpThreads) k_rp_halo_count(int G, int NS, int RG, int L,
-                                                              const int* __restrict__ rp, const int* __restrict__ ci,
-                                                              const int* __restrict__ sn1,
-                                                              const int* __restrict__ g_u1, int* __restrict__ cnt,
-                                                              ReplanCounts* __restrict__ c) {
-    __shared__ int table[kHaloTable];
-    __shared__ int found;
-    const int g = blockIdx.x;
-    if (g == G || L < 2) {  // closes the scan
-        if (threadIdx.x == 0) cnt[g] = 0;
-        return;
-    }
-    halo_collect(NS, RG, g, rp, ci, sn1, table, &found);
-    if (threadIdx.x == 0) {
-        const int n = min(g_u1[g + 1] - g_u1[g] + found, kMaxHalo + 1);
-        cnt[g] = n;
-        atomicMax(&c->h_max, n);
-    }
-}
-
-// First position of each level's corrections (Plan::hy).
-struct LevelBase {
-    int at[kMaxLv];
-};
-
-// Group g's unit list (own units, then the outside ones ascending), their
-// positions at every level and the local unit of every block of the SpMV's
-// storage.
-__global__ void __launch_bounds__(kRpThreads) k_rp_halo_place(int NS, int RG, int L, const int* __restrict__ rp,
-                                                              const int* __restrict__ ci, const int* __restrict__ sn1,
-                                                              const int* __restrict__ g_u1,
-                                                              const int* __restrict__ anc1,
-                                                              const int* __restrict__ hptr, LevelBase base,
-                                                              const int* __restrict__ srp, const int* __restrict__ sci,
-                                                              int* __restrict__ hy, uint16_t* __restrict__ hidx) {
-    __shared__ int table[kHaloTable];
-    __shared__ int list[kMaxHalo];
-    __shared__ int found;
-    const int g = blockIdx.x, t = threadIdx.x;
-    const int r0 = g * RG, r1 = min(r0 + RG, NS);
-    const int* p = srp ? srp : rp;
-    const int* c = srp ? sci : ci;
-    if (L < 2) {  // no coarse level: no units
-        for (int k = p[r0] + t; k < p[r1]; k += kRpThreads) hidx[k] = 0;
-        return;
-    }
-    halo_collect(NS, RG, g, rp, ci, sn1, table, &found);
     for (int i = t; i < kMaxHalo; i += kRpThreads) list[i] = 0x7fffffff;
-    if (t == 0) found = 0;
+    if (t == 0) *found = 0;
     __syncthreads();
     for (int i = t; i < kHaloTable; i += kRpThreads)
-        if (table[i] >= 0) list[atomicAdd(&found, 1)] = table[i];
+        if (table[i] >= 0) list[atomicAdd(found, 1)] = table[i];
     __syncthreads();
-    for (int k = 2; k <= kMaxHalo; k <<= 1)  // bitonic sort, ascending
+    for (int k = 2; k <= kMaxHalo; k <<= 1)  // bitonic sort
         for (int j = k >> 1; j > 0; j >>= 1) {
             for (int i = t; i < kMaxHalo; i += kRpThreads) {
                 const int o = i ^ j;
@@ -519,19 +468,122 @@ __global__ void __launch_bounds__(kRpThreads) k_rp_halo_place(int NS, int RG, in
             }
             __syncthreads();
         }
+}
+
+// Units of one level at the group's columns outside the group (own: and at
+// the group's own slots).
+__device__ __forceinline__ void halo_collect(int NS, int RG, int g, const int* __restrict__ rp,
+                                             const int* __restrict__ ci, const int* __restrict__ sn, bool own,
+                                             int* table, int* found) {
+    set_clear(table, found);
+    const int r0 = g * RG, r1 = min(r0 + RG, NS);
+    for (int p = rp[r0] + threadIdx.x; p < rp[r1]; p += blockDim.x) {
+        const int j = ci[p];
+        if (j < r0 || j >= r1) set_insert(table, found, sn[j]);
+    }
+    if (own)
+        for (int s = r0 + threadIdx.x; s < r1; s += blockDim.x)
+            if (sn[s] >= 0) set_insert(table, found, sn[s]);
+    __syncthreads();
+}
+
+// Units group g's SpMV reads: its own level-1 units and the distinct ones of
+// its outside columns (kMaxHalo + 1 stands for more than kMaxHalo); the
+// distinct level-2 units above all of them.
+__global__ void __launch_bounds__(kRpThreads) k_rp_halo_count(int G, int NS, int RG, int L,
+                                                              const int* __restrict__ rp, const int* __restrict__ ci,
+                                                              const int* __restrict__ sn,
+                                                              const int* __restrict__ g_u1, int* __restrict__ cnt,
+                                                              int* __restrict__ cnt2, ReplanCounts* __restrict__ c) {
+    __shared__ int table[kHaloTable];
+    __shared__ int found;
+    const int g = blockIdx.x;
+    if (g == G || L < 2) {  // closes the scans
+        if (threadIdx.x == 0) cnt[g] = cnt2[g] = 0;
+        return;
+    }
+    halo_collect(NS, RG, g, rp, ci, sn + NS, false, table, &found);
+    if (threadIdx.x == 0) {
+        const int n = min(g_u1[g + 1] - g_u1[g] + found, kMaxHalo + 1);
+        cnt[g] = n;
+        atomicMax(&c->h_max, n);
+        cnt2[g] = 0;
+    }
+    if (L < 3) return;
+    __syncthreads();
+    halo_collect(NS, RG, g, rp, ci, sn + 2 * static_cast<size_t>(NS), true, table, &found);
+    if (threadIdx.x == 0) {
+        cnt2[g] = min(found, kMaxHalo + 1);
+        atomicMax(&c->h2_max, cnt2[g]);
+    }
+}
+
+// First position of each level's corrections (Plan::hy).
+struct LevelBase {
+    int at[kMaxLv];
+};
+
+// Group g's units (own, then the outside ones ascending) with the local index
+// of the level-2 entry above each, the lowest of them below each entry (rep2),
+// and the local unit of every block of the SpMV's storage.
+__global__ void __launch_bounds__(kRpThreads) k_rp_halo_place(
+    int NS, int RG, int L, const int* __restrict__ rp, const int* __restrict__ ci, const int* __restrict__ sn,
+    const int* __restrict__ g_u1, const int* __restrict__ up2, const int* __restrict__ hptr,
+    const int* __restrict__ h2ptr, const int* __restrict__ srp, const int* __restrict__ sci, int* __restrict__ hu,
+    uint16_t* __restrict__ hpar, int* __restrict__ rep2, uint16_t* __restrict__ hidx) {
+    __shared__ int table[kHaloTable];
+    __shared__ int list[kMaxHalo], two[kMaxHalo], rep[kMaxHalo];
+    __shared__ int found;
+    const int g = blockIdx.x, t = threadIdx.x;
+    const int r0 = g * RG, r1 = min(r0 + RG, NS);
+    const int* p = srp ? srp : rp;
+    const int* c = srp ? sci : ci;
+    if (L < 2) {  // no coarse level: no units
+        for (int k = p[r0] + t; k < p[r1]; k += kRpThreads) hidx[k] = 0;
+        return;
+    }
+    halo_collect(NS, RG, g, rp, ci, sn + NS, false, table, &found);
+    set_sorted(table, &found, list);
+    const int n2 = L > 2 ? h2ptr[g + 1] - h2ptr[g] : 0;
+    if (L > 2) {
+        halo_collect(NS, RG, g, rp, ci, sn + 2 * static_cast<size_t>(NS), true, table, &found);
+        set_sorted(table, &found, two);
+        for (int i = t; i < n2; i += kRpThreads) rep[i] = 0x7fffffff;
+        __syncthreads();
+    }
     const int u0 = g_u1[g], own = g_u1[g + 1] - u0;
     const int h0 = hptr[g], n = hptr[g + 1] - h0, ext = n - own;
-    int* y = hy + static_cast<size_t>(L - 1) * h0;
-    for (int e = t; e < (L - 1) * n; e += kRpThreads) {
-        const int l = 1 + e / n, i = e - (l - 1) * n;
+    for (int i = t; i < n; i += kRpThreads) {
         const int u = i < own ? u0 + i : list[i - own];
-        y[e] = base.at[l] + (l == 1 ? u : anc1[static_cast<size_t>(l) * NS + u]);
+        hu[h0 + i] = u;
+        int par = 0;
+        if (L > 2) {
+            par = first_at_least(two, 0, n2, up2[u]);
+            atomicMin(rep + par, u);
+        }
+        hpar[h0 + i] = static_cast<uint16_t>(par);
     }
+    __syncthreads();
+    for (int i = t; i < n2; i += kRpThreads) rep2[h2ptr[g] + i] = rep[i];
     for (int k = p[r0] + t; k < p[r1]; k += kRpThreads) {
         const int j = c[k];
         int h = 0;
-        if (j < r0 || j >= r1) h = own + first_at_least(list, 0, ext, sn1[j]);
+        if (j < r0 || j >= r1) h = own + first_at_least(list, 0, ext, sn[NS + j]);
         hidx[k] = static_cast<uint16_t>(h);
+    }
+}
+
+// Positions of the level-2 entries' corrections at every level, through a
+// level-1 unit below each.
+__global__ void __launch_bounds__(64) k_rp_halo_pos(int NS, int L, const int* __restrict__ anc1,
+                                                    const int* __restrict__ h2ptr, const int* __restrict__ rep2,
+                                                    LevelBase base, int* __restrict__ hy) {
+    const int g = blockIdx.x;
+    const int h0 = h2ptr[g], n = h2ptr[g + 1] - h0;
+    int* y = hy + static_cast<size_t>(L - 2) * h0;
+    for (int e = threadIdx.x; e < (L - 2) * n; e += 64) {
+        const int l = 2 + e / n, i = e - (l - 2) * n;
+        y[e] = base.at[l] + anc1[static_cast<size_t>(l) * NS + rep2[h0 + i]];
     }
 }
 
@@ -716,6 +768,8 @@ ReplanLayout replan_layout(char* ws, int V, int NS, int G, long long nnzb, size_
     R.gstore = reinterpret_cast<int*>(take(I * 3 * G));
     R.hcnt = reinterpret_cast<int*>(take(I * (G + 1)));
     R.hptr = reinterpret_cast<int*>(take(I * (G + 1)));
+    R.h2cnt = reinterpret_cast<int*>(take(I * (G + 1)));
+    R.h2ptr = reinterpret_cast<int*>(take(I * (G + 1)));
     R.t_grp = reinterpret_cast<int*>(take(I * ns));
     R.anc1 = reinterpret_cast<int*>(take(I * kMaxLv * ns));
     R.lpos = reinterpret_cast<int*>(take(I * kMaxLv * ns));
@@ -780,10 +834,11 @@ hipError_t replan_sizes(const ReplanLayout& R, const ReplanShape& S, hipStream_t
     if ((e = scan(R, R.gcnt, R.g_u1, G + 1, s)) != hipSuccess) return e;
     // the units each group's SpMV reads
     launch_kernel(k_rp_halo_count, dim3(G + 1), dim3(kRpThreads), 0, s, G, NS, RG, L, static_cast<const int*>(R.rp0),
-                  static_cast<const int*>(R.ci0), static_cast<const int*>(R.H.sn + NS),
-                  static_cast<const int*>(R.g_u1), R.hcnt, R.counts);
+                  static_cast<const int*>(R.ci0), static_cast<const int*>(R.H.sn),
+                  static_cast<const int*>(R.g_u1), R.hcnt, R.h2cnt, R.counts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = scan(R, R.hcnt, R.hptr, G + 1, s)) != hipSuccess) return e;
+    if ((e = scan(R, R.h2cnt, R.h2ptr, G + 1, s)) != hipSuccess) return e;
     // coarse levels; each level's block count is read back to size the next
     // level's sort (sorting a bound instead costs a full-length sort per
     // level: 4-5 ms over the 16 levels of the membrane with bodies)
@@ -880,16 +935,23 @@ hipError_t replan_place(const ReplanLayout& R, const PlacedShape& P, const PlanD
                 hipSuccess)
                 return e;
     }
-    // the units each group's SpMV reads
+    // the units each group's SpMV reads (R.rows: free after the first pass)
     if (D.hptr) {
         if ((e = copy_ints(D.hptr, R.hptr, G + 1, s)) != hipSuccess) return e;
-        LevelBase base{};
-        for (int l = 2; l < L; ++l) base.at[l] = base.at[l - 1] + S.ndom[l - 1] * S.N;
+        if ((e = copy_ints(D.h2ptr, R.h2ptr, G + 1, s)) != hipSuccess) return e;
+        int* rep2 = R.rows;
         launch_kernel(k_rp_halo_place, dim3(G), dim3(kRpThreads), 0, s, NS, RG, L, static_cast<const int*>(R.rp0),
-                      static_cast<const int*>(R.ci0), static_cast<const int*>(R.H.sn + NS),
-                      static_cast<const int*>(R.g_u1), static_cast<const int*>(R.anc1),
-                      static_cast<const int*>(R.hptr), base, D.hidx_sym ? static_cast<const int*>(D.srp) : nullptr,
-                      static_cast<const int*>(D.sci), D.hy, D.hidx);
+                      static_cast<const int*>(R.ci0), static_cast<const int*>(R.H.sn),
+                      static_cast<const int*>(R.g_u1), static_cast<const int*>(R.anc1 + 2 * static_cast<size_t>(NS)),
+                      static_cast<const int*>(R.hptr), static_cast<const int*>(R.h2ptr),
+                      D.hidx_sym ? static_cast<const int*>(D.srp) : nullptr, static_cast<const int*>(D.sci), D.hu,
+                      D.hpar, rep2, D.hidx);
+        if (L > 2) {
+            LevelBase base{};
+            for (int l = 2; l < L; ++l) base.at[l] = base.at[l - 1] + S.ndom[l - 1] * S.N;
+            launch_kernel(k_rp_halo_pos, dim3(G), dim3(64), 0, s, NS, L, static_cast<const int*>(R.anc1),
+                          static_cast<const int*>(R.h2ptr), static_cast<const int*>(rep2), base, D.hy);
+        }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     // inversion gathers of level 0 (caller block order)

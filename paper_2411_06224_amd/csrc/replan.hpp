@@ -33,7 +33,7 @@ struct ReplanCounts {
     int ndomblk[kMaxLv];     // inversion gather entries of each level
     int cbase[kMaxLv + 1];   // first coarse-partial position of each level >= 2; cbase[L] = n_cpart
     int gw_max;              // most writers of one group
-    int h_max;               // most level-1 units one group's SpMV reads
+    int h_max, h2_max;       // most level-1 units one group's SpMV reads, most level-2 units above them
 };
 
 struct ReplanLayout {
@@ -50,6 +50,7 @@ struct ReplanLayout {
     int *gcnt, *g_u1;        // per-group level-1 units and their scan [G + 1]
     int* gstore;             // per group: stored blocks of the full and symmetric storage, transposed entries [3 G]
     int *hcnt, *hptr;        // level-1 units each group's SpMV reads and their scan [G + 1]
+    int *h2cnt, *h2ptr;      // the distinct level-2 units above them and their scan [G + 1]
     int* t_grp;              // group of each level-1 unit [NS]
     int *anc1, *lpos;        // [kMaxLv NS]: level-l unit / partial position of each level-1 unit
     int* cpp;                // [kMaxLv (NS + 1)]: cp_ptr of each level
@@ -85,8 +86,8 @@ struct PlanDest {
     int *ganc, *gpos;
     int *srp, *sci, *tptr, *tidx;
     uint8_t* srow;
-    int *hptr, *hy;   // null: no unit lists (a group reads more than kMaxHalo units)
-    uint16_t* hidx;   // of the SpMV's storage: symmetric (hidx_sym) or full
+    int *hptr, *hu, *h2ptr, *hy;  // null: no unit lists (a group reads more than kMaxHalo units)
+    uint16_t *hpar, *hidx;        // hidx: of the SpMV's storage, symmetric (hidx_sym) or full
     int hidx_sym;
     int *red_ptr[kMaxLv], *red_src[kMaxLv], *dom_ptr[kMaxLv], *dom_blk[kMaxLv], *dom_ab[kMaxLv], *cp_ptr[kMaxLv];
 };

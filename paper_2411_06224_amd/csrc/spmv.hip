@@ -367,62 +367,85 @@ __device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, 
     }
 }
 
-// The coarse corrections of a group's level-1 units (kSplit), sum over the
-// levels of y_l at the unit's ancestors, level 1 first: the same sum in every
-// group that reads a unit.  unit_load issues the position loads of a thread's
-// first item (unit t / 3, component t % 3), unit_gather the corrections of
-// its first kUnitLevels levels; unit_stage adds up, takes the further levels
-// and items, and leaves them in LDS.  The first item's two round trips
-// overlap the rho sum.
-constexpr int kUnitLevels = 8;
+// The coarse corrections of a group's level-1 units (kSplit), in LDS: y_1 at
+// the unit plus the sum over the levels >= 2 of y_l at its ancestors, the same
+// sum in every group that reads the unit.  The levels >= 2 are summed once per
+// distinct level-2 unit (at 48^3 a group reads about 76 units under 23 of
+// them).  unit_load issues a thread's table loads (level-2 entry t / 3 or
+// unit t / 3, component t % 3), unit_gather the corrections they name;
+// unit_stage adds up, takes what is left over, and leaves the sums in ycor.
+// The two round trips overlap the rho sum.
+constexpr int kUnitLevels = 7;  // levels >= 2 a thread loads ahead
 
 struct UnitLoads {
-    int n;                   // 3 x units of the group
-    const int* pos;          // position of the thread's item at level 1; levels n / 3 apart
-    int at[kUnitLevels];
-    double y[kUnitLevels];
+    int n, n2;       // units and level-2 entries of the group
+    const int* pos;  // position of entry i at level 2 + l: pos[l n2 + i]
+    int at[kUnitLevels], u, par;
+    double y[kUnitLevels], y1;
 };
 
 __device__ __forceinline__ UnitLoads unit_load(const SolverView& v, int g) {
     UnitLoads U;
-    const int h0 = v.hptr[g], n = v.hptr[g + 1] - h0;
-    U.n = 3 * n;
-    U.pos = v.hy + static_cast<long long>(v.L - 1) * h0;
-    const int i = min(static_cast<int>(threadIdx.x) / 3, n - 1);
+    const int h0 = v.hptr[g], q0 = v.h2ptr[g];
+    U.n = v.hptr[g + 1] - h0;
+    U.n2 = v.h2ptr[g + 1] - q0;
+    U.pos = v.hy + static_cast<long long>(max(v.L - 2, 0)) * q0;
+    const int i = static_cast<int>(threadIdx.x) / 3;
+    const int i2 = min(i, U.n2 - 1);
 #pragma unroll
-    for (int l = 0; l < kUnitLevels; ++l) U.at[l] = n > 0 && l + 1 < v.L ? U.pos[l * n + i] : 0;
+    for (int l = 0; l < kUnitLevels; ++l) U.at[l] = l + 2 < v.L ? U.pos[l * U.n2 + i2] : 0;
+    U.u = U.par = 0;
+    if (U.n > 0) {
+        U.u = v.hu[h0 + min(i, U.n - 1)];
+        U.par = v.hpar[h0 + min(i, U.n - 1)];
+    }
     return U;
 }
 
 __device__ __forceinline__ void unit_gather(const SolverView& v, UnitLoads& U) {
     const int c = threadIdx.x % 3;
+    U.y1 = U.n > 0 ? v.yall[3LL * U.u + c] : 0.0;
+    if (static_cast<int>(threadIdx.x) < 3 * U.n2) {
 #pragma unroll
-    for (int l = 0; l < kUnitLevels; ++l) U.y[l] = l + 1 < v.L ? v.yall[3LL * U.at[l] + c] : 0.0;
+        for (int l = 0; l < kUnitLevels; ++l) U.y[l] = l + 2 < v.L ? v.yall[3LL * U.at[l] + c] : 0.0;
+    }
 }
 
-__device__ __forceinline__ void unit_stage(const SolverView& v, const UnitLoads& U, double* ycor) {
-    const int n = U.n / 3;
-    for (int e = threadIdx.x; e < U.n; e += kThreads) {
+// ycor: 3 maxH doubles, then 3 maxH2 for the level-2 sums.  Ends with a
+// barrier.
+__device__ __forceinline__ void unit_stage(const SolverView& v, int g, const UnitLoads& U, double* ycor) {
+    double* up = ycor + 3 * v.maxH;
+    for (int e = threadIdx.x; e < 3 * U.n2; e += kThreads) {
         const int i = e / 3, c = e - 3 * i;
         double s = 0.0;
+        int l0 = 2;
         if (e < kThreads) {
 #pragma unroll
-            for (int l = 0; l < kUnitLevels; ++l)
-                if (l + 1 < v.L) s += U.y[l];
+            for (int l = 0; l < kUnitLevels; ++l) s += U.y[l];  // (0 past the last level)
+            l0 = 2 + kUnitLevels;
         }
-        for (int l0 = e < kThreads ? kUnitLevels : 0; l0 + 1 < v.L; l0 += kUnitLevels) {
-            int at[kUnitLevels];
-            double y[kUnitLevels];
+        for (; l0 < v.L; l0 += 4) {
+            int at[4];
+            double y[4];
 #pragma unroll
-            for (int l = 0; l < kUnitLevels; ++l) at[l] = U.pos[min(l0 + l, v.L - 2) * n + i];
+            for (int l = 0; l < 4; ++l) at[l] = U.pos[(min(l0 + l, v.L - 1) - 2) * U.n2 + i];
 #pragma unroll
-            for (int l = 0; l < kUnitLevels; ++l) y[l] = v.yall[3LL * at[l] + c];
+            for (int l = 0; l < 4; ++l) y[l] = v.yall[3LL * at[l] + c];
 #pragma unroll
-            for (int l = 0; l < kUnitLevels; ++l)
-                if (l0 + l + 1 < v.L) s += y[l];
+            for (int l = 0; l < 4; ++l)
+                if (l0 + l < v.L) s += y[l];
         }
-        ycor[e] = s;
+        up[e] = s;
     }
+    __syncthreads();
+    const int h0 = v.hptr[g];
+    for (int e = threadIdx.x; e < 3 * U.n; e += kThreads) {
+        const int i = e / 3, c = e - 3 * i;
+        const double y1 = e < kThreads ? U.y1 : v.yall[3LL * v.hu[h0 + i] + c];
+        const int par = e < kThreads ? U.par : v.hpar[h0 + i];
+        ycor[e] = v.L > 2 ? y1 + up[3 * par + c] : y1;
+    }
+    __syncthreads();
 }
 
 // The group's own units are the first of its list: local unit of slot s.
@@ -433,7 +456,7 @@ __device__ __forceinline__ int own_unit(const SolverView& v, int g, int slot) {
 // Workgroup G of a split SpMV takes the decision on r_{k-1}.
 __device__ __forceinline__ bool decide_only(const SolverView& v, int k, int flags, double* buf) {
     if (static_cast<int>(blockIdx.x) < v.G) return false;
-    convergence_decision(v, false, k - 1, 0.0, flags, buf);
+    convergence_decision(v, false, k - 1, 0.0, flags, v.GA, spmv_mark(k), buf);
     return true;
 }
 
@@ -449,14 +472,14 @@ constexpr int kRhoPer = 8;  // rho partials a thread loads ahead: up to 2048 in 
 //
 // kSplit: z_{k-1} = v.z + the coarse corrections, which the level-0 apply left
 // out so that it need not wait for the coarse levels.  A group reads few
-// distinct level-1 units (about 60 at 48^3, with nine levels), so it sums
-// each unit's levels once into LDS; an outside column then costs one 16-bit
-// index and three LDS reads more.
+// distinct level-1 units, so it sums each unit's levels once into LDS
+// (unit_stage); an outside column then costs one 16-bit index and three LDS
+// reads more.
 template <typename T, int kRQ, bool kSplit>
 __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __restrict__ H, int k, int flags) {
     __shared__ double prod[3 * kPlane];
     __shared__ double buf[256];
-    extern __shared__ double dyn[];  // xs[3 RG] (+ ycor[3 maxH])
+    extern __shared__ double dyn[];  // xs[3 RG] (+ ycor[3 (maxH + maxH2)])
     if (kSplit && decide_only(v, k, flags, buf)) return;
     const int t = threadIdx.x;
     const int g = spmv_group(v);
@@ -469,7 +492,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     // entries of z and p_{k-1}, unconditionally at clamped indices (see
     // partials_load)
     const double* Prho = v.P_rho[(k - 1) & 1];
-    const int nrho = kSplit ? v.G + v.ncb : v.G;
+    const int nrho = kSplit ? v.GA + v.ncb : v.GA;
     UnitLoads U{};
     if constexpr (kSplit) U = unit_load(v, g);
     const auto rl = partials_load<kSplit ? kRhoPer : 4>(Prho, nrho);
@@ -489,15 +512,14 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     if constexpr (kRQ) pl = restrict_load(v, g);
     const int stop = v.st->done;
     keep_loads_issued();
-    if (stop) return;  // after a stop nothing is written
+    if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
     // rho_{k-1} from the partials; rho_{k-2} as the previous SpMV recorded it
     const double rk2 = v.st->rho[k & 1];
     if constexpr (kSplit) unit_gather(v, U);
     const double rk1 = partials_sum<false>(rl, Prho, nrho, buf);  // buf is next written after later barriers
     if (g == 0 && t == 0) v.st->rho[(k - 1) & 1] = rk1;
     if constexpr (kSplit) {
-        unit_stage(v, U, ycor);
-        __syncthreads();
+        unit_stage(v, g, U, ycor);
     }
     const double beta = k > 1 ? rk1 / rk2 : 0.0;
     double* pk = v.p[k & 1];
@@ -527,7 +549,7 @@ template <typename T, int kRQ, bool kSplit>
 __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T* __restrict__ H, int k, int flags) {
     __shared__ double prod[6 * kSymPlane];
     __shared__ double buf[256];
-    extern __shared__ double dyn[];  // xs[3 RG] doubles (+ ycor[3 maxH]) + tl[maxT] ints
+    extern __shared__ double dyn[];  // xs[3 RG] doubles (+ ycor[3 (maxH + maxH2)]) + tl[maxT] ints
     if (kSplit && decide_only(v, k, flags, buf)) return;
     const int t = threadIdx.x;
     const int g = spmv_group(v);
@@ -535,14 +557,14 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     const int nown = 3 * (r1 - r0);
     double* xs = dyn;
     double* ycor = dyn + 3 * v.RG;
-    int* tl = reinterpret_cast<int*>(ycor + (kSplit ? 3 * v.maxH : 0));
+    int* tl = reinterpret_cast<int*>(ycor + (kSplit ? 3 * (v.maxH + v.maxH2) : 0));
     // every independent load before the first wait: the rho partials first
     // (needed first; loads complete in issue order), then the group's own
     // entries of z and p_{k-1} and its transposed-entry list, all
     // unconditionally at clamped indices (see partials_load); the list goes
     // to LDS only after the rho sum
     const double* Prho = v.P_rho[(k - 1) & 1];
-    const int nrho = kSplit ? v.G + v.ncb : v.G;
+    const int nrho = kSplit ? v.GA + v.ncb : v.GA;
     UnitLoads U{};
     if constexpr (kSplit) U = unit_load(v, g);
     const auto rl = partials_load<kSplit ? kRhoPer : 4>(Prho, nrho);
@@ -567,7 +589,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     if constexpr (kRQ) pl = restrict_load(v, g);
     const int stop = v.st->done;
     keep_loads_issued();
-    if (stop) return;  // after a stop nothing is written
+    if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
     const double rk2 = v.st->rho[k & 1];
     if constexpr (kSplit) unit_gather(v, U);
     // rho_{k-1} from the partials; rho_{k-2} as the previous SpMV recorded it
@@ -578,8 +600,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
         if (t + j * kThreads < tn) tl[t + j * kThreads] = tlr[j];
     for (int e = t + kTlRegs * kThreads; e < tn; e += kThreads) tl[e] = v.tidx[tb0 + e];
     if constexpr (kSplit) {
-        unit_stage(v, U, ycor);
-        __syncthreads();
+        unit_stage(v, g, U, ycor);
     }
     const double beta = k > 1 ? rk1 / rk2 : 0.0;
     double* pk = v.p[k & 1];
@@ -672,7 +693,7 @@ template <int kRQ, bool kSplit>
 void launch_spmv_pq_t(const SolverView& v, bool f32, int k, hipStream_t s) {
     dim3 g(v.G + (kSplit ? 1 : 0)), b(kThreads);
     const int flags = f32 ? kFlagMixed : 0;
-    const size_t vec = sizeof(double) * 3 * (static_cast<size_t>(v.RG) + (kSplit ? v.maxH : 0));
+    const size_t vec = sizeof(double) * 3 * (static_cast<size_t>(v.RG) + (kSplit ? v.maxH + v.maxH2 : 0));
     if (v.sym && !f32) {
         launch_kernel(k_spmv_pq_sym<double, kRQ, kSplit>, g, b, vec + sizeof(int) * v.maxT, s, v,
                       static_cast<const double*>(v.H64), k, flags);
