@@ -317,7 +317,7 @@ SolverView view(const mas_handle* h) {
     v.gu1_slot = at<int>(h, Y.gu1_slot);
     v.gu1_mask = at<uint64_t>(h, Y.gu1_mask);
     v.GW = P.GW;
-    v.rfast = restrict_fast_ok(P.W1, P.GW, spmv_threads()) ? 1 : 0;
+    v.rpass = restrict_passes(P.W1, P.GW, spmv_threads());
     v.gw_pos = at<int>(h, Y.gw_pos);
     v.gw_li = at<int>(h, Y.gw_li);
     v.gw_mask = at<uint64_t>(h, Y.gw_mask);
@@ -736,16 +736,16 @@ namespace {
 void set_fusion(mas_handle* h) {
     const Plan& R = h->plan;
     // two launches per iteration where the SpMV's restriction of q takes
-    // one pass of its threads (restrict_fast_ok): on systems whose groups
-    // have many more coarse units (a group of the membrane + bodies system
-    // has up to 448 writers), the longer restriction in the SpMV costs more
-    // than the x/r update launch it saves, and every iteration restricts r
-    // directly; and where the groups' coarse corrections fit in the 64 KB of
+    // at most two passes of its threads (restrict_passes): on systems whose
+    // groups have many more coarse units (128 rows of the membrane + bodies
+    // system have up to 448 writers), the longer restriction in the SpMV costs
+    // more than the x/r update launch it saves, and every iteration restricts
+    // r directly; and where the groups' coarse corrections fit in the 64 KB of
     // LDS a workgroup may have beside the rest (groups that read more than
     // kMaxHalo units have no lists at all)
     h->fuse_ok = sizeof(double) * (3 * static_cast<size_t>(R.RG) + restrict_smem_doubles(R.RG, R.W1, R.L)) <=
                      spmv_restrict_capacity() &&
-                 restrict_fast_ok(R.W1, R.GW, spmv_threads()) && h->shape.halo &&
+                 restrict_passes(R.W1, R.GW, spmv_threads()) > 0 && h->shape.halo &&
                  spmv_shared_bytes(R.RG, R.maxT, R.sym) + sizeof(double) * 3 * (h->shape.maxH + h->shape.maxH2) <=
                      (size_t{64} << 10);
 }
@@ -1157,7 +1157,7 @@ size_t mas_replan_workspace_size(const mas_handle* h, int64_t nnzb) {
     if (!h || !h->analyzed || nnzb < 1 || nnzb > 0x7fffffffLL) return 0;
     const Plan& P = h->plan;
     size_t t = 0;
-    replan_layout(nullptr, P.V, P.NS, P.G, nnzb, &t);
+    replan_layout(nullptr, P.V, P.NS, P.M, nnzb, &t);
     return t;
 }
 
@@ -1170,7 +1170,7 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
     if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign) return MAS_INVALID_ARG;
     if (ws_bytes < mas_replan_workspace_size(h, nnzb)) return MAS_WORKSPACE_TOO_SMALL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const ReplanLayout R = replan_layout(static_cast<char*>(workspace), P0.V, P0.NS, P0.G, nnzb, nullptr);
+    const ReplanLayout R = replan_layout(static_cast<char*>(workspace), P0.V, P0.NS, P0.M, nnzb, nullptr);
     HIP_TRY(hipMemcpyAsync(R.map, P0.map.data(), sizeof(int) * P0.V, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(R.remap, P0.remap.data(), sizeof(int) * P0.NS, hipMemcpyHostToDevice, s));
     HIP_TRY(replan_validate_order_hierarchy(R, P0.V, P0.NS, P0.N, hier_level_cap(h), nnzb, row_ptr, col_idx, R.map,
@@ -1187,19 +1187,22 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
     S.NS = P0.NS;
     S.M = P0.M;
     S.L = st.levels;
-    S.G = P0.G;
-    S.RG = P0.RG;
+    const int D0 = group_domains(P0.M, P0.N, nnzb, c.window_blocks);
+    S.RG = D0 * P0.N;
+    S.G = (P0.M + D0 - 1) / D0;
     S.nnzb = nnzb;
     for (int l = 0; l < S.L; ++l) {
         S.units[l] = st.units[l];
         S.ndom[l] = (st.units[l] + S.N - 1) / S.N;
     }
     HIP_TRY(replan_sizes(R, S, s));
-    const int G = S.G;
-    std::vector<int> g_u1(static_cast<size_t>(G) + 1), gsz(3 * static_cast<size_t>(G));
+    const int G = S.G, W = storage_window(S.N);
+    const size_t n_win = (static_cast<size_t>(S.NS) + W - 1) / W;
+    std::vector<int> g_u1(static_cast<size_t>(G) + 1), gsz(4 * static_cast<size_t>(G));
     HIP_TRY(hipMemcpyAsync(&c, R.counts, sizeof(c), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(g_u1.data(), R.g_u1, sizeof(int) * g_u1.size(), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(gsz.data(), R.gstore, sizeof(int) * gsz.size(), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(gsz.data(), R.gstore, sizeof(int) * (3 * static_cast<size_t>(G) + n_win), hipMemcpyDeviceToHost,
+                           s));
     int n_halo = 0, n_halo2 = 0;
     HIP_TRY(hipMemcpyAsync(&n_halo, R.hptr + G, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(&n_halo2, R.h2ptr + G, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1219,9 +1222,9 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
     Q.remap = P0.remap;
     Q.units.assign(S.units, S.units + S.L);
     Q.ndom.assign(S.ndom, S.ndom + S.L);
-    Q.D0 = P0.D0;
-    Q.RG = P0.RG;
-    Q.G = P0.G;
+    Q.D0 = D0;
+    Q.RG = S.RG;
+    Q.G = S.G;
     Q.W1 = 1;
     for (int g = 0; g < G; ++g) Q.W1 = std::max(Q.W1, g_u1[g + 1] - g_u1[g]);
     Q.GW = S.L > 2 ? std::max(1, c.gw_max) : 1;
@@ -1233,7 +1236,8 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
         n_tidx += gsz[2 * static_cast<size_t>(G) + g];
         Q.maxT = std::max(Q.maxT, gsz[2 * static_cast<size_t>(G) + g]);
     }
-    Q.sym = Q.RG <= 256 && Q.maxT <= kMaxTransposed;
+    Q.sym = *std::max_element(gsz.begin() + 3 * static_cast<size_t>(G),
+                              gsz.begin() + 3 * static_cast<size_t>(G) + n_win) <= kMaxTransposed;
     std::vector<long long> cnt(G);
     for (int g = 0; g < G; ++g) cnt[g] = Q.sym ? gsz[G + g] : gsz[g];
     Q.gorder = spmv_group_order(cnt);

@@ -69,7 +69,7 @@ struct SolverView {
     const int* gu1_slot;
     const uint64_t* gu1_mask;
     int GW;
-    int rfast;  // restrict_fast_ok for the group kernels' block sizes (256 and 384 threads)
+    int rpass;  // restrict_passes of the SpMV's threads
     const int* gw_pos;
     const int* gw_li;
     const uint64_t* gw_mask;

@@ -358,7 +358,15 @@ void symmetric_storage(Plan& P) {
         const int r0 = g * RG, r1 = std::min(r0 + RG, NS);
         P.maxT = std::max(P.maxT, P.tptr[r1] - P.tptr[r0]);
     }
-    P.sym = P.RG <= 256 && P.maxT <= kMaxTransposed;
+    const int W = storage_window(P.N);
+    std::vector<int> trans((NS + W - 1) / W, 0);
+    for (int s = 0; s < NS; ++s) {
+        const int lo = s / W * W;
+        const int* row = P.ci0.data() + P.rp0[s];
+        const int n = P.rp0[s + 1] - P.rp0[s];
+        trans[s / W] += static_cast<int>(std::lower_bound(row, row + n, s) - std::lower_bound(row, row + n, lo));
+    }
+    P.sym = *std::max_element(trans.begin(), trans.end()) <= kMaxTransposed;
 }
 
 // The level-1 units each group's SpMV reads (see Plan::hptr).  Groups are
@@ -505,6 +513,31 @@ void spmv_order(Plan& P) {
 }
 
 }  // namespace
+
+// A group is one workgroup of the SpMV: its chunks of blocks follow one
+// another, so where the machine is not full of groups the iteration takes as
+// long as one group's chain.  Up to 640 groups (2.5 per CU) the groups are
+// therefore made smaller, 1, 2 or 4 domains instead of 8; beyond that the
+// launch is bound by what it moves, and larger groups store more pairs once
+// and leave fewer partial sums.  Iteration in us with 1 / 2 / 4 / 8 domains per
+// group (FP64 cubes): 308 domains 18.1 / 18.4 / 20.5 / 24.7; 977 domains
+// 21.7 / 20.3 / 22.4 / 26.9; 2,457 domains 42.5 / 29.2 / 29.0 / 32.2; 4,308
+// domains 70 / 49 / 45 / 38.
+// Where one window of 128 rows holds more than three times the mean (rows of
+// bodies with many contacts), its chain alone is the iteration: such groups
+// are halved down to 2,048 blocks as long as there are at most 2,200 groups
+// (sheet of 256^2 cells with bodies in contact, 4,254 domains: 43 / 55 / 72 us
+// with 2 / 4 / 8).  Other domain sizes keep groups of about 128 rows.
+int group_domains(int M, int N, long long nnzb, long long window_blocks) {
+    const int most = std::max(1, kWindowSlots / N);
+    if (N != 16) return most;
+    int d = 1;
+    while (d < most && (M + d - 1) / d > 640) d *= 2;
+    const int windows = (M + most - 1) / most;
+    if (window_blocks * windows > 3 * nnzb)
+        while (d > 1 && window_blocks * d > 2048LL * most && (M + d / 2 - 1) / (d / 2) <= 2200) d /= 2;
+    return d;
+}
 
 std::vector<int> spmv_group_order(const std::vector<long long>& cnt) {
     const int G = static_cast<int>(cnt.size());
@@ -728,7 +761,10 @@ std::string analyze(int V, int nnzb, const int32_t* row_ptr, const int32_t* col_
             P.anc[static_cast<size_t>(l - 1) * P.NS + s] = below < 0 ? -1 : P.up[l - 1][below];
         }
     // ---- work groups and per-group coarse partials
-    P.D0 = std::max(1, 128 / N);
+    long long window_blocks = 0;
+    for (int s = 0, W = storage_window(N); s < P.NS; s += W)
+        window_blocks = std::max<long long>(window_blocks, P.rp0[std::min(s + W, P.NS)] - P.rp0[s]);
+    P.D0 = group_domains(P.M, N, nnzb, window_blocks);
     P.RG = P.D0 * N;
     P.G = (P.M + P.D0 - 1) / P.D0;
     P.g_u1.assign(P.G + 1, 0);

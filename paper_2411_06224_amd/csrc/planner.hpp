@@ -13,6 +13,15 @@ constexpr int kMaxLevels = 16;
 // The symmetric storage keeps a group's transposed-entry list in LDS; groups
 // with more entries than this use the full storage.
 constexpr int kMaxTransposed = 4096;
+// The limit is applied to windows of about 128 rows, whatever the size of the
+// groups, so that a pattern keeps one storage: rows coupled that densely to
+// their neighbours have as many transposed entries to look up as products to
+// add.
+constexpr int kWindowSlots = 128;
+inline int storage_window(int N) { return (kWindowSlots / N > 1 ? kWindowSlots / N : 1) * N; }
+// Level-0 domains per work group, from the number of domains, the blocks of H
+// and the most blocks of one storage window (planner.cpp).
+int group_domains(int M, int N, long long nnzb, long long window_blocks);
 // The SpMV of a two-launch iteration stages the coarse correction of every
 // level-1 unit a group of rows reads (its own and those of the columns
 // outside the group) in LDS: 24 bytes each, so 512 take 12 KB beside the

@@ -45,6 +45,7 @@ __global__ void k_rp_counts_init(ReplanCounts* __restrict__ c) {
     if (threadIdx.x != 0) return;
     c->bad = 0;
     c->nnz_distinct = 0;
+    c->window_blocks = 0;
     for (int l = 0; l < kMaxLv; ++l) {
         c->nnzA[l] = 0;
         c->ndomblk[l] = 0;
@@ -309,6 +310,23 @@ __global__ void k_rp_group_sizes(int G, int RG, int NS, const int* __restrict__ 
     out[g] = rp0[r1] - rp0[r0];
     out[G + g] = srp[r1] - srp[r0];
     out[2 * G + g] = tptr[r1] - tptr[r0];
+}
+
+// Most blocks of one storage window of W slots.
+__global__ void k_rp_window_blocks(int NS, int W, const int* __restrict__ rp, ReplanCounts* __restrict__ c) {
+    const int w = blockIdx.x * kRpThreads + threadIdx.x;
+    if (static_cast<long long>(w) * W < NS) atomicMax(&c->window_blocks, rp[min((w + 1) * W, NS)] - rp[w * W]);
+}
+
+// Transposed entries of every storage window of W slots (the storage rule):
+// the columns of row s in [window start, s).
+__global__ void k_rp_window_trans(int NS, int W, const int* __restrict__ rp, const int* __restrict__ ci,
+                                  int* __restrict__ cnt) {
+    const int s = blockIdx.x * kRpThreads + threadIdx.x;
+    if (s >= NS) return;
+    const int p0 = first_at_least(ci, rp[s], rp[s + 1], s / W * W);
+    const int n = first_at_least(ci, p0, rp[s + 1], s) - p0;
+    if (n) atomicAdd(cnt + s / W, n);
 }
 
 // Level-1 restriction: slot s leads its level-1 unit u if no lower lane of
@@ -765,7 +783,7 @@ ReplanLayout replan_layout(char* ws, int V, int NS, int G, long long nnzb, size_
     R.lmask = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * ns));
     R.gcnt = reinterpret_cast<int*>(take(I * (G + 1)));
     R.g_u1 = reinterpret_cast<int*>(take(I * (G + 1)));
-    R.gstore = reinterpret_cast<int*>(take(I * 3 * G));
+    R.gstore = reinterpret_cast<int*>(take(I * 4 * G));
     R.hcnt = reinterpret_cast<int*>(take(I * (G + 1)));
     R.hptr = reinterpret_cast<int*>(take(I * (G + 1)));
     R.h2cnt = reinterpret_cast<int*>(take(I * (G + 1)));
@@ -802,6 +820,9 @@ hipError_t replan_validate_order_hierarchy(const ReplanLayout& R, int V, int NS,
     if ((e = launch_assemble_sort(R.A, NS, nnzb, R.rows, R.cols, R.rp0, s)) != hipSuccess) return e;
     launch_kernel(k_rp_store, dim3(1), dim3(64), 0, s, &R.counts->nnz_distinct,
                   static_cast<const int*>(R.A.flag + 1));
+    const int W = storage_window(N);
+    launch_kernel(k_rp_window_blocks, dim3(grid((NS + W - 1) / W)), dim3(kRpThreads), 0, s, NS, W,
+                  static_cast<const int*>(R.rp0), R.counts);
     launch_kernel(k_rp_cols, dim3(grid(nnzb)), dim3(kRpThreads), 0, s, nnzb, R.A.cb,
                   static_cast<const uint64_t*>(R.A.key_sorted), static_cast<const int*>(R.A.seg_start),
                   static_cast<const int*>(R.A.flag + 1), R.ci0);
@@ -825,6 +846,11 @@ hipError_t replan_sizes(const ReplanLayout& R, const ReplanShape& S, hipStream_t
     if ((e = scan(R, R.cnt, R.tptr, NS + 1, s)) != hipSuccess) return e;
     launch_kernel(k_rp_group_sizes, dim3(grid(G)), dim3(kRpThreads), 0, s, G, RG, NS, static_cast<const int*>(R.rp0),
                   static_cast<const int*>(R.srp), static_cast<const int*>(R.tptr), R.gstore);
+    const int W = storage_window(S.N), nw = (NS + W - 1) / W;  // nw <= G
+    launch_kernel(k_rp_fill, dim3(grid(nw)), dim3(kRpThreads), 0, s, R.gstore + 3 * static_cast<size_t>(G),
+                  static_cast<long long>(nw), 0);
+    launch_kernel(k_rp_window_trans, dim3(grid(NS)), dim3(kRpThreads), 0, s, NS, W, static_cast<const int*>(R.rp0),
+                  static_cast<const int*>(R.ci0), R.gstore + 3 * static_cast<size_t>(G));
     // level-1 restriction
     launch_kernel(k_rp_lead1, dim3(grid(NS)), dim3(kRpThreads), 0, s, NS, S.N, L,
                   static_cast<const int*>(R.H.sn + NS), R.lead1, R.lmask);

@@ -29,6 +29,7 @@ hipError_t launch_assemble_sort_keys(const AsmLayout& L, int n_rows, long long n
 struct ReplanCounts {
     int bad;                 // bit 0: row_ptr, 1: column range, 2: column order, 3: diagonal, 4: symmetry
     int nnz_distinct;        // distinct blocks of the slot-ordered pattern
+    int window_blocks;       // most blocks of one storage window (group_domains)
     int nnzA[kMaxLv];        // blocks of A_l (level 0: the pattern)
     int ndomblk[kMaxLv];     // inversion gather entries of each level
     int cbase[kMaxLv + 1];   // first coarse-partial position of each level >= 2; cbase[L] = n_cpart
@@ -48,7 +49,8 @@ struct ReplanLayout {
     int* lead1;              // [NS]
     uint64_t* lmask;         // [NS]
     int *gcnt, *g_u1;        // per-group level-1 units and their scan [G + 1]
-    int* gstore;             // per group: stored blocks of the full and symmetric storage, transposed entries [3 G]
+    int* gstore;             // per group: stored blocks of the full and symmetric storage, transposed entries [3 G];
+                             // transposed entries of each storage window (at most G)
     int *hcnt, *hptr;        // level-1 units each group's SpMV reads and their scan [G + 1]
     int *h2cnt, *h2ptr;      // the distinct level-2 units above them and their scan [G + 1]
     int* t_grp;              // group of each level-1 unit [NS]
@@ -60,6 +62,7 @@ struct ReplanLayout {
     size_t scan_bytes;
 };
 
+// G: the most work groups the plan can have (one domain each).
 ReplanLayout replan_layout(char* ws, int V, int NS, int G, long long nnzb, size_t* total);
 
 // Pass 1a: checks of the caller's pattern (node order), the slot-ordered

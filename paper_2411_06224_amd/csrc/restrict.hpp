@@ -31,9 +31,8 @@ struct GroupUnits {
 
 // Plan entries a thread holds in registers: thread t takes component t % 3
 // of the group's level-1 unit t / 3 and, in pass p < kWP of the writers of
-// levels >= 2, of writer (t + p blockDim) / 3 (the common case,
-// restrict_fast_ok, needs one pass; entries of later passes are loaded
-// where they are used).
+// levels >= 2, of writer (t + p blockDim) / 3 (entries of later passes are
+// loaded where they are used).
 template <int kWP = 1>
 struct RestrictLoads {
     GroupUnits gu;
@@ -104,11 +103,16 @@ __device__ __forceinline__ double masked_sum_tree(const double* x, uint64_t mask
 // the plan assigns (the group's level-1 supernodes below it, ascending).
 // No atomics: every output has exactly one writer.  Contains a barrier when
 // L > 2 (every thread must call it).  kFast: the caller guarantees
-// GW <= blockDim.x and W1 <= 64 (restrict_fast_ok), and the restriction then
-// reads no global memory -- a load here would make the stores before it
-// wait too.
-__host__ __device__ inline bool restrict_fast_ok(int W1, int GW, int threads) {
-    return W1 <= 64 && 3 * W1 <= threads && 3 * GW <= threads;
+// 3 W1 <= blockDim.x, W1 <= 64 and at most kWP passes of writers
+// (restrict_passes), and the restriction then reads no global memory -- a
+// load here would make the stores before it wait too.
+//
+// restrict_passes: writer passes of a fast restriction with `threads`
+// threads, 0 where there is none.
+constexpr int kMaxRestrictPasses = 2;
+__host__ __device__ inline int restrict_passes(int W1, int GW, int threads) {
+    const int p = (3 * GW + threads - 1) / threads;
+    return W1 <= 64 && 3 * W1 <= threads && p <= kMaxRestrictPasses ? p : 0;
 }
 
 template <bool kFast = false, int kWP = 1>
@@ -161,9 +165,9 @@ __device__ inline void restrict_group(const SolverView& v, int g, const Restrict
         const int e = o / 3, c = o - 3 * e;
         if (R.w_pos[p] < 0) return;
         write(e, c, R.w_pos[p], R.w_li[p], R.w_mask[p]);
-        if (kFast) return;
         o += blockDim.x;
     }
+    if (kFast) return;
     for (; o < 3 * v.GW; o += blockDim.x) {
         const int e = o / 3, c = o - 3 * e;
         const long long k = static_cast<long long>(g) * v.GW + e;
@@ -174,11 +178,11 @@ __device__ inline void restrict_group(const SolverView& v, int g, const Restrict
 }
 
 // restrict_group with the fast path when the host found it applicable
-// (v.rfast: tables that fit blocks of 256 threads and more).
+// (v.rpass: passes of blocks of 256 threads; larger blocks take no more).
 template <int kWP>
 __device__ inline void restrict_group_any(const SolverView& v, int g, const RestrictLoads<kWP>& R, const double* rs,
                                           double* sm, double* __restrict__ out1, double* __restrict__ outpart) {
-    if (v.rfast)
+    if (v.rpass > 0 && v.rpass <= kWP)
         restrict_group<true, kWP>(v, g, R, rs, sm, out1, outpart);
     else
         restrict_group<false, kWP>(v, g, R, rs, sm, out1, outpart);

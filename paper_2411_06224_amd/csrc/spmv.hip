@@ -331,14 +331,15 @@ __global__ void __launch_bounds__(kThreads) k_spmv_user(int n_rows, const int* _
 }
 
 // Products per launch after the stream: q of the group's rows, the partial
-// of p_k^T q and, with kRQ = 1, the restriction of q to
+// of p_k^T q and, with kRQ > 0 (writer passes), the restriction of q to
 // the coarse levels (q1 and qpart, as restrict_group computes C_l r) from
 // the plan pl loaded at the kernel's start, staged in the product planes
 // (free once the stream's last barrier has passed; the host checks that
 // they hold it, spmv_restrict_capacity).
 template <int kRQ>
 __device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, int r0, const double (&acc)[2],
-                                          const double (&pv)[2], double* prod, double* buf, const RestrictLoads<>& pl) {
+                                          const double (&pv)[2], double* prod, double* buf,
+                                          const RestrictLoads<kRQ ? kRQ : 1>& pl) {
     const int t = threadIdx.x;
     if constexpr (kRQ) restrict_ready(pl);
     double part = 0.0;
@@ -360,7 +361,7 @@ __device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, 
         }
         part = block_sum<false>(part, buf);  // its barriers also publish rs
         if (t == 0) v.P_sigma[g] = part;
-        restrict_group<true>(v, g, pl, rs, rsm, v.q1, v.qpart);  // the host checked restrict_fast_ok
+        restrict_group<true>(v, g, pl, rs, rsm, v.q1, v.qpart);  // the host checked restrict_passes
     } else {
         part = block_sum<false>(part, buf);  // the kernel's last use of buf
         if (t == 0) v.P_sigma[g] = part;
@@ -508,8 +509,8 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
         if constexpr (kSplit) un[q] = own_unit(v, g, r0 + o / 3);
     }
     const ChunkCols c0 = chunk_cols<kSplit>(v.ci0, v.rp0[r0], v.rp0[r1], v.hidx);
-    RestrictLoads<> pl{};
-    if constexpr (kRQ) pl = restrict_load(v, g);
+    RestrictLoads<kRQ ? kRQ : 1> pl{};
+    if constexpr (kRQ) pl = restrict_load<kRQ>(v, g);
     const int stop = v.st->done;
     keep_loads_issued();
     if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
@@ -585,8 +586,8 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
 #pragma unroll
     for (int j = 0; j < kTlRegs; ++j) tlr[j] = tsrc[min(t + j * kThreads, max(tn - 1, 0))];
     const SymCols c0 = sym_cols<kSplit>(v, v.srp[r0], v.srp[r1]);
-    RestrictLoads<> pl{};
-    if constexpr (kRQ) pl = restrict_load(v, g);
+    RestrictLoads<kRQ ? kRQ : 1> pl{};
+    if constexpr (kRQ) pl = restrict_load<kRQ>(v, g);
     const int stop = v.st->done;
     keep_loads_issued();
     if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
@@ -705,16 +706,18 @@ void launch_spmv_pq_t(const SolverView& v, bool f32, int k, hipStream_t s) {
 }
 
 hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool restrict_q, bool split, hipStream_t s) {
-    if (restrict_q && !v.rfast)
-        return hipErrorInvalidValue;  // the solver restricts q in the SpMV only where restrict_fast_ok holds
-    if (restrict_q && split)
-        launch_spmv_pq_t<1, true>(v, f32, k, s);
-    else if (restrict_q)
-        launch_spmv_pq_t<1, false>(v, f32, k, s);
-    else if (split)
-        launch_spmv_pq_t<0, true>(v, f32, k, s);
-    else
-        launch_spmv_pq_t<0, false>(v, f32, k, s);
+    static_assert(kMaxRestrictPasses == 2, "one instance per pass count");
+    if (restrict_q && !v.rpass) return hipErrorInvalidValue;  // the solver restricts q only where restrict_passes > 0
+    const int rq = restrict_q ? v.rpass : 0;
+    if (split) {
+        if (rq == 0) launch_spmv_pq_t<0, true>(v, f32, k, s);
+        if (rq == 1) launch_spmv_pq_t<1, true>(v, f32, k, s);
+        if (rq == 2) launch_spmv_pq_t<2, true>(v, f32, k, s);
+    } else {
+        if (rq == 0) launch_spmv_pq_t<0, false>(v, f32, k, s);
+        if (rq == 1) launch_spmv_pq_t<1, false>(v, f32, k, s);
+        if (rq == 2) launch_spmv_pq_t<2, false>(v, f32, k, s);
+    }
     return hipGetLastError();
 }
 
