@@ -141,26 +141,7 @@ __device__ inline void block_sum2_last(double a, double b, double* scratch, doub
 // bits: thread t < 256 adds p[t], p[t + 256], ... (independent loads, issued
 // together), then wave 0 folds the 256 bucket sums.  Needs blockDim.x >= 256
 // and buf[256] doubles of shared memory; the result is valid in every thread.
-__device__ inline double sum_partials(const double* __restrict__ p, int n, double* buf) {
-    const int t = threadIdx.x;
-    if (t < 256) {
-        double s = 0.0;
-        int i = t;
-        for (; i + 768 < n; i += 1024) s += (p[i] + p[i + 256]) + (p[i + 512] + p[i + 768]);
-        for (; i < n; i += 256) s += p[i];
-        buf[t] = s;
-    }
-    __syncthreads();
-    if (t < 64) {
-        double s = (buf[t] + buf[t + 64]) + (buf[t + 128] + buf[t + 192]);
-        s = wave_sum(s);
-        if (t == 0) buf[0] = s;
-    }
-    __syncthreads();
-    const double r = buf[0];
-    __syncthreads();
-    return r;
-}
+__device__ inline double sum_partials(const double* __restrict__ p, int n, double* buf);
 
 __device__ inline bool finite(double x) { return x - x == 0.0; }
 
@@ -177,14 +158,13 @@ __device__ __forceinline__ void keep_loads_issued() { asm volatile("" ::: "memor
 // latency overlap other loads: partials_load() fetches thread t's bucket
 // entries p[t], p[t + 256], ... into registers (n <= 256 kPer),
 // partials_sum() adds them in sum_partials' order (same bits) and folds the
-// buckets.  For larger n partials_sum() falls back to sum_partials.  Every
-// thread issues its kPer loads unconditionally, at indices clamped to [0, n)
+// buckets; for larger n it loads them itself.  Every thread issues its kPer loads unconditionally, at indices clamped to [0, n)
 // (n >= 1), so that no branch separates them from the loads issued after
 // them and a wait for them need not wait for those too; partials_sum() reads
 // only the entries below n.
 template <int kPer = 4>
 struct PartialLoads {
-    double v[kPer];
+    double v[kPer ? kPer : 1];
 };
 
 template <int kPer = 4>
@@ -198,15 +178,18 @@ __device__ inline PartialLoads<kPer> partials_load(const double* __restrict__ p,
     return L;
 }
 
-// kReuse = false leaves out the closing barrier, for a caller whose next
-// write to buf follows another barrier.
-template <bool kReuse = true, int kPer = 4>
-__device__ inline double partials_sum(const PartialLoads<kPer>& L, const double* __restrict__ p, int n, double* buf) {
+// Bucket t of the sum into buf[t], t < 256.
+template <int kPer = 4>
+__device__ inline void partials_bucket(const PartialLoads<kPer>& L, const double* __restrict__ p, int n, double* buf) {
     static_assert(kPer % 4 == 0, "whole rounds of sum_partials");
-    if (n > 256 * kPer) return sum_partials(p, n, buf);
     const int t = threadIdx.x;
-    if (t < 256) {  // as in partials_load: bucket t holds p[t], p[t + 256], ... below n
-        double s = 0.0;
+    if (t >= 256) return;
+    double s = 0.0;
+    if (n > 256 * kPer) {
+        int i = t;
+        for (; i + 768 < n; i += 1024) s += (p[i] + p[i + 256]) + (p[i + 512] + p[i + 768]);
+        for (; i < n; i += 256) s += p[i];
+    } else {  // as in partials_load: bucket t holds p[t], p[t + 256], ... below n
 #pragma unroll
         for (int r = 0; r < kPer; r += 4) {
             const int i = t + 256 * r;
@@ -218,18 +201,33 @@ __device__ inline double partials_sum(const PartialLoads<kPer>& L, const double*
                 if (i + 512 < n) s += L.v[r + 2];
             }
         }
-        buf[t] = s;
     }
+    buf[t] = s;
+}
+
+// The sum of the buckets (visible to the wave) into buf[0], by one whole wave.
+__device__ inline void partials_fold(double* buf) {
+    const int t = threadIdx.x & 63;
+    double s = (buf[t] + buf[t + 64]) + (buf[t + 128] + buf[t + 192]);
+    s = wave_sum(s);
+    if (t == 0) buf[0] = s;
+}
+
+// kReuse = false leaves out the closing barrier, for a caller whose next
+// write to buf follows another barrier.
+template <bool kReuse = true, int kPer = 4>
+__device__ inline double partials_sum(const PartialLoads<kPer>& L, const double* __restrict__ p, int n, double* buf) {
+    partials_bucket<kPer>(L, p, n, buf);
     __syncthreads();
-    if (t < 64) {
-        double s = (buf[t] + buf[t + 64]) + (buf[t + 128] + buf[t + 192]);
-        s = wave_sum(s);
-        if (t == 0) buf[0] = s;
-    }
+    if (threadIdx.x < 64) partials_fold(buf);
     __syncthreads();
     const double r = buf[0];
     if (kReuse) __syncthreads();
     return r;
+}
+
+__device__ inline double sum_partials(const double* __restrict__ p, int n, double* buf) {
+    return partials_sum<true, 0>(PartialLoads<0>{}, p, n, buf);
 }
 
 inline int ceil_div(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }

@@ -74,14 +74,21 @@ struct Blocks {
     }
 };
 
-// The vector H multiplies: x itself, or the new search direction
-// z + beta p formed on the fly from the previous one.  h: the group's local
-// unit of the column (kUnits: its coarse correction, staged in LDS, is still
-// to be added to z).
+// The vector H multiplies: x itself, z (kSplit: with its coarse correction
+// still to be added, staged in LDS at the group's local unit h / 3 of the
+// column), or the new search direction z + beta p formed on the fly from the
+// previous one.
 struct XVec {
     static constexpr bool kUnits = false;
     const double* __restrict__ x;
     __device__ __forceinline__ double at(int i, int) const { return x[i]; }
+};
+template <bool kSplit>
+struct XZ {
+    static constexpr bool kUnits = kSplit;
+    const double* __restrict__ z;
+    const double* ycor;  // LDS, 3 per local unit
+    __device__ __forceinline__ double at(int i, int h) const { return kSplit ? z[i] + ycor[h] : z[i]; }
 };
 template <bool kSplit>
 struct XDir {
@@ -89,7 +96,7 @@ struct XDir {
     const double* __restrict__ z;
     const double* __restrict__ p;
     double beta;
-    const double* ycor;  // LDS, 3 per local unit
+    const double* ycor;
     __device__ __forceinline__ double at(int i, int h) const {
         return __fma_rn(beta, p[i], kSplit ? z[i] + ycor[h] : z[i]);
     }
@@ -337,7 +344,8 @@ __global__ void __launch_bounds__(kThreads) k_spmv_user(int n_rows, const int* _
 // (free once the stream's last barrier has passed; the host checks that
 // they hold it, spmv_restrict_capacity).
 template <int kRQ>
-__device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, int r0, const double (&acc)[2],
+__device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, int r0, double* __restrict__ qk,
+                                          const double (&acc)[2],
                                           const double (&pv)[2], double* prod, double* buf,
                                           const RestrictLoads<kRQ ? kRQ : 1>& pl) {
     const int t = threadIdx.x;
@@ -347,7 +355,7 @@ __device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, 
     for (int q = 0; q < 2; ++q) {
         const int o = t + q * kThreads;
         if (o < nown) {
-            v.q[3LL * r0 + o] = acc[q];
+            qk[3LL * r0 + o] = acc[q];
             part += pv[q] * acc[q];
         }
     }
@@ -413,8 +421,9 @@ __device__ __forceinline__ void unit_gather(const SolverView& v, UnitLoads& U) {
 }
 
 // ycor: 3 maxH doubles, then 3 maxH2 for the level-2 sums.  Ends with a
-// barrier.
-__device__ __forceinline__ void unit_stage(const SolverView& v, int g, const UnitLoads& U, double* ycor) {
+// barrier.  buf: the rho buckets the caller has written, folded on the way
+// into buf[0] (by the last wave, which has the least to stage).
+__device__ __forceinline__ void unit_stage(const SolverView& v, int g, const UnitLoads& U, double* ycor, double* buf) {
     double* up = ycor + 3 * v.maxH;
     for (int e = threadIdx.x; e < 3 * U.n2; e += kThreads) {
         const int i = e / 3, c = e - 3 * i;
@@ -439,6 +448,7 @@ __device__ __forceinline__ void unit_stage(const SolverView& v, int g, const Uni
         up[e] = s;
     }
     __syncthreads();
+    if (threadIdx.x >= kThreads - 64) partials_fold(buf);
     const int h0 = v.hptr[g];
     for (int e = threadIdx.x; e < 3 * U.n; e += kThreads) {
         const int i = e / 3, c = e - 3 * i;
@@ -465,88 +475,124 @@ constexpr int kRhoPer = 8;  // rho partials a thread loads ahead: up to 2048 in 
 
 // PCG iteration k over the solver's group of slots: the new direction
 // p_k = z_{k-1} + beta_{k-1} p_{k-1} (beta = rho_{k-1} / rho_{k-2} summed from
-// the partials; p_1 = z_0) is formed first on the group's own slots (into LDS
-// and p_k) and, for columns outside the group, wherever H gathers it; q = H p_k
-// and the partial of p_k^T q.  Every workgroup forms the same beta, the same
-// coarse corrections and the same fused multiply-add, so a direction entry has
-// the same bits in every workgroup that reads it.
+// the partials; p_1 = z_0) on the group's own slots, q_k = H p_k and the
+// partial of p_k^T q_k.
+//
+// q_k is formed by the recurrence q_k = H z_{k-1} + beta q_{k-1}, which needs
+// of the columns outside the group z alone: half the gathers of z + beta p.
+// Every replace_every-th iteration (kFresh) forms H p_k itself, which ends the
+// rounding that the recurrence carries on; there the direction is staged in
+// LDS on the group's own slots and formed wherever H gathers it, with the same
+// beta and the same fused multiply-add, so the same bits, in every workgroup.
 //
 // kSplit: z_{k-1} = v.z + the coarse corrections, which the level-0 apply left
 // out so that it need not wait for the coarse levels.  A group reads few
 // distinct level-1 units, so it sums each unit's levels once into LDS
 // (unit_stage); an outside column then costs one 16-bit index and three LDS
 // reads more.
-template <typename T, int kRQ, bool kSplit>
+struct DirLoads {
+    double z[2], p[2], q[2];
+    int unit[2];
+};
+
+template <bool kSplit, bool kFresh>
+__device__ __forceinline__ DirLoads dir_load(const SolverView& v, int g, int r0, int nown, const double* pold,
+                                             const double* qold) {
+    DirLoads D;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int o = min(static_cast<int>(threadIdx.x) + q * kThreads, nown - 1);
+        const long long e = 3LL * r0 + o;
+        D.z[q] = v.z[e];
+        D.p[q] = pold[e];
+        D.q[q] = kFresh ? 0.0 : qold[e];
+        D.unit[q] = kSplit ? own_unit(v, g, r0 + o / 3) : -1;
+    }
+    return D;
+}
+
+// rho_{k-1} and beta, the own part of the vector H multiplies in xs and p_k
+// stored; pv: p_k at the thread's rows.  Ends with a barrier.
+template <bool kSplit, bool kFresh>
+__device__ __forceinline__ double dir_stage(const SolverView& v, int k, int g, int r0, int nown, DirLoads& D,
+                                            const PartialLoads<kSplit ? kRhoPer : 4>& rl, int nrho, double rk2,
+                                            const UnitLoads& U, double* ycor, double* xs, double* buf,
+                                            double (&pv)[2]) {
+    const int t = threadIdx.x;
+    const double* Prho = v.P_rho[(k - 1) & 1];
+    partials_bucket<kSplit ? kRhoPer : 4>(rl, Prho, nrho, buf);
+    if constexpr (kSplit) {
+        unit_stage(v, g, U, ycor, buf);
+    } else {
+        __syncthreads();
+        if (t < 64) partials_fold(buf);
+        __syncthreads();
+    }
+    const double rk1 = buf[0];  // buf is next written after later barriers
+    if (g == 0 && t == 0) v.st->rho[(k - 1) & 1] = rk1;
+    const double beta = k > 1 ? rk1 / rk2 : 0.0;
+    double* pk = v.p[k & 1];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int o = t + q * kThreads;
+        double z = 0.0;
+        pv[q] = 0.0;
+        if (o < nown) {
+            z = D.z[q];
+            if (kSplit && D.unit[q] >= 0) z += ycor[3 * D.unit[q] + o % 3];
+            pv[q] = __fma_rn(beta, D.p[q], z);
+            pk[3LL * r0 + o] = pv[q];
+        }
+        if (o < 3 * v.RG) xs[o] = kFresh ? pv[q] : z;
+    }
+    __syncthreads();
+    return beta;
+}
+
+template <typename T, int kRQ, bool kSplit, bool kFresh>
 __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __restrict__ H, int k, int flags) {
     __shared__ double prod[3 * kPlane];
     __shared__ double buf[256];
     extern __shared__ double dyn[];  // xs[3 RG] (+ ycor[3 (maxH + maxH2)])
     if (kSplit && decide_only(v, k, flags, buf)) return;
-    const int t = threadIdx.x;
     const int g = spmv_group(v);
     const int r0 = g * v.RG, r1 = min(r0 + v.RG, v.NS);
     const int nown = 3 * (r1 - r0);
     double* xs = dyn;
     double* ycor = dyn + 3 * v.RG;
-    // every independent load before the first wait: the rho partials first
-    // (needed first; loads complete in issue order), then the group's own
-    // entries of z and p_{k-1}, unconditionally at clamped indices (see
-    // partials_load)
-    const double* Prho = v.P_rho[(k - 1) & 1];
+    // every independent load before the first wait, unconditionally at
+    // clamped indices (see partials_load); k = 1 has no p_0 and q_0 (beta = 0)
     const int nrho = kSplit ? v.GA + v.ncb : v.GA;
+    const double* pold = k > 1 ? v.p[(k - 1) & 1] : v.z;
     UnitLoads U{};
     if constexpr (kSplit) U = unit_load(v, g);
-    const auto rl = partials_load<kSplit ? kRhoPer : 4>(Prho, nrho);
-    const double* pold = k > 1 ? v.p[(k - 1) & 1] : v.z;  // k = 1: p_1 = z_0 (+ 0 * z_0)
-    double zo[2], po[2];
-    int un[2] = {-1, -1};
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int o = min(t + q * kThreads, nown - 1);
-        const long long e = 3LL * r0 + o;
-        zo[q] = v.z[e];
-        po[q] = pold[e];
-        if constexpr (kSplit) un[q] = own_unit(v, g, r0 + o / 3);
-    }
+    const auto rl = partials_load<kSplit ? kRhoPer : 4>(v.P_rho[(k - 1) & 1], nrho);
+    DirLoads D = dir_load<kSplit, kFresh>(v, g, r0, nown, pold, k > 1 ? v.q[(k - 1) & 1] : v.z);
     const ChunkCols c0 = chunk_cols<kSplit>(v.ci0, v.rp0[r0], v.rp0[r1], v.hidx);
     RestrictLoads<kRQ ? kRQ : 1> pl{};
     if constexpr (kRQ) pl = restrict_load<kRQ>(v, g);
     const int stop = v.st->done;
     keep_loads_issued();
     if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
-    // rho_{k-1} from the partials; rho_{k-2} as the previous SpMV recorded it
-    const double rk2 = v.st->rho[k & 1];
+    const double rk2 = v.st->rho[k & 1];  // rho_{k-2} as the previous SpMV recorded it
     if constexpr (kSplit) unit_gather(v, U);
-    const double rk1 = partials_sum<false>(rl, Prho, nrho, buf);  // buf is next written after later barriers
-    if (g == 0 && t == 0) v.st->rho[(k - 1) & 1] = rk1;
-    if constexpr (kSplit) {
-        unit_stage(v, g, U, ycor);
-    }
-    const double beta = k > 1 ? rk1 / rk2 : 0.0;
-    double* pk = v.p[k & 1];
-    double pv[2];
+    double pv[2], acc[2];
+    const double beta = dir_stage<kSplit, kFresh>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv);
+    const Blocks<T, true> Hb{H, v.nnzb};
+    if constexpr (kFresh) {
+        stream_rows<T, true, XDir<kSplit>, true>(v.rp0, v.ci0, Hb, XDir<kSplit>{v.z, pold, beta, ycor}, r0, r1, prod,
+                                                 acc, c0, xs, v.hidx);
+    } else {
+        stream_rows<T, true, XZ<kSplit>, true>(v.rp0, v.ci0, Hb, XZ<kSplit>{v.z, ycor}, r0, r1, prod, acc, c0, xs,
+                                               v.hidx);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int o = t + q * kThreads;
-        pv[q] = 0.0;
-        if (o < nown) {
-            if (kSplit && un[q] >= 0) zo[q] += ycor[3 * un[q] + o % 3];
-            pv[q] = __fma_rn(beta, po[q], zo[q]);
-            pk[3LL * r0 + o] = pv[q];
-            xs[o] = pv[q];
-        }
+        for (int q = 0; q < 2; ++q) acc[q] = __fma_rn(beta, D.q[q], acc[q]);
     }
-    __syncthreads();
-    double acc[2];
-    stream_rows<T, true, XDir<kSplit>, true>(v.rp0, v.ci0, Blocks<T, true>{H, v.nnzb},
-                                             XDir<kSplit>{v.z, pold, beta, ycor}, r0, r1, prod, acc, c0, xs, v.hidx);
-    finish_pq<kRQ>(v, g, nown, r0, acc, pv, prod, buf, pl);
+    finish_pq<kRQ>(v, g, nown, r0, v.q[k & 1], acc, pv, prod, buf, pl);
 }
 
-// k_spmv_pq on the group-symmetric storage: the group forms the new
-// direction on its own slots first (into LDS and p_k) and gathers it only for
-// columns outside the group.
-template <typename T, int kRQ, bool kSplit>
+// k_spmv_pq on the group-symmetric storage.
+template <typename T, int kRQ, bool kSplit, bool kFresh>
 __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T* __restrict__ H, int k, int flags) {
     __shared__ double prod[6 * kSymPlane];
     __shared__ double buf[256];
@@ -559,27 +605,14 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     double* xs = dyn;
     double* ycor = dyn + 3 * v.RG;
     int* tl = reinterpret_cast<int*>(ycor + (kSplit ? 3 * (v.maxH + v.maxH2) : 0));
-    // every independent load before the first wait: the rho partials first
-    // (needed first; loads complete in issue order), then the group's own
-    // entries of z and p_{k-1} and its transposed-entry list, all
-    // unconditionally at clamped indices (see partials_load); the list goes
-    // to LDS only after the rho sum
-    const double* Prho = v.P_rho[(k - 1) & 1];
+    // loads as in k_spmv_pq, and the group's transposed-entry list, which
+    // goes to LDS with the own part
     const int nrho = kSplit ? v.GA + v.ncb : v.GA;
+    const double* pold = k > 1 ? v.p[(k - 1) & 1] : v.z;
     UnitLoads U{};
     if constexpr (kSplit) U = unit_load(v, g);
-    const auto rl = partials_load<kSplit ? kRhoPer : 4>(Prho, nrho);
-    const double* pold = k > 1 ? v.p[(k - 1) & 1] : v.z;  // k = 1: p_1 = z_0 (+ 0 * z_0)
-    double zo[2], po[2];
-    int un[2] = {-1, -1};
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int o = min(t + q * kThreads, nown - 1);
-        const long long e = 3LL * r0 + o;
-        zo[q] = v.z[e];
-        po[q] = pold[e];
-        if constexpr (kSplit) un[q] = own_unit(v, g, r0 + o / 3);
-    }
+    const auto rl = partials_load<kSplit ? kRhoPer : 4>(v.P_rho[(k - 1) & 1], nrho);
+    DirLoads D = dir_load<kSplit, kFresh>(v, g, r0, nown, pold, k > 1 ? v.q[(k - 1) & 1] : v.z);
     const int tb0 = v.tptr[r0], tn = v.tptr[r1] - tb0;
     const int* tsrc = tn > 0 ? v.tidx + tb0 : v.srp;  // srp: a stand-in with entries when the list is empty
     int tlr[kTlRegs];
@@ -591,36 +624,22 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     const int stop = v.st->done;
     keep_loads_issued();
     if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
-    const double rk2 = v.st->rho[k & 1];
+    const double rk2 = v.st->rho[k & 1];  // rho_{k-2} as the previous SpMV recorded it
     if constexpr (kSplit) unit_gather(v, U);
-    // rho_{k-1} from the partials; rho_{k-2} as the previous SpMV recorded it
-    const double rk1 = partials_sum<false>(rl, Prho, nrho, buf);  // buf is next written after later barriers
-    if (g == 0 && t == 0) v.st->rho[(k - 1) & 1] = rk1;
 #pragma unroll
     for (int j = 0; j < kTlRegs; ++j)
         if (t + j * kThreads < tn) tl[t + j * kThreads] = tlr[j];
     for (int e = t + kTlRegs * kThreads; e < tn; e += kThreads) tl[e] = v.tidx[tb0 + e];
-    if constexpr (kSplit) {
-        unit_stage(v, g, U, ycor);
-    }
-    const double beta = k > 1 ? rk1 / rk2 : 0.0;
-    double* pk = v.p[k & 1];
-    double pv[2];
+    double pv[2], acc[2];
+    const double beta = dir_stage<kSplit, kFresh>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv);
+    if constexpr (kFresh) {
+        stream_sym<T>(v, H, XDir<kSplit>{v.z, pold, beta, ycor}, xs, tl, tb0, r0, r1, prod, acc, c0);
+    } else {
+        stream_sym<T>(v, H, XZ<kSplit>{v.z, ycor}, xs, tl, tb0, r0, r1, prod, acc, c0);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int o = t + q * kThreads;
-        pv[q] = 0.0;
-        if (o < nown) {
-            if (kSplit && un[q] >= 0) zo[q] += ycor[3 * un[q] + o % 3];
-            pv[q] = __fma_rn(beta, po[q], zo[q]);
-            pk[3LL * r0 + o] = pv[q];
-        }
-        if (o < 3 * v.RG) xs[o] = pv[q];
+        for (int q = 0; q < 2; ++q) acc[q] = __fma_rn(beta, D.q[q], acc[q]);
     }
-    __syncthreads();
-    double acc[2];
-    stream_sym<T>(v, H, XDir<kSplit>{v.z, pold, beta, ycor}, xs, tl, tb0, r0, r1, prod, acc, c0);
-    finish_pq<kRQ>(v, g, nown, r0, acc, pv, prod, buf, pl);
+    finish_pq<kRQ>(v, g, nown, r0, v.q[k & 1], acc, pv, prod, buf, pl);
 }
 
 // out = b - H x in FP64 over a group, with the partials of ||out||^2 (and
@@ -690,33 +709,41 @@ hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void
     return hipGetLastError();
 }
 
-template <int kRQ, bool kSplit>
+template <int kRQ, bool kSplit, bool kFresh>
 void launch_spmv_pq_t(const SolverView& v, bool f32, int k, hipStream_t s) {
     dim3 g(v.G + (kSplit ? 1 : 0)), b(kThreads);
     const int flags = f32 ? kFlagMixed : 0;
     const size_t vec = sizeof(double) * 3 * (static_cast<size_t>(v.RG) + (kSplit ? v.maxH + v.maxH2 : 0));
     if (v.sym && !f32) {
-        launch_kernel(k_spmv_pq_sym<double, kRQ, kSplit>, g, b, vec + sizeof(int) * v.maxT, s, v,
+        launch_kernel(k_spmv_pq_sym<double, kRQ, kSplit, kFresh>, g, b, vec + sizeof(int) * v.maxT, s, v,
                       static_cast<const double*>(v.H64), k, flags);
     } else if (f32) {
-        launch_kernel(k_spmv_pq<float, kRQ, kSplit>, g, b, vec, s, v, static_cast<const float*>(v.H32), k, flags);
+        launch_kernel(k_spmv_pq<float, kRQ, kSplit, kFresh>, g, b, vec, s, v, static_cast<const float*>(v.H32), k,
+                      flags);
     } else {
-        launch_kernel(k_spmv_pq<double, kRQ, kSplit>, g, b, vec, s, v, static_cast<const double*>(v.H64), k, flags);
+        launch_kernel(k_spmv_pq<double, kRQ, kSplit, kFresh>, g, b, vec, s, v, static_cast<const double*>(v.H64), k,
+                      flags);
     }
 }
 
-hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool restrict_q, bool split, hipStream_t s) {
+// The forms the solve loop uses: an iteration by recurrence restricts q and
+// forms it by recurrence (z whole after a direct iteration, else split); a
+// direct one does not restrict it, and forms it afresh (every replace_every-th
+// iteration) or by recurrence (the others of a system whose iterations are all
+// direct, z always whole).
+hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool fresh, bool restrict_q, bool split,
+                          hipStream_t s) {
     static_assert(kMaxRestrictPasses == 2, "one instance per pass count");
-    if (restrict_q && !v.rpass) return hipErrorInvalidValue;  // the solver restricts q only where restrict_passes > 0
     const int rq = restrict_q ? v.rpass : 0;
-    if (split) {
-        if (rq == 0) launch_spmv_pq_t<0, true>(v, f32, k, s);
-        if (rq == 1) launch_spmv_pq_t<1, true>(v, f32, k, s);
-        if (rq == 2) launch_spmv_pq_t<2, true>(v, f32, k, s);
+    if ((restrict_q && (fresh || rq == 0)) || (!restrict_q && !fresh && split)) return hipErrorInvalidValue;
+    if (rq == 1) {
+        split ? launch_spmv_pq_t<1, true, false>(v, f32, k, s) : launch_spmv_pq_t<1, false, false>(v, f32, k, s);
+    } else if (rq == 2) {
+        split ? launch_spmv_pq_t<2, true, false>(v, f32, k, s) : launch_spmv_pq_t<2, false, false>(v, f32, k, s);
+    } else if (fresh) {
+        split ? launch_spmv_pq_t<0, true, true>(v, f32, k, s) : launch_spmv_pq_t<0, false, true>(v, f32, k, s);
     } else {
-        if (rq == 0) launch_spmv_pq_t<0, false>(v, f32, k, s);
-        if (rq == 1) launch_spmv_pq_t<1, false>(v, f32, k, s);
-        if (rq == 2) launch_spmv_pq_t<2, false>(v, f32, k, s);
+        launch_spmv_pq_t<0, false, false>(v, f32, k, s);
     }
     return hipGetLastError();
 }
