@@ -45,6 +45,16 @@ __host__ __device__ inline int xcd_group(int b, int G) {
     return x * q + (x < rem ? x : rem) + i;
 }
 
+// *p at an address that is the same in the whole wave, of memory that the
+// launch does not write (plan arrays, scalars of earlier launches), as a
+// scalar load.  The compiler proves neither once a kernel has stores on
+// another path; as a vector load such a value waits for every load issued
+// before it.
+template <typename T>
+__device__ __forceinline__ T uniform_load(const T* p) {
+    return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
+}
+
 // ---------------------------------------------------------------- reductions
 
 // x + x of the lane the DPP control selects (kCtrl: a permutation within

@@ -50,8 +50,8 @@ template <int kWP = 1>
 __device__ inline RestrictLoads<kWP> restrict_load(const SolverView& v, int g) {
     RestrictLoads<kWP> R;
     const int t = threadIdx.x;
-    const int u1_lo = v.g_u1[g];
-    R.gu = v.L >= 2 ? GroupUnits{u1_lo, v.g_u1[g + 1] - u1_lo} : GroupUnits{0, 0};
+    const int u1_lo = uniform_load(v.g_u1 + g);
+    R.gu = v.L >= 2 ? GroupUnits{u1_lo, uniform_load(v.g_u1 + g + 1) - u1_lo} : GroupUnits{0, 0};
     const long long i1 = static_cast<long long>(g) * v.W1 + min(t / 3, v.W1 - 1);
     R.u1_slot = v.gu1_slot[i1];
     R.u1_mask = v.gu1_mask[i1];

@@ -13,6 +13,7 @@
 // load.
 #include "decision.hpp"
 #include "launch.hpp"
+#include "planner.hpp"
 #include "restrict.hpp"
 
 namespace maspcg {
@@ -134,7 +135,7 @@ __device__ __forceinline__ ChunkCols chunk_cols(const int* __restrict__ ci, int 
 // planner's order when the groups' stored blocks are uneven, else the
 // contiguous per-XCD mapping of every group kernel.
 __device__ __forceinline__ int spmv_group(const SolverView& v) {
-    return v.gorder ? v.gorder[blockIdx.x] : xcd_group(blockIdx.x, v.G);
+    return v.gorder ? uniform_load(v.gorder + blockIdx.x) : xcd_group(blockIdx.x, v.G);
 }
 
 // Row sums of rows [r0, r1) of H x.  Owner o = 3 (row - r0) + c is thread
@@ -161,7 +162,7 @@ __device__ __forceinline__ void stream_rows(const int* __restrict__ rp, const in
             re[q] = rp[row + 1];
         }
     }
-    const int kb = rp[r0], ke = rp[r1];
+    const int kb = uniform_load(rp + r0), ke = uniform_load(rp + r1);
     ChunkCols nc = first;
     for (int cs = kb; cs < ke; cs += kChunk) {
         const int ce = min(cs + kChunk, ke);
@@ -264,7 +265,7 @@ __device__ __forceinline__ void stream_sym(const SolverView& v, const T* __restr
             te[q] = v.tptr[row + 1] - tb0;
         }
     }
-    const int kb = v.srp[r0], ke = v.srp[r1];
+    const int kb = uniform_load(v.srp + r0), ke = uniform_load(v.srp + r1);
     SymCols nc = first;
     for (int cs = kb; cs < ke; cs += kSymChunk) {
         const int ce = min(cs + kSymChunk, ke);
@@ -380,95 +381,110 @@ __device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, 
 // the unit plus the sum over the levels >= 2 of y_l at its ancestors, the same
 // sum in every group that reads the unit.  The levels >= 2 are summed once per
 // distinct level-2 unit (at 48^3 a group reads about 76 units under 23 of
-// them).  unit_load issues a thread's table loads (level-2 entry t / 3 or
-// unit t / 3, component t % 3), unit_gather the corrections they name;
-// unit_stage adds up, takes what is left over, and leaves the sums in ycor.
-// The two round trips overlap the rho sum.
-constexpr int kUnitLevels = 7;  // levels >= 2 a thread loads ahead
+// them).  unit_load issues a thread's table loads (level-2 entry t / 3,
+// component t % 3; units t and t + 256), unit_gather the corrections they
+// name; unit_stage adds up, takes what is left over, and leaves the sums in
+// ycor.  The two round trips overlap the rho sum.  Every load of the two is
+// unconditional, at clamped indices: a branch around one would wait for it.
+constexpr int kUnitLevels = 7;     // levels >= 2 whose corrections a thread loads ahead
+constexpr int kUnitTables = 14;    // levels >= 2 whose positions it loads ahead (all of them)
+constexpr int kUnits = 2;          // units whose corrections it loads ahead
+static_assert(kUnitTables >= kMaxLv - 2 && kUnits * kThreads >= kMaxHalo,
+              "only level-2 entries can be left over");
 
 struct UnitLoads {
-    int n, n2;       // units and level-2 entries of the group
+    int n, n2, nl;   // units and level-2 entries of the group, levels >= 2
     const int* pos;  // position of entry i at level 2 + l: pos[l n2 + i]
-    int at[kUnitLevels], u, par;
-    double y[kUnitLevels], y1;
+    int at[kUnitTables], u[kUnits], par[kUnits];
+    double y[kUnitLevels], y1[kUnits][3];
 };
 
 __device__ __forceinline__ UnitLoads unit_load(const SolverView& v, int g) {
     UnitLoads U;
-    const int h0 = v.hptr[g], q0 = v.h2ptr[g];
-    U.n = v.hptr[g + 1] - h0;
-    U.n2 = v.h2ptr[g + 1] - q0;
-    U.pos = v.hy + static_cast<long long>(max(v.L - 2, 0)) * q0;
-    const int i = static_cast<int>(threadIdx.x) / 3;
-    const int i2 = min(i, U.n2 - 1);
+    const int t = threadIdx.x;
+    const int h0 = uniform_load(v.hptr + g), q0 = uniform_load(v.h2ptr + g);
+    U.n = uniform_load(v.hptr + g + 1) - h0;
+    U.n2 = uniform_load(v.h2ptr + g + 1) - q0;
+    U.nl = max(v.L - 2, 0);
+    // (no level >= 2, no unit: stand-ins with entries)
+    U.pos = U.n2 > 0 ? v.hy + static_cast<long long>(U.nl) * q0 : v.hptr;
+    const int* hu = U.n > 0 ? v.hu + h0 : v.hptr;
+    const uint16_t* hpar = U.n > 0 ? v.hpar + h0 : reinterpret_cast<const uint16_t*>(v.hptr);
+    const int i2 = max(min(t / 3, U.n2 - 1), 0), last = max(U.nl - 1, 0);
 #pragma unroll
-    for (int l = 0; l < kUnitLevels; ++l) U.at[l] = l + 2 < v.L ? U.pos[l * U.n2 + i2] : 0;
-    U.u = U.par = 0;
-    if (U.n > 0) {
-        U.u = v.hu[h0 + min(i, U.n - 1)];
-        U.par = v.hpar[h0 + min(i, U.n - 1)];
+    for (int l = 0; l < kUnitTables; ++l) U.at[l] = U.pos[min(l, last) * U.n2 + i2];
+#pragma unroll
+    for (int q = 0; q < kUnits; ++q) {
+        const int i = max(min(t + q * kThreads, U.n - 1), 0);
+        U.u[q] = hu[i];
+        U.par[q] = hpar[i];
     }
     return U;
 }
 
 __device__ __forceinline__ void unit_gather(const SolverView& v, UnitLoads& U) {
     const int c = threadIdx.x % 3;
-    U.y1 = U.n > 0 ? v.yall[3LL * U.u + c] : 0.0;
-    if (static_cast<int>(threadIdx.x) < 3 * U.n2) {
+    const double* y = U.n > 0 ? v.yall : v.z;
+    const int keep = U.n > 0 ? -1 : 0, keep2 = U.n2 > 0 ? -1 : 0;  // (stand-ins name no position)
 #pragma unroll
-        for (int l = 0; l < kUnitLevels; ++l) U.y[l] = l + 2 < v.L ? v.yall[3LL * U.at[l] + c] : 0.0;
-    }
+    for (int l = 0; l < kUnitLevels; ++l) U.y[l] = y[3LL * (U.at[l] & keep2) + c];
+#pragma unroll
+    for (int q = 0; q < kUnits; ++q)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) U.y1[q][e] = y[3LL * (U.u[q] & keep) + e];
 }
 
 // ycor: 3 maxH doubles, then 3 maxH2 for the level-2 sums.  Ends with a
 // barrier.  buf: the rho buckets the caller has written, folded on the way
 // into buf[0] (by the last wave, which has the least to stage).
-__device__ __forceinline__ void unit_stage(const SolverView& v, int g, const UnitLoads& U, double* ycor, double* buf) {
+__device__ __forceinline__ void unit_stage(const SolverView& v, const UnitLoads& U, double* ycor, double* buf) {
+    const int t = threadIdx.x;
     double* up = ycor + 3 * v.maxH;
-    for (int e = threadIdx.x; e < 3 * U.n2; e += kThreads) {
-        const int i = e / 3, c = e - 3 * i;
+    // sum of y_l over kUnitLevels levels from 2 + l0 on, positions at
+    auto levels = [&](double s, const int* at, int l0, int c) {
+        double y[kUnitLevels];
+#pragma unroll
+        for (int l = 0; l < kUnitLevels; ++l) y[l] = v.yall[3LL * at[l] + c];
+#pragma unroll
+        for (int l = 0; l < kUnitLevels; ++l)
+            if (l0 + l < U.nl) s += y[l];
+        return s;
+    };
+    if (t < 3 * U.n2) {
         double s = 0.0;
-        int l0 = 2;
-        if (e < kThreads) {
 #pragma unroll
-            for (int l = 0; l < kUnitLevels; ++l) s += U.y[l];  // (0 past the last level)
-            l0 = 2 + kUnitLevels;
-        }
-        for (; l0 < v.L; l0 += 4) {
-            int at[4];
-            double y[4];
+        for (int l = 0; l < kUnitLevels; ++l)
+            if (l < U.nl) s += U.y[l];
+        if (U.nl > kUnitLevels) s = levels(s, U.at + kUnitLevels, kUnitLevels, t % 3);
+        up[t] = s;
+    }
+    for (int e = t + kThreads; e < 3 * U.n2; e += kThreads) {
+        const int i = e / 3, c = e - 3 * i;
+        int at[kUnitTables];
 #pragma unroll
-            for (int l = 0; l < 4; ++l) at[l] = U.pos[(min(l0 + l, v.L - 1) - 2) * U.n2 + i];
-#pragma unroll
-            for (int l = 0; l < 4; ++l) y[l] = v.yall[3LL * at[l] + c];
-#pragma unroll
-            for (int l = 0; l < 4; ++l)
-                if (l0 + l < v.L) s += y[l];
-        }
+        for (int l = 0; l < kUnitTables; ++l) at[l] = U.pos[min(l, U.nl - 1) * U.n2 + i];
+        double s = levels(0.0, at, 0, c);
+        if (U.nl > kUnitLevels) s = levels(s, at + kUnitLevels, kUnitLevels, c);
         up[e] = s;
     }
     __syncthreads();
-    if (threadIdx.x >= kThreads - 64) partials_fold(buf);
-    const int h0 = v.hptr[g];
-    for (int e = threadIdx.x; e < 3 * U.n; e += kThreads) {
-        const int i = e / 3, c = e - 3 * i;
-        const double y1 = e < kThreads ? U.y1 : v.yall[3LL * v.hu[h0 + i] + c];
-        const int par = e < kThreads ? U.par : v.hpar[h0 + i];
-        ycor[e] = v.L > 2 ? y1 + up[3 * par + c] : y1;
+    if (t >= kThreads - 64) partials_fold(buf);
+#pragma unroll
+    for (int q = 0; q < kUnits; ++q) {
+        const int i = t + q * kThreads;
+        if (i < U.n) {
+#pragma unroll
+            for (int e = 0; e < 3; ++e) ycor[3 * i + e] = U.nl > 0 ? U.y1[q][e] + up[3 * U.par[q] + e] : U.y1[q][e];
+        }
     }
     __syncthreads();
 }
 
-// The group's own units are the first of its list: local unit of slot s.
+// The group's own units are the first of its list: local unit of slot s,
+// negative for an empty slot or without coarse levels (remap: a stand-in).
 __device__ __forceinline__ int own_unit(const SolverView& v, int g, int slot) {
-    return v.L > 1 ? v.anc[slot] - v.g_u1[g] : -1;  // negative: empty slot or no coarse level
-}
-
-// Workgroup G of a split SpMV takes the decision on r_{k-1}.
-__device__ __forceinline__ bool decide_only(const SolverView& v, int k, int flags, double* buf) {
-    if (static_cast<int>(blockIdx.x) < v.G) return false;
-    convergence_decision(v, false, k - 1, 0.0, flags, v.GA, spmv_mark(k), buf);
-    return true;
+    const int u = (v.L > 1 ? v.anc : v.remap)[slot] - uniform_load(v.g_u1 + g);
+    return v.L > 1 ? u : -1;
 }
 
 constexpr int kRhoPer = 8;  // rho partials a thread loads ahead: up to 2048 in all
@@ -522,7 +538,7 @@ __device__ __forceinline__ double dir_stage(const SolverView& v, int k, int g, i
     const double* Prho = v.P_rho[(k - 1) & 1];
     partials_bucket<kSplit ? kRhoPer : 4>(rl, Prho, nrho, buf);
     if constexpr (kSplit) {
-        unit_stage(v, g, U, ycor, buf);
+        unit_stage(v, U, ycor, buf);
     } else {
         __syncthreads();
         if (t < 64) partials_fold(buf);
@@ -554,7 +570,10 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     __shared__ double prod[3 * kPlane];
     __shared__ double buf[256];
     extern __shared__ double dyn[];  // xs[3 RG] (+ ycor[3 (maxH + maxH2)])
-    if (kSplit && decide_only(v, k, flags, buf)) return;
+    if (kSplit && static_cast<int>(blockIdx.x) >= v.G) {  // one workgroup more takes the decision on r_{k-1}
+        convergence_decision(v, false, k - 1, 0.0, flags, v.GA, spmv_mark(k), buf);
+        return;
+    }
     const int g = spmv_group(v);
     const int r0 = g * v.RG, r1 = min(r0 + v.RG, v.NS);
     const int nown = 3 * (r1 - r0);
@@ -568,13 +587,13 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     if constexpr (kSplit) U = unit_load(v, g);
     const auto rl = partials_load<kSplit ? kRhoPer : 4>(v.P_rho[(k - 1) & 1], nrho);
     DirLoads D = dir_load<kSplit, kFresh>(v, g, r0, nown, pold, k > 1 ? v.q[(k - 1) & 1] : v.z);
-    const ChunkCols c0 = chunk_cols<kSplit>(v.ci0, v.rp0[r0], v.rp0[r1], v.hidx);
+    const ChunkCols c0 = chunk_cols<kSplit>(v.ci0, uniform_load(v.rp0 + r0), uniform_load(v.rp0 + r1), v.hidx);
     RestrictLoads<kRQ ? kRQ : 1> pl{};
     if constexpr (kRQ) pl = restrict_load<kRQ>(v, g);
-    const int stop = v.st->done;
+    const int stop = uniform_load(&v.st->done);
     keep_loads_issued();
     if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
-    const double rk2 = v.st->rho[k & 1];  // rho_{k-2} as the previous SpMV recorded it
+    const double rk2 = uniform_load(&v.st->rho[k & 1]);  // rho_{k-2} as the previous SpMV recorded it
     if constexpr (kSplit) unit_gather(v, U);
     double pv[2], acc[2];
     const double beta = dir_stage<kSplit, kFresh>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv);
@@ -597,7 +616,10 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     __shared__ double prod[6 * kSymPlane];
     __shared__ double buf[256];
     extern __shared__ double dyn[];  // xs[3 RG] doubles (+ ycor[3 (maxH + maxH2)]) + tl[maxT] ints
-    if (kSplit && decide_only(v, k, flags, buf)) return;
+    if (kSplit && static_cast<int>(blockIdx.x) >= v.G) {  // one workgroup more takes the decision on r_{k-1}
+        convergence_decision(v, false, k - 1, 0.0, flags, v.GA, spmv_mark(k), buf);
+        return;
+    }
     const int t = threadIdx.x;
     const int g = spmv_group(v);
     const int r0 = g * v.RG, r1 = min(r0 + v.RG, v.NS);
@@ -613,18 +635,18 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     if constexpr (kSplit) U = unit_load(v, g);
     const auto rl = partials_load<kSplit ? kRhoPer : 4>(v.P_rho[(k - 1) & 1], nrho);
     DirLoads D = dir_load<kSplit, kFresh>(v, g, r0, nown, pold, k > 1 ? v.q[(k - 1) & 1] : v.z);
-    const int tb0 = v.tptr[r0], tn = v.tptr[r1] - tb0;
+    const int tb0 = uniform_load(v.tptr + r0), tn = uniform_load(v.tptr + r1) - tb0;
     const int* tsrc = tn > 0 ? v.tidx + tb0 : v.srp;  // srp: a stand-in with entries when the list is empty
     int tlr[kTlRegs];
 #pragma unroll
     for (int j = 0; j < kTlRegs; ++j) tlr[j] = tsrc[min(t + j * kThreads, max(tn - 1, 0))];
-    const SymCols c0 = sym_cols<kSplit>(v, v.srp[r0], v.srp[r1]);
+    const SymCols c0 = sym_cols<kSplit>(v, uniform_load(v.srp + r0), uniform_load(v.srp + r1));
     RestrictLoads<kRQ ? kRQ : 1> pl{};
     if constexpr (kRQ) pl = restrict_load<kRQ>(v, g);
-    const int stop = v.st->done;
+    const int stop = uniform_load(&v.st->done);
     keep_loads_issued();
     if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
-    const double rk2 = v.st->rho[k & 1];  // rho_{k-2} as the previous SpMV recorded it
+    const double rk2 = uniform_load(&v.st->rho[k & 1]);  // rho_{k-2} as the previous SpMV recorded it
     if constexpr (kSplit) unit_gather(v, U);
 #pragma unroll
     for (int j = 0; j < kTlRegs; ++j)
