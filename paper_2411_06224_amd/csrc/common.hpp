@@ -72,6 +72,13 @@ __device__ __forceinline__ double dpp_add(double x) {
     return x + dpp_get<kCtrl>(x);
 }
 
+// The value of lane kLane of each row of 16 lanes in all of the row's lanes
+// (row_newbcast, the DPP form that moves 64 bits).
+template <int kLane>
+__device__ __forceinline__ double dpp_row_lane(double x) {
+    return __builtin_amdgcn_update_dpp(0.0, x, 0x150 + kLane, 0xf, 0xf, false);
+}
+
 __device__ __forceinline__ double lane_value(double x, int lane) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
                             __builtin_amdgcn_readlane(__double2loint(x), lane));

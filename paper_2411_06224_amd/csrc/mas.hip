@@ -85,7 +85,10 @@ __global__ void __launch_bounds__(256) k_coarse_sum_next(int nnzA, int nnzPrev, 
 // domain matrix (3N x 3N, padded to 16T with identity rows on empty lanes so
 // that the inverse of the occupied part comes out directly) sits in LDS and
 // is inverted in place by block Gauss-Jordan over 16x16 tiles:
-//   P = inv(A_kk) (register-resident scalar Gauss-Jordan, 16 pivots, wave 0),
+//   P = inv(A_kk) (register-resident scalar Gauss-Jordan, 16 pivots, wave 0;
+//   these serial pivots bound the kernel: with the pivot and its column by
+//   readlane and DPP instead of six 64-bit shuffles a step, and one
+//   multiply-add per entry, 0.127 -> 0.094 ms at 48^3),
 //   A_kj <- P A_kj, A_ij <- A_ij - A_ik A_kj, A_ik <- -A_ik P, A_kk <- P,
 // with the tile products on v_mfma_f64_16x16x4f64, the tiles of each phase
 // dealt round-robin to the four waves.  Pivots are Schur complement
@@ -106,6 +109,14 @@ __device__ __forceinline__ int level_of(const DomTable& tab, int L, int g) {
 
 constexpr int kInvWaves = 4;
 constexpr int kInvThreads = 64 * kInvWaves;
+
+template <int n, int i = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (i < n) {
+        f(std::integral_constant<int, i>{});
+        static_for<n, i + 1>(f);
+    }
+}
 
 // A domain's share of its packed pair (launch.hpp) from the inverse in LDS,
 // zero on empty lanes: thread t writes entry t of each tile below the
@@ -206,26 +217,25 @@ __global__ void __launch_bounds__(kInvThreads) k_invert(BuildView B, const doubl
             double a[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) a[v] = A[(base + 4 * g4 + v) * LD + base + c16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int jg = j >> 2, jv = j & 3;
-                const double aj = a[jv];
-                const double piv = __shfl(aj, jg * 16 + j);
-                const double rowj = __shfl(aj, jg * 16 + c16);
+            // step j: the pivot by readlane, column j by DPP (lane j of each row
+            // of 16), row j, which no DPP form moves across the rows of 16, by
+            // one shuffle beside the division
+            static_for<16>([&](auto jc) {
+                constexpr int j = jc.value, jg = j >> 2, jv = j & 3;
+                const double rowj = __shfl(a[jv], jg * 16 + c16);
+                const double piv = lane_value(a[jv], jg * 16 + j);
                 double colj[4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) colj[v] = __shfl(a[v], g4 * 16 + j);
+                for (int v = 0; v < 4; ++v) colj[v] = dpp_row_lane<j>(a[v]);
                 ok = ok && (piv > 0.0) && finite(piv);
                 const double inv = 1.0 / piv;
+                // with 1 in place of the pivot column's entry of row j, and 0 in
+                // place of the column's other entries, all entries take one form
+                const double sc = c16 == j ? inv : rowj * inv;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int i = 4 * g4 + v;
-                    if (i == j)
-                        a[v] = (c16 == j) ? inv : a[v] * inv;
-                    else
-                        a[v] = (c16 == j) ? -colj[v] * inv : a[v] - colj[v] * rowj * inv;
-                }
-            }
+                for (int v = 0; v < 4; ++v) a[v] = __fma_rn(-colj[v], sc, c16 == j ? 0.0 : a[v]);
+                if (g4 == jg) a[jv] = sc;
+            });
 #pragma unroll
             for (int v = 0; v < 4; ++v) A[(base + 4 * g4 + v) * LD + base + c16] = a[v];
         }
