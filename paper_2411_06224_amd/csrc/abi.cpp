@@ -848,11 +848,8 @@ int mas_apply(mas_handle* h, const double* r, double* z, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const SolverView v = view(h);
     const bool mixed = h->opts.precision == MAS_PRECISION_MIXED;
-    HIP_TRY(launch_perm_in(v, r, v.r, s));
-    HIP_TRY(timed(h, kKRestrict, s, [&] { return launch_restrict(v, s); }));
-    HIP_TRY(launch_apply_coarse(v, mixed, kApplyPlain, 0, 0.0, false, mixed, false, s));
-    HIP_TRY(launch_apply_level0(v, mixed, kApplyPlain, 0, s));
-    HIP_TRY(launch_perm_out(v, v.z, z, s));
+    HIP_TRY(timed(h, kKRestrict, s, [&] { return launch_restrict(v, r, s); }));
+    HIP_TRY(launch_apply_plain(v, mixed, r, z, s));
     return MAS_OK;
 }
 

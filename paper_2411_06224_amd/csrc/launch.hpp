@@ -238,7 +238,8 @@ hipError_t launch_perm_in(const SolverView& v, const double* src, double* dst, h
 hipError_t launch_perm_out(const SolverView& v, const double* src, double* dst, hipStream_t s);
 hipError_t launch_init_rhs(const SolverView& v, hipStream_t s);
 hipError_t launch_update(const SolverView& v, int k, hipStream_t s);
-hipError_t launch_restrict(const SolverView& v, hipStream_t s);
+// The restriction of a vector r in the caller's node order.
+hipError_t launch_restrict(const SolverView& v, const double* r, hipStream_t s);
 hipError_t launch_adjoint_scatter(int n_rows, const int* rp, const int* ci, const double* lam, const double* x,
                                   void* out, bool f32, hipStream_t s);
 
@@ -253,6 +254,9 @@ hipError_t launch_apply_coarse(const SolverView& v, bool f32, int mode, int k, d
 // The decision on r_k alone, after an iteration k by recurrence.
 hipError_t launch_decision(const SolverView& v, int k, bool mixed, hipStream_t s);
 hipError_t launch_apply_level0(const SolverView& v, bool f32, int mode, int k, hipStream_t s);
+// z = M^-1 r outside PCG after launch_restrict(v, r): the coarse levels, then
+// level 0 with the prolongation (r, z: the caller's node order).
+hipError_t launch_apply_plain(const SolverView& v, bool f32, const double* r, double* z, hipStream_t s);
 // Iteration k by recurrence: x/r update, level 0 and the coarse levels in
 // one launch (see ApplyMode).
 hipError_t launch_apply_rec(const SolverView& v, bool f32, int k, hipStream_t s);

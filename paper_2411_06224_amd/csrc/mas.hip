@@ -795,31 +795,53 @@ __global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_coarse(Solve
 
 // ---- level 0
 // Sum over l >= 1 of y_l at the slot's unit (prolongation of every coarse
-// level, Supp. Eq. 6): eight levels' unit ids at once, then their
-// corrections at once.
+// level, Supp. Eq. 6): kProlong levels' unit ids at once, then their
+// corrections at once, unconditional loads at clamped levels.  The pair kernel
+// loads the first round's ids ahead of the inverses (ahead of them the
+// corrections too, registers spill: 16 -> 31 us at 48^3).
 constexpr int kProlong = 8;
 
-__device__ __forceinline__ double prolong(const SolverView& v, int slot, int c) {
+struct Prolong {
+    int u[kProlong];
+};
+
+__device__ __forceinline__ void prolong_ids(const SolverView& v, Prolong& R, int slot, int l0 = 0) {
+    const int* anc = v.L > 1 ? v.anc : v.remap;  // (no coarse level: a stand-in)
+#pragma unroll
+    for (int j = 0; j < kProlong; ++j) R.u[j] = anc[static_cast<long long>(max(min(l0 + j, v.L - 2), 0)) * v.NS + slot];
+}
+
+__device__ __forceinline__ double prolong_sum(const SolverView& v, const Prolong& R, int c, int l0 = 0) {
+    double y[kProlong];
+#pragma unroll
+    for (int j = 0; j < kProlong; ++j) {
+        const double* yl = v.L > 1 ? v.y[min(l0 + j + 1, v.L - 1)] : v.z;
+        y[j] = yl[3LL * (v.L > 1 ? max(R.u[j], 0) : 0) + c];
+    }
     double s = 0.0;
-    for (int l0 = 0; l0 + 1 < v.L; l0 += kProlong) {
-        int u[kProlong];
-        double y[kProlong];
 #pragma unroll
-        for (int j = 0; j < kProlong; ++j)
-            u[j] = l0 + j + 1 < v.L ? v.anc[static_cast<long long>(l0 + j) * v.NS + slot] : -1;
-#pragma unroll
-        for (int j = 0; j < kProlong; ++j) y[j] = u[j] >= 0 ? v.y[l0 + j + 1][3 * u[j] + c] : 0.0;
-#pragma unroll
-        for (int j = 0; j < kProlong; ++j) s += y[j];
+    for (int j = 0; j < kProlong; ++j)
+        if (l0 + j + 1 < v.L && R.u[j] >= 0) s += y[j];
+    return s;
+}
+
+__device__ __forceinline__ double prolong_rest(const SolverView& v, double s, int slot, int c) {
+    for (int l0 = kProlong; l0 + 1 < v.L; l0 += kProlong) {
+        Prolong R;
+        prolong_ids(v, R, slot, l0);
+        s += prolong_sum(v, R, c, l0);
     }
     return s;
 }
 
 // z = Inv_{0,d} r_d + the prolongation of the coarse corrections and, inside
-// PCG, the partial of rho = r^T z.  Domain size 16: eight domains per
+// PCG, the partial of rho = r^T z.  kApplyPlain: r from src and z to dst, both
+// in the caller's node order.  Domain size 16: eight domains per
 // workgroup, a pair per wave.
 template <typename TI, int kMode>
-__global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_level0_pairs(SolverView v, int k) {
+__global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_level0_pairs(SolverView v, int k,
+                                                                                 const double* __restrict__ src,
+                                                                                 double* __restrict__ dst) {
     __shared__ double sm[4 * kPairLds];
     __shared__ double red[4];
     const int t = threadIdx.x, lane = t & 63;
@@ -830,11 +852,26 @@ __global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_level0_pairs
     int e[2];
     bool own[2];
     double x[2], out[2] = {0.0, 0.0}, cor[2];
+    long long at[2];
+    Prolong R[2];
+    int slot[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         e[q] = 96 * p + pair_row(lane, q);
         own[q] = pair_owns(lane, q) && e[q] < 3 * v.NS;
-        x[q] = own[q] ? v.r[e[q]] : 0.0;
+        slot[q] = own[q] ? e[q] / 3 : 0;
+        at[q] = e[q];
+        prolong_ids(v, R[q], slot[q]);
+        if (kMode == kApplyPlain) {
+            const int node = v.remap[slot[q]];
+            own[q] = own[q] && node >= 0;
+            at[q] = 3LL * node + e[q] % 3;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const double xv = (kMode == kApplyPlain ? src : v.r)[own[q] ? at[q] : 0];
+        x[q] = own[q] ? xv : 0.0;
     }
     PairRegs<TI> P;
     pair_load(P, inverses<TI>(v, 0) + static_cast<long long>(live ? p : 0) * kPairEntries, lane);
@@ -842,14 +879,14 @@ __global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_level0_pairs
     keep_loads_issued();
     if (kMode != kApplyPlain && stop) return;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) cor[q] = own[q] ? prolong(v, e[q] / 3, e[q] % 3) : 0.0;
+    for (int q = 0; q < 2; ++q) cor[q] = own[q] ? prolong_sum(v, R[q], e[q] % 3) : 0.0;
     if (live) pair_product(P, x, sm + w * kPairLds, lane, out);
     double part = 0.0;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
         if (own[q]) {
-            const double z = out[q] + cor[q];
-            v.z[e[q]] = z;
+            const double z = out[q] + prolong_rest(v, cor[q], slot[q], e[q] % 3);
+            (kMode == kApplyPlain ? dst : v.z)[at[q]] = z;
             part += x[q] * z;
         }
     if (kMode == kApplyPlain) return;
@@ -860,19 +897,29 @@ __global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_level0_pairs
 // The same for other domain sizes: a group of D0 domains per workgroup, one
 // thread per DOF.
 template <typename TI, int kMode>
-__global__ void __launch_bounds__(kGroupThreads) k_apply_level0(SolverView v, int k) {
+__global__ void __launch_bounds__(kGroupThreads) k_apply_level0(SolverView v, int k, const double* __restrict__ src,
+                                                                double* __restrict__ dst) {
     __shared__ double rs[kGroupThreads];
     __shared__ double red[16];
     const int n = 3 * v.N;
     const int g = xcd_group(blockIdx.x, v.G), t = threadIdx.x;
     const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
     const bool live = t < nd * n;
-    const long long base = 3LL * g * v.RG;
-    const double rv = live ? v.r[base + t] : 0.0;
+    long long at = 3LL * g * v.RG + t;
+    bool own = live;
+    if (kMode == kApplyPlain) {
+        const int node = live ? v.remap[g * v.RG + t / 3] : -1;
+        own = node >= 0;
+        at = 3LL * node + t % 3;
+    }
+    const double rv = own ? (kMode == kApplyPlain ? src : v.r)[at] : 0.0;
     const int stop = v.st->done;
     keep_loads_issued();
     if (kMode != kApplyPlain && stop) return;
-    const double cor = live ? prolong(v, g * v.RG + t / 3, t % 3) : 0.0;
+    const int slot = live ? g * v.RG + t / 3 : 0;
+    Prolong R;
+    prolong_ids(v, R, slot);
+    const double cor = live ? prolong_rest(v, prolong_sum(v, R, t % 3), slot, t % 3) : 0.0;
     rs[t] = rv;
     __syncthreads();
     double zv = 0.0;
@@ -881,7 +928,7 @@ __global__ void __launch_bounds__(kGroupThreads) k_apply_level0(SolverView v, in
         zv = full_row<TI, true>(inverses<TI>(v, 0) + static_cast<long long>(g * v.D0 + dl) * n * n, n, t - dl * n,
                                 rs + dl * n) +
              cor;
-        v.z[base + t] = zv;
+        if (own) (kMode == kApplyPlain ? dst : v.z)[at] = zv;
     }
     if (kMode == kApplyPlain) return;
     const double part = block_sum_last(rv * zv, red);
@@ -1074,25 +1121,12 @@ CoarseTable coarse_table(const SolverView& v) {
     return t;
 }
 
-template <typename TI>
-void launch_level0_t(const SolverView& v, int mode, int k, hipStream_t s) {
-    if (v.N == 16) {
-        dim3 g(v.GA), b(kPairThreads);
-        if (mode == kApplyPlain)
-            launch_kernel((k_apply_level0_pairs<TI, kApplyPlain>), g, b, 0, s, v, k);
-        else if (mode == kApplyInit)
-            launch_kernel((k_apply_level0_pairs<TI, kApplyInit>), g, b, 0, s, v, k);
-        else
-            launch_kernel((k_apply_level0_pairs<TI, kApplyIter>), g, b, 0, s, v, k);
-        return;
-    }
-    dim3 g(v.G), b(round_waves(3 * v.RG));
-    if (mode == kApplyPlain)
-        launch_kernel((k_apply_level0<TI, kApplyPlain>), g, b, 0, s, v, k);
-    else if (mode == kApplyInit)
-        launch_kernel((k_apply_level0<TI, kApplyInit>), g, b, 0, s, v, k);
+template <typename TI, int kMode>
+void launch_level0_t(const SolverView& v, int k, const double* src, double* dst, hipStream_t s) {
+    if (v.N == 16)
+        launch_kernel((k_apply_level0_pairs<TI, kMode>), dim3(v.GA), dim3(kPairThreads), 0, s, v, k, src, dst);
     else
-        launch_kernel((k_apply_level0<TI, kApplyIter>), g, b, 0, s, v, k);
+        launch_kernel((k_apply_level0<TI, kMode>), dim3(v.G), dim3(round_waves(3 * v.RG)), 0, s, v, k, src, dst);
 }
 
 template <typename TI>
@@ -1130,10 +1164,20 @@ hipError_t launch_decision(const SolverView& v, int k, bool mixed, hipStream_t s
 }
 
 hipError_t launch_apply_level0(const SolverView& v, bool f32, int mode, int k, hipStream_t s) {
-    if (f32)
-        launch_level0_t<float>(v, mode, k, s);
+    if (mode == kApplyInit)
+        f32 ? launch_level0_t<float, kApplyInit>(v, k, nullptr, nullptr, s)
+            : launch_level0_t<double, kApplyInit>(v, k, nullptr, nullptr, s);
     else
-        launch_level0_t<double>(v, mode, k, s);
+        f32 ? launch_level0_t<float, kApplyIter>(v, k, nullptr, nullptr, s)
+            : launch_level0_t<double, kApplyIter>(v, k, nullptr, nullptr, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_apply_plain(const SolverView& v, bool f32, const double* r, double* z, hipStream_t s) {
+    hipError_t e;
+    if (v.ncb > 0 && (e = launch_apply_coarse(v, f32, kApplyPlain, 0, 0.0, false, f32, false, s)) != hipSuccess)
+        return e;
+    f32 ? launch_level0_t<float, kApplyPlain>(v, 0, r, z, s) : launch_level0_t<double, kApplyPlain>(v, 0, r, z, s);
     return hipGetLastError();
 }
 

@@ -158,13 +158,15 @@ __global__ void k_update(SolverView v, int k) {
     restrict_group_any(v, g, pl, rs, sm + 3 * v.RG, v.r1, v.cpart);
 }
 
-// Restriction of the current r only (preconditioner apply outside PCG).
-__global__ void k_restrict(SolverView v) {
+// Restriction of a vector in the caller's node order (preconditioner apply
+// outside PCG).
+__global__ void k_restrict(SolverView v, const double* __restrict__ src) {
     extern __shared__ double sm[];
     double* rs = sm;
     const int g = xcd_group(blockIdx.x, v.G), t = threadIdx.x;
     const long long i = 3LL * g * v.RG + t;
-    const double rv = (t < 3 * v.RG && i < 3LL * v.NS) ? v.r[i] : 0.0;
+    const int node = (t < 3 * v.RG && i < 3LL * v.NS) ? v.remap[i / 3] : -1;
+    const double rv = node >= 0 ? src[3LL * node + i % 3] : 0.0;
     const RestrictLoads<> pl = restrict_load<>(v, g);
     if (t < 3 * v.RG) rs[t] = rv;
     __syncthreads();
@@ -254,9 +256,9 @@ hipError_t launch_update(const SolverView& v, int k, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_restrict(const SolverView& v, hipStream_t s) {
+hipError_t launch_restrict(const SolverView& v, const double* r, hipStream_t s) {
     if (v.L < 2) return hipSuccess;
-    launch_kernel(k_restrict, dim3(v.G), dim3(group_threads(v)), group_smem(v), s, v);
+    launch_kernel(k_restrict, dim3(v.G), dim3(group_threads(v)), group_smem(v), s, v, r);
     return hipGetLastError();
 }
 
