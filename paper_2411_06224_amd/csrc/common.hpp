@@ -247,6 +247,14 @@ __device__ inline double sum_partials(const double* __restrict__ p, int n, doubl
     return partials_sum<true, 0>(PartialLoads<0>{}, p, n, buf);
 }
 
+// Orders the wave's LDS writes before its later reads (other lanes' data): a
+// wave's LDS accesses execute in order, so this only holds the compiler.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 inline int ceil_div(long long a, long long b) { return static_cast<int>((a + b - 1) / b); }
 inline int round_waves(int threads) { return (threads + 63) / 64 * 64; }
 

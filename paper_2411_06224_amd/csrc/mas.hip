@@ -392,14 +392,6 @@ __device__ __forceinline__ double row16_sum4(const double (&col)[4], int lane) {
     return dpp_add<0x124>(k);                                 // row_ror 4
 }
 
-// Orders the wave's LDS writes before its later reads (other lanes' data): a
-// wave's LDS accesses execute in order, so this only holds the compiler.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 constexpr int kPairLds = 96 + 5 * 96;  // doubles of LDS per wave: the vector, four row parts and the column part
 
 // out[q] = the pair's product at the lane's rows, x[q] the vector there

@@ -32,11 +32,12 @@ _ALIGN = 256
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # torch's current stream as the C ABI takes it, without building a Stream object (1.5 us a call)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _need_cuda(t, name, dtype=None):
@@ -87,11 +88,14 @@ def bcsr_spmv(H, x, out=None):
     _need_cuda(x, "x", torch.float64)
     if x.numel() != 3 * H.n_rows:
         raise ValueError("x must have 3 * n_rows entries")
-    y = torch.empty_like(x) if out is None else out
-    _need_cuda(y, "out", torch.float64)
-    L = _lib.load()
-    h = H.c_struct()
-    check("bcsr_spmv", L.bcsr_spmv(ctypes.byref(h), _ptr(x), _ptr(y), _stream()))
+    if out is None:
+        y = torch.empty_like(x)
+    else:
+        y = out
+        _need_cuda(y, "out", torch.float64)
+    rc = _lib.load().bcsr_spmv(ctypes.byref(H.c_struct()), x.data_ptr(), y.data_ptr(), _stream())
+    if rc:
+        check("bcsr_spmv", rc)
     return y
 
 
