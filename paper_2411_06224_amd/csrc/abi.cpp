@@ -901,8 +901,20 @@ int assemble_impl(int32_t n_rows, int64_t n_in, const int32_t* rows, const int32
                   int32_t* row_ptr, int32_t* col_idx, double* val, int64_t capacity, int64_t* nnzb, char* ws,
                   hipStream_t s) {
     const AsmLayout L = assemble_layout(ws, n_rows, n_in, nullptr);
-    HIP_TRY(launch_assemble_sort(L, n_rows, n_in, rows, cols, row_ptr, s));
+    bool taken = false;
+    HIP_TRY(launch_assemble_rows(L, n_rows, n_in, rows, cols, blocks, row_ptr, col_idx, val,
+                                 col_idx && val ? capacity : 0, s, &taken));
     int host[2] = {0, 0};
+    if (taken) {
+        HIP_TRY(hipMemcpyAsync(host, L.flag, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        if (host[0] & 1) return MAS_INVALID_ARG;  // an index out of range
+        if (!(host[0] & 2)) {
+            *nnzb = host[1];
+            return host[1] > capacity || (host[1] > 0 && (!col_idx || !val)) ? MAS_INVALID_ARG : MAS_OK;
+        }
+    }
+    HIP_TRY(launch_assemble_sort(L, n_rows, n_in, rows, cols, row_ptr, s));
     HIP_TRY(hipMemcpyAsync(host, L.flag, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (host[0]) return MAS_INVALID_ARG;  // an index out of range

@@ -285,6 +285,14 @@ hipError_t launch_assemble_sort(const AsmLayout& L, int n_rows, long long n_in, 
 // Sums every (row, col) segment in list order into col_idx / val.
 hipError_t launch_assemble_reduce(const AsmLayout& L, long long n_in, const double* blocks, int* col_idx, double* val,
                                   int nnzb, hipStream_t s);
+// Both steps at once for lists of short rows (*taken: the list is one), with
+// no host round trip between them: row_ptr, and, if every index was in range,
+// no row too long and row_ptr[n_rows] <= capacity, col_idx and val.  flag[0]
+// bit 0: index out of range; bit 1: a row too long for this path; flag[1]:
+// row_ptr[n_rows].
+hipError_t launch_assemble_rows(const AsmLayout& L, int n_rows, long long n_in, const int* rows, const int* cols,
+                                const double* blocks, int* row_ptr, int* col_idx, double* val, long long capacity,
+                                hipStream_t s, bool* taken);
 
 // hierarchy.hip: supernode hierarchy on the device, every level queued at
 // once; the level state on the device ends it (no host round trip).
