@@ -333,7 +333,7 @@ SolverView view(const mas_handle* h) {
         v.hy = at<int>(h, Y.hy);
         v.hpar = at<uint16_t>(h, Y.hpar);
         v.hidx = at<uint16_t>(h, Y.hidx);
-        v.maxH = h->shape.maxH;
+        v.maxH = std::max(h->shape.maxH, 1);  // one of zeros where there are no coarse levels
         v.maxH2 = h->shape.maxH2;
     }
     v.yall = at<double>(h, Y.yall);
@@ -750,7 +750,8 @@ void set_fusion(mas_handle* h) {
     h->fuse_ok = sizeof(double) * (3 * static_cast<size_t>(R.RG) + restrict_smem_doubles(R.RG, R.W1, R.L)) <=
                      spmv_restrict_capacity() &&
                  restrict_passes(R.W1, R.GW, spmv_threads()) > 0 && h->shape.halo &&
-                 spmv_shared_bytes(R.RG, R.maxT, R.sym) + sizeof(double) * 3 * (h->shape.maxH + h->shape.maxH2) <=
+                 spmv_shared_bytes(R.RG, R.maxT, R.sym) +
+                         sizeof(double) * 3 * (std::max(h->shape.maxH, 1) + h->shape.maxH2) <=
                      (size_t{64} << 10);
 }
 

@@ -531,6 +531,7 @@ __device__ __forceinline__ void unit_stage(const SolverView& v, const UnitLoads&
             if (l0 + l < U.nl) s += y[l];
         return s;
     };
+    if (U.n == 0 && t < 3) ycor[t] = 0.0;  // no coarse levels: every block names unit 0
     if (t < 3 * U.n2) {
         double s = 0.0;
 #pragma unroll
