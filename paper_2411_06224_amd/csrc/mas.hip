@@ -29,9 +29,27 @@ __device__ __forceinline__ double inv_load(const TI* p) {
 // weights).  Each coarse block owns a list of fine blocks and sums it in a
 // fixed order: no atomics, bitwise reproducible.  Nine consecutive threads
 // take one coarse block, thread c summing entry c over the list in order,
-// four list entries loaded at a time (their indices, then their values), so
-// that the list's loads overlap instead of following one another.
-constexpr int kSumRound = 4;
+// kRound list entries loaded at a time (their indices, then their values;
+// past the end the last one again), so that the list's loads overlap instead
+// of following one another.
+template <int kRound, typename F>
+__device__ __forceinline__ double list_sum(const int* __restrict__ src, int q, int qe, F&& value) {
+    double s = 0.0;
+    for (; q < qe; q += kRound) {
+        int i[kRound];
+#pragma unroll
+        for (int j = 0; j < kRound; ++j) i[j] = src[min(q + j, qe - 1)];
+        double a[kRound];
+#pragma unroll
+        for (int j = 0; j < kRound; ++j) a[j] = value(i[j]);
+#pragma unroll
+        for (int j = 0; j < kRound; ++j)
+            if (q + j < qe) s += a[j];
+    }
+    return s;
+}
+
+constexpr int kRoundFirst = 4, kRoundNext = 8;
 
 __global__ void __launch_bounds__(256) k_coarse_sum_first(int nnzA, const int* __restrict__ ptr,
                                                            const int* __restrict__ src, const double* __restrict__ Hu,
@@ -39,21 +57,8 @@ __global__ void __launch_bounds__(256) k_coarse_sum_first(int nnzA, const int* _
     const long long gt = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x;
     if (gt >= 9LL * nnzA) return;
     const int t = static_cast<int>(gt / 9), c = static_cast<int>(gt % 9);
-    const int qe = ptr[t + 1];
-    int q = ptr[t];
-    double s = 0.0;
-    for (; q + kSumRound <= qe; q += kSumRound) {
-        int i[kSumRound];
-#pragma unroll
-        for (int j = 0; j < kSumRound; ++j) i[j] = src[q + j];
-        double a[kSumRound];
-#pragma unroll
-        for (int j = 0; j < kSumRound; ++j) a[j] = Hu[9LL * i[j] + c];
-#pragma unroll
-        for (int j = 0; j < kSumRound; ++j) s += a[j];
-    }
-    for (; q < qe; ++q) s += Hu[9LL * src[q] + c];
-    A[static_cast<long long>(c) * nnzA + t] = s;
+    A[static_cast<long long>(c) * nnzA + t] =
+        list_sum<kRoundFirst>(src, ptr[t], ptr[t + 1], [&](int i) { return Hu[9LL * i + c]; });
 }
 
 __global__ void __launch_bounds__(256) k_coarse_sum_next(int nnzA, int nnzPrev, const int* __restrict__ ptr,
@@ -63,32 +68,17 @@ __global__ void __launch_bounds__(256) k_coarse_sum_next(int nnzA, int nnzPrev, 
     if (gt >= 9LL * nnzA) return;
     const int t = static_cast<int>(gt / 9), c = static_cast<int>(gt % 9);
     const double* Apc = Ap + static_cast<long long>(c) * nnzPrev;
-    const int qe = ptr[t + 1];
-    int q = ptr[t];
-    double s = 0.0;
-    for (; q + kSumRound <= qe; q += kSumRound) {
-        int i[kSumRound];
-#pragma unroll
-        for (int j = 0; j < kSumRound; ++j) i[j] = src[q + j];
-        double a[kSumRound];
-#pragma unroll
-        for (int j = 0; j < kSumRound; ++j) a[j] = Apc[i[j]];
-#pragma unroll
-        for (int j = 0; j < kSumRound; ++j) s += a[j];
-    }
-    for (; q < qe; ++q) s += Apc[src[q]];
-    A[static_cast<long long>(c) * nnzA + t] = s;
+    A[static_cast<long long>(c) * nnzA + t] =
+        list_sum<kRoundNext>(src, ptr[t], ptr[t + 1], [&](int i) { return Apc[i]; });
 }
 
 // ------------------------------------------------------- domain inversion
-// One workgroup of four waves per domain (all levels in one launch).  The
+// Domain sizes other than 16 (those: below), one workgroup of four waves per
+// domain (all levels in one launch).  The
 // domain matrix (3N x 3N, padded to 16T with identity rows on empty lanes so
 // that the inverse of the occupied part comes out directly) sits in LDS and
 // is inverted in place by block Gauss-Jordan over 16x16 tiles:
-//   P = inv(A_kk) (register-resident scalar Gauss-Jordan, 16 pivots, wave 0;
-//   these serial pivots bound the kernel: with the pivot and its column by
-//   readlane and DPP instead of six 64-bit shuffles a step, and one
-//   multiply-add per entry, 0.127 -> 0.094 ms at 48^3),
+//   P = inv(A_kk) (register-resident scalar Gauss-Jordan, 16 pivots, wave 0),
 //   A_kj <- P A_kj, A_ij <- A_ij - A_ik A_kj, A_ik <- -A_ik P, A_kk <- P,
 // with the tile products on v_mfma_f64_16x16x4f64, the tiles of each phase
 // dealt round-robin to the four waves.  Pivots are Schur complement
@@ -116,34 +106,6 @@ __device__ __forceinline__ void static_for(F&& f) {
         f(std::integral_constant<int, i>{});
         static_for<n, i + 1>(f);
     }
-}
-
-// A domain's share of its packed pair (launch.hpp) from the inverse in LDS,
-// zero on empty lanes: thread t writes entry t of each tile below the
-// diagonal and, of each diagonal tile, the triangle that is this domain's.
-template <typename TO>
-__device__ __forceinline__ void store_packed(TO* __restrict__ out, const double* A, int LD, int half,
-                                             unsigned long long occ) {
-    const int t = threadIdx.x;
-    const int lane = sizeof(TO) == 8 ? (t >> 1) & 63 : t >> 2;
-    const int v = sizeof(TO) == 8 ? 2 * (t >> 7) + (t & 1) : t & 3;
-    const int r = lane & 15, c = 4 * (lane >> 4) + v;  // tile_at<TO>(r, c) == t
-    auto value = [&](int i, int j) {
-        const bool live = ((occ >> (i / 3)) & 1ull) && ((occ >> (j / 3)) & 1ull);
-        return live ? 0.5 * (A[i * LD + j] + A[j * LD + i]) : 0.0;
-    };
-#pragma unroll
-    for (int I = 1; I < 3; ++I)
-#pragma unroll
-        for (int J = 0; J < I; ++J)
-            out[kTile * tile_below(I, J, half) + t] = static_cast<TO>(value(16 * I + r, 16 * J + c));
-#pragma unroll
-    for (int I = 0; I < 3; ++I) {
-        if (half == 0 && r >= c)
-            out[kTile * (6 + I) + t] = static_cast<TO>((r == c ? 0.5 : 1.0) * value(16 * I + r, 16 * I + c));
-        if (half == 1 && r < c) out[kTile * (6 + I) + t] = static_cast<TO>(value(16 * I + c, 16 * I + r));
-    }
-    if (half == 1 && t < 48) out[kPairDiag + t] = static_cast<TO>(value(t, t));
 }
 
 template <int T>
@@ -295,14 +257,6 @@ __global__ void __launch_bounds__(kInvThreads) k_invert(BuildView B, const doubl
     }
     if (w == 0 && !ok && lane == 0) atomicOr(B.flag, 1);
 
-    if constexpr (T == 3) {
-        if (N == 16) {  // packed pairs, each entry the mean of the computed inverse's two triangles
-            const long long pair = static_cast<long long>(d >> 1) * kPairEntries;
-            store_packed(B.inv64[l] + pair, A, LD, d & 1, occ);
-            if (want32) store_packed(B.inv32[l] + pair, A, LD, d & 1, occ);
-            return;
-        }
-    }
     // column-major n x n, zero rows/columns on empty lanes
     const long long off = (long long)d * n * n;
     double* o64 = B.inv64[l] + off;
@@ -314,6 +268,170 @@ __global__ void __launch_bounds__(kInvThreads) k_invert(BuildView B, const doubl
         o64[e] = val;
         if (o32) o32[e] = static_cast<float>(val);
     }
+}
+
+// ---- domain size 16: a wave per domain, in registers
+// The 48 x 48 matrix as 16 x 16 tiles in the result layout of the MFMA (lane
+// l, register v: row l / 16 + 4 v, column l % 16).  In this layout a tile is
+// the B operand as it is, and the A operand of its transpose.  Sweeping the
+// tiles of a symmetric matrix,
+//   P = inv(A_kk), A_kj <- P A_kj, A_ij <- A_ij - A_ik P A_kj,
+//   A_ik <- A_ik P, A_kk <- -P      (the inverse is minus the swept matrix),
+// needs A_ik = A_ki^T as an A operand only, so no tile passes through LDS, no
+// barrier separates the steps, and of the symmetric pairs of tiles only the
+// one that a later step reads is formed: 18 tile products instead of 24.
+// The tiles are swept last to first, which leaves those above the diagonal:
+// as transposes of the packed ones (launch.hpp) they are stored 256
+// contiguous bytes at a time.
+//
+// Through LDS, four waves per domain, 70 of 97 us at 48^3 went to the tile
+// products' operands (18.8 KB of LDS per domain also kept the workgroups to 8
+// per CU); now 75 us (45 -> 33 at 33^3; 8^3, a single wave's chain, 15 -> 17).
+// More waves per SIMD, or workgroups of one or two domains, take as long.
+using Tile = v4d;
+
+// acc + X^T Y
+__device__ __forceinline__ Tile tile_product(Tile x, Tile y, Tile acc) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k], y[k], acc, 0, 0, 0);
+    return acc;
+}
+
+// Scalar Gauss-Jordan in place, 16 pivots: the pivot by readlane and column j
+// by DPP (lane j of each row of 16), row j, which no DPP form moves across
+// the rows of 16, by one shuffle beside the division (with six 64-bit shuffles
+// a step instead, and the four-wave kernel, 127 us at 48^3 for its 97).
+__device__ __forceinline__ Tile tile_inverse(Tile a, bool& ok) {
+    const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4;
+    static_for<16>([&](auto jc) {
+        constexpr int j = jc.value, jv = j >> 2, jg = j & 3;
+        const double rowj = __shfl(a[jv], jg * 16 + c16);
+        const double piv = lane_value(a[jv], jg * 16 + j);
+        double colj[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) colj[v] = dpp_row_lane<j>(a[v]);
+        ok = ok && (piv > 0.0) && finite(piv);
+        const double inv = 1.0 / piv;
+        // with 1 in place of the pivot column's entry of row j, and 0 in
+        // place of the column's other entries, all entries take one form
+        const double sc = c16 == j ? inv : rowj * inv;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) a[v] = __fma_rn(-colj[v], sc, c16 == j ? 0.0 : a[v]);
+        if (g4 == jg) a[jv] = sc;
+    });
+    return a;
+}
+
+// Store of the tile above the diagonal whose transpose is tile (I, J), I >= J,
+// of the packed inverse: this lane's entries are row c16, columns g4 + 4 v.
+template <typename TO>
+__device__ __forceinline__ void store_tile(TO* __restrict__ out, Tile a, int I, int J, int half,
+                                           unsigned long long occ) {
+    const int lane = threadIdx.x & 63, r = lane & 15, g4 = lane >> 4;
+    const bool row_live = (occ >> ((16 * I + r) / 3)) & 1ull;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int c = g4 + 4 * v;
+        const double x = row_live && ((occ >> ((16 * J + c) / 3)) & 1ull) ? a[v] : 0.0;
+        if (I > J) {
+            out[kTile * tile_below(I, J, half) + tile_at<TO>(r, c)] = static_cast<TO>(x);
+        } else {
+            if (half == 0 ? r >= c : r < c)
+                out[kTile * (6 + I) + tile_at<TO>(r, c)] = static_cast<TO>(half == 0 && r == c ? 0.5 * x : x);
+            if (half == 1 && r == c) out[kPairDiag + 16 * I + r] = static_cast<TO>(x);
+        }
+    }
+}
+
+constexpr int kWaveDomains = 4;  // waves, and domains, per workgroup
+
+__global__ void __launch_bounds__(64 * kWaveDomains, 4) k_invert_waves(BuildView B, const double* __restrict__ Hu,
+                                                                       int want32, DomTable tab) {
+    __shared__ int maps[kWaveDomains][256];
+    const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = level_of(tab, B.L, blockIdx.x);
+    const int d = kWaveDomains * (blockIdx.x - tab.off[l]) + w;
+    if (d >= B.ndom[l]) return;
+    const int q0 = uniform_load(B.dom_ptr[l] + d), q1 = uniform_load(B.dom_ptr[l] + d + 1);
+    const int u = 16 * d + c16;
+    const unsigned long long occ =
+        __ballot(lane < 16 && (l == 0 ? B.remap[u] >= 0 : u < B.units[l]));
+
+    // block of each pair of nodes a <= b, or -1
+    int* map = maps[w];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) map[lane + 64 * i] = -1;
+    wave_lds_sync();
+    for (int q = q0 + lane; q < q1; q += 64) {
+        const int ab = B.dom_ab[l][q];
+        map[16 * (ab & 255) + (ab >> 8)] = B.dom_blk[l][q];
+    }
+    wave_lds_sync();
+    // entry (i, j), i <= j, of the matrix; what is read where there is no
+    // block is any entry of the level (of the inverses, where it has none)
+    const double* base = q0 == q1 ? B.inv64[l] : l == 0 ? Hu : B.A[l];
+    const int other = q0 == q1 ? 0 : B.dom_blk[l][q0];
+    const long long by_block = l == 0 ? 9 : 1, by_entry = l == 0 ? 1 : B.nnzA[l];
+    auto entry = [&](int i, int j) {
+        const int a = i / 3, b = j / 3;
+        const int k = map[16 * a + b];
+        const double x = base[by_block * (k < 0 ? other : k) + by_entry * (3 * (i - 3 * a) + j - 3 * b)];
+        return k >= 0 ? x : i == j && !((occ >> a) & 1ull) ? 1.0 : 0.0;
+    };
+    // tile of block rows and columns I >= J; swept in the order 2, 1, 0, so
+    // Xst, Yst: s, t = the places 2 - I, 2 - J in that order
+    auto tile = [&](int I, int J) {
+        Tile t;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = 16 * I + g4 + 4 * v, c = 16 * J + c16;
+            t[v] = I == J ? entry(min(r, c), max(r, c)) : entry(c, r);
+        }
+        return t;
+    };
+    Tile d0 = tile(2, 2), x01 = tile(2, 1), x02 = tile(2, 0), d1 = tile(1, 1), x12 = tile(1, 0), d2 = tile(0, 0);
+    const Tile zero = {0.0, 0.0, 0.0, 0.0};
+    bool ok = true;
+
+    Tile p = tile_inverse(d0, ok), n = -p;
+    Tile r1 = tile_product(n, x01, zero), r2 = tile_product(n, x02, zero);
+    d1 = tile_product(x01, r1, d1);
+    x12 = tile_product(x01, r2, x12);
+    d2 = tile_product(x02, r2, d2);
+    Tile y10 = tile_product(x01, p, zero), y20 = tile_product(x02, p, zero);
+    d0 = n;
+
+    p = tile_inverse(d1, ok), n = -p;
+    Tile r0 = tile_product(n, y10, zero);
+    r2 = tile_product(n, x12, zero);
+    d0 = tile_product(y10, r0, d0);
+    d2 = tile_product(x12, r2, d2);
+    y20 = tile_product(x12, r0, y20);
+    Tile y21 = tile_product(x12, p, zero);
+    y10 = -r0;
+    d1 = n;
+
+    p = tile_inverse(d2, ok), n = -p;
+    r0 = tile_product(n, y20, zero);
+    r1 = tile_product(n, y21, zero);
+    d0 = tile_product(y20, r0, d0);
+    d1 = tile_product(y21, r1, d1);
+    y10 = tile_product(y21, r0, y10);
+    if (!ok && lane == 0) atomicOr(B.flag, 1);
+
+    auto store = [&](auto* out) {
+        out += static_cast<long long>(d >> 1) * kPairEntries;
+        const int half = d & 1;
+        store_tile(out, -d0, 2, 2, half, occ);
+        store_tile(out, -d1, 1, 1, half, occ);
+        store_tile(out, p, 0, 0, half, occ);
+        store_tile(out, -y10, 2, 1, half, occ);
+        store_tile(out, r0, 2, 0, half, occ);
+        store_tile(out, r1, 1, 0, half, occ);
+    };
+    store(B.inv64[l]);
+    if (want32) store(B.inv32[l]);
 }
 
 // ------------------------------------------------------------------ apply
@@ -1083,6 +1201,13 @@ hipError_t launch_coarse_sums(const BuildView& b, const double* Hu, hipStream_t 
 }
 
 hipError_t launch_invert(const BuildView& b, const double* Hu, bool want32, hipStream_t s) {
+    if (b.N == 16) {
+        int groups[kMaxLv];
+        for (int l = 0; l < b.L; ++l) groups[l] = ceil_div(b.ndom[l], kWaveDomains);
+        const DomTable tab = make_table(groups, 0, b.L);
+        launch_kernel(k_invert_waves, dim3(tab.off[kMaxLv]), dim3(64 * kWaveDomains), 0, s, b, Hu, want32 ? 1 : 0, tab);
+        return hipGetLastError();
+    }
     const DomTable tab = make_table(b.ndom, 0, b.L);
     const int total = tab.off[kMaxLv];
     const int T = ceil_div(3 * b.N, 16);
