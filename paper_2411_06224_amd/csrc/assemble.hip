@@ -198,13 +198,16 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_reduce(int nnzb, int cb, co
 // ranks do not: no two pairs are equal.
 //
 // 9.0 million blocks in 110,592 rows (a 48^3 cube's elements): sort, heads,
-// scan and rows take 690 us, the kernels before the sums here 250; 62 thousand
-// blocks in 729 rows: 121 -> 75 us for the whole call.
+// scan and rows take 690 us, the kernels before the sums here 260; 62 thousand
+// blocks in 729 rows: 121 -> 76 us for the whole call.  Uneven rows (3.8
+// million blocks on the 33 thousand of 279 thousand nodes that touch): 769 ->
+// 640 us for the contact reduction around it.
 
 constexpr int kPool = 448;       // blocks of a workgroup's rows sorted and summed together, rows rounded up to 4
 constexpr int kPoolAim = 336;    // ... aimed at on average
 constexpr int kPoolRows = 63;    // rows of a workgroup, at most
 constexpr int kRowGroup = 2048;  // blocks of a longer row that a workgroup sorts in LDS
+constexpr int kSliceRows = 8;    // a workgroup per so many rows shares the batches of rows beyond the pool
 constexpr int kAsmWaves = kAsmThreads / kWave;
 
 // The arrays of the short-row path in the scratch of the sorting path: each
@@ -215,8 +218,8 @@ struct RowArrays {
     int* start;        // first pair of each row; [n_rows] = their number
     int* slot;         // of each listed block within its row
     uint64_t* pair;    // (column << 32) | list position, in slot order
-    // by workgroup, from start[its first row]: the sorted blocks (as slots, or as list positions where the rows
-    // exceed the pool), the first sorted block of each distinct (row, column), and that column
+    // by workgroup, from start[its first row] (by row, where the rows exceed the pool): the sorted blocks (as slots,
+    // or list positions), the first sorted block of each distinct (row, column) and that column
     int *order, *seg_first, *seg_col;
     int* distinct;     // columns per row; [n_rows] = 0
 };
@@ -239,7 +242,8 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_clear(int n_rows, int* __re
 // 9.0 million blocks; 88 with an atomic per run, 565 with one per block.
 __global__ void __launch_bounds__(kAsmThreads) k_asm_count(int n_in, int n_rows, const int* __restrict__ rows,
                                                            int* __restrict__ cnt, int* __restrict__ slot,
-                                                           int* __restrict__ flag) {
+                                                           int* flag) {
+    if (flag[0] & 2) return;
     const int k = blockIdx.x * kAsmThreads + threadIdx.x, lane = threadIdx.x % kWave;
     const int r = k < n_in ? rows[k] : -1;
     const bool valid = r >= 0 && r < n_rows;
@@ -257,7 +261,10 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_count(int n_in, int n_rows,
         left &= ~match;
     }
     int base = 0;
-    if (valid && lane == first) base = atomicAdd(cnt + r, same);
+    if (valid && lane == first) {
+        base = atomicAdd(cnt + r, same);
+        if (base + same > kRowGroup) atomicOr(flag, 2);  // the sorting path takes the list: nothing below runs
+    }
     base = __shfl(base, first);
     if (k < n_in) slot[k] = base + before;
 }
@@ -266,9 +273,9 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_scatter(int n_in, int n_row
                                                              const int* __restrict__ cols,
                                                              const int* __restrict__ start,
                                                              const int* __restrict__ slot,
-                                                             uint64_t* __restrict__ pair, int* __restrict__ flag) {
+                                                             uint64_t* __restrict__ pair, int* flag) {
     const int k = blockIdx.x * kAsmThreads + threadIdx.x;
-    if (k >= n_in) return;
+    if (k >= n_in || flag[0] & 2) return;
     const int r = rows[k], c = cols[k];
     if (r < 0 || r >= n_rows) return;  // flagged and not counted
     if (c < 0 || c >= n_rows) atomicOr(flag, 1);
@@ -331,109 +338,117 @@ __device__ __forceinline__ int pool_row(const int* at, int nr, int e) {
     return lo;
 }
 
+// A workgroup's rows go through the pool in batches: the rows from w0 that
+// fit it together, or one row.
+__device__ __forceinline__ int batch_end(const PoolRows& P, int nr, int w0) {
+    const int end = P.base[w0] + kPool;
+    return P.base[nr] <= end ? nr : max(w0 + 1, pool_row(P.base, nr, end));
+}
+
 // Sorts the rows.  A pair's place is the number of smaller pairs of its row,
 // counted against the whole row read from LDS four pairs at a time, for two
 // pairs per lane (the LDS reads bound the loop): no exchange steps and no
 // waits between them, and rows of any mix of lengths share the lanes.  The
-// pairs are compared as doubles (rows_path), not as 64-bit integers.  Where
-// the rows exceed the pool they are sorted one after the other by the whole
-// workgroup (bitonic, in LDS).  9.0 million blocks: 131 us (214 with a pair
+// pairs are compared as doubles (rows_path), not as 64-bit integers.  A row
+// beyond the pool is sorted by the whole workgroup (bitonic, in LDS).  9.0 million blocks: 131 us (214 with a pair
 // per lane, 448 with a wave per row).
-__global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int group_rows,
+__global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int group_rows, int slices,
                                                               const int* __restrict__ start,
                                                               const uint64_t* __restrict__ pair,
                                                               int* __restrict__ order, int* __restrict__ seg_first,
                                                               int* __restrict__ seg_col, int* __restrict__ distinct,
-                                                              int* __restrict__ flag) {
+                                                              const int* __restrict__ flag) {
     __shared__ __align__(16) uint64_t sh[kRowGroup];
     __shared__ PoolRows P;
     __shared__ int heads_of[kPoolRows], wave_heads[2][kAsmWaves];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int r0 = blockIdx.x * group_rows, nr = min(group_rows, n_rows - r0);
+    const int groups = gridDim.x / slices, slice = blockIdx.x / groups;
+    const int r0 = (blockIdx.x - slice * groups) * group_rows, nr = min(group_rows, n_rows - r0);
     if (blockIdx.x == 0 && threadIdx.x == 0) distinct[n_rows] = 0;
+    if (uniform_load(flag) & 2) return;
+    const int g0 = uniform_load(start + r0);
+    if (slice > 0 && uniform_load(start + r0 + nr) - g0 + 3 * nr <= kPool) return;  // within the pool
     pool_rows(P, r0, nr, start);
-    const int s0 = uniform_load(start + r0), total = P.st[nr];
-    if (P.base[nr] <= kPool) {
-        double* pool = reinterpret_cast<double*>(sh);
-        int* col = reinterpret_cast<int*>(pool + kPool);
-        int row[2];
-        double a[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int e = threadIdx.x + q * kAsmThreads;
-            if (e < kPool) sh[e] = ~0ull;  // not less than any pair
-            row[q] = pool_row(P.st, nr, min(e, total - 1));
-            if (e < total) a[q] = __longlong_as_double(static_cast<long long>(pair[s0 + e]));
-        }
-        if (threadIdx.x < kPoolRows) heads_of[threadIdx.x] = 0;
+    for (int i = 0, w0 = 0, w1; w0 < nr; ++i, w0 = w1) {
+        w1 = batch_end(P, nr, w0);
+        if (i % slices != slice) continue;
+        const int t0 = P.st[w0], p0 = P.base[w0], s0 = g0 + t0, total = P.st[w1] - t0;
         __syncthreads();
+        if (P.base[w1] - p0 <= kPool) {
+            double* pool = reinterpret_cast<double*>(sh);
+            int* col = reinterpret_cast<int*>(pool + kPool);
+            int row[2];
+            double a[2];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int e = threadIdx.x + q * kAsmThreads;
-            if (e < total) pool[P.base[row[q]] + e - P.st[row[q]]] = a[q];
-        }
-        __syncthreads();
-        const int p = 2 * threadIdx.x;  // two neighbours of the pool, of one row
-        if (p < P.base[nr]) {
-            const int w = pool_row(P.base, nr, p), w0 = P.base[w], w1 = P.base[w + 1];
-            const double2 a = *reinterpret_cast<const double2*>(pool + p);
-            int rank[2] = {0, 0};
-            for (int j = w0; j < w1; j += 4) {
-                const double2 b = *reinterpret_cast<const double2*>(pool + j);
-                const double2 d = *reinterpret_cast<const double2*>(pool + j + 2);
-                rank[0] += (b.x < a.x) + (b.y < a.x) + (d.x < a.x) + (d.y < a.x);
-                rank[1] += (b.x < a.y) + (b.y < a.y) + (d.x < a.y) + (d.y < a.y);
+            for (int q = 0; q < 2; ++q) {
+                const int e = threadIdx.x + q * kAsmThreads;
+                if (e < kPool) sh[e] = ~0ull;  // not less than any pair
+                row[q] = pool_row(P.st, nr, t0 + max(min(e, total - 1), 0));
+                if (e < total) a[q] = __longlong_as_double(static_cast<long long>(pair[s0 + e]));
             }
-            const int s1 = P.st[w], len = P.st[w + 1] - s1;
+            if (threadIdx.x < kPoolRows) heads_of[threadIdx.x] = 0;
+            __syncthreads();
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
-                if (p + q - w0 < len) {
-                    order[s0 + s1 + rank[q]] = s1 + p + q - w0;
-                    col[s1 + rank[q]] = __double2hiint(q ? a.y : a.x);
+            for (int q = 0; q < 2; ++q) {
+                const int e = threadIdx.x + q * kAsmThreads;
+                if (e < total) pool[P.base[row[q]] - p0 + e - (P.st[row[q]] - t0)] = a[q];
+            }
+            __syncthreads();
+            const int p = 2 * threadIdx.x;  // two neighbours of the pool, of one row
+            if (p < P.base[w1] - p0) {
+                const int w = pool_row(P.base, nr, p0 + p), a0 = P.base[w] - p0, a1 = P.base[w + 1] - p0;
+                const double2 a = *reinterpret_cast<const double2*>(pool + p);
+                int rank[2] = {0, 0};
+                for (int j = a0; j < a1; j += 4) {
+                    const double2 b = *reinterpret_cast<const double2*>(pool + j);
+                    const double2 d = *reinterpret_cast<const double2*>(pool + j + 2);
+                    rank[0] += (b.x < a.x) + (b.y < a.x) + (d.x < a.x) + (d.y < a.x);
+                    rank[1] += (b.x < a.y) + (b.y < a.y) + (d.x < a.y) + (d.y < a.y);
                 }
-        }
-        __syncthreads();
-        unsigned long long heads[2];
-        bool head[2];
-        int c[2];
+                const int s1 = P.st[w] - t0, len = P.st[w + 1] - P.st[w];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int e = threadIdx.x + q * kAsmThreads;
-            c[q] = e < total ? col[e] : 0;
-            head[q] = e < total && (e == P.st[row[q]] || col[e - 1] != c[q]);
-            heads[q] = __ballot(head[q]);
-            if (lane == 0) wave_heads[q][wave] = __popcll(heads[q]);
-            if (head[q]) atomicAdd(&heads_of[row[q]], 1);
-        }
-        __syncthreads();
-        int found = 0;
+                for (int q = 0; q < 2; ++q)
+                    if (p + q - a0 < len) {
+                        order[s0 + s1 + rank[q]] = s1 + p + q - a0;
+                        col[s1 + rank[q]] = __double2hiint(q ? a.y : a.x);
+                    }
+            }
+            __syncthreads();
+            unsigned long long heads[2];
+            bool head[2];
+            int c[2];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            int j = found;
-            for (int v = 0; v < kAsmWaves; ++v) {
-                if (v < wave) j += wave_heads[q][v];
-                found += wave_heads[q][v];
+            for (int q = 0; q < 2; ++q) {
+                const int e = threadIdx.x + q * kAsmThreads;
+                c[q] = e < total ? col[e] : 0;
+                head[q] = e < total && (e == (P.st[row[q]] - t0) || col[e - 1] != c[q]);
+                heads[q] = __ballot(head[q]);
+                if (lane == 0) wave_heads[q][wave] = __popcll(heads[q]);
+                if (head[q]) atomicAdd(&heads_of[row[q]], 1);
             }
-            if (head[q]) {
-                j += s0 + __popcll(heads[q] & ((1ull << lane) - 1ull));
-                seg_first[j] = threadIdx.x + q * kAsmThreads;
-                seg_col[j] = c[q];
+            __syncthreads();
+            int found = 0;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                int j = found;
+                for (int v = 0; v < kAsmWaves; ++v) {
+                    if (v < wave) j += wave_heads[q][v];
+                    found += wave_heads[q][v];
+                }
+                if (head[q]) {
+                    j += s0 + __popcll(heads[q] & ((1ull << lane) - 1ull));
+                    seg_first[j] = threadIdx.x + q * kAsmThreads;
+                    seg_col[j] = c[q];
+                }
             }
-        }
-        if (static_cast<int>(threadIdx.x) < nr) distinct[r0 + threadIdx.x] = heads_of[threadIdx.x];
-        return;
-    }
-    int found = 0;
-    for (int w = 0; w < nr; ++w) {
-        const int b0 = P.st[w], n = P.st[w + 1] - b0;
-        if (n > kRowGroup) {  // the sorting path takes the list
-            if (threadIdx.x == 0) atomicOr(flag, 2), distinct[r0 + w] = 0;
+            if (w0 + static_cast<int>(threadIdx.x) < w1)
+                distinct[r0 + w0 + threadIdx.x] = heads_of[w0 + threadIdx.x];
             continue;
         }
-        __syncthreads();
+        const int n = total;  // one row beyond the pool
         int width = 2;
         while (width < n) width *= 2;
-        for (int i = threadIdx.x; i < width; i += kAsmThreads) sh[i] = i < n ? pair[s0 + b0 + i] : ~0ull;
+        for (int i = threadIdx.x; i < width; i += kAsmThreads) sh[i] = i < n ? pair[s0 + i] : ~0ull;
         for (int k = 2; k <= width; k *= 2)
             for (int j = k / 2; j > 0; j /= 2) {
                 __syncthreads();
@@ -444,7 +459,7 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int gr
                 }
             }
         __syncthreads();
-        const int before = found;
+        int found = 0;
         for (int i0 = 0; i0 < n; i0 += kAsmThreads) {
             const int i = i0 + threadIdx.x;
             const uint64_t x = i < n ? sh[i] : 0;
@@ -457,15 +472,15 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int gr
                 if (v < wave) at += wave_heads[0][v];
                 found += wave_heads[0][v];
             }
-            if (i < n) order[s0 + b0 + i] = static_cast<int>(x & 0xffffffffu);
+            if (i < n) order[s0 + i] = static_cast<int>(x & 0xffffffffu);
             if (head) {
                 at += __popcll(heads & ((1ull << lane) - 1ull));
-                seg_first[at] = b0 + i;
+                seg_first[at] = i;
                 seg_col[at] = static_cast<int>(x >> 32);
             }
             __syncthreads();
         }
-        if (threadIdx.x == 0) distinct[r0 + w] = found - before;
+        if (threadIdx.x == 0) distinct[r0 + w0] = found;
     }
 }
 
@@ -480,7 +495,8 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int gr
 // nine threads per column reading straight from memory, now 254 us (2.7
 // TB/s).  Smaller pools of two rows (224, 256, 320 blocks) take 3 to 11 %
 // longer over the whole call, and so do three rows in this one.
-__global__ void __launch_bounds__(kAsmThreads) k_asm_row_sum(int n_rows, int group_rows, long long capacity,
+__global__ void __launch_bounds__(kAsmThreads) k_asm_row_sum(int n_rows, int group_rows, int slices,
+                                                             long long capacity,
                                                              const int* __restrict__ start,
                                                              const uint64_t* __restrict__ pair,
                                                              const int* __restrict__ order,
@@ -497,45 +513,69 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sum(int n_rows, int gro
     const int nnzb = uniform_load(row_ptr + n_rows);
     if (blockIdx.x == 0 && threadIdx.x == 0) flag[1] = nnzb;
     if (uniform_load(static_cast<const int*>(flag)) != 0 || nnzb > capacity) return;
-    const int r0 = blockIdx.x * group_rows, nr = min(group_rows, n_rows - r0);
+    const int groups = gridDim.x / slices, slice = blockIdx.x / groups;
+    const int r0 = (blockIdx.x - slice * groups) * group_rows, nr = min(group_rows, n_rows - r0);
+    const int g0 = uniform_load(start + r0);
+    if (slice > 0 && uniform_load(start + r0 + nr) - g0 + 3 * nr <= kPool) return;  // within the pool
     pool_rows(P, r0, nr, start);
-    const int s0 = uniform_load(start + r0), total = __builtin_amdgcn_readfirstlane(P.st[nr]);
-    const int o0 = uniform_load(row_ptr + r0), n = uniform_load(row_ptr + r0 + nr) - o0;
-    if (P.base[nr] <= kPool) {
-        for (int i = threadIdx.x; i < total; i += kAsmThreads) {
-            pos[i] = static_cast<int>(pair[s0 + i] & 0xffffffffu);
-            ord[i] = 9 * order[s0 + i];
-            first[i] = i < n ? seg_first[s0 + i] : total;
+    for (int i = 0, w0 = 0, w1; w0 < nr; ++i, w0 = w1) {
+        w1 = batch_end(P, nr, w0);
+        if (i % slices != slice) continue;
+        const int s0 = g0 + P.st[w0], total = __builtin_amdgcn_readfirstlane(P.st[w1] - P.st[w0]);
+        const int o0 = row_ptr[r0 + w0], n = row_ptr[r0 + w1] - o0;
+        if (P.base[w1] - P.base[w0] <= kPool) {
+            __syncthreads();
+            for (int i = threadIdx.x; i < total; i += kAsmThreads) {
+                pos[i] = static_cast<int>(pair[s0 + i] & 0xffffffffu);
+                ord[i] = 9 * order[s0 + i];
+                first[i] = i < n ? seg_first[s0 + i] : total;
+            }
+            if (threadIdx.x == 0) first[total] = total;
+            __syncthreads();
+            double v[kBatches][kLoads];
+#pragma unroll
+            for (int b = 0; b < kBatches; ++b)
+                if (b * kLoads * kAsmThreads < 9 * total)
+#pragma unroll
+                    for (int q = 0; q < kLoads; ++q) {
+                        const int t = threadIdx.x, e = min((b * kLoads + q) * kAsmThreads + t, 9 * total - 1);
+                        const int i = e / 9;
+                        v[b][q] = blocks[9LL * pos[i] + (e - 9 * i)];
+                    }
+#pragma unroll
+            for (int b = 0; b < kBatches; ++b)
+                if (b * kLoads * kAsmThreads < 9 * total)
+#pragma unroll
+                    for (int q = 0; q < kLoads; ++q) {
+                        const int e = (b * kLoads + q) * kAsmThreads + threadIdx.x;
+                        if (e < 9 * total) x[e] = v[b][q];
+                    }
+            __syncthreads();
+            const int c = threadIdx.x % 9;
+            for (int j = threadIdx.x / 9; j < n && threadIdx.x < kAsmThreads / 9 * 9; j += kAsmThreads / 9) {
+                const int e0 = first[j], e1 = first[j + 1];
+                double acc = 0.0;
+                for (int e = e0; e < e1; e += kAsmBatch) {
+                    double y[kAsmBatch];
+#pragma unroll
+                    for (int q = 0; q < kAsmBatch; ++q) y[q] = x[ord[min(e + q, e1 - 1)] + c];
+#pragma unroll
+                    for (int q = 0; q < kAsmBatch; ++q)
+                        if (e + q < e1) acc += y[q];
+                }
+                val[9LL * (o0 + j) + c] = acc;
+                if (c == 0) col_idx[o0 + j] = seg_col[s0 + j];
+            }
+            continue;
         }
-        if (threadIdx.x == 0) first[total] = total;
-        __syncthreads();
-        double v[kBatches][kLoads];
-#pragma unroll
-        for (int b = 0; b < kBatches; ++b)
-            if (b * kLoads * kAsmThreads < 9 * total)
-#pragma unroll
-                for (int q = 0; q < kLoads; ++q) {
-                    const int e = min((b * kLoads + q) * kAsmThreads + static_cast<int>(threadIdx.x), 9 * total - 1);
-                    const int i = e / 9;
-                    v[b][q] = blocks[9LL * pos[i] + (e - 9 * i)];
-                }
-#pragma unroll
-        for (int b = 0; b < kBatches; ++b)
-            if (b * kLoads * kAsmThreads < 9 * total)
-#pragma unroll
-                for (int q = 0; q < kLoads; ++q) {
-                    const int e = (b * kLoads + q) * kAsmThreads + threadIdx.x;
-                    if (e < 9 * total) x[e] = v[b][q];
-                }
-        __syncthreads();
-        const int c = threadIdx.x % 9;
-        for (int j = threadIdx.x / 9; j < n && threadIdx.x < kAsmThreads / 9 * 9; j += kAsmThreads / 9) {
-            const int e0 = first[j], e1 = first[j + 1];
+        for (int t = threadIdx.x; t < 9 * n; t += kAsmThreads) {
+            const int j = t / 9, c = t - 9 * j;
+            const int e0 = seg_first[s0 + j], e1 = j + 1 < n ? seg_first[s0 + j + 1] : total;
             double acc = 0.0;
             for (int e = e0; e < e1; e += kAsmBatch) {
                 double y[kAsmBatch];
 #pragma unroll
-                for (int q = 0; q < kAsmBatch; ++q) y[q] = x[ord[min(e + q, e1 - 1)] + c];
+                for (int q = 0; q < kAsmBatch; ++q) y[q] = blocks[9LL * order[s0 + min(e + q, e1 - 1)] + c];
 #pragma unroll
                 for (int q = 0; q < kAsmBatch; ++q)
                     if (e + q < e1) acc += y[q];
@@ -543,23 +583,44 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sum(int n_rows, int gro
             val[9LL * (o0 + j) + c] = acc;
             if (c == 0) col_idx[o0 + j] = seg_col[s0 + j];
         }
-        return;
     }
-    for (int t = threadIdx.x; t < 9 * n; t += kAsmThreads) {
-        const int j = t / 9, c = t - 9 * j;
-        const int e0 = seg_first[s0 + j], e1 = j + 1 < n ? seg_first[s0 + j + 1] : total;
-        double acc = 0.0;
-        for (int e = e0; e < e1; e += kAsmBatch) {
-            double y[kAsmBatch];
-#pragma unroll
-            for (int q = 0; q < kAsmBatch; ++q) y[q] = blocks[9LL * order[s0 + min(e + q, e1 - 1)] + c];
-#pragma unroll
-            for (int q = 0; q < kAsmBatch; ++q)
-                if (e + q < e1) acc += y[q];
+}
+
+// Lists from 2 million blocks are sampled first (6 us): the pairs of equal
+// rows among kSamples blocks of the list are kSamples^2 / (2 n) times the mean
+// length of a block's row.  Beyond 1,000 (bodies in many contacts) the atomics
+// meet on few addresses (20.0 million blocks, most in 8,000 rows: 275 us of
+// counting against 1,770 for the whole by sorting) and some row is beyond
+// kRowGroup.  The launches below then return at once, 135 us in all for that
+// list, so from 16 million blocks the host reads the answer first (20 us).
+constexpr int kSamples = 1024, kSampleSlots = 2 * kSamples, kSampleThreads = kSamples;
+constexpr long long kSampleFrom = 1 << 21, kSampleRead = 1 << 24;
+constexpr int kSampleLength = 1000;
+
+__global__ void __launch_bounds__(kSampleThreads) k_asm_sample(int n_in, const int* __restrict__ rows,
+                                                               int* __restrict__ flag) {
+    __shared__ int key[kSampleSlots], cnt[kSampleSlots];
+    __shared__ int total;
+    for (int i = threadIdx.x; i < kSampleSlots; i += kSampleThreads) key[i] = -1, cnt[i] = 0;
+    if (threadIdx.x == 0) total = 0;
+    __syncthreads();
+    const int step = n_in / kSamples;
+    for (int i = threadIdx.x; i < kSamples; i += kSampleThreads) {
+        const unsigned mix = static_cast<unsigned>(i) * 2654435761u;
+        const int r = rows[static_cast<long long>(i) * step + (mix >> 8) % step];
+        if (r < 0) continue;
+        unsigned at = (static_cast<unsigned>(r) * 2654435761u) >> 21;  // 11 bits
+        while (true) {  // at most half of the slots are ever taken
+            const int old = atomicCAS(&key[at], -1, r);
+            if (old == -1 || old == r) break;
+            at = (at + 1) % kSampleSlots;
         }
-        val[9LL * (o0 + j) + c] = acc;
-        if (c == 0) col_idx[o0 + j] = seg_col[s0 + j];
+        const int before = atomicAdd(&cnt[at], 1);
+        if (before) atomicAdd(&total, before);
     }
+    __syncthreads();
+    if (threadIdx.x == 0 && 2.0 * n_in * total > static_cast<double>(kSampleLength) * kSamples * kSamples)
+        flag[0] = 2;  // the sorting path takes the list: nothing below runs
 }
 
 // At most 512 blocks per row on average, and more blocks than rows, so that
@@ -692,6 +753,17 @@ hipError_t launch_assemble_rows(const AsmLayout& L, int n_rows, long long n_in, 
     };
     launch_kernel(k_asm_clear, dim3(ceil_div(n_rows + 1LL, kAsmThreads)), dim3(kAsmThreads), 0, s, n_rows, A.cnt,
                   L.flag);
+    if (n_in >= kSampleFrom) {
+        launch_kernel(k_asm_sample, dim3(1), dim3(kSampleThreads), 0, s, n, rows, L.flag);
+        if (n_in >= kSampleRead) {
+            int flag = 0;
+            if ((e = hipGetLastError()) != hipSuccess ||
+                (e = hipMemcpyAsync(&flag, L.flag, sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess ||
+                (e = hipStreamSynchronize(s)) != hipSuccess)
+                return e;
+            if (flag & 2) return hipSuccess;
+        }
+    }
     launch_kernel(k_asm_count, dim3(ceil_div(n_in, kAsmThreads)), dim3(kAsmThreads), 0, s, n, n_rows, rows, A.cnt,
                   A.slot, L.flag);
     if ((e = hipGetLastError()) != hipSuccess || (e = scan(A.cnt, A.start)) != hipSuccess) return e;
@@ -699,11 +771,14 @@ hipError_t launch_assemble_rows(const AsmLayout& L, int n_rows, long long n_in, 
                   static_cast<const int*>(A.start), static_cast<const int*>(A.slot), A.pair, L.flag);
     const int group_rows = static_cast<int>(std::clamp<long long>(kPoolAim * static_cast<long long>(n_rows) / n_in, 1,
                                                                   kPoolRows));
-    const dim3 grid(ceil_div(n_rows, group_rows));
-    launch_kernel(k_asm_row_sort, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, static_cast<const int*>(A.start),
-                  static_cast<const uint64_t*>(A.pair), A.order, A.seg_first, A.seg_col, A.distinct, L.flag);
+    const int slices = ceil_div(group_rows, kSliceRows);
+    const dim3 grid(ceil_div(n_rows, group_rows) * slices);
+    launch_kernel(k_asm_row_sort, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, slices,
+                  static_cast<const int*>(A.start),
+                  static_cast<const uint64_t*>(A.pair), A.order, A.seg_first, A.seg_col, A.distinct,
+                  static_cast<const int*>(L.flag));
     if ((e = hipGetLastError()) != hipSuccess || (e = scan(A.distinct, row_ptr)) != hipSuccess) return e;
-    launch_kernel(k_asm_row_sum, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, capacity,
+    launch_kernel(k_asm_row_sum, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, slices, capacity,
                   static_cast<const int*>(A.start),
                   static_cast<const uint64_t*>(A.pair), static_cast<const int*>(A.order),
                   static_cast<const int*>(A.seg_first), static_cast<const int*>(A.seg_col), L.flag,

@@ -1,7 +1,7 @@
 """Assembly of lists of short rows against the oracle's, bit for bit (both sum
 equal blocks in list order): row lengths around one wave, one wave's rows and
-a workgroup's, the ends of the rule that takes the list to this path, the
-scan's limit, and an index out of range."""
+a workgroup's, uneven rows, the ends of the rules that take the list to this
+path, the scan's limit, and an index out of range."""
 
 import numpy as np
 import pytest
@@ -33,6 +33,8 @@ LISTS = [
     (_lengths(4096, 1, [2]), 4),
     (_lengths(4096, 1, []), 4),  # as many blocks as rows: not this path
     (_lengths(70001, 1, [0] * 500 + [90] * 300), 40),
+    (_lengths(3000, 0, [115] * 1000), 30),  # three rows to a batch, eight to a workgroup
+    (_lengths(70000, 4, [1990] * 1000), 200),  # sampled, and sorted as a whole
 ]
 
 
