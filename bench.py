@@ -29,9 +29,9 @@ COPY_BYTES = 256 << 20  # calibration copy: bytes read (and written) per copy
 # Sources that define each hot kernel; HBM traffic measured with rocprofv3
 # counters (profiles/pmc_traffic.json) is used only while they are unchanged.
 KERNEL_SOURCES = {
-    "spmv": ["spmv.hip", "common.hpp", "launch.hpp", "restrict.hpp"],
+    "spmv": ["spmv.hip", "common.hpp", "launch.hpp", "restrict.hpp", "decision.hpp"],
     "apply_level0": ["mas.hip", "common.hpp", "launch.hpp"],
-    "level0_update": ["mas.hip", "common.hpp", "launch.hpp"],
+    "level0_update": ["mas.hip", "common.hpp", "launch.hpp", "decision.hpp"],
 }
 
 
@@ -73,30 +73,37 @@ def algorithmic_bytes(info, mixed):
     val = 36 if mixed else 72
     inv = 4 if mixed else 8
     coarse_y = sum(8 * 3 * info["domains"][l] * N for l in range(1, L))
-    # level-0 inverses: FP64 symmetric-packed for N = 16 (n (n + 1) / 2 entries), else full
-    inv0 = info["domains"][0] * (n * (n + 1) // 2 if (N == 16 and not mixed) else n * n) * inv
+
+    def inverses(nd):  # N = 16: pairs of domains, symmetric-packed, 2352 entries each; else full
+        return inv * ((nd + 1) // 2 * 2352 if N == 16 else nd * n * n)
+
+    inv0 = inverses(info["domains"][0])
+    coarse_inv = sum(inverses(info["domains"][l]) for l in range(1, L))
     r1b = 8 * 3 * info["units"][1] if L > 1 else 0  # one level-1 vector
     if mixed:  # the FP32 copy keeps every block: values, column index, row pointers
+        blocks = nnzb
         stored = nnzb * (val + 4) + 4 * (NS + 1)
     else:  # symmetric FP64 storage: values, column index and local row of each stored block,
         # row pointers and transposed-entry lists
+        blocks = nsb
         stored = nsb * (val + 4 + 1) + 8 * (NS + 1) + 4 * (nnzb - nsb)
     out = {
-        # the stored matrix; z and the previous direction read once (the
-        # direction update is fused in), new direction and q written; the
-        # restriction of q: per-slot plan (16 B) read, q_1 written
-        "spmv": stored + 4 * vb + 16 * NS + r1b,
+        # the stored matrix with the local coarse unit of each column (2 B);
+        # z, the previous direction and the previous q read once, the new
+        # direction and q written; the coarse corrections; the restriction of
+        # q: per-slot plan (16 B) read, q_1 written
+        "spmv": stored + 2 * blocks + 5 * vb + coarse_y + 16 * NS + r1b,
         # level-0 inverses, r read, z written, per-slot coarse ids, coarse corrections
         "apply_level0": inv0 + 2 * vb + 4 * (L - 1) * NS + coarse_y,
-        # coarse inverses, restricted residual read (and, by recurrence, q_1
-        # read and r_1 written), y written
-        "apply_coarse": sum(info["domains"][l] * n * n * inv for l in range(1, L)) + 3 * r1b + coarse_y,
+        # coarse inverses, restricted residual read, y written
+        "apply_coarse": coarse_inv + r1b + coarse_y,
         # x, r read+write, p, q read, per-slot plan ints, r_1 written
-        "update": 6 * vb + 8 * NS + (8 * 3 * info["units"][1] if L > 1 else 0),
+        "update": 6 * vb + 8 * NS + r1b,
+        # x/r update, level 0 and the coarse levels in one launch: x and r read
+        # and written, p and q read, z written; the restricted residual read
+        # and written, the restricted q read, y written
+        "level0_update": inv0 + 7 * vb + coarse_inv + 3 * r1b + coarse_y,
     }
-    # level-0 apply fused with the x/r update: also x read and written, r
-    # written, p and q read
-    out["level0_update"] = out["apply_level0"] + 5 * vb
     return out
 
 

@@ -520,14 +520,14 @@ void spmv_order(Plan& P) {
 // therefore made smaller, 1, 2 or 4 domains instead of 8; beyond that the
 // launch is bound by what it moves, and larger groups store more pairs once
 // and leave fewer partial sums.  Iteration in us with 1 / 2 / 4 / 8 domains per
-// group (FP64 cubes): 308 domains 18.1 / 18.4 / 20.5 / 24.7; 977 domains
-// 21.7 / 20.3 / 22.4 / 26.9; 2,457 domains 42.5 / 29.2 / 29.0 / 32.2; 4,308
-// domains 70 / 49 / 45 / 38.
+// group (cubes): 308 domains 18.6 / 18.7 / 20.9 / 25.0; 977 domains 22.2 /
+// 20.6 / 22.2 / 26.5; 2,457 domains (mixed) 36.8 / 25.6 / 23.5 / 25.9; 7,354
+// domains 94 / 65 / 55 / 46.
 // Where one window of 128 rows holds more than three times the mean (rows of
 // bodies with many contacts), its chain alone is the iteration: such groups
 // are halved down to 2,048 blocks as long as there are at most 2,200 groups
-// (sheet of 256^2 cells with bodies in contact, 4,254 domains: 43 / 55 / 72 us
-// with 2 / 4 / 8).  Other domain sizes keep groups of about 128 rows.
+// (sheet of 256^2 cells with bodies in contact, 4,254 domains: 65 / 49 / 55 /
+// 69 us with 1 / 2 / 4 / 8).  Other domain sizes keep groups of about 128 rows.
 int group_domains(int M, int N, long long nnzb, long long window_blocks) {
     const int most = std::max(1, kWindowSlots / N);
     if (N != 16) return most;
