@@ -95,7 +95,8 @@ typedef struct {
     int32_t max_iter;        /* >= 0 */
     int32_t x0_given;        /* 1: x holds the initial guess, else x0 = 0 */
     int32_t replace_every;   /* period of the iterations that restrict the residual itself rather
-                                than updating its coarse restriction by recurrence, and in mixed
+                                than updating its coarse restriction by recurrence, that form
+                                q = H p itself rather than by q = H z + beta q, and in mixed
                                 mode of the FP64 residual replacement (0 -> 50) */
     int32_t check_every;     /* iterations between host convergence checks (0 -> 8) */
 } pcg_options;
@@ -225,7 +226,7 @@ size_t mas_workspace_size(const mas_handle* h);
 /* Numeric phase on the device (algorithm "Compute MAS preconditioner"):
  * sums the coarse matrices C_l H C_l^T level by level, gathers every domain
  * matrix S_d C_l H C_l^T S_d^T and inverts it over its occupied lanes in FP64
- * (batched, LDS-resident, MFMA tiles); in mixed mode also stores FP32 copies
+ * (batched, MFMA tiles); in mixed mode also stores FP32 copies
  * of the inverses.
  *   H: device matrix with the analysed pattern, dtype MAS_F64.
  *   workspace: device buffer of ws_bytes >= mas_workspace_size(h), 256-byte
@@ -453,9 +454,10 @@ int mas_set_kernel_timing(mas_handle* h, int enable);
 
 /* Totals since the last mas_set_kernel_timing: total_ms[8] and launches[8]
  * for the kernel slots [0] direction update and SpMV q = H p with p^T q
- * (and the restriction of q), [1] x/r update with ||r||^2 and the
- * restriction of r, [2] coarse-level MAS apply, [3] level-0 MAS apply with
- * prolongation and r^T z, [4] the same fused with the x/r update,
+ * (and the restriction of q and the convergence decision), [1] x/r update
+ * with ||r||^2 and the restriction of r, [2] coarse-level MAS apply,
+ * [3] level-0 MAS apply with prolongation and r^T z, [4] x/r update, level 0
+ * and the coarse levels in one launch (the prolongation rides in [0]),
  * [5] FP64 residual replacement, [6] permutation of H, [7] restriction only.
  * Launches queued after the solve had stopped, which return at once, are
  * not counted.  Host arrays. */
