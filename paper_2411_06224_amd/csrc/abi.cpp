@@ -850,7 +850,13 @@ int mas_apply(mas_handle* h, const double* r, double* z, void* stream) {
     const SolverView v = view(h);
     const bool mixed = h->opts.precision == MAS_PRECISION_MIXED;
     HIP_TRY(timed(h, kKRestrict, s, [&] { return launch_restrict(v, r, s); }));
-    HIP_TRY(launch_apply_plain(v, mixed, r, z, s));
+    // level 0 reads r and writes z in one launch: where the two share memory,
+    // z is formed beside it and copied (q holds nothing outside a solve)
+    const size_t bytes = sizeof(double) * 3 * static_cast<size_t>(h->plan.V);
+    const uintptr_t ra = reinterpret_cast<uintptr_t>(r), za = reinterpret_cast<uintptr_t>(z);
+    const bool shared = ra < za + bytes && za < ra + bytes;
+    HIP_TRY(launch_apply_plain(v, mixed, r, shared ? v.q[0] : z, s));
+    if (shared) HIP_TRY(hipMemcpyAsync(z, v.q[0], bytes, hipMemcpyDeviceToDevice, s));
     return MAS_OK;
 }
 
