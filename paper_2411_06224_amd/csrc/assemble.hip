@@ -11,13 +11,14 @@
 // list, and no row length is limited.
 //
 // That path sorts 12 bytes per listed block in five passes.  Where the rows
-// are short (rows_path) the list is grouped by row alone, with one atomic
-// per run of equal rows, and each row is sorted by (column, list position)
-// on its own, in registers and LDS: the same order, the same sums.
+// are short on average (rows_path) the list is grouped by row alone, with one
+// atomic per distinct row of a wave, and each row is sorted by (column, list
+// position) on its own, in registers and LDS: the same order, the same sums.
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "launch.hpp"
 #include "replan.hpp"
@@ -194,20 +195,29 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_reduce(int nnzb, int cb, co
 // row; a scan places the rows; (column, list position) pairs are scattered
 // to their slots; a workgroup per few consecutive rows ranks their pairs; a
 // second scan makes row_ptr of the distinct columns; a workgroup per few
-// rows adds them up.  The slots depend on the order of the atomics, the
+// rows adds them up.  What does not fit a workgroup's pool is dealt to all of
+// them (group_items).  The slots depend on the order of the atomics, the
 // ranks do not: no two pairs are equal.
 //
 // 9.0 million blocks in 110,592 rows (a 48^3 cube's elements): sort, heads,
 // scan and rows take 690 us, the kernels before the sums here 260; 62 thousand
-// blocks in 729 rows: 121 -> 76 us for the whole call.  Uneven rows (3.8
-// million blocks on the 33 thousand of 279 thousand nodes that touch): 769 ->
-// 640 us for the contact reduction around it.
+// blocks in 729 rows: 121 -> 76 us for the whole call.  Bodies in contact
+// beside elements, the whole call by sorting and here: 0.23 million blocks (a
+// sheet of 64^2 cells with 31 bodies) 201 -> 115 us; 3.7 million (256^2, 500
+// bodies, rows of up to 735) 504 -> 340; rows of 1,200 in lists of 0.03, 0.3
+// and 9 million 149 -> 127, 254 -> 145 and 1,091 -> 920 us.  Slower than by
+// sorting are small lists with a single long row (3,000 of 30,000 blocks: 129
+// -> 175 us, of which its pieces take 55) and lists in mixed order whose rows
+// are hit from everywhere (1.5 million blocks, half of them on 250 rows: 339 ->
+// 600 us; see k_asm_sample for longer ones).
 
 constexpr int kPool = 448;       // blocks of a workgroup's rows sorted and summed together, rows rounded up to 4
 constexpr int kPoolAim = 336;    // ... aimed at on average
-constexpr int kPoolRows = 63;    // rows of a workgroup, at most
-constexpr int kRowGroup = 2048;  // blocks of a longer row that a workgroup sorts in LDS
-constexpr int kSliceRows = 8;    // a workgroup per so many rows shares the batches of rows beyond the pool
+constexpr int kPoolRows = 24;    // rows of a workgroup, at most (with 12, 3.0 million blocks, 3 a row, take 829 us for 630)
+constexpr int kPiece = 1024;     // blocks of a longer row that a workgroup places
+constexpr int kChunk = 2048;     // ... among so many at a time
+constexpr int kRowLimit = 8192;  // blocks of a row, at most
+constexpr int kSumTile = kAsmThreads;  // sorted blocks of a longer row that a workgroup sums
 constexpr int kAsmWaves = kAsmThreads / kWave;
 
 // The arrays of the short-row path in the scratch of the sorting path: each
@@ -218,31 +228,34 @@ struct RowArrays {
     int* start;        // first pair of each row; [n_rows] = their number
     int* slot;         // of each listed block within its row
     uint64_t* pair;    // (column << 32) | list position, in slot order
-    // by workgroup, from start[its first row] (by row, where the rows exceed the pool): the sorted blocks (as slots,
-    // or list positions), the first sorted block of each distinct (row, column) and that column
+    // by batch, from start[its first row]: the sorted blocks (as slots of the batch), the first sorted block of each
+    // distinct (row, column) and that column; of a row beyond the pool the sorted list positions and their columns
     int *order, *seg_first, *seg_col;
     int* distinct;     // columns per row; [n_rows] = 0
+    int* item;         // flag[2] pairs of ints: (row, piece) of a row beyond the pool, (row, -rows) of a batch
 };
 
-RowArrays row_arrays(const AsmLayout& L, long long n_in) {
+RowArrays row_arrays(const AsmLayout& L, int n_rows, long long n_in) {
     return {L.head, L.seg, L.pos, L.key, L.pos_sorted, L.seg_start, reinterpret_cast<int*>(L.key_sorted),
-            reinterpret_cast<int*>(L.key_sorted) + n_in};
+            reinterpret_cast<int*>(L.key_sorted) + n_in, L.head + n_rows + 1};
 }
 
 __global__ void __launch_bounds__(kAsmThreads) k_asm_clear(int n_rows, int* __restrict__ cnt,
                                                            int* __restrict__ flag) {
     const long long i = static_cast<long long>(blockIdx.x) * kAsmThreads + threadIdx.x;
     if (i <= n_rows) cnt[i] = 0;
-    if (i < 2) flag[i] = 0;
+    if (i < 3) flag[i] = 0;
 }
 
 // Counting is bound by the atomics (about 25 per ns): one per distinct row of
 // a wave, found a row at a time.  An element lists its blocks row by row,
 // four to a run, and its neighbours in the list share its nodes: 50 us for
-// 9.0 million blocks; 88 with an atomic per run, 565 with one per block.
-__global__ void __launch_bounds__(kAsmThreads) k_asm_count(int n_in, int n_rows, const int* __restrict__ rows,
-                                                           int* __restrict__ cnt, int* __restrict__ slot,
-                                                           int* flag) {
+// 9.0 million blocks; 88 with an atomic per run, 565 with one per block.  In
+// mixed order there is little to find: the search ends after kCountRounds rows.
+constexpr int kCountRounds = 16;  // rows of a wave found so; the rest take an atomic each
+__global__ void __launch_bounds__(kAsmThreads) k_asm_count(int n_in, int n_rows,
+                                                           const int* __restrict__ rows, int* __restrict__ cnt,
+                                                           int* __restrict__ slot, int* flag) {
     if (flag[0] & 2) return;
     const int k = blockIdx.x * kAsmThreads + threadIdx.x, lane = threadIdx.x % kWave;
     const int r = k < n_in ? rows[k] : -1;
@@ -250,7 +263,7 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_count(int n_in, int n_rows,
     if (k < n_in && !valid) atomicOr(flag, 1);
     unsigned long long left = __ballot(valid);
     int first = lane, same = 0, before = 0;
-    while (left) {
+    for (int round = 0; left && round < kCountRounds; ++round) {
         const int l = __ffsll(left) - 1;
         const unsigned long long match = __ballot(r == __builtin_amdgcn_readlane(r, l));
         if (match >> lane & 1) {
@@ -260,26 +273,14 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_count(int n_in, int n_rows,
         }
         left &= ~match;
     }
+    if (left >> lane & 1) same = 1;
     int base = 0;
     if (valid && lane == first) {
         base = atomicAdd(cnt + r, same);
-        if (base + same > kRowGroup) atomicOr(flag, 2);  // the sorting path takes the list: nothing below runs
+        if (base + same > kRowLimit) atomicOr(flag, 2);  // the sorting path takes the list: nothing below runs
     }
     base = __shfl(base, first);
     if (k < n_in) slot[k] = base + before;
-}
-
-__global__ void __launch_bounds__(kAsmThreads) k_asm_scatter(int n_in, int n_rows, const int* __restrict__ rows,
-                                                             const int* __restrict__ cols,
-                                                             const int* __restrict__ start,
-                                                             const int* __restrict__ slot,
-                                                             uint64_t* __restrict__ pair, int* flag) {
-    const int k = blockIdx.x * kAsmThreads + threadIdx.x;
-    if (k >= n_in || flag[0] & 2) return;
-    const int r = rows[k], c = cols[k];
-    if (r < 0 || r >= n_rows) return;  // flagged and not counted
-    if (c < 0 || c >= n_rows) atomicOr(flag, 1);
-    pair[start[r] + slot[k]] = static_cast<uint64_t>(static_cast<uint32_t>(c)) << 32 | static_cast<uint32_t>(k);
 }
 
 // Exclusive scan of n <= kScanOne ints by one workgroup: a launch instead of
@@ -303,8 +304,11 @@ __global__ void __launch_bounds__(kAsmThreads) k_scan_one(const int* __restrict_
     }
 }
 
-// The rows of a workgroup: where each begins among its blocks, and in the
-// pool, with every row rounded up to four.
+// Rows that follow one another: where each begins among their blocks, and in
+// the pool, with every row rounded up to four.  A row beyond the pool counts
+// as more than the pool, so that it stands alone.
+__host__ __device__ __forceinline__ int pool_place(int len) { return len > kPool ? kPool + 4 : (len + 3) & ~3; }
+
 struct PoolRows {
     int st[kPoolRows + 1], base[kPoolRows + 1];
 };
@@ -313,7 +317,8 @@ __device__ __forceinline__ void pool_rows(PoolRows& P, int r0, int nr, const int
     if (threadIdx.x < kWave) {
         const int lane = threadIdx.x;
         const int s = start[r0 + min(lane, nr)], len = start[r0 + min(lane + 1, nr)] - s;
-        int end = (len + 3) & ~3;
+        const int place = pool_place(len);
+        int end = place;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
             const int y = __shfl_up(end, o);
@@ -321,7 +326,7 @@ __device__ __forceinline__ void pool_rows(PoolRows& P, int r0, int nr, const int
         }
         if (lane <= nr) {
             P.st[lane] = s - __shfl(s, 0);
-            P.base[lane] = end - ((len + 3) & ~3);
+            P.base[lane] = end - place;
         }
     }
     __syncthreads();
@@ -338,43 +343,210 @@ __device__ __forceinline__ int pool_row(const int* at, int nr, int e) {
     return lo;
 }
 
-// A workgroup's rows go through the pool in batches: the rows from w0 that
-// fit it together, or one row.
-__device__ __forceinline__ int batch_end(const PoolRows& P, int nr, int w0) {
-    const int end = P.base[w0] + kPool;
-    return P.base[nr] <= end ? nr : max(w0 + 1, pool_row(P.base, nr, end));
+// The rows from the first that fit the pool together, or one row.
+__device__ __forceinline__ int batch_end(const PoolRows& P, int nr) {
+    return P.base[nr] <= kPool ? nr : max(1, pool_row(P.base, nr, kPool));
+}
+
+// A group's rows are cut into batches by that rule.  Its workgroup takes the
+// first; those after it, and the pieces of rows beyond the pool, are items,
+// dealt to all workgroups: rows of any mix of lengths may lie side by side.
+// visit(i, k): pieces k = 0, 1, ... of row r0 + i, or a batch of -k rows from
+// there (k < 0).
+template <typename F>
+__device__ __forceinline__ void group_items(int r0, int nr, const int* __restrict__ start, F&& visit) {
+    constexpr int kLoads = 8;
+    int from = 0, base = 0, s = start[r0];
+    auto batch = [&](int to) {
+        if (from > 0 && base <= kPool) visit(from, from - to);
+        from = to;
+        base = 0;
+    };
+    for (int i0 = 0; i0 < nr; i0 += kLoads) {
+        int e[kLoads];  // (their loads in flight together)
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) e[j] = start[r0 + min(i0 + j + 1, nr)];
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) {
+            const int i = i0 + j, len = e[j] - s;
+            if (i >= nr) break;
+            s = e[j];
+            if (i > from && base + pool_place(len) > kPool) batch(i);
+            base += pool_place(len);
+            if (len > kPool)
+                for (int k = 0; k * kPiece < len; ++k) visit(i, k);
+        }
+    }
+    batch(nr);
+}
+
+__global__ void __launch_bounds__(kAsmThreads) k_asm_scatter(int n_in, int n_rows, const int* __restrict__ rows,
+                                                             const int* __restrict__ cols,
+                                                             const int* __restrict__ start,
+                                                             const int* __restrict__ slot, int group_rows,
+                                                             uint64_t* __restrict__ pair, int* __restrict__ distinct,
+                                                             int* __restrict__ item, int* flag) {
+    if (flag[0] & 2) return;
+    const int k = blockIdx.x * kAsmThreads + threadIdx.x, lane = threadIdx.x % kWave;
+    const int r = k < n_in ? rows[k] : -1;
+    const bool valid = r >= 0 && r < n_rows;  // (else flagged and not counted)
+    int items = 0, r0 = 0, nr = 0;
+    if (valid) {
+        const int c = cols[k], at = slot[k], s0 = start[r];
+        const bool bad = c < 0 || c >= n_rows;
+        if (bad) atomicOr(flag, 1);
+        // (a bad column as 0, so that the pairs always have an order)
+        pair[s0 + at] = static_cast<uint64_t>(static_cast<uint32_t>(bad ? 0 : c)) << 32 | static_cast<uint32_t>(k);
+        if (at == 0) {  // one block of each row; of a group's first row that has any, the group's items
+            r0 = r / group_rows * group_rows;
+            nr = min(group_rows, n_rows - r0);
+            const int g0 = start[r0];
+            if (s0 == g0 && start[r0 + nr] - g0 + 3 * nr > kPool)
+                group_items(r0, nr, start, [&](int, int) { ++items; });
+        }
+    }
+    if (__ballot(items > 0)) {
+        int end = items;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int y = __shfl_up(end, o);
+            if (lane >= o) end += y;
+        }
+        int q = 0;
+        if (lane == kWave - 1) q = atomicAdd(flag + 2, end);
+        q = __shfl(q, kWave - 1) + end - items;
+        if (items)
+            group_items(r0, nr, start, [&](int i, int piece) {
+                item[2 * q] = r0 + i;
+                item[2 * q + 1] = piece;
+                ++q;
+                if (piece == 0) distinct[r0 + i] = 0;
+            });
+    }
+}
+
+// Places the pairs of one piece of a row beyond the pool in the sorted row.
+// The row passes through LDS kPiece pairs at a time, sorted there in tiles of
+// one pair per thread (by rank, as below); a pair's place is the sum of its
+// places in all tiles, found by binary search, and it is the first of its
+// column if its predecessor in no tile has that column.  Bound by the LDS
+// reads of the ranks and searches: 27 us for each kChunk pairs of the row.  With
+// pieces of 2,048 a row of 3,000 takes 68 us instead of 55, rows of 1,200 in
+// their thousands 198 us instead of 302; sorted by one workgroup each (bitonic)
+// and summed by it, they took 100 us apiece, one after another.
+constexpr int kPieceTiles = kPiece / kAsmThreads;
+
+__device__ __forceinline__ void sort_piece(double* sh, int row, int s0, int len, int first,
+                                           const uint64_t* __restrict__ pair, int* __restrict__ order,
+                                           int* __restrict__ sorted_col, int* __restrict__ distinct) {
+    const int t = threadIdx.x;
+    // (past the end: not less than any pair)
+    auto at = [&](int e) { return __longlong_as_double(e < len ? static_cast<long long>(pair[s0 + e]) : ~0ll); };
+    const int own = min(kPiece, len - first);
+    double a[kPieceTiles];
+    int place[kPieceTiles];
+    unsigned heads = 0;
+#pragma unroll
+    for (int q = 0; q < kPieceTiles; ++q) {
+        a[q] = at(first + t + q * kAsmThreads);
+        place[q] = 0;
+        if (t + q * kAsmThreads < own) heads |= 1u << q;
+    }
+    for (int c0 = 0; c0 < len; c0 += kChunk) {
+        const int n = min(kChunk, len - c0);
+        __syncthreads();
+        for (int e = t; e < ((n + kAsmThreads - 1) & -kAsmThreads); e += kAsmThreads) sh[e] = at(c0 + e);
+        __syncthreads();
+#pragma unroll 1
+        for (int p = 0; p < n; p += kAsmThreads) {
+            double* tile = sh + p;
+            const double x = tile[t];
+            const int m = min(kAsmThreads, n - p);
+            int rank = 0;
+#pragma unroll 4
+            for (int j = 0; j < m; j += 4) {
+                const double2 b = *reinterpret_cast<const double2*>(tile + j);
+                const double2 d = *reinterpret_cast<const double2*>(tile + j + 2);
+                rank += (b.x < x) + (b.y < x) + (d.x < x) + (d.y < x);
+            }
+            __syncthreads();
+            if (t < m) tile[rank] = x;
+        }
+        __syncthreads();
+        // the places of K of the thread's pairs, their searches side by side
+        auto search = [&](auto K) {
+#pragma unroll 1
+            for (int p = 0; p < n; p += kAsmThreads) {
+                const double* tile = sh + p;
+                int k[K.value] = {};  // pairs of the tile below each: the pads are not
+#pragma unroll
+                for (int step = kAsmThreads / 2; step > 0; step /= 2)
+#pragma unroll
+                    for (int q = 0; q < K.value; ++q)
+                        if (tile[k[q] + step - 1] < a[q]) k[q] += step;
+#pragma unroll
+                for (int q = 0; q < K.value; ++q) {
+                    if (tile[k[q]] < a[q]) ++k[q];
+                    if (k[q] > 0 && __double2hiint(tile[k[q] - 1]) == __double2hiint(a[q])) heads &= ~(1u << q);
+                    place[q] += k[q];
+                }
+            }
+        };
+        if (own <= 2 * kAsmThreads)
+            search(std::integral_constant<int, 2>{});
+        else
+            search(std::integral_constant<int, kPieceTiles>{});
+    }
+#pragma unroll
+    for (int q = 0; q < kPieceTiles; ++q)
+        if (t + q * kAsmThreads < own) {
+            order[s0 + place[q]] = __double2loint(a[q]);
+            sorted_col[s0 + place[q]] = __double2hiint(a[q]);
+        }
+    int n = __popc(heads);
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o /= 2) n += __shfl_xor(n, o);
+    if (t % kWave == 0 && n) atomicAdd(distinct + row, n);
 }
 
 // Sorts the rows.  A pair's place is the number of smaller pairs of its row,
 // counted against the whole row read from LDS four pairs at a time, for two
 // pairs per lane (the LDS reads bound the loop): no exchange steps and no
 // waits between them, and rows of any mix of lengths share the lanes.  The
-// pairs are compared as doubles (rows_path), not as 64-bit integers.  A row
-// beyond the pool is sorted by the whole workgroup (bitonic, in LDS).  9.0 million blocks: 131 us (214 with a pair
-// per lane, 448 with a wave per row).
-__global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int group_rows, int slices,
+// pairs are compared as doubles (rows_path), not as 64-bit integers.  The
+// items follow.  9.0 million blocks: 140 us (214 with a pair per lane, 448 with
+// a wave per row).
+__global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int group_rows,
                                                               const int* __restrict__ start,
                                                               const uint64_t* __restrict__ pair,
+                                                              const int* __restrict__ item,
                                                               int* __restrict__ order, int* __restrict__ seg_first,
                                                               int* __restrict__ seg_col, int* __restrict__ distinct,
                                                               const int* __restrict__ flag) {
-    __shared__ __align__(16) uint64_t sh[kRowGroup];
+    __shared__ __align__(16) uint64_t sh[kChunk];
     __shared__ PoolRows P;
     __shared__ int heads_of[kPoolRows], wave_heads[2][kAsmWaves];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int groups = gridDim.x / slices, slice = blockIdx.x / groups;
-    const int r0 = (blockIdx.x - slice * groups) * group_rows, nr = min(group_rows, n_rows - r0);
     if (blockIdx.x == 0 && threadIdx.x == 0) distinct[n_rows] = 0;
     if (uniform_load(flag) & 2) return;
-    const int g0 = uniform_load(start + r0);
-    if (slice > 0 && uniform_load(start + r0 + nr) - g0 + 3 * nr <= kPool) return;  // within the pool
-    pool_rows(P, r0, nr, start);
-    for (int i = 0, w0 = 0, w1; w0 < nr; ++i, w0 = w1) {
-        w1 = batch_end(P, nr, w0);
-        if (i % slices != slice) continue;
-        const int t0 = P.st[w0], p0 = P.base[w0], s0 = g0 + t0, total = P.st[w1] - t0;
-        __syncthreads();
-        if (P.base[w1] - p0 <= kPool) {
+    const int items = uniform_load(flag + 2), groups = gridDim.x;
+    // the group's first batch, then items
+    for (int i = static_cast<int>(blockIdx.x) - groups; i < items; i += groups) {
+        int r0 = blockIdx.x * group_rows, nr = min(group_rows, n_rows - r0);
+        if (i >= 0) {
+            r0 = uniform_load(item + 2 * i);
+            nr = -uniform_load(item + 2 * i + 1);
+        }
+        const int s0 = uniform_load(start + r0);
+        if (i >= 0) __syncthreads();
+        if (nr <= 0) {
+            sort_piece(reinterpret_cast<double*>(sh), r0, s0, uniform_load(start + r0 + 1) - s0, -nr * kPiece, pair,
+                       order, seg_col, distinct);
+            continue;
+        }
+        pool_rows(P, r0, nr, start);
+        const int rows = batch_end(P, nr), total = P.st[rows], places = P.base[rows];
+        if (places <= kPool) {
             double* pool = reinterpret_cast<double*>(sh);
             int* col = reinterpret_cast<int*>(pool + kPool);
             int row[2];
@@ -383,7 +555,7 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int gr
             for (int q = 0; q < 2; ++q) {
                 const int e = threadIdx.x + q * kAsmThreads;
                 if (e < kPool) sh[e] = ~0ull;  // not less than any pair
-                row[q] = pool_row(P.st, nr, t0 + max(min(e, total - 1), 0));
+                row[q] = pool_row(P.st, rows, max(min(e, total - 1), 0));
                 if (e < total) a[q] = __longlong_as_double(static_cast<long long>(pair[s0 + e]));
             }
             if (threadIdx.x < kPoolRows) heads_of[threadIdx.x] = 0;
@@ -391,12 +563,12 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int gr
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int e = threadIdx.x + q * kAsmThreads;
-                if (e < total) pool[P.base[row[q]] - p0 + e - (P.st[row[q]] - t0)] = a[q];
+                if (e < total) pool[P.base[row[q]] + e - P.st[row[q]]] = a[q];
             }
             __syncthreads();
             const int p = 2 * threadIdx.x;  // two neighbours of the pool, of one row
-            if (p < P.base[w1] - p0) {
-                const int w = pool_row(P.base, nr, p0 + p), a0 = P.base[w] - p0, a1 = P.base[w + 1] - p0;
+            if (p < places) {
+                const int w = pool_row(P.base, rows, p), a0 = P.base[w], a1 = P.base[w + 1];
                 const double2 a = *reinterpret_cast<const double2*>(pool + p);
                 int rank[2] = {0, 0};
                 for (int j = a0; j < a1; j += 4) {
@@ -405,7 +577,7 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int gr
                     rank[0] += (b.x < a.x) + (b.y < a.x) + (d.x < a.x) + (d.y < a.x);
                     rank[1] += (b.x < a.y) + (b.y < a.y) + (d.x < a.y) + (d.y < a.y);
                 }
-                const int s1 = P.st[w] - t0, len = P.st[w + 1] - P.st[w];
+                const int s1 = P.st[w], len = P.st[w + 1] - P.st[w];
 #pragma unroll
                 for (int q = 0; q < 2; ++q)
                     if (p + q - a0 < len) {
@@ -421,7 +593,7 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int gr
             for (int q = 0; q < 2; ++q) {
                 const int e = threadIdx.x + q * kAsmThreads;
                 c[q] = e < total ? col[e] : 0;
-                head[q] = e < total && (e == (P.st[row[q]] - t0) || col[e - 1] != c[q]);
+                head[q] = e < total && (e == P.st[row[q]] || col[e - 1] != c[q]);
                 heads[q] = __ballot(head[q]);
                 if (lane == 0) wave_heads[q][wave] = __popcll(heads[q]);
                 if (head[q]) atomicAdd(&heads_of[row[q]], 1);
@@ -441,64 +613,111 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sort(int n_rows, int gr
                     seg_col[j] = c[q];
                 }
             }
-            if (w0 + static_cast<int>(threadIdx.x) < w1)
-                distinct[r0 + w0 + threadIdx.x] = heads_of[w0 + threadIdx.x];
-            continue;
+            if (static_cast<int>(threadIdx.x) < rows)
+                distinct[r0 + threadIdx.x] = heads_of[threadIdx.x];
         }
-        const int n = total;  // one row beyond the pool
-        int width = 2;
-        while (width < n) width *= 2;
-        for (int i = threadIdx.x; i < width; i += kAsmThreads) sh[i] = i < n ? pair[s0 + i] : ~0ull;
-        for (int k = 2; k <= width; k *= 2)
-            for (int j = k / 2; j > 0; j /= 2) {
-                __syncthreads();
-                for (int t = threadIdx.x; t < width / 2; t += kAsmThreads) {
-                    const int i = 2 * (t & ~(j - 1)) + (t & (j - 1));
-                    const uint64_t x = sh[i], y = sh[i + j];
-                    if ((x > y) == ((i & k) == 0)) sh[i] = y, sh[i + j] = x;
-                }
-            }
-        __syncthreads();
-        int found = 0;
-        for (int i0 = 0; i0 < n; i0 += kAsmThreads) {
-            const int i = i0 + threadIdx.x;
-            const uint64_t x = i < n ? sh[i] : 0;
-            const bool head = i < n && (i == 0 || sh[i - 1] >> 32 != x >> 32);
-            const unsigned long long heads = __ballot(head);
-            if (lane == 0) wave_heads[0][wave] = __popcll(heads);
-            __syncthreads();
-            int at = s0 + found;
-            for (int v = 0; v < kAsmWaves; ++v) {
-                if (v < wave) at += wave_heads[0][v];
-                found += wave_heads[0][v];
-            }
-            if (i < n) order[s0 + i] = static_cast<int>(x & 0xffffffffu);
-            if (head) {
-                at += __popcll(heads & ((1ull << lane) - 1ull));
-                seg_first[at] = i;
-                seg_col[at] = static_cast<int>(x >> 32);
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) distinct[r0 + w0] = found;
     }
 }
+
+// Sums the columns that begin among kSumTile sorted blocks of a row beyond
+// the pool: their values through LDS, kPool blocks at a time (the last column
+// may go on past the tile).  The columns before them are counted from the
+// sorted column indices.
+__device__ __forceinline__ void sum_tile(double* x, int* pos, int* first, int* wave_heads, int s0, int len, int from,
+                                         int o0, const int* __restrict__ order, const int* __restrict__ sorted_col,
+                                         const double* __restrict__ blocks, int* __restrict__ col_idx,
+                                         double* __restrict__ val) {
+    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    const int* col = sorted_col + s0;
+    const int to = min(from + kSumTile, len);
+    int before = 0;  // columns that begin below the thread's block of the tile, of its wave's
+    for (int e = t; e < from; e += kAsmThreads) before += e == 0 || col[e] != col[e - 1];
+    const int c_last = col[to - 1];
+    int end = to;  // of the last column, the same in every wave
+    while (end < len) {
+        const unsigned long long same = __ballot(end + lane < len && col[end + lane] == c_last);
+        end += ~same ? __ffsll(~same) - 1 : kWave;
+        if (~same) break;
+    }
+    const int e = from + t;
+    const bool head = e < to && (e == 0 || col[e] != col[e - 1]);
+    const unsigned long long heads = __ballot(head);
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o /= 2) before += __shfl_xor(before, o);
+    __syncthreads();
+    if (lane == 0) {
+        wave_heads[wave] = before;
+        wave_heads[kAsmWaves + wave] = __popcll(heads);
+    }
+    __syncthreads();
+    int o = o0, n = 0, j0 = 0;
+    for (int w = 0; w < kAsmWaves; ++w) {
+        o += wave_heads[w];
+        if (w == wave) j0 = n;
+        n += wave_heads[kAsmWaves + w];
+    }
+    if (n == 0) return;  // within a column
+    if (head) {
+        const int j = j0 + __popcll(heads & ((1ull << lane) - 1ull));
+        first[j] = e;
+        col_idx[o + j] = col[e];
+    }
+    if (t == 0) first[n] = end;
+    __syncthreads();
+    const int c = t % 9;
+    double last = 0.0;  // of the last column, threads 0 to 8
+    for (int b0 = first[0], b1; b0 < end; b0 = b1) {
+        b1 = min(b0 + kPool, end);
+        for (int i = t; i < b1 - b0; i += kAsmThreads) pos[i] = order[s0 + b0 + i];
+        __syncthreads();
+        const int values = 9 * (b1 - b0);
+        constexpr int kLoads = 9;  // in flight together
+#pragma unroll 1
+        for (int i0 = 0; i0 < values; i0 += kLoads * kAsmThreads) {
+            double v[kLoads];
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) {
+                const int i = min(i0 + t + q * kAsmThreads, values - 1);
+                v[q] = blocks[9LL * pos[i / 9] + i % 9];
+            }
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) {
+                const int i = i0 + t + q * kAsmThreads;
+                if (i < values) x[i] = v[q];
+            }
+        }
+        __syncthreads();
+        auto add = [&](double s, int e0, int e1) {
+#pragma unroll 4
+            for (int i = e0; i < e1; ++i) s += x[9 * (i - b0) + c];
+            return s;
+        };
+        if (b0 == first[0] && t < kAsmThreads / 9 * 9)  // the pool holds the others whole
+            for (int j = t / 9; j < n - 1; j += kAsmThreads / 9)
+                val[9LL * (o + j) + c] = add(0.0, first[j], first[j + 1]);
+        if (t < 9) last = add(last, max(b0, first[n - 1]), b1);
+        __syncthreads();
+    }
+    if (t < 9) val[9LL * (o + n - 1) + c] = last;
+}
+static_assert(kSumTile <= kAsmThreads && kSumTile <= kPool, "a thread per block, and all but the last column at once");
 
 // Sums the rows, in list order within a distinct column.  The values of a
 // workgroup's rows are loaded flat, in slot order -- an element's run of
 // blocks is one piece of memory -- all in flight at once, turned in LDS and
-// added from there, nine lanes to a column; those of rows that exceed the
-// pool are gathered, kAsmBatch at a time.  Does nothing where an index was
+// added from there, nine lanes to a column; the items follow, pieces tile by
+// tile.  Does nothing where an index was
 // out of range, a row too long, or the result larger than capacity.
 //
 // Bound by the reading of the values, 9.0 million x 72 bytes: 270 us with
-// nine threads per column reading straight from memory, now 254 us (2.7
+// nine threads per column reading straight from memory, now 254 to 265 us (2.5
 // TB/s).  Smaller pools of two rows (224, 256, 320 blocks) take 3 to 11 %
 // longer over the whole call, and so do three rows in this one.
-__global__ void __launch_bounds__(kAsmThreads) k_asm_row_sum(int n_rows, int group_rows, int slices,
+__global__ void __launch_bounds__(kAsmThreads, 4) k_asm_row_sum(int n_rows, int group_rows,
                                                              long long capacity,
                                                              const int* __restrict__ start,
                                                              const uint64_t* __restrict__ pair,
+                                                             const int* __restrict__ item,
                                                              const int* __restrict__ order,
                                                              const int* __restrict__ seg_first,
                                                              const int* __restrict__ seg_col,
@@ -513,18 +732,26 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sum(int n_rows, int gro
     const int nnzb = uniform_load(row_ptr + n_rows);
     if (blockIdx.x == 0 && threadIdx.x == 0) flag[1] = nnzb;
     if (uniform_load(static_cast<const int*>(flag)) != 0 || nnzb > capacity) return;
-    const int groups = gridDim.x / slices, slice = blockIdx.x / groups;
-    const int r0 = (blockIdx.x - slice * groups) * group_rows, nr = min(group_rows, n_rows - r0);
-    const int g0 = uniform_load(start + r0);
-    if (slice > 0 && uniform_load(start + r0 + nr) - g0 + 3 * nr <= kPool) return;  // within the pool
-    pool_rows(P, r0, nr, start);
-    for (int i = 0, w0 = 0, w1; w0 < nr; ++i, w0 = w1) {
-        w1 = batch_end(P, nr, w0);
-        if (i % slices != slice) continue;
-        const int s0 = g0 + P.st[w0], total = __builtin_amdgcn_readfirstlane(P.st[w1] - P.st[w0]);
-        const int o0 = row_ptr[r0 + w0], n = row_ptr[r0 + w1] - o0;
-        if (P.base[w1] - P.base[w0] <= kPool) {
-            __syncthreads();
+    const int items = uniform_load(static_cast<const int*>(flag) + 2), groups = gridDim.x;
+    constexpr int kTiles = kPiece / kSumTile;  // of a piece; a batch is the first
+    for (int i = static_cast<int>(blockIdx.x) - groups; i < kTiles * items; i += groups) {
+        int r0 = blockIdx.x * group_rows, nr = min(group_rows, n_rows - r0);
+        if (i >= 0) {
+            r0 = uniform_load(item + 2 * (i / kTiles));
+            nr = -uniform_load(item + 2 * (i / kTiles) + 1);
+            if (nr > 0 && i % kTiles) continue;
+        }
+        const int s0 = uniform_load(start + r0), o0 = uniform_load(row_ptr + r0);
+        if (nr <= 0) {
+            const int len = uniform_load(start + r0 + 1) - s0, from = -nr * kPiece + i % kTiles * kSumTile;
+            if (from < len) sum_tile(x, pos, first, ord, s0, len, from, o0, order, seg_col, blocks, col_idx, val);
+            continue;
+        }
+        if (i >= 0) __syncthreads();
+        pool_rows(P, r0, nr, start);
+        const int rows = batch_end(P, nr), total = __builtin_amdgcn_readfirstlane(P.st[rows]);
+        const int n = row_ptr[r0 + rows] - o0;
+        if (P.base[rows] <= kPool) {
             for (int i = threadIdx.x; i < total; i += kAsmThreads) {
                 pos[i] = static_cast<int>(pair[s0 + i] & 0xffffffffu);
                 ord[i] = 9 * order[s0 + i];
@@ -566,48 +793,40 @@ __global__ void __launch_bounds__(kAsmThreads) k_asm_row_sum(int n_rows, int gro
                 val[9LL * (o0 + j) + c] = acc;
                 if (c == 0) col_idx[o0 + j] = seg_col[s0 + j];
             }
-            continue;
-        }
-        for (int t = threadIdx.x; t < 9 * n; t += kAsmThreads) {
-            const int j = t / 9, c = t - 9 * j;
-            const int e0 = seg_first[s0 + j], e1 = j + 1 < n ? seg_first[s0 + j + 1] : total;
-            double acc = 0.0;
-            for (int e = e0; e < e1; e += kAsmBatch) {
-                double y[kAsmBatch];
-#pragma unroll
-                for (int q = 0; q < kAsmBatch; ++q) y[q] = blocks[9LL * order[s0 + min(e + q, e1 - 1)] + c];
-#pragma unroll
-                for (int q = 0; q < kAsmBatch; ++q)
-                    if (e + q < e1) acc += y[q];
-            }
-            val[9LL * (o0 + j) + c] = acc;
-            if (c == 0) col_idx[o0 + j] = seg_col[s0 + j];
         }
     }
 }
 
-// Lists from 2 million blocks are sampled first (6 us): the pairs of equal
+// Lists from 2 million blocks are sampled first (4 to 7 us): the pairs of equal
 // rows among kSamples blocks of the list are kSamples^2 / (2 n) times the mean
-// length of a block's row.  Beyond 1,000 (bodies in many contacts) the atomics
-// meet on few addresses (20.0 million blocks, most in 8,000 rows: 275 us of
-// counting against 1,770 for the whole by sorting) and some row is beyond
-// kRowGroup.  The launches below then return at once, 135 us in all for that
-// list, so from 16 million blocks the host reads the answer first (20 us).
+// length of a block's row.  Beyond kSampleLength the rows' pieces and the
+// atomics, which meet on few addresses, take longer than the sort (9 million
+// blocks, 5 in 8 on rows of 3,000: 1,148 us by sorting, 1,124 here; of 7,000:
+// 1,330 by sorting), and rows beyond kRowLimit are likely.  In mixed order
+// (neighbours in the list differ) every block takes an atomic and its values
+// are read alone: from kMixedLength on sorting is faster (9 million blocks,
+// rows of 128: 1,366 and 1,428 us; of 200: 1,275 and 1,490; of 400: 1,273 and
+// 1,570).  The launches below then return at once, 90 us in all for such a list,
+// 135 for 20 million blocks, so from 16 million the host reads the answer
+// first (20 us).
 constexpr int kSamples = 1024, kSampleSlots = 2 * kSamples, kSampleThreads = kSamples;
 constexpr long long kSampleFrom = 1 << 21, kSampleRead = 1 << 24;
-constexpr int kSampleLength = 1000;
+constexpr int kSampleLength = 3000, kMixedLength = 180;
 
 __global__ void __launch_bounds__(kSampleThreads) k_asm_sample(int n_in, const int* __restrict__ rows,
                                                                int* __restrict__ flag) {
     __shared__ int key[kSampleSlots], cnt[kSampleSlots];
-    __shared__ int total;
+    __shared__ int total, ends;
     for (int i = threadIdx.x; i < kSampleSlots; i += kSampleThreads) key[i] = -1, cnt[i] = 0;
-    if (threadIdx.x == 0) total = 0;
+    if (threadIdx.x == 0) total = ends = 0;
     __syncthreads();
     const int step = n_in / kSamples;
     for (int i = threadIdx.x; i < kSamples; i += kSampleThreads) {
         const unsigned mix = static_cast<unsigned>(i) * 2654435761u;
-        const int r = rows[static_cast<long long>(i) * step + (mix >> 8) % step];
+        const int* p = rows + static_cast<long long>(i) * step + (mix >> 8) % (step - 1);
+        const int r = p[0];
+        const unsigned long long differ = __ballot(r != p[1]);
+        if (threadIdx.x % kWave == 0) atomicAdd(&ends, __popcll(differ));
         if (r < 0) continue;
         unsigned at = (static_cast<unsigned>(r) * 2654435761u) >> 21;  // 11 bits
         while (true) {  // at most half of the slots are ever taken
@@ -619,18 +838,29 @@ __global__ void __launch_bounds__(kSampleThreads) k_asm_sample(int n_in, const i
         if (before) atomicAdd(&total, before);
     }
     __syncthreads();
-    if (threadIdx.x == 0 && 2.0 * n_in * total > static_cast<double>(kSampleLength) * kSamples * kSamples)
+    // (8 of 8 neighbours differ in mixed order; where elements list runs of four, 2 of 8)
+    const int longest = 8 * ends > 7 * kSamples ? kMixedLength : kSampleLength;
+    if (threadIdx.x == 0 && 2.0 * n_in * total > static_cast<double>(longest) * kSamples * kSamples)
         flag[0] = 2;  // the sorting path takes the list: nothing below runs
 }
 
-// At most 512 blocks per row on average, and more blocks than rows, so that
-// the arrays by row fit the scratch (of a size by the list): below, most
-// waves would find an empty row; above, the rows are long for one wave and
-// the atomics meet on few addresses.
+// Few blocks per row leave the workgroups little to sort and sum, and the
+// longer the list the less its fixed costs count for the sort: by sorting and
+// here, in mixed order / in runs of two, 1.5 blocks a row in 0.3 million 234 and
+// 152 / 213 and 133 us, in 1.5 million 372 and 420 / 374 and 340; 2 a row in 1.5
+// million 367 and 374 / 363 and 285, in 3 million 618 and 739 / 579 and 544; 3 a
+// row in 3 million 574 and 630 / 526 and 423, in 9 million 1,464 and 1,751 /
+// 1,305 and 1,136; 4 in 9 million 1,467 and 1,612 / 1,282 and 952.  Rows of more
+// than the pool on average are mostly pieces (500 a row, 0.3 million blocks in
+// runs of four: 209 and 157 us, in 1.5 million 268 and 323; 400 a row 266 and
+// 211).  The items take the tail of the counts: there is at most one, two ints,
+// per 180 blocks, and the list exceeds the rows by a sixteenth.
 // The pairs are compared as the doubles of the same bits, which order alike
 // while a column's stay below those of infinity.
 bool rows_path(int n_rows, long long n_in) {
-    return n_in > n_rows && n_in <= 512LL * n_rows && n_rows < 0x7ff00000;
+    const int least = n_in < (1 << 20) ? 1 : n_in < (1 << 21) ? 2 : n_in < (1 << 22) ? 3 : 4;
+    return n_in - n_rows > n_rows / 16 && n_in >= static_cast<long long>(least) * n_rows && n_in <= 400LL * n_rows &&
+           n_rows < 0x7ff00000;
 }
 
 size_t tmp_bytes(long long n_in, int key_bits) {
@@ -669,7 +899,7 @@ AsmLayout assemble_layout(char* ws, int n_rows, long long n_in, size_t* total) {
     L.head = reinterpret_cast<int*>(take(sizeof(int) * m));
     L.seg = reinterpret_cast<int*>(take(sizeof(int) * m));
     L.seg_start = reinterpret_cast<int*>(take(sizeof(int) * (m + 1)));
-    L.flag = reinterpret_cast<int*>(take(sizeof(int) * 2));
+    L.flag = reinterpret_cast<int*>(take(sizeof(int) * 3));
     L.cb = index_bits(n_rows);
     L.tmp_bytes = tmp_bytes(n_in, 2 * L.cb);
     L.tmp = take(L.tmp_bytes);
@@ -741,7 +971,7 @@ hipError_t launch_assemble_rows(const AsmLayout& L, int n_rows, long long n_in, 
     *taken = false;
     if (!rows_path(n_rows, n_in)) return hipSuccess;
     const int n = static_cast<int>(n_in);
-    const RowArrays A = row_arrays(L, n_in);
+    const RowArrays A = row_arrays(L, n_rows, n_in);
     hipError_t e;
     auto scan = [&](const int* in, int* out) -> hipError_t {
         if (n_rows < kScanOne) {
@@ -764,24 +994,23 @@ hipError_t launch_assemble_rows(const AsmLayout& L, int n_rows, long long n_in, 
             if (flag & 2) return hipSuccess;
         }
     }
-    launch_kernel(k_asm_count, dim3(ceil_div(n_in, kAsmThreads)), dim3(kAsmThreads), 0, s, n, n_rows, rows, A.cnt,
-                  A.slot, L.flag);
+    launch_kernel(k_asm_count, dim3(ceil_div(n_in, kAsmThreads)), dim3(kAsmThreads), 0, s, n, n_rows, rows, A.cnt, A.slot, L.flag);
     if ((e = hipGetLastError()) != hipSuccess || (e = scan(A.cnt, A.start)) != hipSuccess) return e;
-    launch_kernel(k_asm_scatter, dim3(ceil_div(n_in, kAsmThreads)), dim3(kAsmThreads), 0, s, n, n_rows, rows, cols,
-                  static_cast<const int*>(A.start), static_cast<const int*>(A.slot), A.pair, L.flag);
     const int group_rows = static_cast<int>(std::clamp<long long>(kPoolAim * static_cast<long long>(n_rows) / n_in, 1,
                                                                   kPoolRows));
-    const int slices = ceil_div(group_rows, kSliceRows);
-    const dim3 grid(ceil_div(n_rows, group_rows) * slices);
-    launch_kernel(k_asm_row_sort, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, slices,
+    const dim3 grid(ceil_div(n_rows, group_rows));
+    launch_kernel(k_asm_scatter, dim3(ceil_div(n_in, kAsmThreads)), dim3(kAsmThreads), 0, s, n, n_rows, rows, cols,
+                  static_cast<const int*>(A.start), static_cast<const int*>(A.slot), group_rows, A.pair, A.distinct, A.item,
+                  L.flag);
+    launch_kernel(k_asm_row_sort, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows,
                   static_cast<const int*>(A.start),
-                  static_cast<const uint64_t*>(A.pair), A.order, A.seg_first, A.seg_col, A.distinct,
-                  static_cast<const int*>(L.flag));
+                  static_cast<const uint64_t*>(A.pair), static_cast<const int*>(A.item), A.order, A.seg_first,
+                  A.seg_col, A.distinct, static_cast<const int*>(L.flag));
     if ((e = hipGetLastError()) != hipSuccess || (e = scan(A.distinct, row_ptr)) != hipSuccess) return e;
-    launch_kernel(k_asm_row_sum, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, slices, capacity,
+    launch_kernel(k_asm_row_sum, grid, dim3(kAsmThreads), 0, s, n_rows, group_rows, capacity,
                   static_cast<const int*>(A.start),
-                  static_cast<const uint64_t*>(A.pair), static_cast<const int*>(A.order),
-                  static_cast<const int*>(A.seg_first), static_cast<const int*>(A.seg_col), L.flag,
+                  static_cast<const uint64_t*>(A.pair), static_cast<const int*>(A.item),
+                  static_cast<const int*>(A.order), static_cast<const int*>(A.seg_first), static_cast<const int*>(A.seg_col), L.flag,
                   static_cast<const int*>(row_ptr), blocks, col_idx, val);
     *taken = true;
     return hipGetLastError();
