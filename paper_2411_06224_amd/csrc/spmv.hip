@@ -328,16 +328,23 @@ __device__ __forceinline__ void stream_sym(const SolverView& v, const T* __restr
 // block per lane and parks the products in LDS, where one lane per (row,
 // component) adds them in column order.  Waves share nothing, so no barrier
 // holds them in step.  A workgroup whose rows hold more than kLongRows blocks
-// (long contact or body rows) streams them with all its waves instead.
-// 48^3: FP64 22.0 -> 18.4 us (6.7 TB/s), FP32 14.5 -> 13.3; 8^3 4.8 -> 2.9 in
-// a graph.  Four rows a wave and one batch between two sums for FP64, eight
-// and two for FP32 (FP64 with eight and two 19.1, FP32 with four and one 14.1).
+// (long contact or body rows), or one of whose waves would have more than half
+// of them and a chain of many batches, streams them with all its waves
+// instead (20,000 rows of 13 blocks with a few of 300 / 700 / 1,500, FP64: 11.4
+// / 19.6 / 36.1 -> 9.8 / 16.1 / 28.8 us, FP32 10.6 / 18.9 / 35.5 -> 10.9 / 16.1 /
+// 28.5; the look at the waves costs 48^3 3 %, so it starts where one can have
+// such a chain at all).
+// 48^3, back to back on cached data: FP64 22.7 -> 19.1 us (6.4 TB/s), FP32 15.4
+// -> 14.0.  Four rows a wave and one batch between two sums for FP64, eight
+// and two for FP32 (FP64 with eight and two 4 % slower, FP32 with four and one
+// 6 %).
 template <typename T>
 struct UserShape {
     static constexpr int rows = sizeof(T) == 8 ? 4 : 8;     // of a wave
     static constexpr int batches = sizeof(T) == 8 ? 1 : 2;  // of 64 blocks between two sums
     static constexpr int plane = 64 * batches + kPad;
     static constexpr int group = rows * (kThreads / 64);    // rows of a workgroup
+    static constexpr int uneven = 64 * rows;                // blocks of a wave that may exceed those of the others together
 };
 constexpr int kLongRows = 2048;
 
@@ -406,7 +413,18 @@ __global__ void __launch_bounds__(kThreads) k_spmv_user(int n_rows, const int* _
     const int g = xcd_group(blockIdx.x, gridDim.x);  // neighbouring rows, which share entries of x, on one XCD
     const int r0 = g * kUserRows, r1 = min(r0 + kUserRows, n_rows);
     const int kb = uniform_load(rp + r0), ke = uniform_load(rp + r1);
-    if (ke - kb <= kLongRows) {
+    bool waves = ke - kb <= kLongRows;
+    if (waves && ke - kb > UserShape<T>::uneven) {
+        int longest = 0;
+#pragma unroll
+        for (int w = 0, k0 = kb; w < kWaves; ++w) {
+            const int k1 = uniform_load(rp + min(r0 + (w + 1) * kWaveRows, r1));
+            longest = max(longest, k1 - k0);
+            k0 = k1;
+        }
+        waves = longest <= UserShape<T>::uneven || 2 * longest <= ke - kb;
+    }
+    if (waves) {
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const int w0 = r0 + w * kWaveRows, w1 = min(w0 + kWaveRows, r1);
         if (w0 < w1)
