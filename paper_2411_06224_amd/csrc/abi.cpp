@@ -418,8 +418,6 @@ int upload_plan(mas_handle* h, hipStream_t s) {
         HIP_TRY(put(Y.tidx, P.tidx));
     }
     if (h->shape.halo) {
-        const std::vector<uint16_t>& hidx =
-            P.sym && h->opts.precision != MAS_PRECISION_MIXED ? P.hidx_sym : P.hidx;
         HIP_TRY(put(Y.hptr, P.hptr));
         HIP_TRY(put(Y.hu, P.hu));
         HIP_TRY(put(Y.h2ptr, P.h2ptr));
@@ -429,7 +427,7 @@ int upload_plan(mas_handle* h, hipStream_t s) {
             return hipMemcpyAsync(h->ws + off, x.data(), sizeof(uint16_t) * x.size(), hipMemcpyHostToDevice, s);
         };
         HIP_TRY(put16(Y.hpar, P.hpar));
-        HIP_TRY(put16(Y.hidx, hidx));
+        HIP_TRY(put16(Y.hidx, P.hidx));
     }
     HIP_TRY(put(Y.rp0, P.rp0));
     HIP_TRY(put(Y.ci0, P.ci0));
@@ -760,7 +758,8 @@ int analyze_impl(mas_handle* h, int32_t n_rows, int32_t nnzb, const int32_t* row
     if (!h) return MAS_INVALID_ARG;
     Plan P;
     const std::string err = analyze(n_rows, nnzb, row_ptr, col_idx, g_ptr, g_adj, h->opts.domain_size,
-                                    h->opts.max_levels, P, part, n_parts);
+                                    h->opts.max_levels, P, part, n_parts,
+                                    h->opts.precision == MAS_PRECISION_MIXED);
     if (!err.empty()) return MAS_INVALID_ARG;
     h->plan = std::move(P);
     h->analyzed = true;

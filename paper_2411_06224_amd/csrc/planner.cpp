@@ -34,6 +34,24 @@ struct Graph {
     std::vector<int> off, nbr;
 };
 
+// f(first, end, t) on ranges t of n independent items, one per thread: as many
+// as the blocks that the items hold are worth starting (62 thousand blocks, the
+// plan of a given partition: 2.3 ms with one thread, 1.7 with four, 2.0 with
+// eight).
+int range_threads(int n, long long blocks) {
+    const int hw = static_cast<int>(std::thread::hardware_concurrency());
+    return std::max(1, std::min({hw, n, blocks >= (1 << 16) ? 8 : blocks >= (1 << 15) ? 4 : 1}));
+}
+
+template <typename F>
+void on_ranges(int n, int threads, F&& f) {
+    auto begin = [&](int t) { return static_cast<int>(static_cast<long long>(n) * t / threads); };
+    std::vector<std::thread> th;
+    for (int t = 1; t < threads; ++t) th.emplace_back([&, t] { f(begin(t), begin(t + 1), t); });
+    f(0, begin(1), 0);
+    for (auto& x : th) x.join();
+}
+
 // Both directions of every edge (self loops and out-of-range ends
 // dropped), each node's neighbours ascending and distinct: the edge list
 // bucketed by node, then each bucket sorted.
@@ -318,70 +336,77 @@ void domain_plan(const std::vector<int>& rp, const std::vector<int>& ci, int uni
     }
 }
 
-// Group-symmetric storage (see Plan::srp).
+// Group-symmetric storage (see Plan::srp).  Storage windows, of whole groups,
+// are independent.
 void symmetric_storage(Plan& P) {
-    const int NS = P.NS, RG = P.RG;
+    const int NS = P.NS, RG = P.RG, W = storage_window(P.N), n_win = (NS + W - 1) / W;
+    const int T = range_threads(n_win, P.nnzb);
     P.srp.assign(NS + 1, 0);
-    P.sci.clear();
-    P.sperm.clear();
-    P.srow.clear();
-    P.sci.reserve(P.ci0.size());
-    P.sperm.reserve(P.ci0.size());
-    P.srow.reserve(P.ci0.size());
-    std::vector<int> cnt(NS + 1, 0);
+    P.tptr.assign(NS + 1, 0);
+    std::vector<int> trans(n_win, 0);  // transposed entries of the window: blocks left of the diagonal in it
+    on_ranges(n_win, T, [&](int w0, int w1, int) {
+        for (int w = w0; w < w1; ++w)
+            for (int s = w * W; s < std::min((w + 1) * W, NS); ++s) {
+                const int r0 = s / RG * RG, r1 = std::min(r0 + RG, NS);
+                int stored = 0;
+                for (int k = P.rp0[s]; k < P.rp0[s + 1]; ++k) {
+                    const int j = P.ci0[k];
+                    trans[w] += j >= w * W && j < s;
+                    if (j >= r0 && j < r1 && j != s) {
+                        if (j < s) continue;
+                        P.tptr[j + 1]++;
+                    }
+                    ++stored;
+                }
+                P.srp[s + 1] = stored;
+            }
+    });
     for (int s = 0; s < NS; ++s) {
-        const int r0 = s / RG * RG, r1 = std::min(r0 + RG, NS);
-        for (int k = P.rp0[s]; k < P.rp0[s + 1]; ++k) {
-            const int j = P.ci0[k];
-            if (j < r0 || j >= r1 || j >= s) {
-                P.sci.push_back(j);
-                P.sperm.push_back(P.perm_src[k]);
-                P.srow.push_back(static_cast<uint8_t>(s - r0));
-                if (j >= r0 && j < r1 && j > s) cnt[j + 1]++;
+        P.srp[s + 1] += P.srp[s];
+        P.tptr[s + 1] += P.tptr[s];
+    }
+    P.sci.resize(P.srp[NS]);
+    P.sperm.resize(P.srp[NS]);
+    P.srow.resize(P.srp[NS]);
+    P.tidx.resize(P.tptr[NS]);
+    std::vector<int> fill(P.tptr.begin(), P.tptr.end() - 1);
+    on_ranges(n_win, T, [&](int w0, int w1, int) {
+        for (int s = w0 * W; s < std::min(w1 * W, NS); ++s) {
+            const int r0 = s / RG * RG, r1 = std::min(r0 + RG, NS);
+            int o = P.srp[s];
+            for (int k = P.rp0[s]; k < P.rp0[s + 1]; ++k) {
+                const int j = P.ci0[k];
+                if (j >= r0 && j < r1 && j != s) {
+                    if (j < s) continue;
+                    P.tidx[fill[j]++] = o;  // ascending within row j
+                }
+                P.sci[o] = j;
+                P.sperm[o] = P.perm_src[k];
+                P.srow[o++] = static_cast<uint8_t>(s - r0);
             }
         }
-        P.srp[s + 1] = static_cast<int>(P.sci.size());
-    }
-    P.tptr.assign(NS + 1, 0);
-    for (int s = 0; s < NS; ++s) P.tptr[s + 1] = P.tptr[s] + cnt[s + 1];
-    P.tidx.assign(P.tptr[NS], 0);
-    std::vector<int> fill(P.tptr.begin(), P.tptr.end() - 1);
-    for (int s = 0; s < NS; ++s) {
-        const int r0 = s / RG * RG, r1 = std::min(r0 + RG, NS);
-        for (int k = P.srp[s]; k < P.srp[s + 1]; ++k) {
-            const int j = P.sci[k];
-            if (j >= r0 && j < r1 && j > s) P.tidx[fill[j]++] = k;  // ascending k within row j
-        }
-    }
+    });
     P.maxT = 0;
     for (int g = 0; g < P.G; ++g) {
         const int r0 = g * RG, r1 = std::min(r0 + RG, NS);
         P.maxT = std::max(P.maxT, P.tptr[r1] - P.tptr[r0]);
     }
-    const int W = storage_window(P.N);
-    std::vector<int> trans((NS + W - 1) / W, 0);
-    for (int s = 0; s < NS; ++s) {
-        const int lo = s / W * W;
-        const int* row = P.ci0.data() + P.rp0[s];
-        const int n = P.rp0[s + 1] - P.rp0[s];
-        trans[s / W] += static_cast<int>(std::lower_bound(row, row + n, s) - std::lower_bound(row, row + n, lo));
-    }
     P.sym = *std::max_element(trans.begin(), trans.end()) <= kMaxTransposed;
 }
 
 // The level-1 units each group's SpMV reads (see Plan::hptr).  Groups are
-// independent: ranges of them on up to eight threads.
-void halo_units(Plan& P) {
+// independent.  full: the SpMV streams the full storage.
+void halo_units(Plan& P, bool full) {
     const int NS = P.NS, RG = P.RG, G = P.G, L = P.L;
     P.halo = true;
     P.maxH = P.maxH2 = 0;
     P.hptr.assign(static_cast<size_t>(G) + 1, 0);
     P.h2ptr.assign(static_cast<size_t>(G) + 1, 0);
-    P.hidx.assign(P.ci0.size(), 0);
-    P.hidx_sym.assign(P.sym ? P.sci.size() : 0, 0);
+    P.hidx.assign(full ? P.ci0.size() : P.sci.size(), 0);
     if (L < 2) return;
-    const int hw = static_cast<int>(std::thread::hardware_concurrency());
-    const int T = P.ci0.size() >= (1u << 16) ? std::max(1, std::min({hw, 8, G})) : 1;
+    const std::vector<int>& rp = full ? P.rp0 : P.srp;
+    const std::vector<int>& ci = full ? P.ci0 : P.sci;  // (both hold every block with a column outside the group)
+    const int T = range_threads(G, P.nnzb);
     struct Part {
         std::vector<int> hu, list2;
         std::vector<uint16_t> hpar;
@@ -389,41 +414,49 @@ void halo_units(Plan& P) {
         bool fits = true;
     };
     std::vector<Part> parts(T);
-    auto each = [&](auto&& f) {
-        std::vector<std::thread> th;
-        for (int w = 1; w < T; ++w) th.emplace_back(f, w);
-        f(0);
-        for (auto& x : th) x.join();
-    };
-    auto begin = [&](int w) { return static_cast<int>(static_cast<long long>(G) * w / T); };
     // units and level-2 entries of each group, and the blocks' local units
-    each([&](int w) {
-        Part& R = parts[w];
-        std::vector<int> ext, two;
-        std::vector<int> local(P.units[1], 0), seen(P.units[1], -1), seen2(L > 2 ? P.units[2] : 0, -1);
-        for (int g = begin(w); g < begin(w + 1); ++g) {
+    on_ranges(G, T, [&](int g0, int g1, int t) {
+        Part& R = parts[t];
+        std::vector<std::pair<int, int>> ext;      // outside units, in the order found
+        std::vector<std::pair<int, uint16_t>> at;  // blocks with a column outside, and the unit's place in that order
+        std::vector<int> two;
+        std::vector<uint16_t> local(kMaxHalo + 1);
+        std::vector<int> seen(P.units[1], -1), seen2(L > 2 ? P.units[2] : 0, -1);
+        std::vector<uint16_t> place(P.units[1]), place2(L > 2 ? P.units[2] : 0);
+        for (int g = g0; g < g1; ++g) {
             const int r0 = g * RG, r1 = std::min(r0 + RG, NS);
+            const int own = P.g_u1[g + 1] - P.g_u1[g];
             ext.clear();
-            for (int k = P.rp0[r0]; k < P.rp0[r1]; ++k) {
-                const int j = P.ci0[k];
+            at.clear();
+            for (int k = rp[r0]; k < rp[r1]; ++k) {
+                const int j = ci[k];
                 if (j >= r0 && j < r1) continue;
                 const int u = P.anc[j];
                 if (seen[u] != g) {
                     seen[u] = g;
-                    ext.push_back(u);
+                    place[u] = static_cast<uint16_t>(ext.size());
+                    if (own + static_cast<int>(ext.size()) == kMaxHalo) {
+                        R.fits = false;
+                        return;
+                    }
+                    ext.emplace_back(u, static_cast<int>(ext.size()));
                 }
+                at.emplace_back(k, place[u]);
             }
-            const int own = P.g_u1[g + 1] - P.g_u1[g], n = own + static_cast<int>(ext.size());
-            R.maxH = std::max(R.maxH, n);
+            const int n = own + static_cast<int>(ext.size());
             if (n > kMaxHalo) {
                 R.fits = false;
                 return;
             }
+            R.maxH = std::max(R.maxH, n);
             std::sort(ext.begin(), ext.end());
             const size_t h0 = R.hu.size();
-            for (int u = P.g_u1[g]; u < P.g_u1[g + 1]; ++u) R.hu.push_back(u);
-            R.hu.insert(R.hu.end(), ext.begin(), ext.end());
-            for (int i = 0; i < n; ++i) local[R.hu[h0 + i]] = i;
+            for (int i = 0; i < own; ++i) R.hu.push_back(P.g_u1[g] + i);
+            for (size_t i = 0; i < ext.size(); ++i) {
+                R.hu.push_back(ext[i].first);
+                local[ext[i].second] = static_cast<uint16_t>(own + i);
+            }
+            for (const auto& [k, i] : at) P.hidx[k] = local[i];
             two.clear();
             if (L > 2)
                 for (int i = 0; i < n; ++i) {
@@ -434,24 +467,12 @@ void halo_units(Plan& P) {
                     }
                 }
             std::sort(two.begin(), two.end());
-            for (int i = 0; i < n; ++i)
-                R.hpar.push_back(
-                    L > 2 ? static_cast<uint16_t>(std::lower_bound(two.begin(), two.end(), P.up[1][R.hu[h0 + i]]) -
-                                                  two.begin())
-                          : 0);
+            for (size_t i = 0; i < two.size(); ++i) place2[two[i]] = static_cast<uint16_t>(i);
+            for (int i = 0; i < n; ++i) R.hpar.push_back(L > 2 ? place2[P.up[1][R.hu[h0 + i]]] : 0);
             R.list2.insert(R.list2.end(), two.begin(), two.end());
             R.maxH2 = std::max(R.maxH2, static_cast<int>(two.size()));
             P.hptr[g + 1] = n;
             P.h2ptr[g + 1] = static_cast<int>(two.size());
-            size_t o = P.sym ? P.srp[r0] : 0;
-            for (int s = r0; s < r1; ++s)
-                for (int k = P.rp0[s]; k < P.rp0[s + 1]; ++k) {
-                    const int j = P.ci0[k];
-                    const bool inside = j >= r0 && j < r1;
-                    const uint16_t h = inside ? 0 : static_cast<uint16_t>(local[P.anc[j]]);
-                    P.hidx[k] = h;
-                    if (P.sym && (!inside || j >= s)) P.hidx_sym[o++] = h;
-                }
         }
     });
     std::vector<int> list2;
@@ -460,7 +481,7 @@ void halo_units(Plan& P) {
             P.halo = false;
             P.maxH = P.maxH2 = 0;
             for (auto* x : {&P.hptr, &P.hu, &P.h2ptr}) x->clear();
-            for (auto* x : {&P.hpar, &P.hidx, &P.hidx_sym}) x->clear();
+            for (auto* x : {&P.hpar, &P.hidx}) x->clear();
             return;
         }
         P.maxH = std::max(P.maxH, R.maxH);
@@ -476,19 +497,20 @@ void halo_units(Plan& P) {
     std::vector<long long> base(L + 1, 0);  // first position of each level's corrections
     for (int l = 1; l < L; ++l) base[l + 1] = base[l] + static_cast<long long>(P.ndom[l]) * P.N;
     P.hy.resize(list2.size() * static_cast<size_t>(std::max(L - 2, 0)));
-    each([&](int w) {
-        for (int g = begin(w); g < begin(w + 1) && L > 2; ++g) {
-            const int h0 = P.h2ptr[g], n = P.h2ptr[g + 1] - h0;
-            int* y = P.hy.data() + static_cast<size_t>(L - 2) * h0;
-            for (int i = 0; i < n; ++i) {
-                int a = list2[h0 + i];
-                for (int l = 2; l < L; ++l) {
-                    if (l > 2) a = P.up[l - 1][a];
-                    y[static_cast<size_t>(l - 2) * n + i] = static_cast<int>(base[l] + a);
+    if (L > 2)
+        on_ranges(G, T, [&](int g0, int g1, int) {
+            for (int g = g0; g < g1; ++g) {
+                const int h0 = P.h2ptr[g], n = P.h2ptr[g + 1] - h0;
+                int* y = P.hy.data() + static_cast<size_t>(L - 2) * h0;
+                for (int i = 0; i < n; ++i) {
+                    int a = list2[h0 + i];
+                    for (int l = 2; l < L; ++l) {
+                        if (l > 2) a = P.up[l - 1][a];
+                        y[static_cast<size_t>(l - 2) * n + i] = static_cast<int>(base[l] + a);
+                    }
                 }
             }
-        }
-    });
+        });
 }
 
 // Workgroup order of the SpMV.  The group kernels give each XCD a
@@ -570,7 +592,8 @@ std::vector<int> spmv_group_order(const std::vector<long long>& cnt) {
 }
 
 std::string analyze(int V, int nnzb, const int32_t* row_ptr, const int32_t* col_idx, const int32_t* g_ptr,
-                    const int32_t* g_adj, int N, int max_levels, Plan& P, const int32_t* part, int n_parts) {
+                    const int32_t* g_adj, int N, int max_levels, Plan& P, const int32_t* part, int n_parts,
+                    bool f32_values) {
     if (V <= 0 || nnzb < V || !row_ptr || !col_idx) return "empty matrix or null pattern";
     if (N < 1 || N > 40) return "domain_size must be in [1, 40]";
     if ((g_ptr == nullptr) != (g_adj == nullptr)) return "graph needs both g_ptr and g_adj";
@@ -659,8 +682,7 @@ std::string analyze(int V, int nnzb, const int32_t* row_ptr, const int32_t* col_
         P.rp0[s + 1] = P.rp0[s] + (i >= 0 ? row_ptr[i + 1] - row_ptr[i] : 0);
     }
     {
-        // rows are independent: ranges of slots on up to eight threads
-        auto rows = [&](int s0, int s1) {
+        auto rows = [&](int s0, int s1, int) {
             std::vector<std::pair<int, int>> row;
             for (int s = s0; s < s1; ++s) {
                 const int i = P.remap[s];
@@ -674,13 +696,7 @@ std::string analyze(int V, int nnzb, const int32_t* row_ptr, const int32_t* col_
                 }
             }
         };
-        const int T = nnzb >= (1 << 16) ? std::max(1, std::min(static_cast<int>(std::thread::hardware_concurrency()), 8)) : 1;
-        std::vector<std::thread> th;
-        for (int w = 1; w < T; ++w)
-            th.emplace_back(rows, static_cast<int>(static_cast<long long>(P.NS) * w / T),
-                            static_cast<int>(static_cast<long long>(P.NS) * (w + 1) / T));
-        rows(0, static_cast<int>(static_cast<long long>(P.NS) / T));
-        for (auto& x : th) x.join();
+        on_ranges(P.NS, range_threads(P.NS, nnzb), rows);
     }
 
     // ---- hierarchy
@@ -785,24 +801,23 @@ std::string analyze(int V, int nnzb, const int32_t* row_ptr, const int32_t* col_
         for (int l = 2; l < P.L; ++l) {
             for (int& v : a) v = P.up[l - 1][v];
             P.anc1[l] = a;
-            // (unit, group, writer) of every distinct (group, unit) pair
-            std::vector<std::array<int, 3>> pairs;
+            // (unit, writer) of every distinct (group, unit) pair, by group;
+            // their positions by (unit, group)
+            std::vector<std::pair<int, int>> pairs;
             std::vector<int> seen(P.units[l], -1);
             for (int g = 0; g < P.G; ++g)
                 for (int t = P.g_u1[g]; t < P.g_u1[g + 1]; ++t)
                     if (seen[a[t]] != g) {
                         seen[a[t]] = g;
-                        pairs.push_back({a[t], g, t});
+                        pairs.emplace_back(a[t], t);
                     }
-            std::sort(pairs.begin(), pairs.end());
             P.lead_pos[l].assign(S1, -1);
             P.cp_ptr[l].assign(P.units[l] + 1, 0);
-            for (size_t k = 0; k < pairs.size(); ++k) {
-                P.lead_pos[l][pairs[k][2]] = P.n_cpart + static_cast<int>(k);
-                P.cp_ptr[l][pairs[k][0] + 1]++;
-            }
+            for (const auto& [u, t] : pairs) P.cp_ptr[l][u + 1]++;
             P.cp_ptr[l][0] = P.n_cpart;
             for (int u = 0; u < P.units[l]; ++u) P.cp_ptr[l][u + 1] += P.cp_ptr[l][u];
+            std::vector<int> next(P.cp_ptr[l].begin(), P.cp_ptr[l].end() - 1);
+            for (const auto& [u, t] : pairs) P.lead_pos[l][t] = next[u]++;
             P.n_cpart += static_cast<int>(pairs.size());
         }
     }
@@ -847,31 +862,27 @@ std::string analyze(int V, int nnzb, const int32_t* row_ptr, const int32_t* col_
             P.gu1_slot[o] = s;
             P.gu1_mask[o] = P.lmask[s];
         }
-    P.GW = 1;
-    std::vector<std::vector<std::array<long long, 3>>> writers(P.G);
+    std::vector<int> writers(P.G, 0);
     for (int l = 2; l < P.L; ++l)
-        for (int g = 0; g < P.G; ++g)
-            for (int i = 0; i < P.W1; ++i) {
-                const size_t o = static_cast<size_t>(g) * P.W1 + i;
-                if (P.gpos[l][o] < 0) continue;
-                writers[g].push_back({P.gpos[l][o], static_cast<long long>(l - 2) * P.W1 + i,
-                                      static_cast<long long>(o)});
-            }
-    for (int g = 0; g < P.G; ++g) P.GW = std::max(P.GW, static_cast<int>(writers[g].size()));
+        for (size_t o = 0; o < P.gpos[l].size(); ++o) writers[o / P.W1] += P.gpos[l][o] >= 0;
+    P.GW = std::max(1, *std::max_element(writers.begin(), writers.end()));
     P.gw_pos.assign(static_cast<size_t>(P.G) * P.GW, -1);
     P.gw_li.assign(static_cast<size_t>(P.G) * P.GW, 0);
     P.gw_mask.assign(static_cast<size_t>(P.G) * P.GW, 0);
-    for (int g = 0; g < P.G; ++g)
-        for (size_t e = 0; e < writers[g].size(); ++e) {
-            const size_t o = static_cast<size_t>(g) * P.GW + e;
-            P.gw_pos[o] = static_cast<int>(writers[g][e][0]);
-            P.gw_li[o] = static_cast<int>(writers[g][e][1]);
-            const int l = 2 + static_cast<int>(writers[g][e][1] / P.W1);
-            P.gw_mask[o] = P.gmask[l][static_cast<size_t>(writers[g][e][2])];
-        }
+    for (int g = 0; g < P.G; ++g) {
+        size_t e = static_cast<size_t>(g) * P.GW;
+        for (int l = 2; l < P.L; ++l)
+            for (int i = 0; i < P.W1; ++i) {
+                const size_t o = static_cast<size_t>(g) * P.W1 + i;
+                if (P.gpos[l][o] < 0) continue;
+                P.gw_pos[e] = P.gpos[l][o];
+                P.gw_li[e] = (l - 2) * P.W1 + i;
+                P.gw_mask[e++] = P.gmask[l][o];
+            }
+    }
 
     symmetric_storage(P);
-    halo_units(P);
+    halo_units(P, f32_values || !P.sym);
     spmv_order(P);
 
     // ---- per-node units for reports

@@ -126,14 +126,14 @@ struct Plan {
     // lists: hy holds, for entry i of the group's n2 and level l >= 2, the
     // position of its ancestor's correction in the coarse vectors laid end to
     // end (level 1 first, ndom[l] * N units each), at
-    // [(L-2) h2ptr[g] + (l-2) n2 + i].  hidx / hidx_sym: the group's local unit
-    // of every slot-ordered / symmetrically stored block whose column lies
-    // outside the group (0 for the others).  All empty (halo = false) when
+    // [(L-2) h2ptr[g] + (l-2) n2 + i].  hidx: the group's local unit of every
+    // block of the storage that the SpMV streams whose column lies outside the
+    // group (0 for the others).  All empty (halo = false) when
     // some group reads more than kMaxHalo units.
     bool halo = false;
     int maxH = 0, maxH2 = 0;  // most units, most level-2 entries of one group
     std::vector<int> hptr, hu, h2ptr, hy;
-    std::vector<uint16_t> hpar, hidx, hidx_sym;
+    std::vector<uint16_t> hpar, hidx;
 
     // SpMV group of each workgroup when the groups' stored blocks are
     // uneven (empty: the contiguous per-XCD mapping of the group kernels)
@@ -148,9 +148,10 @@ std::vector<int> spmv_group_order(const std::vector<long long>& cnt);
 
 // Returns "" on success or a message describing the invalid input.
 // part / n_parts (optional): a caller-given level-0 partition, used instead
-// of the recursive bisection of the node graph.
+// of the recursive bisection of the node graph.  f32_values: the SpMV streams
+// an FP32 copy of the values (which has the full storage).
 std::string analyze(int n_rows, int nnzb, const int32_t* row_ptr, const int32_t* col_idx, const int32_t* g_ptr,
                     const int32_t* g_adj, int N, int max_levels, Plan& out, const int32_t* part = nullptr,
-                    int n_parts = 0);
+                    int n_parts = 0, bool f32_values = false);
 
 }  // namespace maspcg
