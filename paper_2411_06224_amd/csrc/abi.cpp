@@ -1222,9 +1222,6 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
     HIP_TRY(hipMemcpyAsync(g_u1.data(), R.g_u1, sizeof(int) * g_u1.size(), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(gsz.data(), R.gstore, sizeof(int) * (3 * static_cast<size_t>(G) + n_win), hipMemcpyDeviceToHost,
                            s));
-    int n_halo = 0, n_halo2 = 0;
-    HIP_TRY(hipMemcpyAsync(&n_halo, R.hptr + G, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&n_halo2, R.h2ptr + G, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
 
     // the new plan: the partition and its maps stay, every size is new
@@ -1266,8 +1263,8 @@ int mas_replan(mas_handle* h, int64_t nnzb, const int32_t* row_ptr, const int32_
     Z.halo = c.h_max <= kMaxHalo;
     Z.maxH = Z.halo ? c.h_max : 0;
     Z.maxH2 = Z.halo ? c.h2_max : 0;
-    Z.n_hu = Z.halo ? static_cast<size_t>(n_halo) : 0;
-    Z.n_hy = Z.halo && S.L > 2 ? static_cast<size_t>(n_halo2) * (S.L - 2) : 0;
+    Z.n_hu = Z.halo ? static_cast<size_t>(c.h_units) : 0;
+    Z.n_hy = Z.halo && S.L > 2 ? static_cast<size_t>(c.h2_units) * (S.L - 2) : 0;
     PlacedShape ps{};
     ps.S = S;
     ps.sym = Q.sym ? 1 : 0;

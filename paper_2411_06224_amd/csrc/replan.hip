@@ -318,15 +318,25 @@ __global__ void k_rp_window_blocks(int NS, int W, const int* __restrict__ rp, Re
     if (static_cast<long long>(w) * W < NS) atomicMax(&c->window_blocks, rp[min((w + 1) * W, NS)] - rp[w * W]);
 }
 
-// Transposed entries of every storage window of W slots (the storage rule):
-// the columns of row s in [window start, s).
-__global__ void k_rp_window_trans(int NS, int W, const int* __restrict__ rp, const int* __restrict__ ci,
-                                  int* __restrict__ cnt) {
-    const int s = blockIdx.x * kRpThreads + threadIdx.x;
-    if (s >= NS) return;
-    const int p0 = first_at_least(ci, rp[s], rp[s + 1], s / W * W);
-    const int n = first_at_least(ci, p0, rp[s + 1], s) - p0;
-    if (n) atomicAdd(cnt + s / W, n);
+// Transposed entries of every storage window of W <= kWindowSlots slots (the
+// storage rule): the columns of row s in [window start, s).  A workgroup per
+// window (one atomic per row on the windows' counters: 53 us at 48^3, now 4).
+__global__ void __launch_bounds__(kWindowSlots) k_rp_window_trans(int NS, int W, const int* __restrict__ rp,
+                                                                  const int* __restrict__ ci, int* __restrict__ cnt) {
+    __shared__ int total;
+    if (threadIdx.x == 0) total = 0;
+    __syncthreads();
+    const int lo = blockIdx.x * W, s = lo + threadIdx.x;
+    int n = 0;
+    if (static_cast<int>(threadIdx.x) < W && s < NS) {
+        const int p0 = first_at_least(ci, rp[s], rp[s + 1], lo);
+        n = first_at_least(ci, p0, rp[s + 1], s) - p0;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o /= 2) n += __shfl_xor(n, o);
+    if (threadIdx.x % 64 == 0) atomicAdd(&total, n);
+    __syncthreads();
+    if (threadIdx.x == 0) cnt[blockIdx.x] = total;
 }
 
 // Level-1 restriction: slot s leads its level-1 unit u if no lower lane of
@@ -516,7 +526,7 @@ __global__ void __launch_bounds__(kRpThreads) k_rp_halo_count(int G, int NS, int
     __shared__ int table[kHaloTable];
     __shared__ int found;
     const int g = blockIdx.x;
-    if (g == G || L < 2) {  // closes the scans
+    if (L < 2) {
         if (threadIdx.x == 0) cnt[g] = cnt2[g] = 0;
         return;
     }
@@ -533,6 +543,43 @@ __global__ void __launch_bounds__(kRpThreads) k_rp_halo_count(int G, int NS, int
     if (threadIdx.x == 0) {
         cnt2[g] = min(found, kMaxHalo + 1);
         atomicMax(&c->h2_max, cnt2[g]);
+    }
+}
+
+// Exclusive scans of the two counts (hptr, h2ptr [G + 1]) and their totals, a
+// workgroup each: one launch, where two library scans and a copy of the totals
+// are five and two more stops of the host.
+constexpr int kHaloScan = 1024;
+__global__ void __launch_bounds__(kHaloScan) k_rp_halo_scan(int G, const int* __restrict__ cnt,
+                                                            const int* __restrict__ cnt2, int* __restrict__ hptr,
+                                                            int* __restrict__ h2ptr, ReplanCounts* __restrict__ c) {
+    constexpr int kWaves = kHaloScan / 64;
+    __shared__ int wave_sum[kWaves];
+    const int t = threadIdx.x, lane = t & 63;
+    const int* in = blockIdx.x ? cnt2 : cnt;
+    int* out = blockIdx.x ? h2ptr : hptr;
+    int before = 0;
+    for (int i0 = 0; i0 < G; i0 += kHaloScan) {
+        const int v = i0 + t < G ? in[i0 + t] : 0;
+        int end = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(end, o);
+            if (lane >= o) end += y;
+        }
+        __syncthreads();
+        if (lane == 63) wave_sum[t >> 6] = end;
+        __syncthreads();
+        int at = before + end - v;
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < t >> 6) at += wave_sum[w];
+            before += wave_sum[w];
+        }
+        if (i0 + t < G) out[i0 + t] = at;
+    }
+    if (t == 0) {
+        out[G] = before;
+        (blockIdx.x ? c->h2_units : c->h_units) = before;
     }
 }
 
@@ -847,9 +894,7 @@ hipError_t replan_sizes(const ReplanLayout& R, const ReplanShape& S, hipStream_t
     launch_kernel(k_rp_group_sizes, dim3(grid(G)), dim3(kRpThreads), 0, s, G, RG, NS, static_cast<const int*>(R.rp0),
                   static_cast<const int*>(R.srp), static_cast<const int*>(R.tptr), R.gstore);
     const int W = storage_window(S.N), nw = (NS + W - 1) / W;  // nw <= G
-    launch_kernel(k_rp_fill, dim3(grid(nw)), dim3(kRpThreads), 0, s, R.gstore + 3 * static_cast<size_t>(G),
-                  static_cast<long long>(nw), 0);
-    launch_kernel(k_rp_window_trans, dim3(grid(NS)), dim3(kRpThreads), 0, s, NS, W, static_cast<const int*>(R.rp0),
+    launch_kernel(k_rp_window_trans, dim3(nw), dim3(kWindowSlots), 0, s, NS, W, static_cast<const int*>(R.rp0),
                   static_cast<const int*>(R.ci0), R.gstore + 3 * static_cast<size_t>(G));
     // level-1 restriction
     launch_kernel(k_rp_lead1, dim3(grid(NS)), dim3(kRpThreads), 0, s, NS, S.N, L,
@@ -859,12 +904,13 @@ hipError_t replan_sizes(const ReplanLayout& R, const ReplanShape& S, hipStream_t
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = scan(R, R.gcnt, R.g_u1, G + 1, s)) != hipSuccess) return e;
     // the units each group's SpMV reads
-    launch_kernel(k_rp_halo_count, dim3(G + 1), dim3(kRpThreads), 0, s, G, NS, RG, L, static_cast<const int*>(R.rp0),
+    launch_kernel(k_rp_halo_count, dim3(G), dim3(kRpThreads), 0, s, G, NS, RG, L, static_cast<const int*>(R.rp0),
                   static_cast<const int*>(R.ci0), static_cast<const int*>(R.H.sn),
                   static_cast<const int*>(R.g_u1), R.hcnt, R.h2cnt, R.counts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = scan(R, R.hcnt, R.hptr, G + 1, s)) != hipSuccess) return e;
-    if ((e = scan(R, R.h2cnt, R.h2ptr, G + 1, s)) != hipSuccess) return e;
+    launch_kernel(k_rp_halo_scan, dim3(2), dim3(kHaloScan), 0, s, G, static_cast<const int*>(R.hcnt),
+                  static_cast<const int*>(R.h2cnt), R.hptr, R.h2ptr, R.counts);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     // coarse levels; each level's block count is read back to size the next
     // level's sort (sorting a bound instead costs a full-length sort per
     // level: 4-5 ms over the 16 levels of the membrane with bodies)

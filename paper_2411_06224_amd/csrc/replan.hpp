@@ -35,6 +35,7 @@ struct ReplanCounts {
     int cbase[kMaxLv + 1];   // first coarse-partial position of each level >= 2; cbase[L] = n_cpart
     int gw_max;              // most writers of one group
     int h_max, h2_max;       // most level-1 units one group's SpMV reads, most level-2 units above them
+    int h_units, h2_units;   // those of all groups
 };
 
 struct ReplanLayout {
