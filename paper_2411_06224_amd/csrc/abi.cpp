@@ -86,7 +86,7 @@ Shape shape_of(const Plan& P) {
     }
     S.halo = P.halo;
     S.n_hu = P.hu.size();
-    S.n_hy = P.hy.size();
+    S.n_hy = P.h2slot.size() * static_cast<size_t>(std::max(P.L - 2, 0));
     S.maxH = P.maxH;
     S.maxH2 = P.maxH2;
     return S;
@@ -421,7 +421,6 @@ int upload_plan(mas_handle* h, hipStream_t s) {
         HIP_TRY(put(Y.hptr, P.hptr));
         HIP_TRY(put(Y.hu, P.hu));
         HIP_TRY(put(Y.h2ptr, P.h2ptr));
-        HIP_TRY(put(Y.hy, P.hy));
         auto put16 = [&](size_t off, const std::vector<uint16_t>& x) -> hipError_t {
             if (x.empty()) return hipSuccess;
             return hipMemcpyAsync(h->ws + off, x.data(), sizeof(uint16_t) * x.size(), hipMemcpyHostToDevice, s);
@@ -435,6 +434,13 @@ int upload_plan(mas_handle* h, hipStream_t s) {
     HIP_TRY(hipMemcpyAsync(h->ws + Y.lmask, P.lmask.data(), sizeof(uint64_t) * P.lmask.size(), hipMemcpyHostToDevice,
                            s));
     HIP_TRY(put(Y.anc, P.anc));
+    if (h->shape.halo && P.L > 2) {
+        // the slots by way of A_1's place, which the build then fills (each is
+        // of a unit that some unit of the group is coupled with: a block of A_1)
+        HIP_TRY(put(Y.A[1], P.h2slot));
+        HIP_TRY(launch_halo_pos(P.G, P.NS, P.N, P.L, P.ndom.data(), at<int>(h, Y.anc) + P.NS, at<int>(h, Y.h2ptr),
+                                at<int>(h, Y.A[1]), at<int>(h, Y.hy), s));
+    }
     HIP_TRY(put(Y.g_u1, P.g_u1));
     HIP_TRY(put(Y.gu1_slot, P.gu1_slot));
     HIP_TRY(hipMemcpyAsync(h->ws + Y.gu1_mask, P.gu1_mask.data(), sizeof(uint64_t) * P.gu1_mask.size(),

@@ -408,18 +408,21 @@ void halo_units(Plan& P, bool full) {
     const std::vector<int>& ci = full ? P.ci0 : P.sci;  // (both hold every block with a column outside the group)
     const int T = range_threads(G, P.nnzb);
     struct Part {
-        std::vector<int> hu, list2;
+        std::vector<int> hu, h2slot;
         std::vector<uint16_t> hpar;
         int maxH = 0, maxH2 = 0;
         bool fits = true;
     };
     std::vector<Part> parts(T);
+    std::vector<int> lead(P.units[1]);  // first slot of each level-1 unit
+    for (int s = 0; s < NS; ++s)
+        if (P.lead1[s] >= 0) lead[P.lead1[s]] = s;
     // units and level-2 entries of each group, and the blocks' local units
     on_ranges(G, T, [&](int g0, int g1, int t) {
         Part& R = parts[t];
         std::vector<std::pair<int, int>> ext;      // outside units, in the order found
         std::vector<std::pair<int, uint16_t>> at;  // blocks with a column outside, and the unit's place in that order
-        std::vector<int> two;
+        std::vector<std::pair<int, int>> two;  // level-2 units, and a slot below each
         std::vector<uint16_t> local(kMaxHalo + 1);
         std::vector<int> seen(P.units[1], -1), seen2(L > 2 ? P.units[2] : 0, -1);
         std::vector<uint16_t> place(P.units[1]), place2(L > 2 ? P.units[2] : 0);
@@ -463,24 +466,25 @@ void halo_units(Plan& P, bool full) {
                     const int a = P.up[1][R.hu[h0 + i]];
                     if (seen2[a] != g) {
                         seen2[a] = g;
-                        two.push_back(a);
+                        two.emplace_back(a, lead[R.hu[h0 + i]]);
                     }
                 }
             std::sort(two.begin(), two.end());
-            for (size_t i = 0; i < two.size(); ++i) place2[two[i]] = static_cast<uint16_t>(i);
+            for (size_t i = 0; i < two.size(); ++i) {
+                place2[two[i].first] = static_cast<uint16_t>(i);
+                R.h2slot.push_back(two[i].second);
+            }
             for (int i = 0; i < n; ++i) R.hpar.push_back(L > 2 ? place2[P.up[1][R.hu[h0 + i]]] : 0);
-            R.list2.insert(R.list2.end(), two.begin(), two.end());
             R.maxH2 = std::max(R.maxH2, static_cast<int>(two.size()));
             P.hptr[g + 1] = n;
             P.h2ptr[g + 1] = static_cast<int>(two.size());
         }
     });
-    std::vector<int> list2;
     for (Part& R : parts) {
         if (!R.fits) {
             P.halo = false;
             P.maxH = P.maxH2 = 0;
-            for (auto* x : {&P.hptr, &P.hu, &P.h2ptr}) x->clear();
+            for (auto* x : {&P.hptr, &P.hu, &P.h2ptr, &P.h2slot}) x->clear();
             for (auto* x : {&P.hpar, &P.hidx}) x->clear();
             return;
         }
@@ -488,29 +492,12 @@ void halo_units(Plan& P, bool full) {
         P.maxH2 = std::max(P.maxH2, R.maxH2);
         P.hu.insert(P.hu.end(), R.hu.begin(), R.hu.end());
         P.hpar.insert(P.hpar.end(), R.hpar.begin(), R.hpar.end());
-        list2.insert(list2.end(), R.list2.begin(), R.list2.end());
+        P.h2slot.insert(P.h2slot.end(), R.h2slot.begin(), R.h2slot.end());
     }
     for (int g = 0; g < G; ++g) {
         P.hptr[g + 1] += P.hptr[g];
         P.h2ptr[g + 1] += P.h2ptr[g];
     }
-    std::vector<long long> base(L + 1, 0);  // first position of each level's corrections
-    for (int l = 1; l < L; ++l) base[l + 1] = base[l] + static_cast<long long>(P.ndom[l]) * P.N;
-    P.hy.resize(list2.size() * static_cast<size_t>(std::max(L - 2, 0)));
-    if (L > 2)
-        on_ranges(G, T, [&](int g0, int g1, int) {
-            for (int g = g0; g < g1; ++g) {
-                const int h0 = P.h2ptr[g], n = P.h2ptr[g + 1] - h0;
-                int* y = P.hy.data() + static_cast<size_t>(L - 2) * h0;
-                for (int i = 0; i < n; ++i) {
-                    int a = list2[h0 + i];
-                    for (int l = 2; l < L; ++l) {
-                        if (l > 2) a = P.up[l - 1][a];
-                        y[static_cast<size_t>(l - 2) * n + i] = static_cast<int>(base[l] + a);
-                    }
-                }
-            }
-        });
 }
 
 // Workgroup order of the SpMV.  The group kernels give each XCD a

@@ -123,16 +123,16 @@ struct Plan {
     // hptr[g+1]): its own (ascending), then those of its rows' columns outside
     // the group (ascending); hu: the unit; hpar: the local index of its level-2
     // unit among the distinct ones (ascending), which [h2ptr[g], h2ptr[g+1])
-    // lists: hy holds, for entry i of the group's n2 and level l >= 2, the
-    // position of its ancestor's correction in the coarse vectors laid end to
-    // end (level 1 first, ndom[l] * N units each), at
-    // [(L-2) h2ptr[g] + (l-2) n2 + i].  hidx: the group's local unit of every
+    // lists: h2slot: a slot below each.  From it the device forms hy: for entry
+    // i of the group's n2 and level l >= 2, the position of its ancestor's
+    // correction in the coarse vectors laid end to end (level 1 first, ndom[l] *
+    // N units each), at [(L-2) h2ptr[g] + (l-2) n2 + i].  hidx: the group's local unit of every
     // block of the storage that the SpMV streams whose column lies outside the
     // group (0 for the others).  All empty (halo = false) when
     // some group reads more than kMaxHalo units.
     bool halo = false;
     int maxH = 0, maxH2 = 0;  // most units, most level-2 entries of one group
-    std::vector<int> hptr, hu, h2ptr, hy;
+    std::vector<int> hptr, hu, h2ptr, h2slot;
     std::vector<uint16_t> hpar, hidx;
 
     // SpMV group of each workgroup when the groups' stored blocks are

@@ -638,17 +638,17 @@ __global__ void __launch_bounds__(kRpThreads) k_rp_halo_place(
     }
 }
 
-// Positions of the level-2 entries' corrections at every level, through a
-// level-1 unit below each.
-__global__ void __launch_bounds__(64) k_rp_halo_pos(int NS, int L, const int* __restrict__ anc1,
-                                                    const int* __restrict__ h2ptr, const int* __restrict__ rep2,
+// Positions of the level-2 entries' corrections at every level, through one
+// item below each: its ancestor at level l is anc[l stride + item].
+__global__ void __launch_bounds__(64) k_rp_halo_pos(int NS, int L, const int* __restrict__ anc,
+                                                    const int* __restrict__ h2ptr, const int* __restrict__ below,
                                                     LevelBase base, int* __restrict__ hy) {
     const int g = blockIdx.x;
     const int h0 = h2ptr[g], n = h2ptr[g + 1] - h0;
     int* y = hy + static_cast<size_t>(L - 2) * h0;
     for (int e = threadIdx.x; e < (L - 2) * n; e += 64) {
         const int l = 2 + e / n, i = e - (l - 2) * n;
-        y[e] = base.at[l] + anc1[static_cast<size_t>(l) * NS + rep2[h0 + i]];
+        y[e] = base.at[l] + anc[static_cast<size_t>(l - 2) * NS + below[h0 + i]];
     }
 }
 
@@ -959,6 +959,16 @@ hipError_t replan_sizes(const ReplanLayout& R, const ReplanShape& S, hipStream_t
     return hipGetLastError();
 }
 
+hipError_t launch_halo_pos(int G, int NS, int N, int L, const int* ndom, const int* anc, const int* h2ptr,
+                           const int* below, int* hy, hipStream_t s) {
+    if (L > 2) {
+        LevelBase base{};
+        for (int l = 2; l < L; ++l) base.at[l] = base.at[l - 1] + ndom[l - 1] * N;
+        launch_kernel(k_rp_halo_pos, dim3(G), dim3(64), 0, s, NS, L, anc, h2ptr, below, base, hy);
+    }
+    return hipGetLastError();
+}
+
 hipError_t replan_place(const ReplanLayout& R, const PlacedShape& P, const PlanDest& D, hipStream_t s) {
     const ReplanShape& S = P.S;
     const int NS = S.NS, G = S.G, RG = S.RG, L = S.L, W1 = P.W1;
@@ -1018,13 +1028,9 @@ hipError_t replan_place(const ReplanLayout& R, const PlacedShape& P, const PlanD
                       static_cast<const int*>(R.hptr), static_cast<const int*>(R.h2ptr),
                       D.hidx_sym ? static_cast<const int*>(D.srp) : nullptr, static_cast<const int*>(D.sci), D.hu,
                       D.hpar, rep2, D.hidx);
-        if (L > 2) {
-            LevelBase base{};
-            for (int l = 2; l < L; ++l) base.at[l] = base.at[l - 1] + S.ndom[l - 1] * S.N;
-            launch_kernel(k_rp_halo_pos, dim3(G), dim3(64), 0, s, NS, L, static_cast<const int*>(R.anc1),
-                          static_cast<const int*>(R.h2ptr), static_cast<const int*>(rep2), base, D.hy);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_halo_pos(G, NS, S.N, L, S.ndom, R.anc1 + 2 * static_cast<size_t>(NS), R.h2ptr, rep2, D.hy, s)) !=
+            hipSuccess)
+            return e;
     }
     // inversion gathers of level 0 (caller block order)
     if ((e = dom_place(R, NS, S.N, S.ndom[0], R.rp0, R.ci0, R.perm, D.dom_ptr[0], D.dom_blk[0], D.dom_ab[0], s)) !=

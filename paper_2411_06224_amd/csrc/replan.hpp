@@ -105,4 +105,9 @@ struct PlacedShape {
 // Pass 2: every plan array of the solver workspace.
 hipError_t replan_place(const ReplanLayout& R, const PlacedShape& P, const PlanDest& D, hipStream_t s);
 
+// hy (planner.hpp) from one item below each level-2 entry, whose ancestor at
+// level l >= 2 is anc[(l - 2) NS + item].
+hipError_t launch_halo_pos(int G, int NS, int N, int L, const int* ndom, const int* anc, const int* h2ptr,
+                           const int* below, int* hy, hipStream_t s);
+
 }  // namespace maspcg
