@@ -456,8 +456,9 @@ int mas_set_kernel_timing(mas_handle* h, int enable);
  * for the kernel slots [0] direction update and SpMV q = H p with p^T q
  * (and the restriction of q and the convergence decision), [1] x/r update
  * with ||r||^2 and the restriction of r, [2] coarse-level MAS apply,
- * [3] level-0 MAS apply with prolongation and r^T z, [4] x/r update, level 0
- * and the coarse levels in one launch (the prolongation rides in [0]),
+ * [3] level-0 MAS apply with prolongation and r^T z, or the prolongation
+ * alone after [4], [4] x/r update, level 0 and the coarse levels in one launch
+ * (the prolongation rides in [0] or follows in [3]),
  * [5] FP64 residual replacement, [6] permutation of H, [7] restriction only.
  * Launches queued after the solve had stopped, which return at once, are
  * not counted.  Host arrays. */

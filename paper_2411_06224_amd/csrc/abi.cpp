@@ -116,7 +116,8 @@ struct mas_handle {
     size_t ws_size = 0;
     char* uploaded_to = nullptr;
     bool built = false;
-    bool fuse_ok = false;  // two launches per iteration (set_fusion)
+    bool fuse_ok = false;  // iterations by recurrence (set_fusion)
+    bool split_ok = false; // ... in two launches, else three
     DevState* st_host = nullptr;  // pinned: [0] last blocking read, [1..2] per-batch copies
     int* flag_host = nullptr;     // pinned
     hipEvent_t ev[kEvCount]{};
@@ -582,10 +583,11 @@ int read_state(mas_handle* h, const SolverView& v, hipStream_t s) {
 //   and the convergence test on r_{k-1} ->
 //   alpha, x += alpha p, r -= alpha q (||r||^2 partials), the level-0 apply
 //   and, beside it, C_l r_k = C_l r_{k-1} - alpha C_l q_k and the coarse apply
-//   (rho partials of both); the prolongation follows in the next SpMV;
+//   (rho partials of both); the prolongation follows in the next SpMV (or,
+//   where the SpMV cannot lend shared memory to the groups' coarse
+//   corrections, in a third launch, with the convergence test on r_k);
 // every replace_every-th iteration (and every iteration when the SpMV cannot
-// lend shared memory to the restriction or to the groups' coarse
-// corrections) restricts r_k itself instead:
+// lend shared memory to the restriction) restricts r_k itself instead:
 //   SpMV -> x/r update with the restriction of r_k -> [mixed: FP64 residual
 //   replacement] -> convergence test on r_k and coarse apply -> level-0
 //   apply, which also bounds the rounding the recurrences accumulate (the
@@ -627,20 +629,25 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
     // state is copied into a pinned slot; the host looks at a batch's copy
     // only once the next batch is queued, so the device never waits for the
     // host.  Kernels queued after a stop return at once.
-    bool split = false;  // z still lacks the coarse corrections (the last apply was launch_apply_rec)
+    bool rec = false;    // the last apply was launch_apply_rec
+    bool split = false;  // ... and z still lacks the coarse corrections
     auto direct = [&](int kk) { return !h->fuse_ok || kk % opt.replace_every == 0; };
     auto batch = [&](int nb) -> int {
         for (int i = 0; i < nb; ++i) {
             ++k;
             if (!direct(k)) {
-                HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, false, true, split, s); }, 2 * k));
+                HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, false, true, rec, split, s); },
+                              2 * k));
                 HIP_TRY(timed(h, kKLevel0Upd, s, [&] { return launch_apply_rec(v, mixed, k, s); }, 2 * k));
-                split = true;
+                rec = true;
+                split = h->split_ok;
+                if (!split) HIP_TRY(timed(h, kKLevel0, s, [&] { return launch_prolong(v, k, mixed, s); }, 2 * k));
                 continue;
             }
             const bool fresh = k % opt.replace_every == 0;
-            HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, fresh, false, split, s); }, 2 * k));
-            split = false;
+            HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, fresh, false, rec, split, s); },
+                          2 * k));
+            rec = split = false;
             HIP_TRY(timed(h, kKUpdate, s, [&] { return launch_update(v, k, s); }, 2 * k));
             bool replaced = false;
             if (mixed && k % opt.replace_every == 0) {
@@ -649,10 +656,9 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
             }
             HIP_TRY(apply_iter(h, v, mixed, k, replaced, s));
         }
-        // a last iteration by recurrence leaves its decision to the next
+        // a last iteration in two launches leaves its decision to the next
         // SpMV: at max_iter, take it here
-        if (k == opt.max_iter && k > 0 && !direct(k))
-            HIP_TRY(launch_decision(v, k, mixed, s));
+        if (k == opt.max_iter && split) HIP_TRY(launch_decision(v, k, mixed, s));
         return MAS_OK;
     };
     int inflight = 0, head = 0, next = 0;  // batch copies not yet looked at; ring slots 1 + (0|1)
@@ -682,7 +688,7 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
         HIP_TRY(launch_clear_stop(v, s));
         HIP_TRY(timed(h, kKResidual, s, [&] { return launch_residual(v, kResidConfirm, v.r, s); }, 2 * k));
         HIP_TRY(apply_iter(h, v, mixed, k, true, s));
-        split = false;
+        rec = split = false;
         if ((rc = read_state(h, v, s)) != MAS_OK) return rc;
         if (st.done || st.status < 0) break;
     }
@@ -743,20 +749,21 @@ namespace {
 
 void set_fusion(mas_handle* h) {
     const Plan& R = h->plan;
-    // two launches per iteration where the SpMV's restriction of q takes
-    // at most two passes of its threads (restrict_passes): on systems whose
-    // groups have many more coarse units (128 rows of the membrane + bodies
-    // system have up to 448 writers), the longer restriction in the SpMV costs
-    // more than the x/r update launch it saves, and every iteration restricts
-    // r directly; and where the groups' coarse corrections fit in the 64 KB of
-    // LDS a workgroup may have beside the rest (groups that read more than
-    // kMaxHalo units have no lists at all)
+    // iterations by recurrence where the SpMV's restriction of q takes at most
+    // two passes of its threads (restrict_passes): on systems whose groups have
+    // many more coarse units (128 rows of the membrane + bodies system have up
+    // to 448 writers), the longer restriction in the SpMV costs more than the
+    // x/r update launch it saves, and every iteration restricts r directly
     h->fuse_ok = sizeof(double) * (3 * static_cast<size_t>(R.RG) + restrict_smem_doubles(R.RG, R.W1, R.L)) <=
                      spmv_restrict_capacity() &&
-                 restrict_passes(R.W1, R.GW, spmv_threads()) > 0 && h->shape.halo &&
-                 spmv_shared_bytes(R.RG, R.maxT, R.sym) +
-                         sizeof(double) * 3 * (std::max(h->shape.maxH, 1) + h->shape.maxH2) <=
-                     (size_t{64} << 10);
+                 restrict_passes(R.W1, R.GW, spmv_threads()) > 0;
+    // in two launches where the groups' coarse corrections fit in the 64 KB of
+    // LDS a workgroup may have beside the rest (if a group reads more than
+    // kMaxHalo units there are no lists at all), else in three
+    h->split_ok = h->fuse_ok && h->shape.halo &&
+                  spmv_shared_bytes(R.RG, R.maxT, R.sym) +
+                          sizeof(double) * 3 * (std::max(h->shape.maxH, 1) + h->shape.maxH2) <=
+                      (size_t{64} << 10);
 }
 
 int analyze_impl(mas_handle* h, int32_t n_rows, int32_t nnzb, const int32_t* row_ptr, const int32_t* col_idx,

@@ -205,7 +205,8 @@ enum ResidMode {
 // C_l r_k = C_l r_{k-1} - alpha_k C_l q_k from the restriction of q_k the SpMV
 // left and the coarse corrections y_l beside x += alpha p, r -= alpha q and
 // z = Inv_0 r; the next SpMV adds the corrections to z where it reads it and
-// takes the decision on r_k.
+// takes the decision on r_k.  Where some group reads more units than the SpMV
+// can stage (Plan::hptr), a third launch does both (launch_prolong).
 enum ApplyMode { kApplyPlain = 0, kApplyInit = 1, kApplyIter = 2 };
 
 // spmv.hip
@@ -214,10 +215,10 @@ hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void
 // iteration k: p_k = z_{k-1} + beta p_{k-1} (p_1 = z_0) into p[k & 1], q_k = H p_k into q[k & 1], sigma
 // partials.  fresh: q_k as the product H p_k itself, else by the recurrence q_k = H z_{k-1} + beta q_{k-1};
 // restrict_q: also the restriction of q to the coarse levels (q1, qpart);
-// split: z_{k-1} is v.z plus the coarse corrections in yall (the previous
-// iteration ran launch_apply_rec), and one workgroup more takes the decision
-// on r_{k-1}
-hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool fresh, bool restrict_q, bool split,
+// rec: the previous iteration ran launch_apply_rec; split: and no
+// launch_prolong, so that z_{k-1} is v.z plus the coarse corrections in yall,
+// and one workgroup more takes the decision on r_{k-1}
+hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool fresh, bool restrict_q, bool rec, bool split,
                           hipStream_t s);
 // Shared memory of the SpMV kernels besides a group's staged corrections
 // (24 bytes for each of maxH units and maxH2 level-2 entries).
@@ -260,6 +261,9 @@ hipError_t launch_apply_plain(const SolverView& v, bool f32, const double* r, do
 // Iteration k by recurrence: x/r update, level 0 and the coarse levels in
 // one launch (see ApplyMode).
 hipError_t launch_apply_rec(const SolverView& v, bool f32, int k, hipStream_t s);
+// After launch_apply_rec: the coarse corrections added to z, and the decision
+// on r_k.
+hipError_t launch_prolong(const SolverView& v, int k, bool mixed, hipStream_t s);
 
 // assemble.hip: block-list assembly (scratch in the caller's workspace).
 struct AsmLayout {

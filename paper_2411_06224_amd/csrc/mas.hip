@@ -1165,6 +1165,24 @@ __global__ void __launch_bounds__(kGroupThreads) k_apply_rec(SolverView v, Coars
     }
 }
 
+// z += the prolongation of every coarse level, a thread per DOF, and the
+// decision on r_k in workgroup 0: the rest of the iteration where the SpMV
+// cannot stage the corrections (launch_prolong).
+__global__ void __launch_bounds__(256) k_prolong(SolverView v, int k, int flags) {
+    __shared__ double buf[256];
+    if (blockIdx.x == 0) {
+        convergence_decision(v, false, k, 0.0, flags, v.GA, 1, buf);
+        return;
+    }
+    const long long e = static_cast<long long>(blockIdx.x - 1) * 256 + threadIdx.x;
+    if (e >= 3LL * v.NS) return;
+    const int slot = static_cast<int>(e / 3), c = static_cast<int>(e - 3LL * slot);
+    Prolong R;
+    prolong_ids(v, R, slot);
+    const double z = v.z[e];
+    v.z[e] = z + prolong_rest(v, prolong_sum(v, R, c), slot, c);  // (unused after a stop)
+}
+
 DomTable make_table(const int* ndom, int first, int L) {
     DomTable t{};
     int acc = 0;
@@ -1295,6 +1313,11 @@ hipError_t launch_apply_plain(const SolverView& v, bool f32, const double* r, do
     if (v.ncb > 0 && (e = launch_apply_coarse(v, f32, kApplyPlain, 0, 0.0, false, f32, false, s)) != hipSuccess)
         return e;
     f32 ? launch_level0_t<float, kApplyPlain>(v, 0, r, z, s) : launch_level0_t<double, kApplyPlain>(v, 0, r, z, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_prolong(const SolverView& v, int k, bool mixed, hipStream_t s) {
+    launch_kernel(k_prolong, dim3(1 + ceil_div(3LL * v.NS, 256)), dim3(256), 0, s, v, k, mixed ? kFlagMixed : 0);
     return hipGetLastError();
 }
 

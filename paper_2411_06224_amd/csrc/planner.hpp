@@ -25,7 +25,7 @@ int group_domains(int M, int N, long long nnzb, long long window_blocks);
 // The SpMV of a two-launch iteration stages the coarse correction of every
 // level-1 unit a group of rows reads (its own and those of the columns
 // outside the group) in LDS: 24 bytes each, so 512 take 12 KB beside the
-// product planes.  A system with a larger group keeps the direct iteration.
+// product planes.  A system with a larger group takes a third launch instead.
 constexpr int kMaxHalo = 512;
 // The group kernels deal workgroup b to XCD b % kXcdCount, each XCD taking a
 // contiguous range of groups (xcd_group on the device).

@@ -666,7 +666,8 @@ __device__ __forceinline__ double dir_stage(const SolverView& v, int k, int g, i
 }
 
 template <typename T, int kRQ, bool kSplit, bool kFresh>
-__global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __restrict__ H, int k, int flags) {
+__global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __restrict__ H, int k, int nrho,
+                                                      int flags) {
     __shared__ double prod[3 * kPlane];
     __shared__ double buf[256];
     extern __shared__ double dyn[];  // xs[3 RG] (+ ycor[3 (maxH + maxH2)])
@@ -681,7 +682,6 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     double* ycor = dyn + 3 * v.RG;
     // every independent load before the first wait, unconditionally at
     // clamped indices (see partials_load); k = 1 has no p_0 and q_0 (beta = 0)
-    const int nrho = kSplit ? v.GA + v.ncb : v.GA;
     const double* pold = k > 1 ? v.p[(k - 1) & 1] : v.z;
     UnitLoads U{};
     if constexpr (kSplit) U = unit_load(v, g);
@@ -712,7 +712,8 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
 
 // k_spmv_pq on the group-symmetric storage.
 template <typename T, int kRQ, bool kSplit, bool kFresh>
-__global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T* __restrict__ H, int k, int flags) {
+__global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T* __restrict__ H, int k, int nrho,
+                                                          int flags) {
     __shared__ double prod[6 * kSymPlane];
     __shared__ double buf[256];
     extern __shared__ double dyn[];  // xs[3 RG] doubles (+ ycor[3 (maxH + maxH2)]) + tl[maxT] ints
@@ -729,7 +730,6 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     int* tl = reinterpret_cast<int*>(ycor + (kSplit ? 3 * (v.maxH + v.maxH2) : 0));
     // loads as in k_spmv_pq, and the group's transposed-entry list, which
     // goes to LDS with the own part
-    const int nrho = kSplit ? v.GA + v.ncb : v.GA;
     const double* pold = k > 1 ? v.p[(k - 1) & 1] : v.z;
     UnitLoads U{};
     if constexpr (kSplit) U = unit_load(v, g);
@@ -834,40 +834,41 @@ hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void
 }
 
 template <int kRQ, bool kSplit, bool kFresh>
-void launch_spmv_pq_t(const SolverView& v, bool f32, int k, hipStream_t s) {
+void launch_spmv_pq_t(const SolverView& v, bool f32, int k, bool rec, hipStream_t s) {
     dim3 g(v.G + (kSplit ? 1 : 0)), b(kThreads);
-    const int flags = f32 ? kFlagMixed : 0;
+    const int flags = f32 ? kFlagMixed : 0, nrho = rec ? v.GA + v.ncb : v.GA;
     const size_t vec = sizeof(double) * 3 * (static_cast<size_t>(v.RG) + (kSplit ? v.maxH + v.maxH2 : 0));
     if (v.sym && !f32) {
         launch_kernel(k_spmv_pq_sym<double, kRQ, kSplit, kFresh>, g, b, vec + sizeof(int) * v.maxT, s, v,
-                      static_cast<const double*>(v.H64), k, flags);
+                      static_cast<const double*>(v.H64), k, nrho, flags);
     } else if (f32) {
         launch_kernel(k_spmv_pq<float, kRQ, kSplit, kFresh>, g, b, vec, s, v, static_cast<const float*>(v.H32), k,
-                      flags);
+                      nrho, flags);
     } else {
         launch_kernel(k_spmv_pq<double, kRQ, kSplit, kFresh>, g, b, vec, s, v, static_cast<const double*>(v.H64), k,
-                      flags);
+                      nrho, flags);
     }
 }
 
 // The forms the solve loop uses: an iteration by recurrence restricts q and
-// forms it by recurrence (z whole after a direct iteration, else split); a
-// direct one does not restrict it, and forms it afresh (every replace_every-th
-// iteration) or by recurrence (the others of a system whose iterations are all
-// direct, z always whole).
-hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool fresh, bool restrict_q, bool split,
+// forms it by recurrence (z whole after a direct iteration or launch_prolong,
+// else split); a direct one does not restrict it, and forms it afresh (every
+// replace_every-th iteration) or by recurrence (the others of a system whose
+// iterations are all direct, z always whole).
+hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool fresh, bool restrict_q, bool rec, bool split,
                           hipStream_t s) {
     static_assert(kMaxRestrictPasses == 2, "one instance per pass count");
     const int rq = restrict_q ? v.rpass : 0;
-    if ((restrict_q && (fresh || rq == 0)) || (!restrict_q && !fresh && split)) return hipErrorInvalidValue;
+    if ((restrict_q && (fresh || rq == 0)) || (!restrict_q && !fresh && rec) || (split && !rec))
+        return hipErrorInvalidValue;
     if (rq == 1) {
-        split ? launch_spmv_pq_t<1, true, false>(v, f32, k, s) : launch_spmv_pq_t<1, false, false>(v, f32, k, s);
+        split ? launch_spmv_pq_t<1, true, false>(v, f32, k, rec, s) : launch_spmv_pq_t<1, false, false>(v, f32, k, rec, s);
     } else if (rq == 2) {
-        split ? launch_spmv_pq_t<2, true, false>(v, f32, k, s) : launch_spmv_pq_t<2, false, false>(v, f32, k, s);
+        split ? launch_spmv_pq_t<2, true, false>(v, f32, k, rec, s) : launch_spmv_pq_t<2, false, false>(v, f32, k, rec, s);
     } else if (fresh) {
-        split ? launch_spmv_pq_t<0, true, true>(v, f32, k, s) : launch_spmv_pq_t<0, false, true>(v, f32, k, s);
+        split ? launch_spmv_pq_t<0, true, true>(v, f32, k, rec, s) : launch_spmv_pq_t<0, false, true>(v, f32, k, rec, s);
     } else {
-        launch_spmv_pq_t<0, false, false>(v, f32, k, s);
+        launch_spmv_pq_t<0, false, false>(v, f32, k, rec, s);
     }
     return hipGetLastError();
 }
