@@ -1,7 +1,8 @@
 """Iterations of systems with a heavy window, with a group that reads more
 units than its list holds (three launches per iteration), and with both,
 against the oracle: eight iterations to 1e-10 relative and mixed solves to the
-residual they confirm, as the tests of the iteration's shapes hold them.  Re-plans between such systems, which
+residual they confirm, as the tests of the iteration's shapes hold them.
+Re-plans between such systems, which
 change the groups and the launches, against the host analysis byte for byte."""
 
 import numpy as np
