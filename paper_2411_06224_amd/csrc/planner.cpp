@@ -525,27 +525,40 @@ void spmv_order(Plan& P) {
 
 // A group is one workgroup of the SpMV: its chunks of blocks follow one
 // another, so where the machine is not full of groups the iteration takes as
-// long as one group's chain.  Up to 640 groups (2.5 per CU) the groups are
-// therefore made smaller, 1, 2 or 4 domains instead of 8; beyond that the
-// launch is bound by what it moves, and larger groups store more pairs once
-// and leave fewer partial sums.  Iteration in us with 1 / 2 / 4 / 8 domains per
-// group (cubes): 308 domains 18.6 / 18.7 / 20.9 / 25.0; 977 domains 22.2 /
-// 20.6 / 22.2 / 26.5; 2,457 domains (mixed) 36.8 / 25.6 / 23.5 / 25.9; 7,354
-// domains 94 / 65 / 55 / 46.
+// long as one group's chain, and smaller groups, of 1, 2 or 4 domains instead of
+// 8, shorten it.  Each workgroup has its prologue, its partial sums and its
+// writers, though, and stores fewer pairs once; and past the number that runs at
+// once (kGroupsPerCu per CU: four of 33 KB of LDS) a second round begins.
+// Iteration in us with 1 / 2 / 4 / 8 domains per group, FP64 and mixed, on both
+// sides of each limit (cubes, * plain grids):
+//   308 domains   18.8 / 19.0 / 21.1 / 25.3,  17.4 / 17.3 / 18.3 / 21.3
+//   400 *         18.4 / 18.0 / 18.1 / 20.8,  17.4 / 16.8 / 16.9 / 18.4
+//   1,372         29.4 / 22.5 / 23.9 / 27.8,  25.5 / 20.0 / 20.3 / 23.0
+//   1,600 *       29.9 / 21.3 / 20.1 / 22.0,  27.8 / 20.0 / 18.0 / 18.7
+//   4,000         60.0 / 44.3 / 33.7 / 35.2,  54.1 / 38.6 / 28.4 / 28.7
+//   4,308         63.6 / 46.1 / 43.0 / 37.2,  56.7 / 40.2 / 30.9 / 29.6
 // Where one window of 128 rows holds more than three times the mean (rows of
 // bodies with many contacts), its chain alone is the iteration: such groups
-// are halved down to 2,048 blocks as long as there are at most 2,200 groups
-// (sheet of 256^2 cells with bodies in contact, 4,254 domains: 65 / 49 / 55 /
-// 69 us with 1 / 2 / 4 / 8).  Other domain sizes keep groups of about 128 rows.
+// are halved down to 1,024 blocks while that leaves no more than kHeavyGroups per
+// CU (sheets with bodies in contact):
+//   822 domains   23.5 / 24.7 / 30.4 / 44.2,  21.7 / 21.4 / 24.9 / 34.2
+//   1,072         25.9 / 27.0 / 32.5 / 45.8,  24.3 / 23.5 / 26.3 / 34.6
+//   5,835         82.3 / 58.6 / 59.4 / 72.0,  74.0 / 52.9 / 52.0 / 59.2
+//   6,636         92.0 / 64.3 / 63.8 / 76.0,  82.6 / 59.1 / 56.0 / 63.2
+//   12,984        209 / 141 / 118.6 / 120.4,  166 / 112 / 88.8 / 88.7
+// Other domain sizes keep groups of about 128 rows.
 int group_domains(int M, int N, long long nnzb, long long window_blocks) {
+    constexpr int kCus = 256;
+    constexpr double kGroupsPerCu[3] = {1.5, 3, 4}, kHeavyGroups[3] = {3.5, 12, 12};  // of 1, 2 and 4 domains
     const int most = std::max(1, kWindowSlots / N);
     if (N != 16) return most;
-    int d = 1;
-    while (d < most && (M + d - 1) / d > 640) d *= 2;
+    auto fits = [&](int i, const double (&per_cu)[3]) { return M <= (1 << i) * kCus * per_cu[i]; };
+    int i = 0;
+    while (i < 3 && !fits(i, kGroupsPerCu)) ++i;
     const int windows = (M + most - 1) / most;
     if (window_blocks * windows > 3 * nnzb)
-        while (d > 1 && window_blocks * d > 2048LL * most && (M + d / 2 - 1) / (d / 2) <= 2200) d /= 2;
-    return d;
+        while (i > 0 && (window_blocks << i) > 1024LL * most && fits(i - 1, kHeavyGroups)) --i;
+    return 1 << i;
 }
 
 std::vector<int> spmv_group_order(const std::vector<long long>& cnt) {

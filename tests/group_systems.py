@@ -42,3 +42,16 @@ def system(name):
     s = synth.bcsr.spd_system_from_edges(n, e, seed=n + hub + clique)
     s.gptr, s.gadj = synth.bcsr.graph_from_edges(n, grid)  # the couplings come later than the partition
     return s
+
+
+# nodes of a line, 16 to a domain -> domains per group: both sides of 384,
+# 1,536 and 4,096 domains
+EDGES = [(6144, 1), (6160, 2), (24576, 2), (24592, 4), (65536, 4), (65552, 8)]
+
+
+@functools.lru_cache(maxsize=2)
+def line(n):
+    """A line with some second neighbours."""
+    i = np.arange(n)
+    e = np.concatenate([np.stack([i[:-1], i[1:]], 1), np.stack([i[:-5:3], i[5::3]], 1)])
+    return synth.bcsr.spd_system_from_edges(n, e, seed=n)

@@ -1,16 +1,16 @@
 """Iterations of systems with a heavy window, with a group that reads more
-units than its list holds (three launches per iteration), and with both,
-against the oracle: eight iterations to 1e-10 relative and mixed solves to the
-residual they confirm, as the tests of the iteration's shapes hold them.
-Re-plans between such systems, which
+units than its list holds (three launches per iteration), with both, and at
+the domain counts where the groups grow, against the oracle: eight iterations
+to 1e-10 relative and mixed solves to the residual they confirm, as the tests
+of the iteration's shapes hold them.  Re-plans between such systems, which
 change the groups and the launches, against the host analysis byte for byte."""
 
 import numpy as np
 import pytest
 
 import oracle
-from group_systems import SYSTEMS, system
-from test_gpu_replan import _compare, _same_bytes
+from group_systems import EDGES, SYSTEMS, line, system
+from test_gpu_replan import _compare
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -49,6 +49,25 @@ def test_iterates(name):
             x = x.cpu().numpy()
             assert np.linalg.norm(s.b - oracle.spmv(s.row_ptr, s.col_idx, s.val, x)) <= 1e-7 * np.linalg.norm(s.b)
         S.close()
+
+
+@pytest.mark.parametrize("n,domains", EDGES)
+def test_group_size_edges(n, domains):
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2411_06224_amd as mp
+
+    print("[case]", n, domains, flush=True)
+    s = line(n)
+    P = oracle.MAS(s.row_ptr, s.col_idx, s.val, N=16, gptr=s.gptr, gadj=s.gadj)
+    S = mp.MasPcg(s.row_ptr, s.col_idx, graph=(s.gptr, s.gadj), poison=True)
+    H = mp.BlockMatrix.from_numpy(s.row_ptr, s.col_idx, s.val, device="cuda:0")
+    S.build(H)
+    want = P.pcg(s.b, tol=0.0, max_iter=8)[0]
+    x, res = S.solve(H, torch.as_tensor(s.b, device="cuda:0"), tol=0.0, max_iter=8)
+    assert res["iterations"] == 8
+    assert np.linalg.norm(x.cpu().numpy() - want) <= 1e-10 * np.linalg.norm(want)
+    S.close()
 
 
 @pytest.mark.parametrize("precision", ["f64", "mixed"])

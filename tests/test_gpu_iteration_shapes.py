@@ -1,10 +1,9 @@
 """The iteration's kernels and the domain inversion at the sizes where their
 splits change -- one domain, an odd number (the last pair half empty), a
-remainder of a workgroup's four, one and two levels, the domain counts at
-which the work groups grow (640, 1,280, 2,560), far couplings and one row of
-many blocks (fewer domains than the rule halves groups of, and fewer units
-than the lists hold: those are in test_gpu_group_branches) -- against the
-oracle.
+remainder of a workgroup's four, one and two levels, some hundred to some
+thousand domains, far couplings and one row of many blocks -- against the
+oracle.  (Where the work groups grow, and groups halved for a heavy window or
+reading more units than their lists hold: test_gpu_group_branches.)
 
 Iterates: as the parity tests hold ten iterations to 1e-10 relative, eight
 here (rounding of a step, about 1e-15 sqrt(3 n) in the dot products, grows by

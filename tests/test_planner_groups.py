@@ -9,7 +9,7 @@ import subprocess
 import numpy as np
 import pytest
 
-from group_systems import SYSTEMS, system
+from group_systems import EDGES, SYSTEMS, line, system
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2411_06224_amd", "csrc")
@@ -59,3 +59,10 @@ def test_group_branches(probe, name):
     assert bool(P["halo"]) == SYSTEMS[name][2]
     # at most two passes of 256 threads over the group's writers: by recurrence
     assert P["W1"] <= 64 and 3 * P["GW"] <= 512
+
+
+@pytest.mark.parametrize("n,domains", EDGES)
+def test_group_size_edges(probe, n, domains):
+    P = probe(line(n))
+    assert P["M"] == n // 16
+    assert P["D0"] == domains and P["halo"] == 1
