@@ -7,10 +7,13 @@
 
 namespace maspcg {
 
-// Host-visible scalars of one PCG solve in device memory.  Only block 0 of
-// the kernel that decides a value writes it; the values the iteration itself
-// needs (alpha, beta, rho, sigma, ||r||^2) are recomputed by every consumer
-// block from per-group partial sums, so no kernel waits on another block.
+// Host-visible scalars of one PCG solve in device memory.  Each has one writer
+// in a launch: the workgroup that takes the decision (workgroup 0, or the one
+// after the groups in the SpMV of a two-launch iteration), the workgroup of
+// group 0 for rho, that of the first domains for a breakdown.  The values the
+// iteration itself needs (alpha, beta, rho, sigma, ||r||^2) are recomputed by
+// every consumer block from per-group partial sums, so no kernel waits on
+// another block.
 struct DevState {
     double rr;       // ||r||^2 used by the last convergence test
     double bb;       // ||b||^2
@@ -30,6 +33,18 @@ constexpr int kStatusConvergedRecurrence = 2;
 // see it is a race), so what they write does not depend on it.
 __host__ __device__ constexpr int spmv_mark(int k) { return k + 2; }
 
+// Whether an earlier launch has stopped the solve, from the stop flag that the
+// SpMV of iteration k read (uniform_load, beside its other loads).  With the
+// decision beside it (kSplit) the flag may change from 0 to spmv_mark(k) while
+// the launch runs; both mean no.  The flag is of use for this question alone:
+// the value read is taken here once, so that the compiler, which is told that
+// it does not change, has no reason to read it again.
+template <bool kSplit>
+__device__ __forceinline__ bool stopped_before(int flag, int k) {
+    asm volatile("" : "+s"(flag));
+    return flag != 0 && !(kSplit && flag == spmv_mark(k));
+}
+
 // ------------------------------------------------------------ XCD placement
 
 // The dispatcher deals workgroups to the 8 XCDs round-robin (workgroup b runs
@@ -46,10 +61,10 @@ __host__ __device__ inline int xcd_group(int b, int G) {
 }
 
 // *p at an address that is the same in the whole wave, of memory that the
-// launch does not write (plan arrays, scalars of earlier launches), as a
-// scalar load.  The compiler proves neither once a kernel has stores on
-// another path; as a vector load such a value waits for every load issued
-// before it.
+// launch does not write (plan arrays, scalars of earlier launches; the one
+// exception is the stop flag, see stopped_before), as a scalar load.  The
+// compiler proves neither once a kernel has stores on another path; as a
+// vector load such a value waits for every load issued before it.
 template <typename T>
 __device__ __forceinline__ T uniform_load(const T* p) {
     return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));

@@ -700,7 +700,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     if constexpr (kRQ) pl = restrict_load<kRQ>(v, g);
     const int stop = uniform_load(&v.st->done);
     keep_loads_issued();
-    if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
+    if (stopped_before<kSplit>(stop, k)) return;  // after a stop nothing is written
     const double rk2 = uniform_load(&v.st->rho[k & 1]);  // rho_{k-2} as the previous SpMV recorded it
     if constexpr (kSplit) unit_gather(v, U);
     double pv[2], acc[2];
@@ -753,7 +753,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     if constexpr (kRQ) pl = restrict_load<kRQ>(v, g);
     const int stop = uniform_load(&v.st->done);
     keep_loads_issued();
-    if (stop && !(kSplit && stop == spmv_mark(k))) return;  // after a stop nothing is written
+    if (stopped_before<kSplit>(stop, k)) return;  // after a stop nothing is written
     const double rk2 = uniform_load(&v.st->rho[k & 1]);  // rho_{k-2} as the previous SpMV recorded it
     if constexpr (kSplit) unit_gather(v, U);
 #pragma unroll
