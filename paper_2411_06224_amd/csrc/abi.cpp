@@ -30,7 +30,7 @@ struct Layout {
     size_t red_ptr[kMaxLv], red_src[kMaxLv], dom_ptr[kMaxLv], dom_blk[kMaxLv], dom_ab[kMaxLv];
     size_t ganc, gpos, gmask, cp_ptr[kMaxLv], lmask, gorder, gu1_slot, gu1_mask, gw_pos, gw_li, gw_mask, hptr, hu, h2ptr, hy, hpar, hidx;
     size_t H64, H32, A[kMaxLv], inv64[kMaxLv], inv32[kMaxLv];
-    size_t b, x, r, z, p0, p1, qv0, qv1, r1, q1, yall, y[kMaxLv], rc[kMaxLv], cpart, qpart, P_sigma, P_rr, P_bb, P_rho0, P_rho1, st, flag;
+    size_t b, x, r, z, p0, p1, q, r1, q1, yall, y[kMaxLv], rc[kMaxLv], cpart, qpart, P_sigma, P_rr, P_bb, P_rho0, P_rho1, st, flag;
     size_t inverse_bytes = 0;
 
     size_t take(size_t bytes) {
@@ -257,8 +257,7 @@ void make_layout(mas_handle* h) {
     Y.z = Y.take(vec);
     Y.p0 = Y.take(vec);
     Y.p1 = Y.take(vec);
-    Y.qv0 = Y.take(vec);
-    Y.qv1 = Y.take(vec);
+    Y.q = Y.take(vec);
     Y.r1 = Y.take(Dd * 3 * (P.L > 1 ? P.units[1] : 1));
     Y.q1 = Y.take(Dd * 3 * (P.L > 1 ? P.units[1] : 1));
     // the coarse corrections of all levels end to end (one index reaches any)
@@ -364,8 +363,7 @@ SolverView view(const mas_handle* h) {
     v.z = at<double>(h, Y.z);
     v.p[0] = at<double>(h, Y.p0);
     v.p[1] = at<double>(h, Y.p1);
-    v.q[0] = at<double>(h, Y.qv0);
-    v.q[1] = at<double>(h, Y.qv1);
+    v.q = at<double>(h, Y.q);
     v.r1 = at<double>(h, Y.r1);
     v.q1 = at<double>(h, Y.q1);
     v.st = at<DevState>(h, Y.st);
@@ -579,19 +577,18 @@ int read_state(mas_handle* h, const SolverView& v, hipStream_t s) {
 
 // The PCG driver shared by pcg_solve and pcg_adjoint.  Iteration k takes
 // two launches:
-//   p = z + beta p, q = H z + beta q (sigma partials), the restriction of q
-//   and the convergence test on r_{k-1} ->
+//   p = z + beta p, q = H p (sigma partials), the restriction of q and the
+//   convergence test on r_{k-1} ->
 //   alpha, x += alpha p, r -= alpha q (||r||^2 partials), the level-0 apply
 //   and, beside it, C_l r_k = C_l r_{k-1} - alpha C_l q_k and the coarse apply
 //   (rho partials of both); the prolongation follows in the next SpMV (or,
 //   where the SpMV cannot lend shared memory to the groups' coarse
 //   corrections, in a third launch, with the convergence test on r_k);
-// every replace_every-th iteration (and every iteration when the SpMV cannot
-// lend shared memory to the restriction) restricts r_k itself instead:
+// every replace_every-th iteration (and every one when the SpMV cannot lend
+// shared memory to the restriction) restricts r_k itself instead:
 //   SpMV -> x/r update with the restriction of r_k -> [mixed: FP64 residual
 //   replacement] -> convergence test on r_k and coarse apply -> level-0
-//   apply, which also bounds the rounding the recurrences accumulate (the
-//   product of every replace_every-th iteration is q = H p itself).
+//   apply, which also bounds the rounding the recurrence accumulates.
 // The host reads the state every check_every iterations; iterations queued
 // after a stop return at once.
 int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, const pcg_options* o, pcg_result* res,
@@ -636,7 +633,7 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
         for (int i = 0; i < nb; ++i) {
             ++k;
             if (!direct(k)) {
-                HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, false, true, rec, split, s); },
+                HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, true, rec, split, s); },
                               2 * k));
                 HIP_TRY(timed(h, kKLevel0Upd, s, [&] { return launch_apply_rec(v, mixed, k, s); }, 2 * k));
                 rec = true;
@@ -644,8 +641,7 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
                 if (!split) HIP_TRY(timed(h, kKLevel0, s, [&] { return launch_prolong(v, k, mixed, s); }, 2 * k));
                 continue;
             }
-            const bool fresh = k % opt.replace_every == 0;
-            HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, fresh, false, rec, split, s); },
+            HIP_TRY(timed(h, kKSpmv, s, [&] { return launch_spmv_pq(v, mixed, k, false, rec, split, s); },
                           2 * k));
             rec = split = false;
             HIP_TRY(timed(h, kKUpdate, s, [&] { return launch_update(v, k, s); }, 2 * k));
@@ -695,7 +691,7 @@ int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, con
     if ((rc = read_state(h, v, s)) != MAS_OK) return rc;
     if (st.bb == 0.0)  // b = 0: the solution is x = b = 0 (also when an x0 was given)
         HIP_TRY(hipMemcpyAsync(v.x, v.b, sizeof(double) * 3 * v.NS, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(launch_residual(v, kResidFinal, v.q[0], s));
+    HIP_TRY(launch_residual(v, kResidFinal, v.q, s));
     HIP_TRY(launch_finalize(v, s));
     HIP_TRY(launch_perm_out(v, v.x, x, s));
     HIP_TRY(hipEventRecord(h->ev[kEvSolve2], s));
@@ -867,8 +863,8 @@ int mas_apply(mas_handle* h, const double* r, double* z, void* stream) {
     const size_t bytes = sizeof(double) * 3 * static_cast<size_t>(h->plan.V);
     const uintptr_t ra = reinterpret_cast<uintptr_t>(r), za = reinterpret_cast<uintptr_t>(z);
     const bool shared = ra < za + bytes && za < ra + bytes;
-    HIP_TRY(launch_apply_plain(v, mixed, r, shared ? v.q[0] : z, s));
-    if (shared) HIP_TRY(hipMemcpyAsync(z, v.q[0], bytes, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(launch_apply_plain(v, mixed, r, shared ? v.q : z, s));
+    if (shared) HIP_TRY(hipMemcpyAsync(z, v.q, bytes, hipMemcpyDeviceToDevice, s));
     return MAS_OK;
 }
 

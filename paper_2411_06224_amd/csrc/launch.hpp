@@ -92,8 +92,8 @@ struct SolverView {
     double* inv64[kMaxLv];
     float* inv32[kMaxLv];
     // vectors in slot order (3*NS doubles)
-    double *b, *x, *r, *z;
-    double *p[2], *q[2];  // search direction p_k lives in p[k & 1], q_k = H p_k in q[k & 1]
+    double *b, *x, *r, *z, *q;
+    double* p[2];  // search direction p_k lives in p[k & 1]
     // coarse vectors: r1 [3*units[1]], y_l [3*ndom[l]*N] for l >= 1, coarse partials [3*n_cpart]
     double* r1;
     double* y[kMaxLv];  // laid end to end from yall
@@ -212,13 +212,12 @@ enum ApplyMode { kApplyPlain = 0, kApplyInit = 1, kApplyIter = 2 };
 // spmv.hip
 hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void* val, bool f32, const double* x,
                             double* y, hipStream_t s);
-// iteration k: p_k = z_{k-1} + beta p_{k-1} (p_1 = z_0) into p[k & 1], q_k = H p_k into q[k & 1], sigma
-// partials.  fresh: q_k as the product H p_k itself, else by the recurrence q_k = H z_{k-1} + beta q_{k-1};
+// iteration k: p_k = z_{k-1} + beta p_{k-1} (p_1 = z_0) into p[k & 1], q = H p_k, sigma partials.
 // restrict_q: also the restriction of q to the coarse levels (q1, qpart);
 // rec: the previous iteration ran launch_apply_rec; split: and no
 // launch_prolong, so that z_{k-1} is v.z plus the coarse corrections in yall,
 // and one workgroup more takes the decision on r_{k-1}
-hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool fresh, bool restrict_q, bool rec, bool split,
+hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool restrict_q, bool rec, bool split,
                           hipStream_t s);
 // Shared memory of the SpMV kernels besides a group's staged corrections
 // (24 bytes for each of maxH units and maxH2 level-2 entries).

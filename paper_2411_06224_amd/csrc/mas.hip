@@ -1075,7 +1075,7 @@ __global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_rec_pairs(So
     int e[2];
     bool own[2];
     double xv[2], pv[2], ro[2], qv[2];
-    const double *pk = v.p[k & 1], *qk = v.q[k & 1];
+    const double *pk = v.p[k & 1], *qk = v.q;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         e[q] = 96 * p + pair_row(lane, q);
@@ -1136,7 +1136,7 @@ __global__ void __launch_bounds__(kGroupThreads) k_apply_rec(SolverView v, Coars
     const bool live = t < nd * n;
     const long long i = 3LL * g * v.RG + (live ? t : 0);
     const RecLoads R = rec_load(v, k);
-    const double xv = v.x[i], pv = v.p[k & 1][i], ro = v.r[i], qv = v.q[k & 1][i];
+    const double xv = v.x[i], pv = v.p[k & 1][i], ro = v.r[i], qv = v.q[i];
     const int stop = v.st->done;
     keep_loads_issued();
     if (stop) return;

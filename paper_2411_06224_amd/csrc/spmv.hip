@@ -82,21 +82,14 @@ struct Blocks {
     }
 };
 
-// The vector H multiplies: x itself, z (kSplit: with its coarse correction
+// The vector H multiplies: x itself, or the new search direction z + beta p
+// formed on the fly from the previous one (kSplit: z with its coarse correction
 // still to be added, staged in LDS at the group's local unit h / 3 of the
-// column), or the new search direction z + beta p formed on the fly from the
-// previous one.
+// column).
 struct XVec {
     static constexpr bool kUnits = false;
     const double* __restrict__ x;
     __device__ __forceinline__ double at(int i, int) const { return x[i]; }
-};
-template <bool kSplit>
-struct XZ {
-    static constexpr bool kUnits = kSplit;
-    const double* __restrict__ z;
-    const double* ycor;  // LDS, 3 per local unit
-    __device__ __forceinline__ double at(int i, int h) const { return kSplit ? z[i] + ycor[h] : z[i]; }
 };
 template <bool kSplit>
 struct XDir {
@@ -602,12 +595,12 @@ constexpr int kRhoPer = 8;  // rho partials a thread loads ahead: up to 2048 in 
 // the partials; p_1 = z_0) on the group's own slots, q_k = H p_k and the
 // partial of p_k^T q_k.
 //
-// q_k is formed by the recurrence q_k = H z_{k-1} + beta q_{k-1}, which needs
-// of the columns outside the group z alone: half the gathers of z + beta p.
-// Every replace_every-th iteration (kFresh) forms H p_k itself, which ends the
-// rounding that the recurrence carries on; there the direction is staged in
-// LDS on the group's own slots and formed wherever H gathers it, with the same
-// beta and the same fused multiply-add, so the same bits, in every workgroup.
+// The direction is staged in LDS on the group's own slots and formed wherever H
+// gathers it, with the same beta and the same fused multiply-add, so the same
+// bits, in every workgroup.  (Formed by the recurrence q_k = H z_{k-1} + beta
+// q_{k-1}, which gathers z alone, the product takes 1.4 us less at 48^3, but
+// what it carries on costs the solution of a sheet with bodies up to 20 times
+// its accuracy, even with q formed afresh every 50 iterations.)
 //
 // kSplit: z_{k-1} = v.z + the coarse corrections, which the level-0 apply left
 // out so that it need not wait for the coarse levels.  A group reads few
@@ -615,13 +608,12 @@ constexpr int kRhoPer = 8;  // rho partials a thread loads ahead: up to 2048 in 
 // (unit_stage); an outside column then costs one 16-bit index and three LDS
 // reads more.
 struct DirLoads {
-    double z[2], p[2], q[2];
+    double z[2], p[2];
     int unit[2];
 };
 
-template <bool kSplit, bool kFresh>
-__device__ __forceinline__ DirLoads dir_load(const SolverView& v, int g, int r0, int nown, const double* pold,
-                                             const double* qold) {
+template <bool kSplit>
+__device__ __forceinline__ DirLoads dir_load(const SolverView& v, int g, int r0, int nown, const double* pold) {
     DirLoads D;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -629,15 +621,14 @@ __device__ __forceinline__ DirLoads dir_load(const SolverView& v, int g, int r0,
         const long long e = 3LL * r0 + o;
         D.z[q] = v.z[e];
         D.p[q] = pold[e];
-        D.q[q] = kFresh ? 0.0 : qold[e];
         D.unit[q] = kSplit ? own_unit(v, g, r0 + o / 3) : -1;
     }
     return D;
 }
 
-// rho_{k-1} and beta, the own part of the vector H multiplies in xs and p_k
-// stored; pv: p_k at the thread's rows.  Ends with a barrier.
-template <bool kSplit, bool kFresh>
+// rho_{k-1} and beta, the own part of p_k in xs and stored; pv: p_k at the
+// thread's rows.  Ends with a barrier.
+template <bool kSplit>
 __device__ __forceinline__ double dir_stage(const SolverView& v, int k, int g, int r0, int nown, DirLoads& D,
                                             const PartialLoads<kSplit ? kRhoPer : 4>& rl, int nrho, double rk2,
                                             const UnitLoads& U, double* ycor, double* xs, double* buf,
@@ -659,21 +650,20 @@ __device__ __forceinline__ double dir_stage(const SolverView& v, int k, int g, i
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int o = t + q * kThreads;
-        double z = 0.0;
         pv[q] = 0.0;
         if (o < nown) {
-            z = D.z[q];
+            double z = D.z[q];
             if (kSplit && D.unit[q] >= 0) z += ycor[3 * D.unit[q] + o % 3];
             pv[q] = __fma_rn(beta, D.p[q], z);
             pk[3LL * r0 + o] = pv[q];
         }
-        if (o < 3 * v.RG) xs[o] = kFresh ? pv[q] : z;
+        if (o < 3 * v.RG) xs[o] = pv[q];
     }
     __syncthreads();
     return beta;
 }
 
-template <typename T, int kRQ, bool kSplit, bool kFresh>
+template <typename T, int kRQ, bool kSplit>
 __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __restrict__ H, int k, int nrho,
                                                       int flags) {
     __shared__ double prod[3 * kPlane];
@@ -689,12 +679,12 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     double* xs = dyn;
     double* ycor = dyn + 3 * v.RG;
     // every independent load before the first wait, unconditionally at
-    // clamped indices (see partials_load); k = 1 has no p_0 and q_0 (beta = 0)
+    // clamped indices (see partials_load); k = 1 has no p_0 (beta = 0)
     const double* pold = k > 1 ? v.p[(k - 1) & 1] : v.z;
     UnitLoads U{};
     if constexpr (kSplit) U = unit_load(v, g);
     const auto rl = partials_load<kSplit ? kRhoPer : 4>(v.P_rho[(k - 1) & 1], nrho);
-    DirLoads D = dir_load<kSplit, kFresh>(v, g, r0, nown, pold, k > 1 ? v.q[(k - 1) & 1] : v.z);
+    DirLoads D = dir_load<kSplit>(v, g, r0, nown, pold);
     const ChunkCols c0 = chunk_cols<kSplit>(v.ci0, uniform_load(v.rp0 + r0), uniform_load(v.rp0 + r1), v.hidx);
     RestrictLoads<kRQ ? kRQ : 1> pl{};
     if constexpr (kRQ) pl = restrict_load<kRQ>(v, g);
@@ -704,22 +694,15 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     const double rk2 = uniform_load(&v.st->rho[k & 1]);  // rho_{k-2} as the previous SpMV recorded it
     if constexpr (kSplit) unit_gather(v, U);
     double pv[2], acc[2];
-    const double beta = dir_stage<kSplit, kFresh>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv);
+    const double beta = dir_stage<kSplit>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv);
     const Blocks<T, true> Hb{H, v.nnzb};
-    if constexpr (kFresh) {
-        stream_rows<T, true, XDir<kSplit>, true>(v.rp0, v.ci0, Hb, XDir<kSplit>{v.z, pold, beta, ycor}, r0, r1, prod,
-                                                 acc, c0, xs, v.hidx);
-    } else {
-        stream_rows<T, true, XZ<kSplit>, true>(v.rp0, v.ci0, Hb, XZ<kSplit>{v.z, ycor}, r0, r1, prod, acc, c0, xs,
-                                               v.hidx);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) acc[q] = __fma_rn(beta, D.q[q], acc[q]);
-    }
-    finish_pq<kRQ>(v, g, nown, r0, v.q[k & 1], acc, pv, prod, buf, pl);
+    stream_rows<T, true, XDir<kSplit>, true>(v.rp0, v.ci0, Hb, XDir<kSplit>{v.z, pold, beta, ycor}, r0, r1, prod, acc,
+                                             c0, xs, v.hidx);
+    finish_pq<kRQ>(v, g, nown, r0, v.q, acc, pv, prod, buf, pl);
 }
 
 // k_spmv_pq on the group-symmetric storage.
-template <typename T, int kRQ, bool kSplit, bool kFresh>
+template <typename T, int kRQ, bool kSplit>
 __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T* __restrict__ H, int k, int nrho,
                                                           int flags) {
     __shared__ double prod[6 * kSymPlane];
@@ -742,7 +725,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     UnitLoads U{};
     if constexpr (kSplit) U = unit_load(v, g);
     const auto rl = partials_load<kSplit ? kRhoPer : 4>(v.P_rho[(k - 1) & 1], nrho);
-    DirLoads D = dir_load<kSplit, kFresh>(v, g, r0, nown, pold, k > 1 ? v.q[(k - 1) & 1] : v.z);
+    DirLoads D = dir_load<kSplit>(v, g, r0, nown, pold);
     const int tb0 = uniform_load(v.tptr + r0), tn = uniform_load(v.tptr + r1) - tb0;
     const int* tsrc = tn > 0 ? v.tidx + tb0 : v.srp;  // srp: a stand-in with entries when the list is empty
     int tlr[kTlRegs];
@@ -761,15 +744,9 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
         if (t + j * kThreads < tn) tl[t + j * kThreads] = tlr[j];
     for (int e = t + kTlRegs * kThreads; e < tn; e += kThreads) tl[e] = v.tidx[tb0 + e];
     double pv[2], acc[2];
-    const double beta = dir_stage<kSplit, kFresh>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv);
-    if constexpr (kFresh) {
-        stream_sym<T>(v, H, XDir<kSplit>{v.z, pold, beta, ycor}, xs, tl, tb0, r0, r1, prod, acc, c0);
-    } else {
-        stream_sym<T>(v, H, XZ<kSplit>{v.z, ycor}, xs, tl, tb0, r0, r1, prod, acc, c0);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) acc[q] = __fma_rn(beta, D.q[q], acc[q]);
-    }
-    finish_pq<kRQ>(v, g, nown, r0, v.q[k & 1], acc, pv, prod, buf, pl);
+    const double beta = dir_stage<kSplit>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv);
+    stream_sym<T>(v, H, XDir<kSplit>{v.z, pold, beta, ycor}, xs, tl, tb0, r0, r1, prod, acc, c0);
+    finish_pq<kRQ>(v, g, nown, r0, v.q, acc, pv, prod, buf, pl);
 }
 
 // out = b - H x in FP64 over a group, with the partials of ||out||^2 (and
@@ -841,42 +818,34 @@ hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void
     return hipGetLastError();
 }
 
-template <int kRQ, bool kSplit, bool kFresh>
+template <int kRQ, bool kSplit>
 void launch_spmv_pq_t(const SolverView& v, bool f32, int k, bool rec, hipStream_t s) {
     dim3 g(v.G + (kSplit ? 1 : 0)), b(kThreads);
     const int flags = f32 ? kFlagMixed : 0, nrho = rec ? v.GA + v.ncb : v.GA;
     const size_t vec = sizeof(double) * 3 * (static_cast<size_t>(v.RG) + (kSplit ? v.maxH + v.maxH2 : 0));
     if (v.sym && !f32) {
-        launch_kernel(k_spmv_pq_sym<double, kRQ, kSplit, kFresh>, g, b, vec + sizeof(int) * v.maxT, s, v,
+        launch_kernel(k_spmv_pq_sym<double, kRQ, kSplit>, g, b, vec + sizeof(int) * v.maxT, s, v,
                       static_cast<const double*>(v.H64), k, nrho, flags);
     } else if (f32) {
-        launch_kernel(k_spmv_pq<float, kRQ, kSplit, kFresh>, g, b, vec, s, v, static_cast<const float*>(v.H32), k,
+        launch_kernel(k_spmv_pq<float, kRQ, kSplit>, g, b, vec, s, v, static_cast<const float*>(v.H32), k,
                       nrho, flags);
     } else {
-        launch_kernel(k_spmv_pq<double, kRQ, kSplit, kFresh>, g, b, vec, s, v, static_cast<const double*>(v.H64), k,
+        launch_kernel(k_spmv_pq<double, kRQ, kSplit>, g, b, vec, s, v, static_cast<const double*>(v.H64), k,
                       nrho, flags);
     }
 }
 
-// The forms the solve loop uses: an iteration by recurrence restricts q and
-// forms it by recurrence (z whole after a direct iteration or launch_prolong,
-// else split); a direct one does not restrict it, and forms it afresh (every
-// replace_every-th iteration) or by recurrence (the others of a system whose
-// iterations are all direct, z always whole).
-hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool fresh, bool restrict_q, bool rec, bool split,
+hipError_t launch_spmv_pq(const SolverView& v, bool f32, int k, bool restrict_q, bool rec, bool split,
                           hipStream_t s) {
     static_assert(kMaxRestrictPasses == 2, "one instance per pass count");
     const int rq = restrict_q ? v.rpass : 0;
-    if ((restrict_q && (fresh || rq == 0)) || (!restrict_q && !fresh && rec) || (split && !rec))
-        return hipErrorInvalidValue;
+    if ((restrict_q && rq == 0) || (split && !rec)) return hipErrorInvalidValue;
     if (rq == 1) {
-        split ? launch_spmv_pq_t<1, true, false>(v, f32, k, rec, s) : launch_spmv_pq_t<1, false, false>(v, f32, k, rec, s);
+        split ? launch_spmv_pq_t<1, true>(v, f32, k, rec, s) : launch_spmv_pq_t<1, false>(v, f32, k, rec, s);
     } else if (rq == 2) {
-        split ? launch_spmv_pq_t<2, true, false>(v, f32, k, rec, s) : launch_spmv_pq_t<2, false, false>(v, f32, k, rec, s);
-    } else if (fresh) {
-        split ? launch_spmv_pq_t<0, true, true>(v, f32, k, rec, s) : launch_spmv_pq_t<0, false, true>(v, f32, k, rec, s);
+        split ? launch_spmv_pq_t<2, true>(v, f32, k, rec, s) : launch_spmv_pq_t<2, false>(v, f32, k, rec, s);
     } else {
-        launch_spmv_pq_t<0, false, false>(v, f32, k, rec, s);
+        split ? launch_spmv_pq_t<0, true>(v, f32, k, rec, s) : launch_spmv_pq_t<0, false>(v, f32, k, rec, s);
     }
     return hipGetLastError();
 }

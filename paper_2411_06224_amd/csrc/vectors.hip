@@ -128,7 +128,7 @@ __global__ void k_update(SolverView v, int k) {
     const bool own = t < 3 * v.RG && i < 3LL * v.NS;
     const long long ic = own ? i : 0;  // unconditional loads (see partials_load)
     const double* pk = v.p[k & 1];
-    const double xv = v.x[ic], pv = pk[ic], rv0 = v.r[ic], qv = v.q[k & 1][ic];
+    const double xv = v.x[ic], pv = pk[ic], rv0 = v.r[ic], qv = v.q[ic];
     const RestrictLoads<kUpdatePasses> pl = restrict_load<kUpdatePasses>(v, g);
     const int stop = v.st->done;
     keep_loads_issued();

@@ -1,0 +1,50 @@
+"""The residual that a solve attains when it goes on past rounding (tol 0,
+1,000 iterations): the true residual b - H x against the oracle's.  Both are
+sums of the roundings of the same products and updates in another order, which
+moves the sum by a small factor (0.8 to 1.3 between summation orders): 3 times
+the oracle's is allowed.  A recurrence that carries rounding on from one
+iteration to the next shows up as more."""
+
+import functools
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+SYSTEMS = {
+    "membrane_24": lambda: synth.membrane_system(24, 30, seed=3),
+    "membrane_48": lambda: synth.membrane_system(48, 60, seed=3),
+    "membrane_64": lambda: synth.membrane_system(64, 60, seed=1003),
+    "cube_8": lambda: synth.cube_system(8, 1e6, 0.45, seed=5),
+    "random": lambda: synth.bcsr.random_spd_system(3000, 9000, 4),
+}
+
+
+@functools.lru_cache(maxsize=None)
+def _case(name):
+    s = SYSTEMS[name]()
+    P = oracle.MAS(s.row_ptr, s.col_idx, s.val, N=16, gptr=s.gptr, gadj=s.gadj)
+    return s, P.pcg(s.b, tol=0.0, max_iter=1000)[4]
+
+
+@pytest.mark.parametrize("every", [1, 50])
+@pytest.mark.parametrize("name", list(SYSTEMS))
+def test_attained_residual(name, every):
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2411_06224_amd as mp
+
+    print("[case]", name, every, flush=True)
+    s, want = _case(name)
+    S = mp.MasPcg(s.row_ptr, s.col_idx, graph=(s.gptr, s.gadj), poison=True)
+    H = mp.BlockMatrix.from_numpy(s.row_ptr, s.col_idx, s.val, device="cuda:0")
+    S.build(H)
+    x, _ = S.solve(H, torch.as_tensor(s.b, device="cuda:0"), tol=0.0, max_iter=1000, replace_every=every)
+    r = s.b - oracle.spmv(s.row_ptr, s.col_idx, s.val, x.cpu().numpy())
+    assert np.linalg.norm(r) <= 3 * want * np.linalg.norm(s.b)
+    S.close()
