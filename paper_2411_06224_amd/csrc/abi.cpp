@@ -30,7 +30,7 @@ struct Layout {
     size_t red_ptr[kMaxLv], red_src[kMaxLv], dom_ptr[kMaxLv], dom_blk[kMaxLv], dom_ab[kMaxLv];
     size_t ganc, gpos, gmask, cp_ptr[kMaxLv], lmask, gorder, gu1_slot, gu1_mask, gw_pos, gw_li, gw_mask, hptr, hu, h2ptr, hy, hpar, hidx;
     size_t H64, H32, A[kMaxLv], inv64[kMaxLv], inv32[kMaxLv];
-    size_t b, x, r, z, p0, p1, q, r1, q1, yall, y[kMaxLv], rc[kMaxLv], cpart, qpart, P_sigma, P_rr, P_bb, P_rho0, P_rho1, st, flag;
+    size_t b, x, r, z, p0, p1, q, r1, q1, yall, y[kMaxLv], rc[kMaxLv], cpart, qpart, P_sp, P_rr, P_bb, P_rho0, P_rho1, st, flag;
     size_t inverse_bytes = 0;
 
     size_t take(size_t bytes) {
@@ -271,7 +271,7 @@ void make_layout(mas_handle* h) {
     for (int l = 2; l < P.L; ++l) Y.rc[l] = Y.take(Dd * 3 * static_cast<size_t>(P.ndom[l]) * P.N);
     Y.cpart = Y.take(Dd * 3 * std::max(P.n_cpart, 1));
     Y.qpart = Y.take(Dd * 3 * std::max(P.n_cpart, 1));
-    Y.P_sigma = Y.take(Dd * P.G);
+    Y.P_sp = Y.take(2 * Dd * P.G);
     Y.P_rr = Y.take(Dd * std::max(P.G, apply_blocks(P.N, P.M, P.G)));
     Y.P_bb = Y.take(Dd * P.G);
     const size_t nrho = static_cast<size_t>(apply_blocks(P.N, P.M, P.G)) + all_coarse_blocks(P.L, P.N, P.ndom.data());
@@ -341,7 +341,7 @@ SolverView view(const mas_handle* h) {
     v.GA = apply_blocks(P.N, P.M, P.G);
     v.cpart = at<double>(h, Y.cpart);
     v.qpart = at<double>(h, Y.qpart);
-    v.P_sigma = at<double>(h, Y.P_sigma);
+    v.P_sp = at<double2>(h, Y.P_sp);
     v.P_rr = at<double>(h, Y.P_rr);
     v.P_bb = at<double>(h, Y.P_bb);
     v.P_rho[0] = at<double>(h, Y.P_rho0);
@@ -577,9 +577,9 @@ int read_state(mas_handle* h, const SolverView& v, hipStream_t s) {
 
 // The PCG driver shared by pcg_solve and pcg_adjoint.  Iteration k takes
 // two launches:
-//   p = z + beta p, q = H p (sigma partials), the restriction of q and the
-//   convergence test on r_{k-1} ->
-//   alpha, x += alpha p, r -= alpha q (||r||^2 partials), the level-0 apply
+//   p = z + beta p, q = H p (partials of p^T q and r^T p), the restriction of q
+//   and the convergence test on r_{k-1} ->
+//   alpha = r^T p / p^T q, x += alpha p, r -= alpha q (||r||^2 partials), the level-0 apply
 //   and, beside it, C_l r_k = C_l r_{k-1} - alpha C_l q_k and the coarse apply
 //   (rho partials of both); the prolongation follows in the next SpMV (or,
 //   where the SpMV cannot lend shared memory to the groups' coarse
@@ -589,6 +589,11 @@ int read_state(mas_handle* h, const SolverView& v, hipStream_t s) {
 //   SpMV -> x/r update with the restriction of r_k -> [mixed: FP64 residual
 //   replacement] -> convergence test on r_k and coarse apply -> level-0
 //   apply, which also bounds the rounding the recurrence accumulates.
+// alpha is formed from r^T p, not from rho = r^T z, which the two-launch form
+// sums from coarse residuals carried by recurrence: once r is below their
+// rounding rho is theirs, and with it the steps would grow without end (3,600
+// nodes, 1e-15 after 15 iterations, 1e+14 after 49).  With r^T p each step is
+// the least error along p, whatever beta made of it.
 // The host reads the state every check_every iterations; iterations queued
 // after a stop return at once.
 int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, const pcg_options* o, pcg_result* res,

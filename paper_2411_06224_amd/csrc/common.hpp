@@ -168,6 +168,12 @@ __device__ inline void block_sum2_last(double a, double b, double* scratch, doub
         }
 }
 
+// block_sum2_last for a scratch that the kernel has used before.
+__device__ inline void block_sum2(double a, double b, double* scratch, double& sa, double& sb) {
+    __syncthreads();
+    block_sum2_last(a, b, scratch, sa, sb);
+}
+
 // Sum of n per-group partials in a fixed order that does not depend on the
 // workgroup shape, so every kernel that needs the value computes the same
 // bits: thread t < 256 adds p[t], p[t + 256], ... (independent loads, issued
@@ -176,6 +182,17 @@ __device__ inline void block_sum2_last(double a, double b, double* scratch, doub
 __device__ inline double sum_partials(const double* __restrict__ p, int n, double* buf);
 
 __device__ inline bool finite(double x) { return x - x == 0.0; }
+
+// r^T p / p^T q, or NaN where the solve has to stop (H not positive definite
+// along p, or a sum that is not finite).  Far below rounding (tol = 0) both
+// sums underflow to zero: no step then.
+__device__ inline double line_step(double sigma, double rp) {
+    if (finite(sigma) && finite(rp)) {
+        if (sigma > 0.0) return rp / sigma;
+        if (sigma == 0.0 && rp == 0.0) return 0.0;
+    }
+    return __builtin_nan("");
+}
 
 // Ends a kernel's block of early loads: an empty statement that the compiler
 // must treat as touching memory, so that it keeps those loads in the order
@@ -194,14 +211,15 @@ __device__ __forceinline__ void keep_loads_issued() { asm volatile("" ::: "memor
 // (n >= 1), so that no branch separates them from the loads issued after
 // them and a wait for them need not wait for those too; partials_sum() reads
 // only the entries below n.
-template <int kPer = 4>
+// V: double, or double2 for two sums whose partials lie side by side.
+template <int kPer = 4, typename V = double>
 struct PartialLoads {
-    double v[kPer ? kPer : 1];
+    V v[kPer ? kPer : 1];
 };
 
-template <int kPer = 4>
-__device__ inline PartialLoads<kPer> partials_load(const double* __restrict__ p, int n) {
-    PartialLoads<kPer> L;
+template <int kPer = 4, typename V>
+__device__ inline PartialLoads<kPer, V> partials_load(const V* __restrict__ p, int n) {
+    PartialLoads<kPer, V> L;
     const int t = threadIdx.x;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
@@ -210,13 +228,19 @@ __device__ inline PartialLoads<kPer> partials_load(const double* __restrict__ p,
     return L;
 }
 
-// Bucket t of the sum into buf[t], t < 256.
-template <int kPer = 4>
-__device__ inline void partials_bucket(const PartialLoads<kPer>& L, const double* __restrict__ p, int n, double* buf) {
+__device__ __forceinline__ void store_bucket(double s, double* buf) { buf[threadIdx.x] = s; }
+__device__ __forceinline__ void store_bucket(double2 s, double* buf) {
+    buf[threadIdx.x] = s.x;
+    buf[256 + threadIdx.x] = s.y;
+}
+
+// Bucket t of the sum into buf[t] (and buf[256 + t]), t < 256.
+template <int kPer = 4, typename V>
+__device__ inline void partials_bucket(const PartialLoads<kPer, V>& L, const V* __restrict__ p, int n, double* buf) {
     static_assert(kPer % 4 == 0, "whole rounds of sum_partials");
     const int t = threadIdx.x;
     if (t >= 256) return;
-    double s = 0.0;
+    V s{};
     if (n > 256 * kPer) {
         int i = t;
         for (; i + 768 < n; i += 1024) s += (p[i] + p[i + 256]) + (p[i + 512] + p[i + 768]);
@@ -234,7 +258,7 @@ __device__ inline void partials_bucket(const PartialLoads<kPer>& L, const double
             }
         }
     }
-    buf[t] = s;
+    store_bucket(s, buf);
 }
 
 // The sum of the buckets (visible to the wave) into buf[0], by one whole wave.
@@ -248,7 +272,7 @@ __device__ inline void partials_fold(double* buf) {
 // kReuse = false leaves out the closing barrier, for a caller whose next
 // write to buf follows another barrier.
 template <bool kReuse = true, int kPer = 4>
-__device__ inline double partials_sum(const PartialLoads<kPer>& L, const double* __restrict__ p, int n, double* buf) {
+__device__ inline double partials_sum(const PartialLoads<kPer, double>& L, const double* __restrict__ p, int n, double* buf) {
     partials_bucket<kPer>(L, p, n, buf);
     __syncthreads();
     if (threadIdx.x < 64) partials_fold(buf);
@@ -256,6 +280,16 @@ __device__ inline double partials_sum(const PartialLoads<kPer>& L, const double*
     const double r = buf[0];
     if (kReuse) __syncthreads();
     return r;
+}
+
+// Two sums at once (buf[512]), each with the bits of partials_sum.
+__device__ inline double2 partials_sum(const PartialLoads<4, double2>& L, const double2* __restrict__ p, int n,
+                                       double* buf) {
+    partials_bucket(L, p, n, buf);
+    __syncthreads();
+    if (threadIdx.x < 128) partials_fold(buf + 256 * (threadIdx.x >> 6));
+    __syncthreads();
+    return {buf[0], buf[256]};
 }
 
 __device__ inline double sum_partials(const double* __restrict__ p, int n, double* buf) {

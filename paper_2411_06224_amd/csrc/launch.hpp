@@ -109,7 +109,8 @@ struct SolverView {
     // apply [GA] after an iteration by recurrence), P_rho [GA + ncb]: the
     // level-0 workgroups' r^T z, then (by recurrence) the coarse workgroups'
     // r_l^T y_l
-    double *P_sigma, *P_rr, *P_bb, *P_rho[2];
+    double2* P_sp;  // one per group [G]: p_k^T q_k and r_{k-1}^T p_k
+    double *P_rr, *P_bb, *P_rho[2];
     DevState* st;
     int* flag;  // inversion status
 };
@@ -212,7 +213,8 @@ enum ApplyMode { kApplyPlain = 0, kApplyInit = 1, kApplyIter = 2 };
 // spmv.hip
 hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void* val, bool f32, const double* x,
                             double* y, hipStream_t s);
-// iteration k: p_k = z_{k-1} + beta p_{k-1} (p_1 = z_0) into p[k & 1], q = H p_k, sigma partials.
+// iteration k: p_k = z_{k-1} + beta p_{k-1} (p_1 = z_0) into p[k & 1], q = H p_k, the
+// partials of p_k^T q_k and r_{k-1}^T p_k.
 // restrict_q: also the restriction of q to the coarse levels (q1, qpart);
 // rec: the previous iteration ran launch_apply_rec; split: and no
 // launch_prolong, so that z_{k-1} is v.z plus the coarse corrections in yall,

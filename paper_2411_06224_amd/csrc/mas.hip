@@ -615,34 +615,26 @@ __device__ __forceinline__ double full_row(const TI* __restrict__ inv, int n, in
 }
 
 // ---- the scalars of an iteration by recurrence
-struct RecLoads {
-    PartialLoads<> sig;
-    double rho;
-};
+using RecLoads = PartialLoads<4, double2>;
 
-__device__ __forceinline__ RecLoads rec_load(const SolverView& v, int k) {
-    RecLoads R;
-    R.sig = partials_load(v.P_sigma, v.G);
-    R.rho = v.st->rho[(k - 1) & 1];
-    return R;
-}
+__device__ __forceinline__ RecLoads rec_load(const SolverView& v) { return partials_load(v.P_sp, v.G); }
 
-// alpha_k = rho_{k-1} / sigma_k, or false (after flagging NOT_SPD or
+// alpha_k = r_{k-1}^T p_k / sigma_k, or false (after flagging NOT_SPD or
 // NOT_FINITE where report is set) when sigma <= 0 or a value is not finite:
-// every workgroup sees the same sigma and returns without writing.  buf: 256
+// every workgroup sees the same sums and returns without writing.  buf: 512
 // doubles of shared memory, not written again before another barrier.
 __device__ __forceinline__ bool rec_alpha(const SolverView& v, int k, bool report, const RecLoads& R, double* buf,
                                           double& alpha) {
-    const double sigma = partials_sum<false>(R.sig, v.P_sigma, v.G, buf);
-    if (!(sigma > 0.0) || !finite(sigma) || !finite(R.rho)) {
+    const double2 s = partials_sum(R, v.P_sp, v.G, buf);
+    alpha = line_step(s.x, s.y);
+    if (!(alpha == alpha)) {
         if (report && threadIdx.x == 0) {
-            v.st->status = (finite(sigma) && finite(R.rho)) ? -2 : -6;
+            v.st->status = (finite(s.x) && finite(s.y)) ? -2 : -6;
             v.st->done = 1;
             v.st->iter = k - 1;
         }
         return false;
     }
-    alpha = R.rho / sigma;
     return true;
 }
 
@@ -657,7 +649,7 @@ __device__ __forceinline__ bool rec_alpha(const SolverView& v, int k, bool repor
 // partials the restriction left for it (up to about a hundred at the top).
 
 // Domain size 16: eight level-1 domains, a pair per wave, or one pair of a
-// higher level (three waves gather, one multiplies).  sm: 4 kPairLds doubles, buf: 256, red: 16.
+// higher level (three waves gather, one multiplies).  sm: 4 kPairLds doubles, buf: 512 (256 without kRec), red: 16.
 constexpr int kItem = 8;     // partials of an item
 constexpr int kItems = 192;  // items at a time: one per thread of the gathering waves
 
@@ -669,7 +661,7 @@ __device__ __forceinline__ void coarse_pairs(const SolverView& v, const CoarseTa
     const int l = coarse_level(tab, v.L, b);
     const int pairs = (v.ndom[l] + 1) / 2, nrow = 3 * v.units[l];
     RecLoads R{};
-    if constexpr (kRec) R = rec_load(v, k);
+    if constexpr (kRec) R = rec_load(v);
     PairRegs<TI> P;
     double x[2] = {0.0, 0.0}, out[2] = {0.0, 0.0}, part = 0.0;
     if (l == 1) {
@@ -830,7 +822,7 @@ __device__ __forceinline__ void coarse_pairs(const SolverView& v, const CoarseTa
 }
 
 // Other domain sizes: one domain per workgroup, a wave per unit for the
-// gather, a thread per row.  rl: 128 doubles, buf: 256, red: 16.
+// gather, a thread per row.  rl: 128 doubles, buf: 512 (256 without kRec), red: 16.
 template <typename TI, bool kRec>
 __device__ __forceinline__ void coarse_domain(const SolverView& v, const CoarseTable& tab, int mode, int k, int b,
                                               double* rl, double* buf, double* red) {
@@ -839,7 +831,7 @@ __device__ __forceinline__ void coarse_domain(const SolverView& v, const CoarseT
     const int d = b - tab.off[l], N = v.N, n = 3 * N;
     const int u0 = d * N, nu = min(N, v.units[l] - u0);
     RecLoads R{};
-    if constexpr (kRec) R = rec_load(v, k);
+    if constexpr (kRec) R = rec_load(v);
     const int stop = v.st->done;
     keep_loads_issued();
     if (mode != kApplyPlain && stop) return;
@@ -1060,7 +1052,7 @@ __global__ void __launch_bounds__(kGroupThreads) k_apply_level0(SolverView v, in
 template <typename TI>
 __global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_rec_pairs(SolverView v, CoarseTable tab, int pad, int k) {
     __shared__ double sm[4 * kPairLds];
-    __shared__ double buf[256];
+    __shared__ double buf[512];
     __shared__ double red[16];
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -1071,7 +1063,7 @@ __global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_rec_pairs(So
     const int b = xcd_group(blockIdx.x - pad, v.GA);
     const int p = 4 * b + w;
     const bool live = 2 * p < v.M;
-    const RecLoads R = rec_load(v, k);
+    const RecLoads R = rec_load(v);
     int e[2];
     bool own[2];
     double xv[2], pv[2], ro[2], qv[2];
@@ -1123,7 +1115,7 @@ __global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_rec_pairs(So
 template <typename TI>
 __global__ void __launch_bounds__(kGroupThreads) k_apply_rec(SolverView v, CoarseTable tab, int pad, int k) {
     __shared__ double rs[kGroupThreads];
-    __shared__ double buf[256];
+    __shared__ double buf[512];
     __shared__ double red[16];
     const int t = threadIdx.x;
     if (static_cast<int>(blockIdx.x) < pad) {
@@ -1135,7 +1127,7 @@ __global__ void __launch_bounds__(kGroupThreads) k_apply_rec(SolverView v, Coars
     const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
     const bool live = t < nd * n;
     const long long i = 3LL * g * v.RG + (live ? t : 0);
-    const RecLoads R = rec_load(v, k);
+    const RecLoads R = rec_load(v);
     const double xv = v.x[i], pv = v.p[k & 1][i], ro = v.r[i], qv = v.q[i];
     const int stop = v.st->done;
     keep_loads_issued();

@@ -438,8 +438,8 @@ __global__ void __launch_bounds__(kThreads) k_spmv_user(int n_rows, const int* _
     if (t < 3 * (r1 - r0)) y[3LL * r0 + t] = acc[0];
 }
 
-// Products per launch after the stream: q of the group's rows, the partial
-// of p_k^T q and, with kRQ > 0 (writer passes), the restriction of q to
+// Products per launch after the stream: q of the group's rows, the partials
+// of p_k^T q and r^T p_k (rp) and, with kRQ > 0 (writer passes), the restriction of q to
 // the coarse levels (q1 and qpart, as restrict_group computes C_l r) from
 // the plan pl loaded at the kernel's start, staged in the product planes
 // (free once the stream's last barrier has passed; the host checks that
@@ -447,7 +447,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_user(int n_rows, const int* _
 template <int kRQ>
 __device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, int r0, double* __restrict__ qk,
                                           const double (&acc)[2],
-                                          const double (&pv)[2], double* prod, double* buf,
+                                          const double (&pv)[2], double rp, double* prod, double* buf,
                                           const RestrictLoads<kRQ ? kRQ : 1>& pl) {
     const int t = threadIdx.x;
     if constexpr (kRQ) restrict_ready(pl);
@@ -468,12 +468,14 @@ __device__ __forceinline__ void finish_pq(const SolverView& v, int g, int nown, 
             const int o = t + q * kThreads;
             if (o < 3 * v.RG) rs[o] = o < nown ? acc[q] : 0.0;
         }
-        part = block_sum<false>(part, buf);  // its barriers also publish rs
-        if (t == 0) v.P_sigma[g] = part;
+        double sigma, srp;
+        block_sum2(part, rp, buf, sigma, srp);  // its barriers also publish rs
+        if (t == 0) v.P_sp[g] = {sigma, srp};
         restrict_group<true>(v, g, pl, rs, rsm, v.q1, v.qpart);  // the host checked restrict_passes
     } else {
-        part = block_sum<false>(part, buf);  // the kernel's last use of buf
-        if (t == 0) v.P_sigma[g] = part;
+        double sigma, srp;
+        block_sum2(part, rp, buf, sigma, srp);
+        if (t == 0) v.P_sp[g] = {sigma, srp};
     }
 }
 
@@ -593,7 +595,7 @@ constexpr int kRhoPer = 8;  // rho partials a thread loads ahead: up to 2048 in 
 // PCG iteration k over the solver's group of slots: the new direction
 // p_k = z_{k-1} + beta_{k-1} p_{k-1} (beta = rho_{k-1} / rho_{k-2} summed from
 // the partials; p_1 = z_0) on the group's own slots, q_k = H p_k and the
-// partial of p_k^T q_k.
+// partials of p_k^T q_k and r_{k-1}^T p_k.
 //
 // The direction is staged in LDS on the group's own slots and formed wherever H
 // gathers it, with the same beta and the same fused multiply-add, so the same
@@ -608,7 +610,7 @@ constexpr int kRhoPer = 8;  // rho partials a thread loads ahead: up to 2048 in 
 // (unit_stage); an outside column then costs one 16-bit index and three LDS
 // reads more.
 struct DirLoads {
-    double z[2], p[2];
+    double z[2], p[2], r[2];
     int unit[2];
 };
 
@@ -621,19 +623,21 @@ __device__ __forceinline__ DirLoads dir_load(const SolverView& v, int g, int r0,
         const long long e = 3LL * r0 + o;
         D.z[q] = v.z[e];
         D.p[q] = pold[e];
+        D.r[q] = v.r[e];
         D.unit[q] = kSplit ? own_unit(v, g, r0 + o / 3) : -1;
     }
     return D;
 }
 
 // rho_{k-1} and beta, the own part of p_k in xs and stored; pv: p_k at the
-// thread's rows.  Ends with a barrier.
+// thread's rows; rp: its part of r_{k-1}^T p_k.  Ends with a barrier.
 template <bool kSplit>
 __device__ __forceinline__ double dir_stage(const SolverView& v, int k, int g, int r0, int nown, DirLoads& D,
                                             const PartialLoads<kSplit ? kRhoPer : 4>& rl, int nrho, double rk2,
                                             const UnitLoads& U, double* ycor, double* xs, double* buf,
-                                            double (&pv)[2]) {
+                                            double (&pv)[2], double& rp) {
     const int t = threadIdx.x;
+    rp = 0.0;
     const double* Prho = v.P_rho[(k - 1) & 1];
     partials_bucket<kSplit ? kRhoPer : 4>(rl, Prho, nrho, buf);
     if constexpr (kSplit) {
@@ -645,7 +649,7 @@ __device__ __forceinline__ double dir_stage(const SolverView& v, int k, int g, i
     }
     const double rk1 = buf[0];  // buf is next written after later barriers
     if (g == 0 && t == 0) v.st->rho[(k - 1) & 1] = rk1;
-    const double beta = k > 1 ? rk1 / rk2 : 0.0;
+    const double beta = k > 1 && rk2 != 0.0 ? rk1 / rk2 : 0.0;  // (r^T z underflows before r does)
     double* pk = v.p[k & 1];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -656,6 +660,7 @@ __device__ __forceinline__ double dir_stage(const SolverView& v, int k, int g, i
             if (kSplit && D.unit[q] >= 0) z += ycor[3 * D.unit[q] + o % 3];
             pv[q] = __fma_rn(beta, D.p[q], z);
             pk[3LL * r0 + o] = pv[q];
+            rp += D.r[q] * pv[q];
         }
         if (o < 3 * v.RG) xs[o] = pv[q];
     }
@@ -693,12 +698,12 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq(SolverView v, const T* __r
     if (stopped_before<kSplit>(stop, k)) return;  // after a stop nothing is written
     const double rk2 = uniform_load(&v.st->rho[k & 1]);  // rho_{k-2} as the previous SpMV recorded it
     if constexpr (kSplit) unit_gather(v, U);
-    double pv[2], acc[2];
-    const double beta = dir_stage<kSplit>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv);
+    double pv[2], acc[2], rp;
+    const double beta = dir_stage<kSplit>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv, rp);
     const Blocks<T, true> Hb{H, v.nnzb};
     stream_rows<T, true, XDir<kSplit>, true>(v.rp0, v.ci0, Hb, XDir<kSplit>{v.z, pold, beta, ycor}, r0, r1, prod, acc,
                                              c0, xs, v.hidx);
-    finish_pq<kRQ>(v, g, nown, r0, v.q, acc, pv, prod, buf, pl);
+    finish_pq<kRQ>(v, g, nown, r0, v.q, acc, pv, rp, prod, buf, pl);
 }
 
 // k_spmv_pq on the group-symmetric storage.
@@ -743,10 +748,10 @@ __global__ void __launch_bounds__(kThreads) k_spmv_pq_sym(SolverView v, const T*
     for (int j = 0; j < kTlRegs; ++j)
         if (t + j * kThreads < tn) tl[t + j * kThreads] = tlr[j];
     for (int e = t + kTlRegs * kThreads; e < tn; e += kThreads) tl[e] = v.tidx[tb0 + e];
-    double pv[2], acc[2];
-    const double beta = dir_stage<kSplit>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv);
+    double pv[2], acc[2], rp;
+    const double beta = dir_stage<kSplit>(v, k, g, r0, nown, D, rl, nrho, rk2, U, ycor, xs, buf, pv, rp);
     stream_sym<T>(v, H, XDir<kSplit>{v.z, pold, beta, ycor}, xs, tl, tb0, r0, r1, prod, acc, c0);
-    finish_pq<kRQ>(v, g, nown, r0, v.q, acc, pv, prod, buf, pl);
+    finish_pq<kRQ>(v, g, nown, r0, v.q, acc, pv, rp, prod, buf, pl);
 }
 
 // out = b - H x in FP64 over a group, with the partials of ||out||^2 (and

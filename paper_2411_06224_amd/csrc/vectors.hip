@@ -74,9 +74,9 @@ __global__ void __launch_bounds__(kVecThreads) k_perm_out(int V, const int* __re
     dst[t] = src[3 * map[t / 3] + t % 3];
 }
 
-// Shared memory of the group kernels: rs[3*RG] + restriction scratch + 256.
+// Shared memory of the group kernels: rs[3*RG] + restriction scratch + 512.
 inline size_t group_smem(const SolverView& v) {
-    return sizeof(double) * (3 * v.RG + restrict_smem_doubles(v.RG, v.W1, v.L) + 256);
+    return sizeof(double) * (3 * v.RG + restrict_smem_doubles(v.RG, v.W1, v.L) + 512);
 }
 
 // r = b, x = 0, partials of ||b||^2 (as both ||r||^2 and ||b||^2), and the
@@ -105,8 +105,8 @@ __global__ void k_init_rhs(SolverView v) {
     restrict_group_any(v, g, pl, rs, sm + 3 * v.RG, v.r1, v.cpart);
 }
 
-// Iteration k: alpha = rho_{k-1} / sigma_k (sigma summed here from the group
-// partials, rho_{k-1} as the SpMV of this iteration recorded it), x += alpha p,
+// Iteration k: alpha = r_{k-1}^T p_k / sigma_k (both summed here from the group
+// partials), x += alpha p,
 // r -= alpha q, the partial of ||r||^2 and the restriction of the new
 // residual.  sigma <= 0 stops the solve (NOT_SPD).
 // Writer passes of the restriction whose plan entries k_update loads with
@@ -122,8 +122,7 @@ __global__ void k_update(SolverView v, int k) {
     // issue every independent load (the stop flag's included) before the
     // first wait, the partials of sigma first (they are needed first, and
     // loads complete in issue order); after a stop nothing is written
-    const PartialLoads sig = partials_load(v.P_sigma, v.G);
-    const double rho = v.st->rho[(k - 1) & 1];
+    const auto sp = partials_load(v.P_sp, v.G);
     const long long i = 3LL * g * v.RG + t;
     const bool own = t < 3 * v.RG && i < 3LL * v.NS;
     const long long ic = own ? i : 0;  // unconditional loads (see partials_load)
@@ -134,16 +133,16 @@ __global__ void k_update(SolverView v, int k) {
     keep_loads_issued();
     if (stop) return;
     // (block_sum's first barrier orders scratch's reuse)
-    const double sigma = partials_sum<false>(sig, v.P_sigma, v.G, scratch);
-    if (!(sigma > 0.0) || !finite(sigma) || !finite(rho)) {
+    const double2 s = partials_sum(sp, v.P_sp, v.G, scratch);
+    const double alpha = line_step(s.x, s.y);
+    if (!(alpha == alpha)) {
         if (g == 0 && t == 0) {
-            v.st->status = (finite(sigma) && finite(rho)) ? -2 : -6;
+            v.st->status = (finite(s.x) && finite(s.y)) ? -2 : -6;
             v.st->done = 1;
             v.st->iter = k - 1;
         }
         return;
     }
-    const double alpha = rho / sigma;
     restrict_ready(pl);
     double rv = 0.0;
     if (own) {

@@ -12,6 +12,7 @@ import pytest
 
 import oracle
 import synth
+from group_systems import _grid
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -32,7 +33,7 @@ def _case(name):
     return s, P.pcg(s.b, tol=0.0, max_iter=1000)[4]
 
 
-@pytest.mark.parametrize("every", [1, 50])
+@pytest.mark.parametrize("every", [1, 50, 2**31 - 1])
 @pytest.mark.parametrize("name", list(SYSTEMS))
 def test_attained_residual(name, every):
     if not torch.cuda.is_available():
@@ -47,4 +48,40 @@ def test_attained_residual(name, every):
     x, _ = S.solve(H, torch.as_tensor(s.b, device="cuda:0"), tol=0.0, max_iter=1000, replace_every=every)
     r = s.b - oracle.spmv(s.row_ptr, s.col_idx, s.val, x.cpu().numpy())
     assert np.linalg.norm(r) <= 3 * want * np.linalg.norm(s.b)
+    S.close()
+
+
+# Systems that reach rounding within 10 to 40 iterations, stopped at counts
+# before and after it, with and without a direct iteration in between.
+EARLY = {
+    "grid": (3600, lambda: _grid(60)),
+    "chain": (5000, lambda: np.concatenate([_steps(5000, 1), _steps(5000, 5)[::3]])),
+}
+
+
+def _steps(n, d):
+    i = np.arange(n - d)
+    return np.stack([i, i + d], 1)
+
+
+@pytest.mark.parametrize("mass", [1e2, 1e3, 1e4, 1e6])
+@pytest.mark.parametrize("name", list(EARLY))
+def test_past_rounding(name, mass):
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2411_06224_amd as mp
+
+    n, edges = EARLY[name]
+    s = synth.bcsr.spd_system_from_edges(n, edges(), seed=1, mass=mass)
+    P = oracle.MAS(s.row_ptr, s.col_idx, s.val, N=16, gptr=s.gptr, gadj=s.gadj)
+    S = mp.MasPcg(s.row_ptr, s.col_idx, graph=(s.gptr, s.gadj), poison=True)
+    H = mp.BlockMatrix.from_numpy(s.row_ptr, s.col_idx, s.val, device="cuda:0")
+    S.build(H)
+    for its in (8, 20, 30, 49, 80, 120):
+        want = P.pcg(s.b, tol=0.0, max_iter=its)[4]
+        for every in (1, 50, 2**31 - 1):
+            print("[case]", name, mass, its, every, flush=True)
+            x, _ = S.solve(H, torch.as_tensor(s.b, device="cuda:0"), tol=0.0, max_iter=its, replace_every=every)
+            r = s.b - oracle.spmv(s.row_ptr, s.col_idx, s.val, x.cpu().numpy())
+            assert np.linalg.norm(r) <= 3 * want * np.linalg.norm(s.b), (its, every)
     S.close()
