@@ -95,8 +95,9 @@ typedef struct {
     int32_t max_iter;        /* >= 0 */
     int32_t x0_given;        /* 1: x holds the initial guess, else x0 = 0 */
     int32_t replace_every;   /* period of the iterations that restrict the residual itself rather
-                                than updating its coarse restriction by recurrence, and in mixed
-                                mode of the FP64 residual replacement (0 -> 50) */
+                                than updating its coarse restriction by recurrence (and every 50th
+                                does where it is larger), and in mixed mode of the FP64 residual
+                                replacement (0 -> 50) */
     int32_t check_every;     /* iterations between host convergence checks (0 -> 8) */
 } pcg_options;
 
