@@ -801,8 +801,12 @@ __global__ void __launch_bounds__(kAsmThreads, 4) k_asm_row_sum(int n_rows, int 
 // rows among kSamples blocks of the list are kSamples^2 / (2 n) times the mean
 // length of a block's row.  Beyond kSampleLength the rows' pieces and the
 // atomics, which meet on few addresses, take longer than the sort (9 million
-// blocks, 5 in 8 on rows of 3,000: 1,148 us by sorting, 1,124 here; of 7,000:
-// 1,330 by sorting), and rows beyond kRowLimit are likely.  In mixed order
+// blocks, 5 in 8 on rows of 7,000: 1,330 us by sorting), and rows beyond
+// kRowLimit are likely.  The longer the list, the less the sort's fixed costs
+// count: kSampleProduct divided by its blocks is the limit then (contacts of
+// bodies, by sorting and here: 7 million of a mean of 1,650 947 and 924 us, 10
+// million 1,145 and 1,239, 18 million 1,683 and 2,126; 10 million of 834 1,013
+// and 992, 20 million 1,818 and 1,933, of 1,106 1,820 and 2,168).  In mixed order
 // (neighbours in the list differ) every block takes an atomic and its values
 // are read alone: from kMixedLength on sorting is faster (9 million blocks,
 // rows of 128: 1,366 and 1,428 us; of 200: 1,275 and 1,490; of 400: 1,273 and
@@ -812,6 +816,7 @@ __global__ void __launch_bounds__(kAsmThreads, 4) k_asm_row_sum(int n_rows, int 
 constexpr int kSamples = 1024, kSampleSlots = 2 * kSamples, kSampleThreads = kSamples;
 constexpr long long kSampleFrom = 1 << 21, kSampleRead = 1 << 24;
 constexpr int kSampleLength = 3000, kMixedLength = 180;
+constexpr double kSampleProduct = 1.2e10;
 
 __global__ void __launch_bounds__(kSampleThreads) k_asm_sample(int n_in, const int* __restrict__ rows,
                                                                int* __restrict__ flag) {
@@ -839,8 +844,9 @@ __global__ void __launch_bounds__(kSampleThreads) k_asm_sample(int n_in, const i
     }
     __syncthreads();
     // (8 of 8 neighbours differ in mixed order; where elements list runs of four, 2 of 8)
-    const int longest = 8 * ends > 7 * kSamples ? kMixedLength : kSampleLength;
-    if (threadIdx.x == 0 && 2.0 * n_in * total > static_cast<double>(longest) * kSamples * kSamples)
+    const double limit = 8 * ends > 7 * kSamples ? kMixedLength : kSampleLength;
+    const double longest = fmin(limit, kSampleProduct / n_in);
+    if (threadIdx.x == 0 && 2.0 * n_in * total > longest * kSamples * kSamples)
         flag[0] = 2;  // the sorting path takes the list: nothing below runs
 }
 
