@@ -89,7 +89,7 @@ def algorithmic_bytes(info, mixed):
         stored = nsb * (val + 4 + 1) + 8 * (NS + 1) + 4 * (nnzb - nsb)
     out = {
         # the stored matrix with the local coarse unit of each column (2 B);
-        # z, the previous direction and the previous q read once, the new
+        # z, the previous direction and the residual read once, the new
         # direction and q written; the coarse corrections; the restriction of
         # q: per-slot plan (16 B) read, q_1 written
         "spmv": stored + 2 * blocks + 5 * vb + coarse_y + 16 * NS + r1b,

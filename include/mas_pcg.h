@@ -281,9 +281,11 @@ size_t bcsr_assemble_workspace_size(int32_t n_rows, int64_t n_in);
 /* Assembles a list of 3x3 blocks into 3x3-block CSR on the device: the
  * operation the hash-based parallel reduction of Sec. 6.2 performs (blocks
  * with the same (row, col) summed; rows ascending, columns ascending within
- * a row), here deterministic: a stable radix sort of (row, col) keys keeps
- * equal blocks in list order and each is summed in that order, so the
- * result is that of a sequential pass over the list.
+ * a row), here deterministic: the list is grouped by row and each row sorted
+ * by (column, list position), or the whole list by a stable radix sort of
+ * (row, col) keys (few blocks per row, very long rows); either way equal
+ * blocks are summed in list order, so the result is that of a sequential
+ * pass over the list.
  *   rows, cols: device int32[n_in], 0 <= index < n_rows.
  *   blocks: device double[9 n_in], row-major 3x3 blocks.
  *   row_ptr: device int32[n_rows + 1]; col_idx: device int32[capacity];
@@ -292,8 +294,8 @@ size_t bcsr_assemble_workspace_size(int32_t n_rows, int64_t n_in);
  *         exceeds capacity, so the caller can size the outputs).
  *   workspace: device scratch of ws_bytes >= bcsr_assemble_workspace_size,
  *              256-byte aligned.
- * Limits: n_in < 2^31, n_rows < 2^31 - 1 (the sort runs over 2 ceil(log2
- * (n_rows + 1)) key bits: 34 for a 110,592-row system).  Synchronises the
+ * Limits: n_in < 2^31, n_rows < 2^31 - 1 (the radix sort runs over 2
+ * ceil(log2 (n_rows + 1)) key bits: 34 for a 110,592-row system).  Synchronises the
  * stream.
  * Errors: MAS_INVALID_ARG (an index out of range, a limit exceeded,
  * nnzb > capacity: then col_idx and val are not written),

@@ -157,8 +157,8 @@ inline size_t inverse_entries(int N, int nd) {
 }
 
 // Workgroups of the apply.  N = 16: kApplyDomains consecutive level-0 (or
-// level-1) domains per workgroup, two of its four waves each, and one pair of
-// domains of the levels above per workgroup; other sizes: one group of
+// level-1) domains per workgroup, a pair per wave, and one pair of domains of
+// the levels above per workgroup; other sizes: one group of
 // level-0 domains (apply_blocks = G) and one coarse domain each.
 constexpr int kApplyDomains = 8;
 inline int apply_blocks(int N, int M, int G) { return N == 16 ? (M + kApplyDomains - 1) / kApplyDomains : G; }
@@ -213,8 +213,8 @@ enum ApplyMode { kApplyPlain = 0, kApplyInit = 1, kApplyIter = 2 };
 // spmv.hip
 hipError_t launch_spmv_user(int n_rows, const int* rp, const int* ci, const void* val, bool f32, const double* x,
                             double* y, hipStream_t s);
-// iteration k: p_k = z_{k-1} + beta p_{k-1} (p_1 = z_0) into p[k & 1], q = H p_k, the
-// partials of p_k^T q_k and r_{k-1}^T p_k.
+// iteration k: p_k = z_{k-1} + beta p_{k-1} (p_1 = z_0) into p[k & 1], q = H
+// p_k, the partials of p_k^T q_k and r_{k-1}^T p_k.
 // restrict_q: also the restriction of q to the coarse levels (q1, qpart);
 // rec: the previous iteration ran launch_apply_rec; split: and no
 // launch_prolong, so that z_{k-1} is v.z plus the coarse corrections in yall,

@@ -649,7 +649,8 @@ __device__ __forceinline__ bool rec_alpha(const SolverView& v, int k, bool repor
 // partials the restriction left for it (up to about a hundred at the top).
 
 // Domain size 16: eight level-1 domains, a pair per wave, or one pair of a
-// higher level (three waves gather, one multiplies).  sm: 4 kPairLds doubles, buf: 512 (256 without kRec), red: 16.
+// higher level (three waves gather, one multiplies).  sm: 4 kPairLds doubles,
+// buf: 512 (256 without kRec), red: 16.
 constexpr int kItem = 8;     // partials of an item
 constexpr int kItems = 192;  // items at a time: one per thread of the gathering waves
 
@@ -1039,7 +1040,7 @@ __global__ void __launch_bounds__(kGroupThreads) k_apply_level0(SolverView v, in
 
 // ---- apply of a two-launch iteration
 // Iteration k by recurrence, in one launch after the SpMV.  Every workgroup
-// forms alpha_k from the sigma partials; the first workgroups take the coarse
+// forms alpha_k from the partials of p^T q and r^T p; the first workgroups take the coarse
 // levels (coarse_pairs / coarse_domain), the others perform x += alpha p_k and
 // r -= alpha q_k on their level-0 domains and z = Inv_{0,d} r_d, with the
 // partials of r^T z and ||r_k||^2.  rho_k = r^T z + sum_l (C_l r)^T y_l is the

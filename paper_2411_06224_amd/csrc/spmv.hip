@@ -439,8 +439,8 @@ __global__ void __launch_bounds__(kThreads) k_spmv_user(int n_rows, const int* _
 }
 
 // Products per launch after the stream: q of the group's rows, the partials
-// of p_k^T q and r^T p_k (rp) and, with kRQ > 0 (writer passes), the restriction of q to
-// the coarse levels (q1 and qpart, as restrict_group computes C_l r) from
+// of p_k^T q and r^T p_k (rp) and, with kRQ > 0 (writer passes), the
+// restriction of q to the coarse levels (q1 and qpart, as restrict_group computes C_l r) from
 // the plan pl loaded at the kernel's start, staged in the product planes
 // (free once the stream's last barrier has passed; the host checks that
 // they hold it, spmv_restrict_capacity).

@@ -106,9 +106,8 @@ __global__ void k_init_rhs(SolverView v) {
 }
 
 // Iteration k: alpha = r_{k-1}^T p_k / sigma_k (both summed here from the group
-// partials), x += alpha p,
-// r -= alpha q, the partial of ||r||^2 and the restriction of the new
-// residual.  sigma <= 0 stops the solve (NOT_SPD).
+// partials), x += alpha p, r -= alpha q, the partial of ||r||^2 and the
+// restriction of the new residual.  sigma <= 0 stops the solve (NOT_SPD).
 // Writer passes of the restriction whose plan entries k_update loads with
 // its other early loads (systems whose groups write many coarse partials,
 // such as affine bodies carried through many levels, take several passes).
