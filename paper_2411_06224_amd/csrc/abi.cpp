@@ -579,7 +579,7 @@ int read_state(mas_handle* h, const SolverView& v, hipStream_t s) {
 // two launches:
 //   p = z + beta p, q = H p (partials of p^T q and r^T p), the restriction of q
 //   and the convergence test on r_{k-1} ->
-//   alpha = r^T p / p^T q, x += alpha p, r -= alpha q (||r||^2 partials), the level-0 apply
+//   alpha, x += alpha p, r -= alpha q (||r||^2 partials), the level-0 apply
 //   and, beside it, C_l r_k = C_l r_{k-1} - alpha C_l q_k and the coarse apply
 //   (rho partials of both); the prolongation follows in the next SpMV (or,
 //   where the SpMV cannot lend shared memory to the groups' coarse
@@ -589,11 +589,13 @@ int read_state(mas_handle* h, const SolverView& v, hipStream_t s) {
 //   SpMV -> x/r update with the restriction of r_k -> [mixed: FP64 residual
 //   replacement] -> convergence test on r_k and coarse apply -> level-0
 //   apply, which also bounds the rounding the recurrence accumulates.
-// alpha is formed from r^T p, not from rho = r^T z, which the two-launch form
-// sums from coarse residuals carried by recurrence: once r is below their
-// rounding rho is theirs, and with it the steps would grow without end (3,600
-// nodes, 1e-15 after 15 iterations, 1e+14 after 49).  With r^T p each step is
-// the least error along p, whatever beta made of it.
+// alpha = rho / p^T q, with rho = r^T z summed by the two-launch form from coarse
+// residuals that are carried by recurrence: once r is below their rounding rho
+// is theirs, and the steps would grow without end (3,600 nodes, 1e-15 after 15
+// iterations, 1e+14 after 49).  So where rho is beyond 2 r^T p, and the step
+// would make the error larger, r^T p takes its place, the least error along p.
+// (r^T p throughout: mixed solves with the FP64 replacement near the limit of
+// FP32 storage take 2 % more iterations, single ones twice as many.)
 // The host reads the state every check_every iterations; iterations queued
 // after a stop return at once.
 int solve_impl(mas_handle* h, const mas_bcsr* H, const double* b, double* x, const pcg_options* o, pcg_result* res,

@@ -183,12 +183,13 @@ __device__ inline double sum_partials(const double* __restrict__ p, int n, doubl
 
 __device__ inline bool finite(double x) { return x - x == 0.0; }
 
-// r^T p / p^T q, or NaN where the solve has to stop (H not positive definite
-// along p, or a sum that is not finite).  Far below rounding (tol = 0) both
-// sums underflow to zero: no step then.
-__device__ inline double line_step(double sigma, double rp) {
+// rho / p^T q, or r^T p / p^T q (the least error along p) where that step would
+// make the error larger, or NaN where the solve has to stop (H not positive
+// definite along p, or a sum that is not finite).  Far below rounding (tol = 0)
+// sigma and r^T p underflow to zero: no step then.
+__device__ inline double line_step(double sigma, double rp, double rho) {
     if (finite(sigma) && finite(rp)) {
-        if (sigma > 0.0) return rp / sigma;
+        if (sigma > 0.0) return (rho > 0.0 && rho < 2.0 * rp ? rho : rp) / sigma;
         if (sigma == 0.0 && rp == 0.0) return 0.0;
     }
     return __builtin_nan("");

@@ -615,18 +615,26 @@ __device__ __forceinline__ double full_row(const TI* __restrict__ inv, int n, in
 }
 
 // ---- the scalars of an iteration by recurrence
-using RecLoads = PartialLoads<4, double2>;
+struct RecLoads {
+    PartialLoads<4, double2> sp;
+    double rho;
+};
 
-__device__ __forceinline__ RecLoads rec_load(const SolverView& v) { return partials_load(v.P_sp, v.G); }
+__device__ __forceinline__ RecLoads rec_load(const SolverView& v, int k) {
+    RecLoads R;
+    R.sp = partials_load(v.P_sp, v.G);
+    R.rho = uniform_load(&v.st->rho[(k - 1) & 1]);
+    return R;
+}
 
-// alpha_k = r_{k-1}^T p_k / sigma_k, or false (after flagging NOT_SPD or
+// alpha_k = rho_{k-1} / sigma_k (see line_step), or false (after flagging NOT_SPD or
 // NOT_FINITE where report is set) when sigma <= 0 or a value is not finite:
 // every workgroup sees the same sums and returns without writing.  buf: 512
 // doubles of shared memory, not written again before another barrier.
 __device__ __forceinline__ bool rec_alpha(const SolverView& v, int k, bool report, const RecLoads& R, double* buf,
                                           double& alpha) {
-    const double2 s = partials_sum(R, v.P_sp, v.G, buf);
-    alpha = line_step(s.x, s.y);
+    const double2 s = partials_sum(R.sp, v.P_sp, v.G, buf);
+    alpha = line_step(s.x, s.y, R.rho);
     if (!(alpha == alpha)) {
         if (report && threadIdx.x == 0) {
             v.st->status = (finite(s.x) && finite(s.y)) ? -2 : -6;
@@ -662,7 +670,7 @@ __device__ __forceinline__ void coarse_pairs(const SolverView& v, const CoarseTa
     const int l = coarse_level(tab, v.L, b);
     const int pairs = (v.ndom[l] + 1) / 2, nrow = 3 * v.units[l];
     RecLoads R{};
-    if constexpr (kRec) R = rec_load(v);
+    if constexpr (kRec) R = rec_load(v, k);
     PairRegs<TI> P;
     double x[2] = {0.0, 0.0}, out[2] = {0.0, 0.0}, part = 0.0;
     if (l == 1) {
@@ -832,7 +840,7 @@ __device__ __forceinline__ void coarse_domain(const SolverView& v, const CoarseT
     const int d = b - tab.off[l], N = v.N, n = 3 * N;
     const int u0 = d * N, nu = min(N, v.units[l] - u0);
     RecLoads R{};
-    if constexpr (kRec) R = rec_load(v);
+    if constexpr (kRec) R = rec_load(v, k);
     const int stop = v.st->done;
     keep_loads_issued();
     if (mode != kApplyPlain && stop) return;
@@ -1064,7 +1072,7 @@ __global__ void __launch_bounds__(kPairThreads, kPairWaves) k_apply_rec_pairs(So
     const int b = xcd_group(blockIdx.x - pad, v.GA);
     const int p = 4 * b + w;
     const bool live = 2 * p < v.M;
-    const RecLoads R = rec_load(v);
+    const RecLoads R = rec_load(v, k);
     int e[2];
     bool own[2];
     double xv[2], pv[2], ro[2], qv[2];
@@ -1128,7 +1136,7 @@ __global__ void __launch_bounds__(kGroupThreads) k_apply_rec(SolverView v, Coars
     const int nd = min(v.D0, v.M - g * v.D0);  // domains of this group
     const bool live = t < nd * n;
     const long long i = 3LL * g * v.RG + (live ? t : 0);
-    const RecLoads R = rec_load(v);
+    const RecLoads R = rec_load(v, k);
     const double xv = v.x[i], pv = v.p[k & 1][i], ro = v.r[i], qv = v.q[i];
     const int stop = v.st->done;
     keep_loads_issued();

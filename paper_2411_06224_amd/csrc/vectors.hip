@@ -105,9 +105,10 @@ __global__ void k_init_rhs(SolverView v) {
     restrict_group_any(v, g, pl, rs, sm + 3 * v.RG, v.r1, v.cpart);
 }
 
-// Iteration k: alpha = r_{k-1}^T p_k / sigma_k (both summed here from the group
-// partials), x += alpha p, r -= alpha q, the partial of ||r||^2 and the
-// restriction of the new residual.  sigma <= 0 stops the solve (NOT_SPD).
+// Iteration k: alpha = rho_{k-1} / sigma_k (sigma and r^T p, which guards the
+// step, summed here from the group partials, rho_{k-1} as the SpMV of this
+// iteration recorded it), x += alpha p, r -= alpha q, the partial of ||r||^2 and
+// the restriction of the new residual.  sigma <= 0 stops the solve (NOT_SPD).
 // Writer passes of the restriction whose plan entries k_update loads with
 // its other early loads (systems whose groups write many coarse partials,
 // such as affine bodies carried through many levels, take several passes).
@@ -122,6 +123,7 @@ __global__ void k_update(SolverView v, int k) {
     // first wait, the partials of sigma first (they are needed first, and
     // loads complete in issue order); after a stop nothing is written
     const auto sp = partials_load(v.P_sp, v.G);
+    const double rho = v.st->rho[(k - 1) & 1];
     const long long i = 3LL * g * v.RG + t;
     const bool own = t < 3 * v.RG && i < 3LL * v.NS;
     const long long ic = own ? i : 0;  // unconditional loads (see partials_load)
@@ -133,7 +135,7 @@ __global__ void k_update(SolverView v, int k) {
     if (stop) return;
     // (block_sum's first barrier orders scratch's reuse)
     const double2 s = partials_sum(sp, v.P_sp, v.G, scratch);
-    const double alpha = line_step(s.x, s.y);
+    const double alpha = line_step(s.x, s.y, rho);
     if (!(alpha == alpha)) {
         if (g == 0 && t == 0) {
             v.st->status = (finite(s.x) && finite(s.y)) ? -2 : -6;

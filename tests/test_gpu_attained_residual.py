@@ -108,3 +108,22 @@ def test_converges_without_replacement(name):
         its.append(r["iterations"])
     assert its[1] <= 1.05 * its[0]
     S.close()
+
+
+# With the FP64 replacement near the limit of FP32 storage the step rho / p^T H p
+# keeps more of the old direction than the least error along p does: 396
+# iterations, 500 with the latter throughout.  Both are sums in some order: 10 %
+# are allowed.
+def test_mixed_replacement_keeps_its_count():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2411_06224_amd as mp
+
+    s = SYSTEMS["random"]()
+    S = mp.MasPcg(s.row_ptr, s.col_idx, graph=(s.gptr, s.gadj), precision="mixed", max_levels=2, poison=True)
+    H = mp.BlockMatrix.from_numpy(s.row_ptr, s.col_idx, s.val, device="cuda:0")
+    S.build(H)
+    print("[case] random mixed", flush=True)
+    _, r = S.solve(H, torch.as_tensor(s.b, device="cuda:0"), tol=1e-8, max_iter=2000)
+    assert r["status"] == 0 and r["iterations"] <= 1.1 * 396
+    S.close()
